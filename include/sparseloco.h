@@ -271,7 +271,8 @@ int sparseloco_outer_step_batch(const sparseloco_plan* plan, int n_replicas,
  *                       2^-23 |x y| per product, the size of an fp32 rounding
  *                       step.  Operands must be finite and normal-or-zero.
  * A projection onto at most 32 columns (16 with both tables of section 2.2) is
- * bound by memory traffic and always uses fp32 products.
+ * bound by memory traffic, one of few rows (at most 128 tiles of 64 rows x 64
+ * columns, d >= 256) by latency: both always use fp32 products.
  * Measured: 1.15-1.45 times the fp32 rate (the chip lowers its clock under the
  * bf16 matrix load, which caps the gain).  Another value: SPLC_EINVAL.
  */
@@ -338,7 +339,8 @@ int sparseloco_subspace_reconstruct(const float* x_tilde, const float* t_perp, c
  * tuning.  op: SPLC_OP_*; rows = rows of x (project / reconstruct) or the vocabulary (re-projection);
  * tables: how many of the two tables of section 2.2 are present (0..2; ignored for the re-projection).
  * Returns tile_rows * 256 + tile_cols of a workgroup's output tile -- 128 or 64 by 128 or 64 for the GEMM
- * kernel, 16 by 16 or 16 by 32 for the narrow projection kernel -- or a negative status.
+ * kernel, 16 by 16 or 16 by 32 for the narrow projection kernel, 16 by 32 or 16 by 64 for the projection of few
+ * rows -- or a negative status.
  */
 enum { SPLC_OP_PROJECT = 0, SPLC_OP_RECONSTRUCT = 1, SPLC_OP_REPROJECT_PASS1 = 2, SPLC_OP_REPROJECT_PASS2 = 3 };
 int sparseloco_subspace_kernel_choice(int op, int64_t rows, int d, int k, int tables, int matmul);

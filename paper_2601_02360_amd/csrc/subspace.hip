@@ -765,6 +765,170 @@ __global__ __launch_bounds__(kThreads, NB == 1 ? 4 : (NB == 2 ? 3 : 2)) void pro
     }
 }
 
+// Projection of few rows: out[rows, k] = (x - T_perp[token] - PosEmbed) U where the GEMM tiles above would leave most
+// of the chip idle (2048 rows onto 96 columns are 32 of its workgroups, each with the whole reduction as one serial
+// chain).  One workgroup takes 16 rows x 16 NB columns and its KS waves share the reduction: wave w takes the 32-wide
+// d tiles w, w + KS, ..., and the partial sums are added in wave order through LDS at the end.
+// Operands of v_mfma_f32_16x16x4_f32 go from global memory straight into registers, PD tiles ahead, and nothing is
+// shared before the end, so the loop has no barrier:
+//   * A as in the narrow kernel: lane (g, c) holds four consecutive d of row c, step s multiplies the set {4 g + s};
+//   * B: lane (g, c) holds U[d][col0 + NB c .. + NB - 1] for its d's -- one 4 NB-byte load per d.  Block nb of the
+//     product is then made of the columns NB c + nb, a permutation that only the final store has to know about.
+template <int NB, int KS, bool TP, bool PE>
+__global__ __launch_bounds__(64 * KS) void project_rows_kernel(const float* __restrict__ x, HighRank h,
+                                                               const float* __restrict__ u, float* __restrict__ out,
+                                                               int rows, int d, int k) {
+    typedef float v4f __attribute__((ext_vector_type(4)));
+    typedef float vcols __attribute__((ext_vector_type(NB), aligned(4)));
+    constexpr int KT = 32, PD = 2, COLS = 16 * NB;
+    __shared__ __attribute__((aligned(16))) float part[KS][16][COLS];
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int g = lane >> 4, c = lane & 15;
+    // column tiles of a row block on one XCD, as in gemm_kernel
+    const int col_tiles = (k + COLS - 1) / COLS;
+    const int xcd = blockIdx.x & 7, slot = blockIdx.x >> 3;
+    const int r0 = ((slot / col_tiles) * 8 + xcd) * 16, col0 = (slot % col_tiles) * COLS;
+    if (r0 >= rows) return;
+    const int row = r0 + c < rows ? r0 + c : rows - 1;         // rows past the end repeat the last one; never stored
+    const float* const px = x + (int64_t)row * d + 4 * g;
+    const float* const pt = TP ? h.perp_row(row) + 4 * g : nullptr;
+    const float* const pp = PE ? h.pos_row(row) + 4 * g : nullptr;
+    const int bcol = col0 + NB * c;
+    const float* const pu = u + (int64_t)(4 * g) * k + (bcol < k ? bcol : 0);     // columns past k: never stored
+
+    struct Stage { vfloat4 x[2], t[2], p[2]; vcols b[2][4]; };
+    Stage st[PD];
+    v4f acc[NB];
+#pragma unroll
+    for (int nb = 0; nb < NB; ++nb) acc[nb] = v4f{0.f, 0.f, 0.f, 0.f};
+
+    auto fetch = [&](int t, Stage& q) {
+#pragma unroll
+        for (int hh = 0; hh < 2; ++hh) {
+            const int at = t * KT + 16 * hh;
+            q.x[hh] = ldg4(px + at);
+            if (TP) q.t[hh] = ldg4(pt + at);
+            if (PE) q.p[hh] = ldg4(pp + at);
+#pragma unroll
+            for (int s = 0; s < 4; ++s) q.b[hh][s] = *(const SPLC_GLOBAL vcols*)(pu + (int64_t)(at + s) * k);
+        }
+    };
+    // the last tiles: element by element, zeros from row d of U (column d of x) on
+    auto fetch_guarded = [&](int t, Stage& q) {
+#pragma unroll
+        for (int hh = 0; hh < 2; ++hh)
+#pragma unroll
+            for (int s = 0; s < 4; ++s) {
+                const int at = t * KT + 16 * hh + s;
+                const bool there = at + 4 * g < d;
+                q.x[hh][s] = there ? px[at] : 0.f;
+                if (TP) q.t[hh][s] = there ? pt[at] : 0.f;
+                if (PE) q.p[hh][s] = there ? pp[at] : 0.f;
+#pragma unroll
+                for (int nb = 0; nb < NB; ++nb)
+                    q.b[hh][s][nb] = there && bcol + nb < k ? pu[(int64_t)at * k + nb] : 0.f;
+            }
+    };
+    auto multiply = [&](const Stage& q) {
+#pragma unroll
+        for (int hh = 0; hh < 2; ++hh) {
+            vfloat4 a = q.x[hh];
+            if (TP) {
+#pragma unroll
+                for (int i = 0; i < 4; ++i) a[i] = __fsub_rn(a[i], q.t[hh][i]);
+            }
+            if (PE) {
+#pragma unroll
+                for (int i = 0; i < 4; ++i) a[i] = __fsub_rn(a[i], q.p[hh][i]);
+            }
+#pragma unroll
+            for (int s = 0; s < 4; ++s)
+#pragma unroll
+                for (int nb = 0; nb < NB; ++nb)
+                    acc[nb] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[s], q.b[hh][s][nb], acc[nb], 0, 0, 0);
+        }
+    };
+
+    // A lane that straddles column k reads on into the next row of U, which the leading n_fast tiles have.
+    const int n_tiles = (d + KT - 1) / KT;
+    const int n_fast = (k % NB == 0 ? d : d - 1) / KT;
+    auto fetch_any = [&](int t, Stage& q) {
+        if (t < n_fast) fetch(t, q);
+        else if (t < n_tiles) fetch_guarded(t, q);
+    };
+    int t = wave;
+#pragma unroll
+    for (int j = 0; j < PD; ++j) fetch_any(wave + KS * j, st[j]);
+    for (; t + KS * (2 * PD - 1) < n_fast; t += KS * PD) {
+#pragma unroll
+        for (int j = 0; j < PD; ++j) {
+            multiply(st[j]);
+            fetch(t + KS * (PD + j), st[j]);
+        }
+    }
+    for (; t < n_tiles; t += KS * PD) {
+#pragma unroll
+        for (int j = 0; j < PD; ++j)
+            if (t + KS * j < n_tiles) {
+                multiply(st[j]);
+                fetch_any(t + KS * (PD + j), st[j]);
+            }
+    }
+
+    // D layout of the 16 x 16 MFMA: register v of lane l holds row 4 (l / 16) + v, column l % 16 of the block.
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+        vcols w;
+#pragma unroll
+        for (int nb = 0; nb < NB; ++nb) w[nb] = acc[nb][v];
+        *reinterpret_cast<vcols*>(&part[wave][4 * g + v][NB * c]) = w;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < 16 * COLS / (64 * KS); ++i) {
+        const int f = tid + 64 * KS * i, orow = f / COLS, oc = f % COLS;
+        float sum = part[0][orow][oc];
+#pragma unroll
+        for (int w = 1; w < KS; ++w) sum = __fadd_rn(sum, part[w][orow][oc]);
+        if (r0 + orow < rows && col0 + oc < k) out[(int64_t)(r0 + orow) * k + col0 + oc] = sum;
+    }
+}
+
+template <int NB, int KS>
+void launch_project_rows(const float* x, const HighRank& h, const float* u, float* out, int rows, int d, int k,
+                         hipStream_t st) {
+    const int64_t row_blocks = ((int64_t)(rows + 15) / 16 + 7) / 8 * 8;
+    const dim3 grid((unsigned)(row_blocks * ((k + 16 * NB - 1) / (16 * NB)))), block(64 * KS);
+    if (h.t_perp && h.pos)
+        hipLaunchKernelGGL((project_rows_kernel<NB, KS, true, true>), grid, block, 0, st, x, h, u, out, rows, d, k);
+    else if (h.t_perp)
+        hipLaunchKernelGGL((project_rows_kernel<NB, KS, true, false>), grid, block, 0, st, x, h, u, out, rows, d, k);
+    else if (h.pos)
+        hipLaunchKernelGGL((project_rows_kernel<NB, KS, false, true>), grid, block, 0, st, x, h, u, out, rows, d, k);
+    else
+        hipLaunchKernelGGL((project_rows_kernel<NB, KS, false, false>), grid, block, 0, st, x, h, u, out, rows, d, k);
+}
+// Few rows: at most 128 tiles of 64 x 64 -- at least half of the compute units would get none -- and a reduction long
+// enough to share.  The GEMM kernel's time is then one tile's serial reduction, whatever the number of tiles; this
+// kernel's grows with it, and the two meet at 128 tiles (2048 x 2048 onto 256 columns with both tables: 42.5 us here,
+// 45.9 us there; 4096 x 1536 onto 64: 18.7 / 37.8; 2048 x 768 onto 96: 9.4 / 18.7; 256 tiles, 8192 x 768 onto 96:
+// 33.4 / 21.1).  With split-bf16 products too: the fp32 ones used here are no less exact.
+bool rows_apply(int rows, int d, int k) {
+    return (int64_t)((rows + 63) / 64) * ((k + 63) / 64) <= 128 && d >= 256;
+}
+// Columns per workgroup: 64, or 32 where even twice as many workgroups are at most one per compute unit (700 rows onto
+// 87: 7.4 us with 32, 9.2 with 64).
+bool rows_wide(int rows, int k) { return (int64_t)((rows + 15) / 16) * ((k + 63) / 64) > 128; }
+void launch_project_rows(const float* x, const HighRank& h, const float* u, float* out, int rows, int d, int k,
+                         hipStream_t st) {
+    const int64_t groups = (int64_t)((rows + 15) / 16) * ((k + 63) / 64);
+    // eight waves share the reduction while there is one workgroup per compute unit (2048 x 768 onto 96: 9.4 us against
+    // 10.7), four beyond (2048 x 2048 onto 256: 42.5 against 44.9)
+    if (!rows_wide(rows, k)) launch_project_rows<2, 8>(x, h, u, out, rows, d, k, st);
+    else if (groups <= 256) launch_project_rows<4, 8>(x, h, u, out, rows, d, k, st);
+    else launch_project_rows<4, 4>(x, h, u, out, rows, d, k, st);
+}
 template <bool TP, bool PE>
 void launch_project_narrow_tables(const float* x, const HighRank& h, const float* u, float* out, int rows, int d,
                                   int k, hipStream_t st) {
@@ -803,7 +967,9 @@ void launch_gemm_tile(const float* A, int64_t lda, const float* B, int64_t ldb, 
 }
 // Tile choice (measured on the shapes of sections 2.2 and 2.4 at d 1536 / 2048, k = d/8 ... d/16):
 //   columns: 64 wide when N spans an odd number of 64-column blocks (the last 128-wide tile would be at
-//            most half used), else 128 wide;
+//            most half used), else 128 wide -- unless a projection then has at most 128 tiles, where the time is one
+//            tile's serial reduction (4096 x 2048 onto 256: 87 us with 128 columns, 55 with 64; 8192 x 768 onto 96:
+//            36 / 23; 192 tiles, 12288 x 1280 onto 100: 58 / 58);
 //   rows:    128 when that still leaves (nearly) two workgroups per compute unit -- 480 of them: the first pass of
 //            the re-projection at 32000 x 2048, k = 256 has 500 and takes 272 us so, 288 us with 64 rows --, else 64;
 //   a product with the basis as the N x K operand has K = k: up to K = 192 the K loop is so short that
@@ -814,7 +980,7 @@ void launch_gemm_tile(const float* A, int64_t lda, const float* B, int64_t ldb, 
 struct GemmTile { bool tall, wide; };
 GemmTile choose_gemm_tile(bool b_nk, int M, int N, int K, bool light_epilogue, int matmul) {
     auto groups = [&](int tm, int tn) { return (int64_t)((M + tm - 1) / tm) * ((N + tn - 1) / tn); };
-    bool wide = ((N + 63) / 64) % 2 == 0;
+    bool wide = ((N + 63) / 64) % 2 == 0 && (b_nk || groups(64, 128) > 128);
     bool tall;
     if (matmul == SPLC_MATMUL_BF16X3) {
         // split operands: a tile's matrix work is a third as long and splitting costs per staged value, so the
@@ -863,6 +1029,8 @@ int reproject_impl(float* t_s, float* t_perp, const float* u, float* coeff_ws, i
     // pass 1: coeff = T_S U            (M x k) = (M x d)(d x k)
     if (narrow_applies(d, k, HighRank{nullptr, nullptr, 0, nullptr, 1, (int64_t)d}))
         launch_project_narrow(t_s, HighRank{nullptr, nullptr, 0, nullptr, 1, (int64_t)d}, u, coeff_ws, M, d, k, st);
+    else if (rows_apply(M, d, k))
+        launch_project_rows(t_s, HighRank{nullptr, nullptr, 0, nullptr, 1, (int64_t)d}, u, coeff_ws, M, d, k, st);
     else
         launch_gemm<false>(t_s, (int64_t)d, u, (int64_t)k, M, k, d, NoPrologue{}, StoreCoeff{coeff_ws, (int64_t)k}, matmul,
                            st);
@@ -951,6 +1119,7 @@ extern "C" int sparseloco_subspace_kernel_choice(int op, int64_t rows, int d, in
             const int n_tab = op == SPLC_OP_PROJECT ? tables : 0;
             const HighRank h{n_tab >= 1 ? some : nullptr, nullptr, 0, n_tab >= 2 ? some : nullptr, 1, (int64_t)d};
             if (narrow_applies(d, k, h)) return 16 * 256 + (k <= 16 ? 16 : 32);
+            if (rows_apply(M, d, k)) return 16 * 256 + (rows_wide(M, k) ? 64 : 32);
             t = choose_gemm_tile(false, M, k, d, false, matmul);
             break;
         }
@@ -975,6 +1144,8 @@ extern "C" int sparseloco_subspace_project(const float* x, const float* t_perp, 
     hipStream_t st = static_cast<hipStream_t>(stream);
     if (narrow_applies(d, k, h)) {
         launch_project_narrow(x, h, u, x_tilde, M, d, k, st);
+    } else if (rows_apply(M, d, k)) {
+        launch_project_rows(x, h, u, x_tilde, M, d, k, st);
     } else if (t_perp && pos_embed)
         launch_gemm<false>(x, (int64_t)d, u, (int64_t)k, M, k, d, SubtractHighRank<true, true>{h, {nullptr, nullptr}},
                            StoreCoeff{x_tilde, (int64_t)k}, matmul, st);

@@ -212,6 +212,24 @@ def test_stage_boundary_at_the_benchmarked_shape(matmul_mode):
     print("largest error / bar at the stage-boundary bench shape: %.3f" % worst)
 
 
+# Few rows: 16 x 32 tiles (up to 128 tiles of 16 x 64), 16 x 64 with eight waves sharing the reduction (up to 256) and
+# with four (beyond, up to 128 tiles of 64 x 64).  Reductions that end inside a 32-wide tile or leave waves without one,
+# widths that end inside a column tile or a lane's columns, row counts off the 16-row grid, the largest of the range.
+FEW_ROWS_SHAPES = [
+    (1, 1, 256, 33, 3, True, True, 32), (15, 5, 257, 65, 4, False, False, 32), (700, 700, 697, 87, 50, True, True, 32),
+    (2048, 1024, 256, 33, 100, True, False, 32), (2049, 500, 768, 34, 100, False, True, 64),
+    (2048, 1024, 768, 96, 300, True, True, 64), (1000, 100, 2050, 255, 64, True, False, 64),
+    (2000, 1000, 1023, 170, 33, False, True, 64), (8192, 1024, 288, 64, 500, True, True, 64),
+    (2047, 89, 2048, 256, 77, False, False, 64)]
+
+
+@pytest.mark.parametrize("rows,seq,d,k,vocab,use_perp,use_pos,columns", FEW_ROWS_SHAPES)
+def test_projection_of_few_rows_matches_the_oracle(rows, seq, d, k, vocab, use_perp, use_pos, columns, matmul_mode):
+    tables = int(use_perp) + int(use_pos)
+    assert B.subspace_kernel_choice(B.SPLC_OP_PROJECT, rows, d, k, tables, matmul_mode) == (16, columns)
+    check_stage_boundary(rows, seq, d, k, vocab, use_perp, use_pos, seed=rows + d + k, mode=matmul_mode)
+
+
 def test_every_kernel_variant_is_reached(matmul_mode):
     """The shapes above, run through the library's own launch rule, cover all eight tile shapes of the GEMM
     kernel (rows x columns x operand form) and both narrow kernels, in this matmul mode."""
