@@ -97,7 +97,7 @@ enum {
 };
 
 enum {
-    SPLC_SELECT_AUTO = 0,        /* candidate filter + exact ranking, radix select when it does not apply */
+    SPLC_SELECT_AUTO = 0,        /* candidate filter + exact selection among the candidates, radix select when it does not apply */
     SPLC_SELECT_RADIX = 1        /* always the radix select (same result; for tests and comparison) */
 };
 

@@ -31,7 +31,8 @@ namespace {
 
 constexpr int kChunk = SPLC_CHUNK;
 constexpr int kThreads = 256;            // one workgroup per chunk
-constexpr int kCandCap = 256;            // candidates the exact ranking handles (one per lane)
+constexpr int kCandCap = 448;            // candidates the exact selection handles (seven per lane; two strip workgroups'
+                                         // shares of the LDS end here)
 constexpr int kFilterKappaMax = 256;     // the candidate filter needs kappa <= number of lanes
 
 struct ChunkDesc {
@@ -58,6 +59,11 @@ __device__ __forceinline__ bool present(const ChunkDesc& d, uint32_t idx) {
 __device__ __forceinline__ uint32_t elem_of(const ChunkDesc& d, uint32_t idx) {
     return (idx >> 6) * d.stride + (idx & 63u);
 }
+// The same for an element that is present, 0 (the chunk's first element) for one that is not: a load that need not be
+// made conditional.
+__device__ __forceinline__ uint32_t present_or_first(const ChunkDesc& d, uint32_t idx) {
+    return present(d, idx) ? elem_of(d, idx) : 0u;
+}
 // Address of lane tid's 4-element vector in slot s (local rows 16 s + tid / 16, columns 4 (tid % 16)...).
 // The slot part is uniform and stays in scalar registers; the per-lane part is one 32-bit byte
 // offset shared by all slots and arrays (a chunk spans less than 4 GiB: stride < 2^24).
@@ -76,6 +82,13 @@ __device__ __forceinline__ uint32_t present_mask(const ChunkDesc& d, int tid) {
     for (int el = 0; el < 16; ++el)
         m |= present(d, (uint32_t)((el >> 2) * 1024 + tid * 4 + (el & 3))) ? (1u << el) : 0u;
     return m;
+}
+
+// Element `at` of a chunk, as "uniform base + 32-bit byte offset of the lane" (a chunk spans less than 4 GiB).
+template <class T>
+__device__ __forceinline__ T* elem_at(T* origin, uint32_t at) {
+    using Byte = typename std::conditional<std::is_const<T>::value, const char, char>::type;
+    return reinterpret_cast<T*>(reinterpret_cast<Byte*>(origin) + at * (uint32_t)sizeof(T));
 }
 
 enum { MODE_PARAMS_F32 = 0, MODE_DIRECT_F32 = 1, MODE_DIRECT_BF16 = 2 };
@@ -173,234 +186,405 @@ __device__ __forceinline__ void load_fold_full(const void* __restrict__ a, const
     }
 }
 
-// Edge chunks and rows that do not allow vector accesses: element by element, absent elements = +0.
+// Edge chunks: element by element, absent elements = +0.  An absent element's loads go to element 0 of the chunk, which
+// every chunk has: with unconditional loads all of a lane's elements are in flight at once (under a condition each
+// waits for its own before the next is requested).
 template <int MODE>
 __device__ __forceinline__ void load_fold_scalar(const void* __restrict__ a, const void* __restrict__ b,
                                                  const float* __restrict__ e, const ChunkDesc& d, int tid,
                                                  float beta, uint32_t pmask, float (&x)[16]) {
+    using Source = typename std::conditional<MODE == MODE_DIRECT_BF16, uint16_t, float>::type;
+    const Source* pa = static_cast<const Source*>(a) + d.offset;
+    const float* pb = MODE == MODE_PARAMS_F32 ? static_cast<const float*>(b) + d.offset : nullptr;
+    const float* pe = e + d.offset;
+    // eight elements at a time, indices from an opaque copy of the lane number (none of them is kept for the
+    // selection): otherwise this path would set the register count of the kernel
 #pragma unroll
-    for (int el = 0; el < 16; ++el) {
-        const uint32_t idx = (el >> 2) * 1024 + tid * 4 + (el & 3);
-        float v = 0.f;
-        if (pmask & (1u << el)) {
-            const uint64_t at = d.offset + elem_of(d, idx);
-            float dl;
-            if (MODE == MODE_PARAMS_F32)
-                dl = __fsub_rn(static_cast<const float*>(a)[at], static_cast<const float*>(b)[at]);
-            else if (MODE == MODE_DIRECT_F32)
-                dl = static_cast<const float*>(a)[at];
-            else
-                dl = __uint_as_float((uint32_t) static_cast<const uint16_t*>(a)[at] << 16);
-            v = fold(beta, e[at], dl);
+    for (int half = 0; half < 16; half += 8) {
+        int t = tid;
+        asm volatile("" : "+v"(t));
+        float ev[8], dv[8], lv[8];
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+            const int el = half + i;
+            const uint32_t idx = (el >> 2) * 1024 + t * 4 + (el & 3);
+            const uint32_t at = (pmask & (1u << el)) ? elem_of(d, idx) : 0u;
+            ev[i] = *elem_at(pe, at);
+            if (MODE == MODE_DIRECT_BF16) dv[i] = __uint_as_float((uint32_t)*elem_at(pa, at) << 16);
+            else dv[i] = *elem_at(pa, at);
+            if (MODE == MODE_PARAMS_F32) lv[i] = *elem_at(pb, at);
         }
-        x[el] = v;
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+            if (MODE == MODE_PARAMS_F32) dv[i] = __fsub_rn(dv[i], lv[i]);
+            x[half + i] = (pmask & (1u << (half + i))) ? fold(beta, ev[i], dv[i]) : 0.f;
+        }
+        __builtin_amdgcn_sched_barrier(0);
     }
 }
 
 // Shared state of one chunk's selection.
 struct SelectShared {
-    uint64_t cand[kCandCap + 2];         // (key << 12 | 4095 - idx) of the candidates, zero padded
-    uint32_t hist[256];                  // radix select digit histogram
-    uint32_t bucket[16];                 // selected entries per 256-element bucket (bucket = idx >> 8)
-    uint32_t t0[4];                      // per-wave lower bounds of the threshold
-    uint32_t wmax[4];                    // per-wave maxima of the keys (largest selected magnitude)
-    uint64_t thr;                        // composite of the kappa_c-th entry in (key desc, idx asc) order
-    uint32_t ncand;
-    uint32_t digit;
-    uint32_t need;
+    union {
+        alignas(16) uint2 cand[kCandCap];    // filter: candidates, ascending index: {value bits, index}
+        alignas(16) uint32_t hist[4][128];   // general path: digit counts of its four passes, two per word
+    };
+    alignas(16) uint32_t count[4][4];        // filter: candidates per wave and slot
+    uint32_t bucket[16];                     // general path: entries per 256-element bucket (bucket = idx >> 8)
+    uint32_t t0[4];                          // per-wave lower bounds of the threshold
+    uint32_t t1[4];                          // the same, second kind (edge chunks)
+    uint32_t wmax[4];                        // per-wave maxima of the keys
+    uint32_t cut;                            // general path: index of the last kept entry among equals
 };
 
-// Exact kappa_c-th largest composite by most-significant-digit radix select over
-// the 43-bit composites (31 key bits, 12 inverted index bits).  Composites of
-// present elements are distinct, so the result identifies one element: the last
-// one kept.  Works for any set of present elements (bit el of pmask = element el of this lane is
-// present), any kappa_c in 1..n_c, any tie pattern.
-__device__ void radix_select(SelectShared& sh, const float (&x)[16], int tid, uint32_t pmask, uint32_t kappa_c) {
-    const int lane = tid & 63;
-    const int wave = tid >> 6;
-    uint64_t prefix = 0;
-    uint32_t need = kappa_c;
-    int hi_bit = 43;
-    // The filter path may already have published counts for this chunk (when another group of the workgroup
-    // forced the general path): start from zero.  The first barrier of the loop below orders this.
-    if (tid < 16) sh.bucket[tid] = 0;
-    if (tid < 4) sh.wmax[tid] = 0;
-#pragma unroll 1
-    for (int pass = 0; pass < 6; ++pass) {
-        const int width = pass < 5 ? 8 : 3;
-        const int shift = hi_bit - width;
-        sh.hist[tid] = 0;
-        __syncthreads();
-#pragma unroll
-        for (int el = 0; el < 16; ++el) {
-            uint32_t idx = (el >> 2) * 1024 + tid * 4 + (el & 3);
-            // The composite is rebuilt in every pass: kept across the passes, the sixteen 64-bit values
-            // of this rarely taken path would set the register count of the whole kernel.
-            uint32_t bits = __float_as_uint(x[el]);
-            asm volatile("" : "+v"(bits));
-            uint64_t comp = ((uint64_t)(bits & 0x7FFFFFFFu) << 12) | (uint64_t)(4095u - idx);
-            if ((pmask & (1u << el)) && (comp >> hi_bit) == prefix)
-                atomicAdd(&sh.hist[(uint32_t)(comp >> shift) & ((1u << width) - 1u)], 1u);
-        }
-        __syncthreads();
-        if (wave == 0) {
-            // lane owns bins 4*lane .. 4*lane+3; find the bin where the count from the top reaches `need`
-            uint32_t h0 = sh.hist[4 * lane], h1 = sh.hist[4 * lane + 1], h2 = sh.hist[4 * lane + 2],
-                     h3 = sh.hist[4 * lane + 3];
-            uint32_t own = h0 + h1 + h2 + h3;
-            uint32_t suffix = own;               // inclusive sum over lanes >= this one
-#pragma unroll
-            for (int o = 1; o < 64; o <<= 1) {
-                uint32_t v = (uint32_t)__shfl_down((int)suffix, o);
-                if (lane + o < 64) suffix += v;
-            }
-            uint32_t above = suffix - own;
-            if (above < need && need <= suffix) {
-                uint32_t bin;
-                if (above + h3 >= need) bin = 3;
-                else { above += h3;
-                    if (above + h2 >= need) bin = 2;
-                    else { above += h2;
-                        if (above + h1 >= need) bin = 1;
-                        else { above += h1; bin = 0; } } }
-                sh.digit = 4 * lane + bin;
-                sh.need = need - above;
-            }
-        }
-        __syncthreads();
-        prefix = (prefix << width) | (uint64_t)sh.digit;
-        need = sh.need;
-        hi_bit = shift;
-    }
-    // publish the threshold, the largest key and the selected count of every 256-element bucket
+// What find_threshold found: an element is kept if its key exceeds T, or equals T and its index is at most idxT.
+struct Threshold {
+    uint32_t T, idxT;                    // key of the kappa_c-th entry; largest index kept among entries with that key
+    uint32_t amax;                       // largest key
+    uint32_t n_cand;                     // entries of sh.cand, or 0 if the general path ran (then sh.bucket is valid)
+};
+
+// Maximum / minimum over the 64 lanes by DPP (four steps inside the rows of 16, two across), result in every lane.
+template <bool MAX>
+__device__ __forceinline__ uint32_t wave_extreme_u32(uint32_t v) {
+    constexpr uint32_t neutral = MAX ? 0u : 0xFFFFFFFFu;
+    auto pick = [](uint32_t a, uint32_t b) { return MAX ? (a > b ? a : b) : (a < b ? a : b); };
+    v = pick(v, (uint32_t)__builtin_amdgcn_update_dpp((int)neutral, (int)v, 0x111, 0xf, 0xf, false));   // row_shr:1
+    v = pick(v, (uint32_t)__builtin_amdgcn_update_dpp((int)neutral, (int)v, 0x112, 0xf, 0xf, false));   // row_shr:2
+    v = pick(v, (uint32_t)__builtin_amdgcn_update_dpp((int)neutral, (int)v, 0x114, 0xf, 0xf, false));   // row_shr:4
+    v = pick(v, (uint32_t)__builtin_amdgcn_update_dpp((int)neutral, (int)v, 0x118, 0xf, 0xf, false));   // row_shr:8
+    v = pick(v, (uint32_t)__builtin_amdgcn_update_dpp((int)neutral, (int)v, 0x142, 0xa, 0xf, false));   // row_bcast:15
+    v = pick(v, (uint32_t)__builtin_amdgcn_update_dpp((int)neutral, (int)v, 0x143, 0xc, 0xf, false));   // row_bcast:31
+    return (uint32_t)__builtin_amdgcn_readlane((int)v, 63);
+}
+
+// Sum over the lanes up to and including this one (DPP: four steps inside the rows of 16, two across).
+__device__ __forceinline__ uint32_t wave_inclusive_sum(uint32_t v) {
+    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x111, 0xf, 0xf, false);      // row_shr:1
+    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x112, 0xf, 0xf, false);      // row_shr:2
+    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x114, 0xf, 0xf, false);      // row_shr:4
+    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x118, 0xf, 0xf, false);      // row_shr:8
+    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x142, 0xa, 0xf, false);      // row_bcast:15
+    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x143, 0xc, 0xf, false);      // row_bcast:31
+    return v;
+}
+
+// The general path of the selection: any set of present elements (bit el of pmask = element el of this lane is
+// present), any kappa_c in 1..n_c, any tie pattern.  Most-significant-digit radix select over the 31 key bits, four
+// passes with a histogram each, then the last kept index among the elements with the last key.  The keys are formed
+// anew in every pass, so that this rarely taken path does not set the register count of the kernel.  Also counts the
+// kept entries of every 256-element bucket in sh.bucket.  Ends behind a barrier; the number of barriers does not
+// depend on the chunk (the groups of a strip go through here side by side).
+__device__ __forceinline__ void general_select(SelectShared& sh, const float (&x)[16], int tid, int lane, int wave,
+                                               uint32_t pmask, uint32_t kappa_c, Threshold& th) {
+    auto key = [&](int el) {
+        uint32_t bits = __float_as_uint(x[el]);
+        asm volatile("" : "+v"(bits));
+        return bits & 0x7FFFFFFFu;
+    };
+    __syncthreads();                                          // the candidates share the histograms' memory
+    (&sh.hist[0][0])[tid] = 0;
+    (&sh.hist[0][0])[256 + tid] = 0;
     uint32_t tmax = 0;
 #pragma unroll
-    for (int el = 0; el < 16; ++el) {
-        uint32_t idx = (el >> 2) * 1024 + tid * 4 + (el & 3);
-        uint32_t key = __float_as_uint(x[el]) & 0x7FFFFFFFu;
-        uint64_t comp = ((uint64_t)key << 12) | (uint64_t)(4095u - idx);
-        if (pmask & (1u << el)) {
-            tmax = key > tmax ? key : tmax;
-            if (comp >= prefix) atomicAdd(&sh.bucket[idx >> 8], 1u);
+    for (int el = 0; el < 16; ++el) tmax = (pmask & (1u << el)) && key(el) > tmax ? key(el) : tmax;
+    tmax = wave_extreme_u32<true>(tmax);
+    if (lane == 0) sh.wmax[wave] = tmax;
+    __syncthreads();
+    uint32_t T = 0, need = kappa_c;                           // digits so far; entries still to find below them
+#pragma unroll 1
+    for (int pass = 0; pass < 4; ++pass) {
+        const int shift = pass == 3 ? 0 : 23 - 8 * pass, width = pass == 3 ? 7 : 8;
+        uint32_t* hist = sh.hist[pass];
+#pragma unroll
+        for (int el = 0; el < 16; ++el) {
+            const uint32_t k = key(el);
+            const uint32_t digit = (k >> shift) & ((1u << width) - 1u);
+            if ((pmask & (1u << el)) && ((k >> shift) >> width) == T)
+                atomicAdd(&hist[digit >> 1], 1u << (16 * (digit & 1u)));
+        }
+        __syncthreads();
+        // every wave for itself: lane l owns the digits 4 l .. 4 l + 3; find where the count from the top reaches `need`
+        const uint2 h = *reinterpret_cast<const uint2*>(&hist[2 * lane]);
+        const uint32_t h0 = h.x & 0xFFFFu, h1 = h.x >> 16, h2 = h.y & 0xFFFFu, h3 = h.y >> 16;
+        const uint32_t own = h0 + h1 + h2 + h3, upto = wave_inclusive_sum(own);
+        uint32_t above = (uint32_t)__builtin_amdgcn_readlane((int)upto, 63) - upto;       // digits of higher lanes
+        const bool here = above < need && need <= above + own;
+        uint32_t digit = 4u * (uint32_t)lane + 3u;
+        if (above + h3 < need) {
+            above += h3; --digit;
+            if (above + h2 < need) {
+                above += h2; --digit;
+                if (above + h1 < need) { above += h1; --digit; }
+            }
+        }
+        const int at = __ffsll((unsigned long long)__ballot(here)) - 1;
+        T = (T << width) | (uint32_t)__builtin_amdgcn_readlane((int)digit, at);
+        need -= (uint32_t)__builtin_amdgcn_readlane((int)above, at);
+    }
+    // the first `need` elements with key T, by index, are kept: find the bucket of the last one, then its index
+#pragma unroll
+    for (int s = 0; s < 4; ++s) {
+        uint32_t c = 0;
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+            c += (uint32_t)__popcll(__ballot((pmask & (1u << (4 * s + j))) && key(4 * s + j) == T));
+        if (lane == 0) sh.bucket[4 * s + wave] = c;
+    }
+    __syncthreads();
+    {
+        const uint32_t own = lane < 16 ? sh.bucket[lane] : 0u, upto = wave_inclusive_sum(own);
+        const int at = __ffsll((unsigned long long)__ballot(upto >= need)) - 1;           // its bucket
+        const uint32_t left = need - (uint32_t)__builtin_amdgcn_readlane((int)(upto - own), at);
+#pragma unroll
+        for (int s = 0; s < 4; ++s) {
+            if (at != 4 * s + wave) continue;
+            uint32_t mine = 0;
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+                mine |= ((pmask & (1u << (4 * s + j))) && key(4 * s + j) == T) ? 1u << j : 0u;
+            uint32_t before = wave_inclusive_sum(__popc(mine)) - __popc(mine);
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                if ((mine >> j) & 1u) {
+                    if (++before == left) sh.cut = (uint32_t)(s * 1024 + tid * 4 + j);
+                }
+            }
         }
     }
-    tmax = wave_max_u32(tmax);
-    if (lane == 0) sh.wmax[wave] = tmax;
-    if (tid == 0) sh.thr = prefix;
+    __syncthreads();
+    th.T = T;
+    th.idxT = sh.cut;
+    uint32_t amax = sh.wmax[0];
+    amax = sh.wmax[1] > amax ? sh.wmax[1] : amax;
+    amax = sh.wmax[2] > amax ? sh.wmax[2] : amax;
+    th.amax = sh.wmax[3] > amax ? sh.wmax[3] : amax;
+#pragma unroll
+    for (int s = 0; s < 4; ++s) {
+        uint32_t c = 0;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const uint32_t k = key(4 * s + j);
+            const bool first = tid * 4 <= (int)th.idxT - (s * 1024 + j);
+            c += (uint32_t)__popcll(__ballot((pmask & (1u << (4 * s + j))) && (k > T || (k == T && first))));
+        }
+        if (lane == 0) sh.bucket[4 * s + wave] = c;
+    }
     __syncthreads();
 }
 
-// Top-kappa selection of the chunk held in x[16] (already folded): finds the composite of the last kept entry
-// in (key descending, index ascending) order and publishes it in sh.thr, with the largest key (sh.wmax) and the
-// number of kept entries per 256-element bucket (sh.bucket).  Only the magnitudes of x are used, and only at the
-// start: a caller that can fetch its values again afterwards need not keep them in registers meanwhile.
-// All 256 lanes (of the group) must call it; it ends behind a workgroup barrier.
+// Exact kappa_c-th largest of the n candidates in sh.cand (n <= 64 NJ), in (key descending, index ascending) order.
+// Every wave does this for itself, 64 candidates per register, by bisection on the key bits: a step is compares,
+// ballots and population counts per 64 candidates for two bits, and it starts at the highest bit in which T0 (which no candidate
+// is below) and the largest key differ and ends as soon as exactly kappa_c candidates remain -- some ten steps of 40
+// cycles, where ranking every candidate against every other one took 900, 1900 and 6300 cycles for kappa 32, 64, 128.
+template <int NJ>
+__device__ __forceinline__ void solve_candidates(const SelectShared& sh, int lane, uint32_t n, uint32_t kappa_c,
+                                                 uint32_t T0, Threshold& th) {
+    uint32_t key[NJ];
+    uint64_t valid[NJ];
+#pragma unroll
+    for (int j = 0; j < NJ; ++j) {
+        const bool there = (uint32_t)lane + 64u * j < n;
+        key[j] = there ? sh.cand[lane + 64 * j].x & 0x7FFFFFFFu : 0u;
+        valid[j] = __ballot(there);
+    }
+    const uint32_t diff = T0 ^ th.amax;
+    const int top = 31 - __clz((int)diff);                    // -1 if all candidates have the same key
+    uint32_t X = T0 & ~((2u << (top < 0 ? 0 : top)) - 1u);
+    if (top < 0) X = T0;
+    bool exact = n == kappa_c;
+    if constexpr (NJ <= 2) {
+        for (int b = top; b >= 0 && !exact; b -= 2) {         // two bits a step (t2, t3 exceed every key if one is left)
+            const int sh2 = b > 0 ? b - 1 : 0;
+            const uint32_t t1 = X + (1u << sh2), t2 = X + (2u << sh2), t3 = X + (3u << sh2);
+            uint32_t c1 = 0, c2 = 0, c3 = 0;
+#pragma unroll
+            for (int j = 0; j < NJ; ++j) {
+                c1 += (uint32_t)__popcll(__ballot(key[j] >= t1));
+                c2 += (uint32_t)__popcll(__ballot(key[j] >= t2));
+                c3 += (uint32_t)__popcll(__ballot(key[j] >= t3));
+            }
+            X = c3 >= kappa_c ? t3 : (c2 >= kappa_c ? t2 : (c1 >= kappa_c ? t1 : X));
+            exact = c1 == kappa_c || c2 == kappa_c || c3 == kappa_c;
+        }
+    } else {
+        for (int b = top; b >= 0 && !exact; --b) {            // one bit: a step has enough independent work, and fewer
+            const uint32_t t = X + (1u << b);                 // instructions count where memory is what bounds
+            uint32_t c = 0;
+#pragma unroll
+            for (int j = 0; j < NJ; ++j) c += (uint32_t)__popcll(__ballot(key[j] >= t));
+            X = c >= kappa_c ? t : X;
+            exact = c == kappa_c;
+        }
+    }
+    if (exact) {
+        // exactly the candidates >= X are kept: the smallest of them is the threshold
+        uint32_t low = 0xFFFFFFFFu;
+#pragma unroll
+        for (int j = 0; j < NJ; ++j) {
+            const bool kept = key[j] >= X && (uint32_t)lane + 64u * j < n;
+            low = kept && key[j] < low ? key[j] : low;
+        }
+        th.T = wave_extreme_u32<false>(low);
+        th.idxT = 4095u;
+    } else {
+        // X is the key of the last kept entry and more candidates have it than are kept: the first ones by index are
+        uint32_t above = 0;
+#pragma unroll
+        for (int j = 0; j < NJ; ++j) above += (uint32_t)__popcll(__ballot(key[j] > X));
+        uint32_t run = above;
+        th.T = X;
+        th.idxT = 4095u;
+#pragma unroll
+        for (int j = 0; j < NJ; ++j) {
+            const uint64_t eq = __ballot(key[j] == X) & valid[j];
+            const uint64_t last = __ballot(((eq >> lane) & 1u) && run + lanes_below(eq) == kappa_c - 1);
+            if (last) th.idxT = sh.cand[64 * j + __ffsll((unsigned long long)last) - 1].y;
+            run += (uint32_t)__popcll(eq);
+        }
+    }
+}
+
+// Top-kappa selection of the chunk held in x[16] (already folded): the threshold in (key descending, index ascending)
+// order.  Only the values at the start are used: a caller that can fetch its values again afterwards need not keep
+// them in registers meanwhile.
+// All 256 lanes (of the group) must call it.
+// FROM_LDS: the chunk sits in LDS in local index order at lds_chunk and is read from there (x is ignored): once
+// for the filter, and again by the (rare) general path, so that nothing but the sixteen values stays in registers.
 // group_ok: four flags in LDS when four 256-lane groups of one workgroup each select a chunk of their own side
 // by side (tid, lane, wave are then group-local and `sh` is the group's own).  Workgroup barriers must be
-// reached by all groups alike, so the groups agree on the path: if one needs the radix select, all take it.
-// lds_chunk: if not null, the chunk sits in LDS in local index order and is read from there (x is ignored): once
-// for the keys, and again by the (rare) radix select, so that nothing but the keys stays in registers.
-__device__ __forceinline__ void find_threshold(SelectShared& sh, const float (&x)[16], int tid, int lane, int wave,
-                                               uint32_t kappa_c, uint32_t kappa, uint32_t pmask, int force_radix,
-                                               uint32_t* radix_counter, const float* lds_chunk = nullptr,
-                                               uint32_t* group_ok = nullptr, int group = 0) {
-    sh.cand[tid] = 0;
-    if (tid < 2) sh.cand[kCandCap + tid] = 0;
-    if (tid < 16) sh.bucket[tid] = 0;
-    if (tid < 4) sh.wmax[tid] = 0;
-    if (tid == 0) sh.ncand = 0;
-
-    bool selected_by_filter = false;
+// reached by all groups alike, so the groups agree on the path: if one needs the general path, all take it.
+template <bool FROM_LDS = false>
+__device__ __forceinline__ Threshold find_threshold(SelectShared& sh, const float (&x)[16], int tid, int lane, int wave,
+                                                    uint32_t kappa_c, uint32_t kappa, uint32_t pmask, bool edge,
+                                                    int force_radix, uint32_t* radix_counter, const float* lds_chunk = nullptr,
+                                                    uint32_t* group_ok = nullptr, int group = 0) {
+    Threshold th = {0u, 4095u, 0u, 0u};
     if (kappa <= (uint32_t)kFilterKappaMax && !force_radix) {
         // ---- candidate filter: a lower bound T0 of the threshold from the lane maxima ----
-        uint32_t key[16];
-        if (lds_chunk) {
+        uint32_t bits[16];
+        if constexpr (FROM_LDS) {
 #pragma unroll
             for (int s = 0; s < 4; ++s) {
                 const float4 v = *reinterpret_cast<const float4*>(lds_chunk + s * 1024 + tid * 4);
-                key[4 * s] = __float_as_uint(v.x) & 0x7FFFFFFFu;
-                key[4 * s + 1] = __float_as_uint(v.y) & 0x7FFFFFFFu;
-                key[4 * s + 2] = __float_as_uint(v.z) & 0x7FFFFFFFu;
-                key[4 * s + 3] = __float_as_uint(v.w) & 0x7FFFFFFFu;
+                bits[4 * s] = __float_as_uint(v.x);
+                bits[4 * s + 1] = __float_as_uint(v.y);
+                bits[4 * s + 2] = __float_as_uint(v.z);
+                bits[4 * s + 3] = __float_as_uint(v.w);
             }
         } else {
 #pragma unroll
-            for (int el = 0; el < 16; ++el) key[el] = __float_as_uint(x[el]) & 0x7FFFFFFFu;
+            for (int el = 0; el < 16; ++el) bits[el] = __float_as_uint(x[el]);
         }
+        auto key = [&](int el) { return bits[el] & 0x7FFFFFFFu; };
         uint32_t tmax = 0;
 #pragma unroll
-        for (int el = 0; el < 16; ++el) tmax = ((pmask >> el) & 1u) && key[el] > tmax ? key[el] : tmax;
-        // Largest X (low 10 bits zero) with at least m lanes of this wave that hold a present element
+        for (int el = 0; el < 16; ++el) tmax = key(el) > tmax ? key(el) : tmax;      // (absent ones are 0)
+        // Largest X (low 13 bits zero) with at least m = kappa_c / 4 lanes of this wave that hold a present element
         // >= X.  Those elements are distinct, so over four waves at least 4*m >= kappa_c elements are
         // >= min X: the threshold cannot be below it.  A wave with fewer than m non-empty lanes (edge
         // chunks) leaves X = 0, which makes every present element a candidate.
-        const uint32_t m = (kappa_c + 3) >> 2;
-        uint32_t X = 0;
+        auto reached_by = [&](uint32_t lanes) {               // two bits a step: the chain of steps is what it costs
+            uint32_t X = 0;
 #pragma unroll
-        for (int b = 30; b >= 10; --b) {
-            uint32_t t = X | (1u << b);
-            uint32_t cnt = (uint32_t)__popcll(__ballot(pmask != 0 && tmax >= t));
-            X = cnt >= m ? t : X;
+            for (int b = 29; b >= 13; b -= 2) {
+                const uint32_t t1 = X + (1u << b), t2 = X + (2u << b), t3 = X + (3u << b);
+                const uint32_t c1 = (uint32_t)__popcll(__ballot(tmax >= t1));
+                const uint32_t c2 = (uint32_t)__popcll(__ballot(tmax >= t2));
+                const uint32_t c3 = (uint32_t)__popcll(__ballot(tmax >= t3));
+                X = c3 >= lanes ? t3 : (c2 >= lanes ? t2 : (c1 >= lanes ? t1 : X));
+            }
+            return X;
+        };
+        const uint32_t X = reached_by((kappa_c + 3) >> 2);
+        const uint32_t wave_max = wave_extreme_u32<true>(tmax);
+        // Edge chunks may leave waves with too few elements for that; a wave that alone holds kappa_c lanes with an
+        // element >= Y bounds the threshold as well.
+        const uint32_t Y = edge ? reached_by(kappa_c) : 0u;
+        if (lane == 0) {
+            sh.t0[wave] = X;
+            sh.wmax[wave] = wave_max;
+            if (edge) sh.t1[wave] = Y;
         }
-        if (lane == 0) sh.t0[wave] = X;
         __syncthreads();
         uint32_t T0 = sh.t0[0];
         T0 = sh.t0[1] < T0 ? sh.t0[1] : T0;
         T0 = sh.t0[2] < T0 ? sh.t0[2] : T0;
         T0 = sh.t0[3] < T0 ? sh.t0[3] : T0;
+        if (edge) {
+#pragma unroll
+            for (int w = 0; w < 4; ++w) T0 = sh.t1[w] > T0 ? sh.t1[w] : T0;
+        }
+        T0 = __builtin_amdgcn_readfirstlane(T0);
+        uint32_t amax = sh.wmax[0];
+        amax = sh.wmax[1] > amax ? sh.wmax[1] : amax;
+        amax = sh.wmax[2] > amax ? sh.wmax[2] : amax;
+        amax = sh.wmax[3] > amax ? sh.wmax[3] : amax;
+        th.amax = __builtin_amdgcn_readfirstlane(amax);
 
-        // ---- compact the candidates (present, key >= T0) into LDS, wave by wave ----
-        uint64_t msk[16];
-        uint32_t cnt = 0;
+        // ---- compact the candidates (present, key >= T0) into LDS in index order, i.e. by slot, wave, lane, element.
+        // Every lane collects its candidates in a mask; positions inside a slot of a wave come from a sum over the
+        // lanes (slots 0, 1 and 2, 3 packed into one word each), those of the slots from the counts of all waves. ----
+        uint32_t mask = 0;
 #pragma unroll
-        for (int el = 0; el < 16; ++el) {
-            msk[el] = __ballot(((pmask >> el) & 1u) && key[el] >= T0);
-            cnt += (uint32_t)__popcll(msk[el]);
-        }
-        uint32_t base = 0;
-        if (lane == 0) base = atomicAdd(&sh.ncand, cnt);
-        base = __builtin_amdgcn_readfirstlane(base);
-        if (base + cnt <= (uint32_t)kCandCap) {
-            uint32_t run = base;
-#pragma unroll
-            for (int el = 0; el < 16; ++el) {
-                if (msk[el] != 0) {
-                    if (((pmask >> el) & 1u) && key[el] >= T0) {
-                        uint32_t idx = (el >> 2) * 1024 + tid * 4 + (el & 3);
-                        sh.cand[run + lanes_below(msk[el])] = ((uint64_t)key[el] << 12) | (uint64_t)(4095u - idx);
-                    }
-                    run += (uint32_t)__popcll(msk[el]);
-                }
-            }
-        }
+        for (int el = 15; el >= 0; --el) mask = mask + mask + (key(el) >= T0 ? 1u : 0u);
+        mask &= pmask;
+        const uint32_t n01 = (uint32_t)__popc(mask & 0xFu) | ((uint32_t)__popc(mask & 0xF0u) << 16);
+        const uint32_t n23 = (uint32_t)__popc(mask & 0xF00u) | ((uint32_t)__popc(mask & 0xF000u) << 16);
+        const uint32_t s01 = wave_inclusive_sum(n01), s23 = wave_inclusive_sum(n23);
+        if (lane == 63)
+            *reinterpret_cast<uint4*>(sh.count[wave]) = make_uint4(s01 & 0xFFFFu, s01 >> 16, s23 & 0xFFFFu, s23 >> 16);
         __syncthreads();
-        const uint32_t n = sh.ncand;
+        uint32_t base[4], n = 0;
+        {
+            uint4 c[4];
+#pragma unroll
+            for (int w = 0; w < 4; ++w) c[w] = *reinterpret_cast<const uint4*>(sh.count[w]);
+            auto slot = [&](uint32_t c0, uint32_t c1, uint32_t c2, uint32_t c3) {
+                const uint32_t first = n + (wave > 0 ? c0 : 0u) + (wave > 1 ? c1 : 0u) + (wave > 2 ? c2 : 0u);
+                n += c0 + c1 + c2 + c3;
+                return first;
+            };
+            base[0] = slot(c[0].x, c[1].x, c[2].x, c[3].x);
+            base[1] = slot(c[0].y, c[1].y, c[2].y, c[3].y);
+            base[2] = slot(c[0].z, c[1].z, c[2].z, c[3].z);
+            base[3] = slot(c[0].w, c[1].w, c[2].w, c[3].w);
+        }
+        n = __builtin_amdgcn_readfirstlane(n);
         if (n <= (uint32_t)kCandCap) {
-            // ---- exact rank of every candidate among the candidates (composites are distinct) ----
-            if ((uint32_t)tid < n) {
-                const uint64_t mine = sh.cand[tid];
-                uint32_t rank = 0;
-                for (uint32_t i = 0; i < n; i += 2) {
-                    uint64_t c0 = sh.cand[i], c1 = sh.cand[i + 1];
-                    rank += (c0 > mine ? 1u : 0u) + (c1 > mine ? 1u : 0u);
+            const uint32_t at01 = s01 - n01 + (base[0] | (base[1] << 16)), at23 = s23 - n23 + (base[2] | (base[3] << 16));
+            for (uint32_t left = mask; __any(left != 0); left &= left - 1) {   // as many rounds as a lane has candidates
+                if (left != 0) {
+                    const uint32_t el = (uint32_t)__ffs((int)left) - 1, slot = el >> 2;
+                    auto pick = [](bool second, uint32_t a, uint32_t b) { return second ? b : a; };
+                    uint32_t v[8];                                             // bits[el], by halving
+#pragma unroll
+                    for (int i = 0; i < 8; ++i) v[i] = pick(el & 8u, bits[i], bits[8 + i]);
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) v[i] = pick(el & 4u, v[i], v[4 + i]);
+                    v[0] = pick(el & 2u, v[0], v[2]);
+                    v[1] = pick(el & 2u, v[1], v[3]);
+                    v[0] = pick(el & 1u, v[0], v[1]);
+                    const uint32_t lower = mask & ((1u << el) - 1u) & (0xFu << (4 * slot));
+                    const uint32_t pos = (((slot & 2u) ? at23 : at01) >> (16 * (slot & 1u)) & 0xFFFFu) + (uint32_t)__popc(lower);
+                    sh.cand[pos] = make_uint2(v[0], slot * 1024u + (uint32_t)tid * 4u + (el & 3u));
                 }
-                if (rank == kappa_c - 1) sh.thr = mine;
-                if (rank == 0) sh.wmax[0] = (uint32_t)(mine >> 12);
-                if (rank < kappa_c) atomicAdd(&sh.bucket[(4095u - ((uint32_t)mine & 4095u)) >> 8], 1u);
             }
-            selected_by_filter = true;
+            th.n_cand = n;
+        }
+        if (FROM_LDS && tid == 0) group_ok[group] = th.n_cand != 0 ? 1u : 0u;
+        __syncthreads();
+        if (FROM_LDS && (group_ok[0] & group_ok[1] & group_ok[2] & group_ok[3]) == 0) th.n_cand = 0;
+        if (th.n_cand != 0) {
+            if (n <= 128) solve_candidates<2>(sh, lane, n, kappa_c, T0, th);
+            else if (n <= 256) solve_candidates<4>(sh, lane, n, kappa_c, T0, th);
+            else solve_candidates<7>(sh, lane, n, kappa_c, T0, th);
         }
     }
-    if (group_ok) {
-        if (tid == 0) group_ok[group] = selected_by_filter ? 1u : 0u;
-        __syncthreads();
-        selected_by_filter = (group_ok[0] & group_ok[1] & group_ok[2] & group_ok[3]) != 0;
-    } else {
-        __syncthreads();
-    }
-    if (!selected_by_filter) {
-        if (lds_chunk) {
-            // (the index is made opaque so that these reads are not merged with the caller's earlier ones, which
+    if (th.n_cand == 0) {
+        if constexpr (FROM_LDS) {
+            // (the index is made opaque so that these reads are not merged with the earlier ones, which
             // would keep all sixteen values in registers from there to here)
             int t = tid;
             asm volatile("" : "+v"(t));
@@ -410,85 +594,106 @@ __device__ __forceinline__ void find_threshold(SelectShared& sh, const float (&x
                 const float4 v = *reinterpret_cast<const float4*>(lds_chunk + s * 1024 + t * 4);
                 y[4 * s] = v.x; y[4 * s + 1] = v.y; y[4 * s + 2] = v.z; y[4 * s + 3] = v.w;
             }
-            radix_select(sh, y, tid, pmask, kappa_c);
+            general_select(sh, y, tid, lane, wave, pmask, kappa_c, th);
         } else {
-            radix_select(sh, x, tid, pmask, kappa_c);
+            general_select(sh, x, tid, lane, wave, pmask, kappa_c, th);
         }
         if (radix_counter && tid == 0) atomicAdd(radix_counter, 1u);      // diagnostic: chunks on the general path
     }
+    return th;
 }
 
-// Quantiser, packing and residual of the chunk held in x[16], given the threshold that find_threshold published
-// in `sh`.  On return x holds the new error-feedback values; the chunk's pairs, its levels (or sent values) and
-// its padding have been written.  It ends with every lane past its last read of `sh`, but callers that reuse
-// `sh` must place a barrier first.
-// With SUM, every sent value is also added to sum[index in the chunk] (LDS; an element is only ever touched by
-// the lane that holds it, so replicas that follow each other in one workgroup need no synchronisation for it).
+// Quantiser, packing and residual of the chunk held in x[16], given the threshold that find_threshold returned.
+// On return x holds the new error-feedback values; the chunk's pairs, its levels (or sent values) and its padding have
+// been written.  Callers that reuse `sh` must place a barrier first.
+// With SUM, every sent value is also added to sum[index in the chunk] (LDS).  Any lane may do that: replicas that
+// follow each other in one workgroup are separated by a barrier.
+// The candidates of the filter are in index order, so the message is written by the lanes that hold a candidate: an
+// entry's position is the number of kept candidates before it.  The lanes that hold the elements only form the
+// residual, without a branch.  After the general path there is no such list, and the elements' lanes write the
+// message themselves (positions from the bucket counts and ballots).
 template <int QUANT, bool SUM>
-__device__ __forceinline__ void quantise_pack_sum(const SelectShared& sh, float (&x)[16], float* sum, int tid,
-                                                  int wave, uint32_t kappa_c, uint32_t kappa, uint32_t pmask,
-                                                  uint16_t* __restrict__ pairs_c, float* __restrict__ values_c,
-                                                  float* __restrict__ scales_c) {
-    // ---- final pass: selection predicate, output positions, quantise, pack, residual ----
-    const uint64_t thr = sh.thr;
-    const uint32_t T = (uint32_t)(thr >> 12);
-    const uint32_t idxT = 4095u - ((uint32_t)thr & 4095u);
-    uint32_t amax_k = sh.wmax[0];
-    amax_k = sh.wmax[1] > amax_k ? sh.wmax[1] : amax_k;
-    amax_k = sh.wmax[2] > amax_k ? sh.wmax[2] : amax_k;
-    amax_k = sh.wmax[3] > amax_k ? sh.wmax[3] : amax_k;
+__device__ __forceinline__ void quantise_pack_sum(const SelectShared& sh, const Threshold& th, float (&x)[16], float* sum,
+                                                  int tid, int lane, int wave, uint32_t kappa_c, uint32_t kappa,
+                                                  uint32_t pmask, uint16_t* __restrict__ pairs_c,
+                                                  float* __restrict__ values_c, float* __restrict__ scales_c) {
+    const uint32_t T = th.T, idxT = th.idxT;
     // The smallest selected magnitude is the threshold key itself; the largest is the chunk maximum.
-    const float amin = __uint_as_float(T), amax = __uint_as_float(amax_k);
+    const float amin = __uint_as_float(T), amax = __uint_as_float(th.amax);
     const float dd = __fsub_rn(amax, amin);
     const float lo = __fadd_rn(amin, __fmul_rn(0.25f, dd));
     const float tau = __fadd_rn(amin, __fmul_rn(0.5f, dd));
     const float hi = __fadd_rn(amin, __fmul_rn(0.75f, dd));
     const uint32_t tau_bits = __float_as_uint(tau);
+    auto kept = [&](uint32_t key, uint32_t idx) { return key > T || (key == T && idx <= idxT); };
+    auto decoded = [&](uint32_t bits) {                       // of a kept entry
+        const uint32_t upper = (bits & 0x7FFFFFFFu) >= tau_bits ? 1u : 0u;
+        return __builtin_copysignf(upper ? hi : lo, __uint_as_float(bits));
+    };
+    auto write_entry = [&](uint32_t pos, uint32_t bits, uint32_t idx) {
+        if (QUANT == SPLC_QUANT_2BIT) {
+            const uint32_t upper = (bits & 0x7FFFFFFFu) >= tau_bits ? 1u : 0u;
+            pairs_c[pos] = (uint16_t)(idx | ((((bits >> 31) << 1) | upper) << 12));
+            if (SUM) sum[idx] = __fadd_rn(sum[idx], decoded(bits));
+        } else {
+            pairs_c[pos] = (uint16_t)idx;
+            values_c[pos] = __uint_as_float(bits);
+            if (SUM) sum[idx] = __fadd_rn(sum[idx], __uint_as_float(bits));
+        }
+    };
 
-    uint32_t base_of_slot[4];
-    {
-        uint32_t run = 0;
+    if (th.n_cand != 0) {
+        uint32_t pos = 0;
+        for (uint32_t j = 0; 64u * j < th.n_cand; ++j) {      // 64 candidates at a time, written by the waves in turn
+            const uint32_t i = 64u * j + (uint32_t)lane;
+            const uint2 c = sh.cand[i];
+            const bool mine = i < th.n_cand && kept(c.x & 0x7FFFFFFFu, c.y);
+            const uint64_t m = __ballot(mine);
+            if (mine && (j & 3u) == (uint32_t)wave) write_entry(pos + lanes_below(m), c.x, c.y);
+            pos += (uint32_t)__popcll(m);
+        }
+    } else {
+        uint32_t base_of_slot[4], run = 0;
 #pragma unroll
         for (int b = 0; b < 16; ++b) {
             if ((b & 3) == wave) base_of_slot[b >> 2] = run;
             run += sh.bucket[b];
         }
-    }
 #pragma unroll
-    for (int s = 0; s < 4; ++s) {
-        bool sel[4];
-        uint64_t m4[4];
+        for (int s = 0; s < 4; ++s) {
+            bool sel[4];
+            uint64_t m4[4];
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            uint32_t idx = s * 1024 + tid * 4 + j;
-            uint32_t key = __float_as_uint(x[4 * s + j]) & 0x7FFFFFFFu;
-            sel[j] = (pmask & (1u << (4 * s + j))) && (key > T || (key == T && idx <= idxT));
-            m4[j] = __ballot(sel[j]);
-        }
-        if ((m4[0] | m4[1] | m4[2] | m4[3]) != 0) {
+            for (int j = 0; j < 4; ++j) {
+                const uint32_t idx = s * 1024 + tid * 4 + j;
+                sel[j] = (pmask & (1u << (4 * s + j))) && kept(__float_as_uint(x[4 * s + j]) & 0x7FFFFFFFu, idx);
+                m4[j] = __ballot(sel[j]);
+            }
             uint32_t pos = base_of_slot[s] + lanes_below(m4[0]) + lanes_below(m4[1]) + lanes_below(m4[2]) +
                            lanes_below(m4[3]);
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
-                if (sel[j]) {
-                    uint32_t idx = s * 1024 + tid * 4 + j;
-                    uint32_t bits = __float_as_uint(x[4 * s + j]);
-                    if (QUANT == SPLC_QUANT_2BIT) {
-                        uint32_t upper = (bits & 0x7FFFFFFFu) >= tau_bits ? 1u : 0u;
-                        uint32_t sign = bits >> 31;
-                        float q = __uint_as_float(__float_as_uint(upper ? hi : lo) | (bits & 0x80000000u));
-                        pairs_c[pos] = (uint16_t)(idx | (((sign << 1) | upper) << 12));
-                        if (SUM) sum[idx] = __fadd_rn(sum[idx], q);
-                        x[4 * s + j] = __fsub_rn(x[4 * s + j], q);
-                    } else {
-                        pairs_c[pos] = (uint16_t)idx;
-                        values_c[pos] = x[4 * s + j];
-                        if (SUM) sum[idx] = __fadd_rn(sum[idx], x[4 * s + j]);
-                        x[4 * s + j] = __fsub_rn(x[4 * s + j], x[4 * s + j]);
-                    }
-                    ++pos;
-                }
+                if (sel[j]) write_entry(pos++, __float_as_uint(x[4 * s + j]), s * 1024 + tid * 4 + j);
             }
+        }
+    }
+    // (absent elements may be changed too; nobody stores them)
+    auto residual = [&](int el, bool sel) {
+        const float rest = QUANT == SPLC_QUANT_2BIT ? __fsub_rn(x[el], decoded(__float_as_uint(x[el])))
+                                                    : __fsub_rn(x[el], x[el]);
+        x[el] = sel ? rest : x[el];
+    };
+    if (idxT == 4095u) {                                      // every present element with key T is kept
+#pragma unroll
+        for (int el = 0; el < 16; ++el)
+            residual(el, (__float_as_uint(x[el]) & 0x7FFFFFFFu) >= T);
+    } else {
+        const int at4 = tid * 4;
+#pragma unroll
+        for (int el = 0; el < 16; ++el) {
+            const uint32_t key = __float_as_uint(x[el]) & 0x7FFFFFFFu;
+            const bool first = at4 <= (int)idxT - ((el >> 2) * 1024 + (el & 3));          // index <= idxT
+            residual(el, key > T || (key == T && first));
         }
     }
     for (uint32_t t = kappa_c + tid; t < kappa; t += kThreads) {
@@ -501,14 +706,6 @@ __device__ __forceinline__ void quantise_pack_sum(const SelectShared& sh, float 
     }
 }
 
-template <int QUANT>
-__device__ __forceinline__ void quantise_pack(const SelectShared& sh, float (&x)[16], int tid, int wave,
-                                              uint32_t kappa_c, uint32_t kappa, uint32_t pmask,
-                                              uint16_t* __restrict__ pairs_c, float* __restrict__ values_c,
-                                              float* __restrict__ scales_c) {
-    quantise_pack_sum<QUANT, false>(sh, x, nullptr, tid, wave, kappa_c, kappa, pmask, pairs_c, values_c, scales_c);
-}
-
 // Both steps for a chunk that stays in registers throughout.
 template <int QUANT>
 __device__ __forceinline__ void select_quantise_pack(SelectShared& sh, float (&x)[16], int tid, int lane, int wave,
@@ -516,8 +713,10 @@ __device__ __forceinline__ void select_quantise_pack(SelectShared& sh, float (&x
                                                      uint32_t* radix_counter, uint16_t* __restrict__ pairs_c,
                                                      float* __restrict__ values_c, float* __restrict__ scales_c) {
     const uint32_t kappa_c = kappa < n_c ? kappa : n_c;
-    find_threshold(sh, x, tid, lane, wave, kappa_c, kappa, pmask, force_radix, radix_counter);
-    quantise_pack<QUANT>(sh, x, tid, wave, kappa_c, kappa, pmask, pairs_c, values_c, scales_c);
+    const Threshold th = find_threshold(sh, x, tid, lane, wave, kappa_c, kappa, pmask, n_c != (uint32_t)kChunk, force_radix,
+                                        radix_counter);
+    quantise_pack_sum<QUANT, false>(sh, th, x, nullptr, tid, lane, wave, kappa_c, kappa, pmask, pairs_c, values_c,
+                                    scales_c);
 }
 
 // The error-feedback buffer is rewritten densely (line 4 of the update equations).
@@ -530,19 +729,23 @@ __device__ __forceinline__ void store_ef(float* __restrict__ e, const ChunkDesc&
         for (int s = 0; s < 4; ++s)
             stream_store4(vec_at(pe, d, tid, s), make_float4(x[4 * s], x[4 * s + 1], x[4 * s + 2], x[4 * s + 3]));
     } else {
+        // from an opaque copy of the lane number: the sixteen offsets of the loads are not kept for these stores
+        int t = tid;
+        asm volatile("" : "+v"(t));
 #pragma unroll
         for (int el = 0; el < 16; ++el) {
-            const uint32_t idx = (el >> 2) * 1024 + tid * 4 + (el & 3);
-            if (pmask & (1u << el)) pe[elem_of(d, idx)] = x[el];
+            const uint32_t idx = (el >> 2) * 1024 + t * 4 + (el & 3);
+            if (pmask & (1u << el)) *elem_at(pe, elem_of(d, idx)) = x[el];
         }
     }
 }
 
 // Lines 1-4 of the update equations, one replica, one chunk per workgroup.
-// VEC = true: the chunk is complete and allows 4-element vector accesses (the streaming path);
-// VEC = false: edge chunks and rows that start at odd bf16 elements, element by element.
-template <int MODE, int QUANT, bool VEC>
-__device__ __forceinline__ void compress_body(SelectShared& sh, const ChunkDesc* __restrict__ chunks,
+// vec: the chunk is complete and allows 4-element vector accesses (the streaming path); else edge chunks and rows that
+// start at odd bf16 elements, element by element.  Only the loads and stores differ: one copy of the selection keeps
+// the code, which a cold launch fetches from memory, short.
+template <int MODE, int QUANT>
+__device__ __forceinline__ void compress_body(SelectShared& sh, bool vec, const ChunkDesc* __restrict__ chunks,
                                               const void* const* __restrict__ src_a,
                                               const void* const* __restrict__ src_b,
                                               float* const* __restrict__ ef_tab, float beta, uint32_t kappa,
@@ -557,14 +760,18 @@ __device__ __forceinline__ void compress_body(SelectShared& sh, const ChunkDesc*
     const void* pb = MODE == MODE_PARAMS_F32 ? src_b[d.tensor] : nullptr;
     float* pe = ef_tab[d.tensor];
 
-    const uint32_t pmask = VEC ? 0xFFFFu : present_mask(d, tid);
-    const uint32_t n_c = VEC ? (uint32_t)kChunk : d.n_c;
+    uint32_t pmask = 0xFFFFu;
     float x[16];
-    if (VEC) load_fold_full<MODE>(pa, pb, pe, d, tid, beta, x);
-    else load_fold_scalar<MODE>(pa, pb, pe, d, tid, beta, pmask, x);
-    select_quantise_pack<QUANT>(sh, x, tid, lane, wave, n_c, pmask, kappa, force_radix, radix_counter,
+    if (vec) {
+        load_fold_full<MODE>(pa, pb, pe, d, tid, beta, x);
+    } else {
+        pmask = present_mask(d, tid);
+        load_fold_scalar<MODE>(pa, pb, pe, d, tid, beta, pmask, x);
+    }
+    select_quantise_pack<QUANT>(sh, x, tid, lane, wave, d.n_c, pmask, kappa, force_radix, radix_counter,
                                 pairs_out + c * kappa, aux_out + c * kappa, aux_out + 2 * c);
-    store_ef<VEC>(pe, d, tid, pmask, x);
+    if (vec) store_ef<true>(pe, d, tid, pmask, x);
+    else store_ef<false>(pe, d, tid, pmask, x);
 }
 
 // The chunk table lists the n_gen element-wise chunks first: workgroups from n_gen on take the
@@ -579,12 +786,8 @@ __global__ __launch_bounds__(kThreads) void compress_kernel(const ChunkDesc* __r
                                                             uint16_t* __restrict__ pairs_out,
                                                             float* __restrict__ aux_out) {
     __shared__ __align__(16) SelectShared sh;
-    if (blockIdx.x >= n_gen)
-        compress_body<MODE, QUANT, true>(sh, chunks, src_a, src_b, ef_tab, beta, kappa, force_radix, radix_counter,
-                                         pairs_out, aux_out);
-    else
-        compress_body<MODE, QUANT, false>(sh, chunks, src_a, src_b, ef_tab, beta, kappa, force_radix, radix_counter,
-                                          pairs_out, aux_out);
+    compress_body<MODE, QUANT>(sh, blockIdx.x >= n_gen, chunks, src_a, src_b, ef_tab, beta, kappa, force_radix,
+                               radix_counter, pairs_out, aux_out);
 }
 
 // ---- 64 x 64 tiles, four at a time ("strip"): rows of a strip are 1024 contiguous bytes ----
@@ -725,11 +928,11 @@ __global__ __launch_bounds__(kStripThreads, 8) void compress_strip_kernel(const 
         // The threshold search reads the tile from LDS by itself (it needs only the magnitudes); the values are
         // fetched afterwards: 64 registers per lane (two of these workgroups per compute unit) do not hold values
         // and keys side by side.
-        find_threshold(sm.sel[group], x, gtid, lane, gwave, kappa_c, kappa, 0xFFFFu, force_radix, radix_counter,
-                       &sm.tile[group][0], sm.group_ok, group);
+        const Threshold th = find_threshold<true>(sm.sel[group], x, gtid, lane, gwave, kappa_c, kappa, 0xFFFFu, false,
+                                            force_radix, radix_counter, &sm.tile[group][0], sm.group_ok, group);
         fetch_tile();
-        quantise_pack<QUANT>(sm.sel[group], x, gtid, gwave, kappa_c, kappa, 0xFFFFu, pairs_out + c * kappa,
-                             aux_out + c * kappa, aux_out + 2 * c);
+        quantise_pack_sum<QUANT, false>(sm.sel[group], th, x, nullptr, gtid, lane, gwave, kappa_c, kappa, 0xFFFFu,
+                                        pairs_out + c * kappa, aux_out + c * kappa, aux_out + 2 * c);
 #pragma unroll
         for (int s = 0; s < 4; ++s)
             *reinterpret_cast<float4*>(&sm.tile[group][s * 1024 + gtid * 4]) =
@@ -788,7 +991,8 @@ __device__ __forceinline__ void compress_batch_body(SelectShared& sh, float* so,
 #pragma unroll
         for (int el = 0; el < 16; ++el) {
             const uint32_t idx = (el >> 2) * 1024 + tid * 4 + (el & 3);
-            so[idx] = (pmask0 & (1u << el)) ? po[elem_of(d, idx)] : 0.f;
+            const float v = *elem_at(po, (pmask0 & (1u << el)) ? elem_of(d, idx) : 0u);
+            so[idx] = (pmask0 & (1u << el)) ? v : 0.f;
         }
     }
     float4* sum4 = reinterpret_cast<float4*>(sum);
@@ -821,15 +1025,29 @@ __device__ __forceinline__ void compress_batch_body(SelectShared& sh, float* so,
             }
         } else {
 #pragma unroll
-            for (int el = 0; el < 16; ++el) {
-                const uint32_t idx = (el >> 2) * 1024 + t * 4 + (el & 3);
-                const uint32_t at = elem_of(d, idx);
-                x[el] = (pmask & (1u << el)) ? fold(beta, pe[d.offset + at], __fsub_rn(so[idx], pl[at])) : 0.f;
+            for (int half = 0; half < 16; half += 8) {    // absent elements: as in load_fold_scalar
+                float lv[8], ev[8];
+#pragma unroll
+                for (int i = 0; i < 8; ++i) {
+                    const int el = half + i;
+                    const uint32_t idx = (el >> 2) * 1024 + t * 4 + (el & 3);
+                    const uint32_t at = (pmask & (1u << el)) ? elem_of(d, idx) : 0u;
+                    lv[i] = *elem_at(pl, at);
+                    ev[i] = *elem_at(pe + d.offset, at);
+                }
+#pragma unroll
+                for (int i = 0; i < 8; ++i) {
+                    const int el = half + i;
+                    const float v = fold(beta, ev[i], __fsub_rn(so[(el >> 2) * 1024 + t * 4 + (el & 3)], lv[i]));
+                    x[el] = (pmask & (1u << el)) ? v : 0.f;
+                }
+                __builtin_amdgcn_sched_barrier(0);
             }
         }
         float* aux_r = aux_tab[r];
-        find_threshold(sh, x, t, t & 63, wave, kappa_c, kappa, pmask, force_radix, radix_counter);
-        quantise_pack_sum<QUANT, STEP>(sh, x, sum, t, wave, kappa_c, kappa, pmask, pairs_tab[r] + c * kappa,
+        const Threshold th = find_threshold(sh, x, t, t & 63, wave, kappa_c, kappa, pmask, !VEC, force_radix,
+                                            radix_counter);
+        quantise_pack_sum<QUANT, STEP>(sh, th, x, sum, t, t & 63, wave, kappa_c, kappa, pmask, pairs_tab[r] + c * kappa,
                                        aux_r + c * kappa, aux_r + 2 * c);
         store_ef<VEC>(pe, d, t, pmask, x);
         __syncthreads();          // every lane is done with `sh` before the next replica re-initialises it
@@ -1070,13 +1288,20 @@ __device__ __forceinline__ void aggregate_body(float* acc, const ChunkDesc* __re
             }
         }
     } else {
-        for (uint32_t idx = tid; idx < (uint32_t)kChunk; idx += kThreads) {
+        float te[16];
+        if (UPDATE) {
+#pragma unroll
+            for (int i = 0; i < 16; ++i) te[i] = *elem_at(th, present_or_first(d, tid + kThreads * i));
+        }
+#pragma unroll
+        for (int i = 0; i < 16; ++i) {
+            const uint32_t idx = tid + kThreads * i;
             if (!present(d, idx)) continue;
             const uint32_t at = elem_of(d, idx);
             const float v = __fdiv_rn(acc[idx], m);
             if (po) po[at] = v;
             if (UPDATE) {
-                const float t = __fsub_rn(th[at], __fmul_rn(eta, v));
+                const float t = __fsub_rn(te[i], __fmul_rn(eta, v));
                 th[at] = t;
                 for (int r = 0; r < n_reset; ++r) reset_tab[(size_t)r * n_tensors + d.tensor][d.offset + at] = t;
             }
@@ -1191,10 +1416,17 @@ __device__ __forceinline__ void outer_update_body(const ChunkDesc* __restrict__ 
             stream_store4(vec_at(th, d, tid, s), t[s]);
         }
     } else {
-        for (uint32_t idx = tid; idx < (uint32_t)kChunk; idx += kThreads) {
-            if (!present(d, idx)) continue;
-            const uint32_t at = elem_of(d, idx);
-            th[at] = __fsub_rn(th[at], __fmul_rn(eta, db[at]));
+        float t[16], g[16];
+#pragma unroll
+        for (int i = 0; i < 16; ++i) {
+            const uint32_t at = present_or_first(d, tid + kThreads * i);
+            t[i] = *elem_at(th, at);
+            g[i] = *elem_at(db, at);
+        }
+#pragma unroll
+        for (int i = 0; i < 16; ++i) {
+            const uint32_t idx = tid + kThreads * i;
+            if (present(d, idx)) th[elem_of(d, idx)] = __fsub_rn(t[i], __fmul_rn(eta, g[i]));
         }
     }
 }
@@ -1305,6 +1537,20 @@ unsigned gen_entries(const sparseloco_plan* plan, bool bf16_source) {
     return (unsigned)(bf16_source ? plan->n_gen_bf16 : plan->n_gen_f32);
 }
 
+// Large plans stream far more than the last-level cache holds, and there fewer workgroups per compute unit than would
+// fit keep the memory busier (fewer streams in flight at once).  Their launches reserve LDS so that only
+// `groups_per_unit` fit.  Measured, all that fit -> reserved:
+//   compress, 3: 16,384 chunks, kappa 32 / 128: 173.3 / 174.4 -> 166.4 / 169.2 us; 37,105: 396.8 / 395.5 -> 377.5 /
+//     376.6; 8192: 86.8 / 86.9 -> 84.9 / 87.0; but 4096: 43.3 / 43.7 -> 44.1 / 46.1 (a few rounds of workgroups only, where
+//     latency counts).  With 2, 4: slower (0.9B model, one compress + aggregate + update: 5.15, 4.86 ms; 3: 4.72).
+//   one-launch step, 3: 150M parameters, 8 replicas: 2938 -> 2889 us; with 2: 3138.
+//   outer update, 2: 0.9B model, whole step 4.72 -> 4.65 ms; 24,000 chunks: 184.2 -> 182.7 us; 8192: 61.9 -> 62.3.
+constexpr int64_t kStreamingChunks = 8192, kStreamingChunksUpdate = 24000;
+unsigned reserve_lds(int64_t chunks, int64_t from, int groups_per_unit, size_t used) {
+    const size_t share = 160 * 1024 / (size_t)groups_per_unit / 1280 * 1280;       // LDS is handed out in 1280-byte units
+    return chunks >= from && used < share ? (unsigned)(share - used) : 0u;
+}
+
 template <int MODE, int QUANT>
 void launch_compress(const sparseloco_plan* plan, const void* const* a, const void* const* b, float* const* ef,
                      float beta, uint16_t* pairs_out, float* aux_out, hipStream_t stream) {
@@ -1314,9 +1560,10 @@ void launch_compress(const sparseloco_plan* plan, const void* const* a, const vo
                            stream, plan->d_strips, a, b, ef, beta, (uint32_t)plan->kappa, force_radix,
                            plan->radix_counter, pairs_out, aux_out);
     if (plan->n_entries > 0)
-        hipLaunchKernelGGL((compress_kernel<MODE, QUANT>), dim3((unsigned)plan->n_entries), dim3(kThreads), 0, stream,
-                           plan->d_chunks, gen_entries(plan, MODE == MODE_DIRECT_BF16), a, b, ef, beta,
-                           (uint32_t)plan->kappa, force_radix, plan->radix_counter, pairs_out, aux_out);
+        hipLaunchKernelGGL((compress_kernel<MODE, QUANT>), dim3((unsigned)plan->n_entries), dim3(kThreads),
+                           reserve_lds(plan->n_entries, kStreamingChunks, 3, sizeof(SelectShared)), stream, plan->d_chunks,
+                           gen_entries(plan, MODE == MODE_DIRECT_BF16), a, b, ef, beta, (uint32_t)plan->kappa,
+                           force_radix, plan->radix_counter, pairs_out, aux_out);
 }
 
 template <int QUANT, bool STEP>
@@ -1325,7 +1572,9 @@ void launch_compress_batch(const sparseloco_plan* plan, int n_replicas, float* c
                            float* const* dbar, int reset, hipStream_t stream) {
     // Strips are taken tile by tile here: a strip entry is followed, in the device table, by nothing this kernel
     // could use, so the batched path walks the per-chunk view kept behind the update table.
-    hipLaunchKernelGGL((compress_batch_kernel<QUANT, STEP>), dim3((unsigned)plan->n_chunks), dim3(kThreads), 0, stream,
+    const size_t used = sizeof(SelectShared) + sizeof(float) * (kChunk + (STEP ? kChunk : 4));
+    hipLaunchKernelGGL((compress_batch_kernel<QUANT, STEP>), dim3((unsigned)plan->n_chunks), dim3(kThreads),
+                       reserve_lds(plan->n_chunks, kStreamingChunks, 3, used), stream,
                        plan->d_all, (unsigned)plan->n_all_gen, n_replicas, (uint32_t)plan->n_tensors, to, tl, ef,
                        beta, (uint32_t)plan->kappa, plan->select == SPLC_SELECT_RADIX ? 1 : 0, plan->radix_counter, pairs,
                        aux, eta, dbar, reset);
@@ -1862,8 +2111,8 @@ int sparseloco_outer_update(const sparseloco_plan* plan, const sparseloco_tensor
     if (theta_outer->n_sets != 1 || delta_bar->n_sets != 1 || !finite(outer_lr)) return SPLC_EINVAL;
     if ((rc = current_device_is(plan->device)) != SPLC_OK) return rc;
     if (plan->n_chunks == 0) return SPLC_OK;
-    hipLaunchKernelGGL(outer_update_kernel, dim3((unsigned)plan->n_update), dim3(kThreads), 0,
-                       static_cast<hipStream_t>(stream), plan->d_update, (unsigned)plan->n_update_gen,
+    hipLaunchKernelGGL(outer_update_kernel, dim3((unsigned)plan->n_update), dim3(kThreads),
+                       reserve_lds(plan->n_update, kStreamingChunksUpdate, 2, 0), static_cast<hipStream_t>(stream), plan->d_update, (unsigned)plan->n_update_gen,
                        set_table<float*>(theta_outer, 0), set_table<const float*>(delta_bar, 0), outer_lr);
     return hipGetLastError() == hipSuccess ? SPLC_OK : SPLC_EHIP;
 }

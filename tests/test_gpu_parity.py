@@ -598,3 +598,51 @@ def test_aggregate_survives_malformed_messages():
     for b, n in zip(bufs, numels):
         assert bool(torch.isfinite(b[:n]).all()) and bool((b[n:] == guard).all())
     plan.close()
+
+
+@pytest.mark.parametrize("quant", [True, False])
+@pytest.mark.parametrize("kappa", [1, 31, 64, 128, 200, 256])
+def test_selection_by_candidates_at_its_limits(kappa, quant):
+    """Candidate lists around 64, 128, 256 and 448 entries, ties at the cut (values on a coarse grid, and one value that
+    most elements share), chunks that leave waves of the workgroup few or no elements, and chunks whose candidates do
+    not fit, which take the general path: bit for bit against the oracle."""
+    rng = np.random.default_rng(kappa)
+    numels = [4096 * 2, 4095, 1025, 1024, 768, 500, 300, 257, 65, 33, 4096]
+    th = [(rng.standard_normal(n) * 0.02).astype(np.float32) for n in numels]
+    delta = []
+    for r in range(3):
+        one = []
+        for i, n in enumerate(numels):
+            x = rng.standard_normal(n).astype(np.float32)
+            if r == 1:
+                x = np.round(x * 8) / 8                              # many ties at every cut
+            elif r == 2:
+                x[rng.random(n) < 0.9] = 0.5                         # far more equal elements than candidates fit
+            one.append(x.astype(np.float32))
+        delta.append(one)
+    ef = [[np.zeros(n, np.float32) for n in numels] for _ in range(3)]
+    parity.check(parity.HostCase(th, ef, delta=delta), kappa=kappa, beta=0.95, lr=1.0, quant=quant,
+                 what="kappa %d" % kappa)
+
+
+@pytest.mark.parametrize("chunks", [8191, 8192, 24001])
+def test_plans_at_the_line_of_the_reserved_launches(chunks):
+    """Launches that reserve LDS (large plans) give what the others give: the same values in every chunk must come out
+    the same, whatever the size of the plan."""
+    g = torch.Generator(device="cuda").manual_seed(3)
+    th1, d1, e1 = (torch.randn(4096, generator=g, device="cuda") * s for s in (0.02, 1e-3, 1e-4))
+
+    def outer_step(n):
+        plan = B.Plan([4096 * n], 32)
+        th, ef = th1.repeat(n), e1.repeat(n)
+        tl = th - d1.repeat(n)
+        p, a = plan.message_buffers()
+        mean = torch.empty_like(th)
+        B.sparseloco_compress(plan, [ef], p, a, 0.95, theta_outer=[th], theta_local=[tl])
+        B.sparseloco_aggregate(plan, [p], [mean], aux=[a])
+        B.sparseloco_outer_update(plan, [th], [mean], 1.0)
+        torch.cuda.synchronize()
+        return p.view(n, -1), a.view(n, -1), ef.view(n, -1), mean.view(n, -1), th.view(n, -1)
+
+    for got, want in zip(outer_step(chunks), outer_step(1)):
+        assert torch.equal(got, want.expand_as(got))
