@@ -58,6 +58,8 @@ class SparseLoCoError(RuntimeError):
 
 def lib():
     global _lib
+    if _lib is not None:
+        return _lib
     if _lib is None:
         if not os.path.exists(LIB_PATH):
             raise RuntimeError("libsparseloco.so is not built; run `python -m paper_2601_02360_amd.build`")
@@ -105,8 +107,14 @@ def lib():
     return _lib
 
 
+# The current stream's handle without building a torch.cuda.Stream object (2 us of a call that otherwise takes 4).
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+
 def _stream(stream) -> Optional[int]:
     if stream is None:
+        if _raw_stream is not None and torch.cuda.is_initialized():
+            return _raw_stream(torch._C._cuda_getDevice()) or None
         stream = torch.cuda.current_stream()
     h = stream.cuda_stream if hasattr(stream, "cuda_stream") else int(stream)
     return h or None
@@ -148,6 +156,9 @@ def chunk_table(shapes: Sequence, tiled: bool):
 def _check_tensor(t, numel: int, dtype, what: str, device: bool = True):
     """Host-side refusal of anything that would turn into an out-of-bounds device access.  device=False leaves
     the device check to a later pass (lists are checked for sizes first, then for where they live)."""
+    if (isinstance(t, torch.Tensor) and t.numel() == numel and t.dtype == dtype and t.is_contiguous()
+            and (not device or t.is_cuda)):
+        return
     if numel == 0 and t is None:
         return
     if t is None:
@@ -276,6 +287,7 @@ class Plan:
         self.tiled = bool(tiled)
         self.kappa = int(kappa)
         self.quant = bool(quant)
+        self._num_chunks = int(lib().sparseloco_plan_num_chunks(self._h))
         self._temps = []           # bindings made on the fly by the convenience wrappers below
 
     def close(self):
@@ -298,7 +310,9 @@ class Plan:
 
     @property
     def num_chunks(self) -> int:
-        return int(lib().sparseloco_plan_num_chunks(self._h))
+        if not self._h.value:                    # closed
+            return int(lib().sparseloco_plan_num_chunks(self._h))
+        return self._num_chunks                  # a plan's chunks never change
 
     @property
     def num_params(self) -> int:
@@ -452,6 +466,13 @@ def sparseloco_stream_probe(pattern: int, a, b, c, sink, *, slots: int = 4, run:
 
 def _check_matrices(specs):
     """specs: (tensor, shape, name[, dtype]).  Shapes, dtypes and strides of all first, then where they live."""
+    for spec in specs:                           # one pass when all is well; the passes below find what is not
+        t = spec[0]
+        if not (isinstance(t, torch.Tensor) and t.shape == spec[1] and t.dtype == (spec[3] if len(spec) > 3 else torch.float32)
+                and t.is_contiguous() and t.is_cuda):
+            break
+    else:
+        return
     for spec in specs:
         t, shape, what = spec[:3]
         dtype = spec[3] if len(spec) > 3 else torch.float32
