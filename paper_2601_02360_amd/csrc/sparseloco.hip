@@ -1111,6 +1111,23 @@ __global__ __launch_bounds__(kThreads, 4) void compress_batch_kernel(const Chunk
                                                 reset);
 }
 
+// The same lines for all replicas of a small plan, one workgroup per chunk and replica: with few chunks the walk over
+// the replicas above is a serial chain on a chip that is mostly idle.
+template <int QUANT>
+__global__ __launch_bounds__(kThreads) void compress_each_kernel(const ChunkDesc* __restrict__ chunks, uint32_t n_gen,
+                                                                 uint32_t n_tensors, const void* const* __restrict__ to_tab,
+                                                                 const void* const* __restrict__ tl_tab,
+                                                                 float* const* __restrict__ ef_tab, float beta,
+                                                                 uint32_t kappa, int force_radix, uint32_t* radix_counter,
+                                                                 uint16_t* const* __restrict__ pairs_tab,
+                                                                 float* const* __restrict__ aux_tab) {
+    __shared__ __align__(16) SelectShared sh;
+    const uint32_t r = blockIdx.y;
+    compress_body<MODE_PARAMS_F32, QUANT>(sh, blockIdx.x >= n_gen, chunks, to_tab, tl_tab + (size_t)r * n_tensors,
+                                          ef_tab + (size_t)r * n_tensors, beta, kappa, force_radix, radix_counter,
+                                          pairs_tab[r], aux_tab[r]);
+}
+
 // Line 5, first half: sum of the decoded messages of one chunk into a dense LDS accumulator.
 // Replicas are applied in batches of eight; a batch is applied by ONE wave: LDS operations of a
 // wave complete in program order, so the add of replica r+1 at some index sees the add of replica
@@ -1566,10 +1583,42 @@ void launch_compress(const sparseloco_plan* plan, const void* const* a, const vo
                            force_radix, plan->radix_counter, pairs_out, aux_out);
 }
 
+template <int QUANT, int UPDATE>
+void launch_aggregate(const sparseloco_plan* plan, int n_replicas, const uint16_t* const* pairs,
+                      const float* const* aux, float* const* dbar, float* const* theta, float eta, int n_reset,
+                      float* const* reset, hipStream_t stream) {
+    if (plan->n_strips > 0)
+        hipLaunchKernelGGL((aggregate_strip_kernel<QUANT, UPDATE>), dim3((unsigned)plan->n_strips), dim3(kStripThreads),
+                           0, stream, plan->d_strips, n_replicas, (uint32_t)plan->kappa, pairs, aux, dbar, theta, eta,
+                           n_reset, (uint32_t)plan->n_tensors, reset);
+    if (plan->n_entries > 0)
+        hipLaunchKernelGGL((aggregate_kernel<QUANT, UPDATE>), dim3((unsigned)plan->n_entries), dim3(kThreads), 0, stream,
+                           plan->d_chunks, gen_entries(plan, false), n_replicas, (uint32_t)plan->kappa, pairs, aux,
+                           dbar, theta, eta, n_reset, (uint32_t)plan->n_tensors, reset);
+}
+
+// Up to this many chunks the batched calls give every replica of a chunk a workgroup of its own, and the one-launch step
+// becomes two launches with the same results: the walk over the replicas is a chain, some 5 us each (one chunk, 8
+// replicas: 30.6 us in one launch, 10.6 in two; 300 chunks, 4 replicas: 24.5 / 18.0; 512, 8: 48.5 / 41.5; 700, 8:
+// 56.6 / 61.6).
+constexpr int64_t kFewChunks = 512;
+
 template <int QUANT, bool STEP>
 void launch_compress_batch(const sparseloco_plan* plan, int n_replicas, float* const* to, float* const* tl,
                            float* const* ef, float beta, uint16_t* const* pairs, float* const* aux, float eta,
                            float* const* dbar, int reset, hipStream_t stream) {
+    if (plan->n_chunks <= kFewChunks) {
+        hipLaunchKernelGGL((compress_each_kernel<QUANT>), dim3((unsigned)plan->n_chunks, (unsigned)n_replicas),
+                           dim3(kThreads), 0, stream, plan->d_all, (unsigned)plan->n_all_gen, (uint32_t)plan->n_tensors,
+                           reinterpret_cast<const void* const*>(to), reinterpret_cast<const void* const*>(tl), ef, beta,
+                           (uint32_t)plan->kappa, plan->select == SPLC_SELECT_RADIX ? 1 : 0, plan->radix_counter, pairs,
+                           aux);
+        if (STEP)
+            launch_aggregate<QUANT, 1>(plan, n_replicas, const_cast<const uint16_t* const*>(pairs),
+                                       const_cast<const float* const*>(aux), dbar, to, eta, reset ? n_replicas : 0, tl,
+                                       stream);
+        return;
+    }
     // Strips are taken tile by tile here: a strip entry is followed, in the device table, by nothing this kernel
     // could use, so the batched path walks the per-chunk view kept behind the update table.
     const size_t used = sizeof(SelectShared) + sizeof(float) * (kChunk + (STEP ? kChunk : 4));
@@ -1617,20 +1666,6 @@ int compress_batch_impl(const sparseloco_plan* plan, int n_replicas, const spars
     else
         launch_compress_batch<SPLC_QUANT_NONE, true>(plan, n_replicas, d_to, d_tl, d_ef, beta, d_pairs, d_aux, outer_lr, d_dbar, reset, st);
     return hipGetLastError() == hipSuccess ? SPLC_OK : SPLC_EHIP;
-}
-
-template <int QUANT, int UPDATE>
-void launch_aggregate(const sparseloco_plan* plan, int n_replicas, const uint16_t* const* pairs,
-                      const float* const* aux, float* const* dbar, float* const* theta, float eta, int n_reset,
-                      float* const* reset, hipStream_t stream) {
-    if (plan->n_strips > 0)
-        hipLaunchKernelGGL((aggregate_strip_kernel<QUANT, UPDATE>), dim3((unsigned)plan->n_strips), dim3(kStripThreads),
-                           0, stream, plan->d_strips, n_replicas, (uint32_t)plan->kappa, pairs, aux, dbar, theta, eta,
-                           n_reset, (uint32_t)plan->n_tensors, reset);
-    if (plan->n_entries > 0)
-        hipLaunchKernelGGL((aggregate_kernel<QUANT, UPDATE>), dim3((unsigned)plan->n_entries), dim3(kThreads), 0, stream,
-                           plan->d_chunks, gen_entries(plan, false), n_replicas, (uint32_t)plan->kappa, pairs, aux,
-                           dbar, theta, eta, n_reset, (uint32_t)plan->n_tensors, reset);
 }
 
 // Shared by sparseloco_aggregate and sparseloco_aggregate_update.

@@ -646,3 +646,35 @@ def test_plans_at_the_line_of_the_reserved_launches(chunks):
 
     for got, want in zip(outer_step(chunks), outer_step(1)):
         assert torch.equal(got, want.expand_as(got))
+
+
+@pytest.mark.parametrize("tiled", [False, True])
+@pytest.mark.parametrize("chunk_rows", [511, 512, 513, 900])
+def test_batched_calls_on_both_sides_of_the_few_chunks_line(chunk_rows, tiled):
+    """Up to 512 chunks the batched calls take a workgroup per chunk and replica, beyond one per chunk: both must give
+    the bits of the single calls, with the mean and the reset."""
+    R, shapes = 3, [(64 * chunk_rows - 64, 64), (50, 30)] if tiled else [4096 * (chunk_rows - 1) + 17]
+    g = torch.Generator(device="cuda").manual_seed(chunk_rows)
+    numels = [s if isinstance(s, int) else s[0] * s[1] for s in shapes]
+    rn = lambda std: [torch.randn(n, generator=g, device="cuda") * std for n in numels]
+    plan = B.Plan(shapes, 32, tiled=tiled)
+    assert plan.num_chunks == chunk_rows
+    th = rn(0.02)
+    tl = [[t - d for t, d in zip(th, rn(1e-3))] for _ in range(R)]
+    ef = [rn(1e-4) for _ in range(R)]
+    th1, ef1 = [t.clone() for t in th], [[e.clone() for e in r] for r in ef]
+    messages, mean1 = [plan.message_buffers() for _ in range(R)], [torch.empty_like(t) for t in th]
+    for r in range(R):
+        B.sparseloco_compress(plan, ef1[r], *messages[r], 0.95, theta_outer=th1, theta_local=tl[r])
+    B.sparseloco_aggregate_update(plan, [p for p, _ in messages], th1, 0.8, aux=[a for _, a in messages],
+                                  delta_bar_out=mean1)
+    own, mean = [plan.message_buffers() for _ in range(R)], [torch.empty_like(t) for t in th]
+    B.sparseloco_outer_step_batch(plan, th, tl, ef, [p for p, _ in own], 0.95, 0.8, aux_out=[a for _, a in own],
+                                  delta_bar_out=mean, reset=True)
+    torch.cuda.synchronize()
+    for (p, a), (p1, a1) in zip(own, messages):
+        assert torch.equal(p, p1) and torch.equal(a, a1)
+    for i in range(len(numels)):
+        assert torch.equal(th[i], th1[i]) and torch.equal(mean[i], mean1[i])
+        for r in range(R):
+            assert torch.equal(ef[r][i], ef1[r][i]) and torch.equal(tl[r][i], th1[i])
