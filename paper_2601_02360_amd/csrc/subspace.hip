@@ -438,8 +438,6 @@ __global__ __launch_bounds__(kThreads, (gemm_min_waves<MATH, TM_, TN_, Pro>())) 
         }
     };
     // operand layout of v_mfma_f32_32x32x2_f32: lane l supplies A[l % 32][l / 32] and B[l / 32][l % 32].
-    // The operands of the next k pair are read from LDS before the MFMAs of the current pair are
-    // issued, so that the LDS latency hides behind the matrix pipe.
     // With split operands: v_mfma_f32_32x32x16_bf16 takes from lane l the eight k = 8 (l / 32) .. + 7 of row
     // (column) l % 32 -- one 16-byte half row of a plane -- and one K tile is one such MFMA per piece pair.
     auto multiply = [&](int buf) {
@@ -471,30 +469,69 @@ __global__ __launch_bounds__(kThreads, (gemm_min_waves<MATH, TM_, TN_, Pro>())) 
                     for (int j = 0; j < NJ; ++j)
                         acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(pa_[pairs[c][0]][i], pb_[pairs[c][1]][j],
                                                                             acc[i][j], 0, 0, 0);
-        } else {
-        float fa[2][MI], fb[2][NJ];
-        auto operands = [&](int kk, int st) {
+        }
+    };
+    // fp32, one K tile: multiply the tile in LDS buffer `buf` and move the next one, staged in `next`, to the other
+    // buffer.  Operands are read from LDS one k pair ahead.  The stores sit between the MFMAs of k pairs 1..4, and the
+    // barrier comes before the last k pair, whose operands are in registers by then; behind it the first operands of the
+    // next tile are requested.  So their latency, the barrier and the stores hide behind products, and one wave per SIMD
+    // keeps the matrix pipe busy.  (The other buffer was last read before the previous tile's barrier, so the stores
+    // need no barrier of their own.)
+    // Against stores and barrier after the last product: the passes of the re-projection at 32000 x 2048, k = 256 take
+    // 254 + 306 us instead of 265 + 313.
+    const int kq32 = lane >> 5, rc32 = lane & 31;
+    float fa[2][MI], fb[2][NJ];
+    auto operands = [&](int buf, int kk, int set) {
+        if constexpr (!SPLIT) {
 #pragma unroll
-            for (int i = 0; i < MI; ++i) fa[st][i] = sm.a[buf][kk + kq][wm * (32 * MI) + 32 * i + rc];
+            for (int i = 0; i < MI; ++i) fa[set][i] = sm.a[buf][kk + kq32][wm * (32 * MI) + 32 * i + rc32];
 #pragma unroll
             for (int j = 0; j < NJ; ++j) {
-                const int col = wn * (32 * NJ) + 32 * j + rc;
-                fb[st][j] = B_NK ? b_rows(buf, kk + kq, col) : sm.b[buf][kk + kq][col];
+                const int col = wn * (32 * NJ) + 32 * j + rc32;
+                fb[set][j] = B_NK ? b_rows(buf, kk + kq32, col) : sm.b[buf][kk + kq32][col];
             }
-        };
-        operands(0, 0);
-#pragma unroll
-        for (int p = 0; p < TK / 2; ++p) {
-            const int st = p & 1;
-            if (p + 1 < TK / 2) operands(2 * (p + 1), st ^ 1);
-            __builtin_amdgcn_sched_barrier(0);      // keep the reads above ahead of the MFMAs below
-#pragma unroll
-            for (int i = 0; i < MI; ++i)
-#pragma unroll
-                for (int j = 0; j < NJ; ++j)
-                    acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(fa[st][i], fb[st][j], acc[i][j], 0, 0, 0);
-            __builtin_amdgcn_sched_barrier(0);
         }
+    };
+    // quarter `part` of a staged tile to LDS (the prologue is applied with the first)
+    auto stash_quarter = [&](int buf, Stage& q, auto part) {
+        if constexpr (!SPLIT) {
+            constexpr int P = decltype(part)::value;
+            if constexpr (P == 0) pro.template apply<AF>(q.a, q.t);
+#pragma unroll
+            for (int i = P * AF / 4; i < (P + 1) * AF / 4; ++i) sm.a[buf][ak + i][ar] = q.a[i];
+#pragma unroll
+            for (int i = P * BF / 4; i < (P + 1) * BF / 4; ++i) {
+                if (B_NK) b_rows(buf, bkk + i, br) = q.b[i];
+                else sm.b[buf][bk][bn + i] = q.b[i];
+            }
+        }
+    };
+    auto tile_step = [&](int buf, auto has_next, Stage& next) {
+        if constexpr (!SPLIT) {
+            constexpr bool MORE = decltype(has_next)::value;
+#pragma unroll
+            for (int p = 0; p < TK / 2; ++p) {
+                const int cur = p & 1;
+                if (p + 1 < TK / 2) {
+                    operands(buf, 2 * (p + 1), cur ^ 1);
+                } else {
+                    __syncthreads();
+                    if (MORE) operands(buf ^ 1, 0, cur ^ 1);
+                }
+                __builtin_amdgcn_sched_barrier(0);      // keep the reads above ahead of the MFMAs below
+#pragma unroll
+                for (int i = 0; i < MI; ++i)
+#pragma unroll
+                    for (int j = 0; j < NJ; ++j)
+                        acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(fa[cur][i], fb[cur][j], acc[i][j], 0, 0, 0);
+                __builtin_amdgcn_sched_barrier(0);
+                if (MORE) {
+                    if (p == 1) stash_quarter(buf ^ 1, next, std::integral_constant<int, 0>{});
+                    if (p == 2) stash_quarter(buf ^ 1, next, std::integral_constant<int, 1>{});
+                    if (p == 3) stash_quarter(buf ^ 1, next, std::integral_constant<int, 2>{});
+                    if (p == 4) stash_quarter(buf ^ 1, next, std::integral_constant<int, 3>{});
+                }
+            }
         }
     };
 
@@ -519,23 +556,41 @@ __global__ __launch_bounds__(kThreads, (gemm_min_waves<MATH, TM_, TN_, Pro>())) 
     if (n_tiles > 1) fetch_any(1, s0);
     __syncthreads();
     int t = 0;
-    for (; t + 3 < n_fast; t += 2) {          // t is even here: tile t sits in LDS buffer 0
-        fetch(plain, (t + 2) * TK, s1);
-        multiply(0);
-        stash(1, s0);
-        __syncthreads();
-        fetch(plain, (t + 3) * TK, s0);
-        multiply(1);
-        stash(0, s1);
-        __syncthreads();
-    }
-    for (; t < n_tiles; ++t) {
-        const int buf = t & 1;
-        if (t + 2 < n_tiles) fetch_any(t + 2, s1);
-        multiply(buf);
-        if (t + 1 < n_tiles) stash(buf ^ 1, s0);
-        s0 = s1;
-        __syncthreads();
+    if constexpr (SPLIT) {
+        for (; t + 3 < n_fast; t += 2) {          // t is even here: tile t sits in LDS buffer 0
+            fetch(plain, (t + 2) * TK, s1);
+            multiply(0);
+            stash(1, s0);
+            __syncthreads();
+            fetch(plain, (t + 3) * TK, s0);
+            multiply(1);
+            stash(0, s1);
+            __syncthreads();
+        }
+        for (; t < n_tiles; ++t) {
+            const int buf = t & 1;
+            if (t + 2 < n_tiles) fetch_any(t + 2, s1);
+            multiply(buf);
+            if (t + 1 < n_tiles) stash(buf ^ 1, s0);
+            s0 = s1;
+            __syncthreads();
+        }
+    } else {
+        const std::integral_constant<bool, true> more;
+        const std::integral_constant<bool, false> last;
+        operands(0, 0, 0);
+        for (; t + 3 < n_fast; t += 2) {
+            fetch(plain, (t + 2) * TK, s1);
+            tile_step(0, more, s0);
+            fetch(plain, (t + 3) * TK, s0);
+            tile_step(1, more, s1);
+        }
+        for (; t + 1 < n_tiles; ++t) {
+            if (t + 2 < n_tiles) fetch_any(t + 2, s1);
+            tile_step(t & 1, more, s0);
+            s0 = s1;
+        }
+        tile_step(t & 1, last, s0);       // its barrier leaves both B buffers free: its last operands are in registers
     }
 
     // Epilogue through LDS, 32 output rows at a time, so that global memory sees whole rows
