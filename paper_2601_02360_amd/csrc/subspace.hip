@@ -1039,8 +1039,15 @@ GemmTile choose_gemm_tile(bool b_nk, int M, int N, int K, bool light_epilogue, i
     bool tall;
     if (matmul == SPLC_MATMUL_BF16X3) {
         // split operands: a tile's matrix work is a third as long and splitting costs per staged value, so the
-        // large tile, which stages fewest values per product, wins wherever it leaves 1.5 groups per compute unit
-        tall = b_nk || groups(128, wide ? 128 : 64) >= 3 * 128;
+        // large tile, which stages fewest values per product, wins wherever it leaves 1.75 groups per compute unit
+        // (16384 x 1536 onto 192 columns has 384: 94 us with 64 rows, 100 with 128; the first pass at 32000 rows 750).
+        // With many column blocks an odd one does not count: 128 columns take 2050 of them in 17 tiles instead of 33
+        // (re-projection 32001 x 2050, k = 170: 505 -> 470 us)
+        if (b_nk && N > 16 * 64) wide = true;
+        tall = b_nk || groups(128, wide ? 128 : 64) >= 448;
+    } else if (light_epilogue && K > 128 && K <= 192) {
+        // reconstruction, 16384 x 1536 from 192 columns: 101 us with 64 columns, 95 with 128 (from 64: 49.3 / 50.7)
+        tall = false;
     } else if (b_nk && K <= 192) {
         wide = tall = false;
     } else if (light_epilogue) {
