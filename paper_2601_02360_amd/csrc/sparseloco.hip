@@ -954,12 +954,11 @@ __global__ __launch_bounds__(kStripThreads, 8) void compress_strip_kernel(const 
 // workgroup reads its theta_outer chunk once and walks the replicas, so theta_outer costs 4 bytes
 // per parameter per launch instead of per replica.  Per replica the arithmetic, the selection and
 // the outputs are those of compress_kernel.
-// With STEP the workgroup finishes the outer step for its chunk (line 5): what each replica sends is
-// added, replica after replica, to a sum in LDS (an element always sits in the same lane, so the mean needs
-// neither the messages nor any synchronisation), and after the last replica the chunk's mean is applied to
-// theta_outer, written to delta_bar if asked for, and the new parameters are copied to the replicas'
-// theta_local if asked for.  The sums start at +0 and are divided once by M: the bits of
-// sparseloco_aggregate_update.
+// With STEP the workgroup finishes the outer step for its chunk (line 5): what each replica sends is added, replica
+// after replica, to a sum in LDS by the lanes that write the message (the barrier between replicas orders the adds), and
+// after the last replica the chunk's mean is applied to theta_outer, written to delta_bar if asked for, and the new
+// parameters are copied to the replicas' theta_local if asked for.  The sums start at +0 and are divided once by M: the
+// bits of sparseloco_aggregate_update.
 // Table layout (device): theta_local[r][t] at tl_tab[r * n_tensors + t], likewise ef_tab; message
 // buffers pairs_tab[r], aux_tab[r].
 template <int QUANT, bool VEC, bool STEP>
