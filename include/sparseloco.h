@@ -198,7 +198,8 @@ int sparseloco_compress(const sparseloco_plan* plan, int delta_mode,
 /*
  * Lines 1-4 for several replicas that share theta_outer and live on this GPU
  * (the single-node simulation of M replicas): one launch, theta_outer read once
- * per chunk instead of once per replica.  Per replica the result is bit-identical
+ * per chunk instead of once per replica (plans of more than 512 chunks; smaller ones,
+ * which latency bounds, give every replica of a chunk a workgroup of its own).  Per replica the result is bit-identical
  * to sparseloco_compress in SPLC_DELTA_FROM_PARAMS mode.
  *   theta_outer: one set; theta_local, ef: at least n_replicas sets (replica r = set r); messages_out: at
  *   least n_replicas messages (replica r writes message r).  1 <= n_replicas <= SPLC_MAX_REPLICAS.
