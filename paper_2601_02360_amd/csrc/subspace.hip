@@ -23,6 +23,7 @@
 #include <mutex>
 #include <type_traits>
 
+#include "launch_rules.h"
 #include "sparseloco.h"
 
 namespace {
@@ -905,9 +906,9 @@ __global__ __launch_bounds__(64 * KS) void project_rows_kernel(const float* __re
         }
     };
 
-    // A lane that straddles column k reads on into the next row of U, which the leading n_fast tiles have.
+    // A lane that straddles column k reads on into the next rows of U, which the leading n_fast tiles have.
     const int n_tiles = (d + KT - 1) / KT;
-    const int n_fast = (k % NB == 0 ? d : d - 1) / KT;
+    const int n_fast = splc::unguarded_tiles(d, k, NB, KT);
     auto fetch_any = [&](int t, Stage& q) {
         if (t < n_fast) fetch(t, q);
         else if (t < n_tiles) fetch_guarded(t, q);

@@ -220,7 +220,10 @@ FEW_ROWS_SHAPES = [
     (2048, 1024, 256, 33, 100, True, False, 32), (2049, 500, 768, 34, 100, False, True, 64),
     (2048, 1024, 768, 96, 300, True, True, 64), (1000, 100, 2050, 255, 64, True, False, 64),
     (2000, 1000, 1023, 170, 33, False, True, 64), (8192, 1024, 288, 64, 500, True, True, 64),
-    (2047, 89, 2048, 256, 77, False, False, 64)]
+    (2047, 89, 2048, 256, 77, False, False, 64),
+    # a basis narrower than a lane's load, and a reduction that ends one or two rows into a 32-wide tile
+    (2049, 500, 257, 1, 100, True, True, 64), (2049, 300, 258, 2, 50, False, True, 64), (4100, 41, 2050, 1, 9, False, False, 64),
+    (2100, 70, 2049, 3, 33, True, False, 64), (1000, 100, 257, 1, 20, True, False, 32)]
 
 
 @pytest.mark.parametrize("rows,seq,d,k,vocab,use_perp,use_pos,columns", FEW_ROWS_SHAPES)
