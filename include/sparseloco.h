@@ -203,6 +203,9 @@ int sparseloco_compress(const sparseloco_plan* plan, int delta_mode,
  * to sparseloco_compress in SPLC_DELTA_FROM_PARAMS mode.
  *   theta_outer: one set; theta_local, ef: at least n_replicas sets (replica r = set r); messages_out: at
  *   least n_replicas messages (replica r writes message r).  1 <= n_replicas <= SPLC_MAX_REPLICAS.
+ * As everywhere, no buffer may overlap another, with one exception: the replicas' messages, and likewise their ef
+ * sets, may share memory if the caller has no use for what is overwritten.  Replicas are then taken in ascending
+ * order (the last one's message, or ef, remains), each chunk in one workgroup whatever the plan's size.
  */
 int sparseloco_compress_batch(const sparseloco_plan* plan, int n_replicas,
                               const sparseloco_tensors* theta_outer, const sparseloco_tensors* theta_local,
@@ -253,6 +256,7 @@ int sparseloco_aggregate_update(const sparseloco_plan* plan, const sparseloco_me
  *   dense mean is written.  reset_theta_local != 0: the new theta_outer is also written into
  *   theta_local sets 0 .. n_replicas-1 (section 2.1, inner step: replicas restart from the
  *   synchronised parameters).  1 <= n_replicas <= SPLC_MAX_REPLICAS.
+ * Overlapping messages or ef sets: as in sparseloco_compress_batch; the mean is that of all replicas.
  */
 int sparseloco_outer_step_batch(const sparseloco_plan* plan, int n_replicas,
                                 const sparseloco_tensors* theta_outer, const sparseloco_tensors* theta_local,

@@ -2,6 +2,12 @@
 // code, and by themselves into a CPU test.
 #pragma once
 
+#include <stdint.h>
+
+#include <algorithm>
+#include <utility>
+#include <vector>
+
 namespace splc {
 
 // A product walks the rows of a row-major `rows` x `width` operand in tiles of `tile_rows`, every lane loading `floats`
@@ -12,6 +18,30 @@ namespace splc {
 constexpr int unguarded_tiles(int rows, int width, int floats, int tile_rows) {
     const int spare = width % floats == 0 ? 0 : (floats - 1 + width - 1) / width;
     return rows > spare ? (rows - spare) / tile_rows : 0;
+}
+
+// Batched calls (compress of several replicas, one-launch step): up to this many chunks every replica of a chunk gets a
+// workgroup of its own, and the one-launch step becomes two launches with the same results: the walk over the replicas
+// is a chain, some 5 us each (one chunk, 8 replicas: 30.6 us in one launch, 10.6 in two; 300 chunks, 4 replicas: 24.5 /
+// 18.0; 512, 8: 48.5 / 41.5; 700, 8: 56.6 / 61.6).
+// Workgroups of different replicas then run in any order, and the second launch reads the messages back.  Where the
+// replicas' message buffers or error-feedback sets share memory (a caller may have no use for them), the walk, which
+// takes the replicas in order and keeps their sum on chip, is what gives the documented result.
+constexpr int64_t kFewChunks = 512;
+constexpr bool replicas_side_by_side(int64_t chunks, bool buffers_disjoint) {
+    return chunks <= kFewChunks && buffers_disjoint;
+}
+
+// Whether no two of these address ranges [first, second) share a byte; empty ranges share none.
+inline bool disjoint(std::vector<std::pair<uintptr_t, uintptr_t>> ranges) {
+    std::sort(ranges.begin(), ranges.end());
+    uintptr_t end = 0;
+    for (const auto& r : ranges) {
+        if (r.first >= r.second) continue;
+        if (r.first < end) return false;
+        end = r.second;
+    }
+    return true;
 }
 
 }  // namespace splc

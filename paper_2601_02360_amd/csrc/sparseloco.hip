@@ -25,6 +25,7 @@
 #include <type_traits>
 #include <vector>
 
+#include "launch_rules.h"
 #include "sparseloco.h"
 
 namespace {
@@ -1496,6 +1497,7 @@ struct sparseloco_tensors {
     int n_tensors = 0;
     int n_sets = 0;
     int dtype = SPLC_F32;
+    bool disjoint = false;               // no tensor shares memory with another (looked at where it matters: small plans)
     void** d_table = nullptr;
     void** h_table = nullptr;            // pinned source of the upload
 };
@@ -1507,6 +1509,7 @@ struct sparseloco_messages {
     int quant = SPLC_QUANT_2BIT;
     int kappa = 0;
     int64_t n_chunks = 0;
+    bool disjoint = false;               // no buffer shares memory with another (as above)
     void** d_table = nullptr;
     void** h_table = nullptr;
 };
@@ -1546,6 +1549,24 @@ int upload_table(size_t n_ptrs, void*** h_out, void*** d_out) {
     if (hipHostMalloc(reinterpret_cast<void**>(h_out), bytes, hipHostMallocDefault) != hipSuccess) return SPLC_ENOMEM;
     if (hipMalloc(reinterpret_cast<void**>(d_out), bytes) != hipSuccess) return SPLC_ENOMEM;
     return SPLC_OK;
+}
+
+std::pair<uintptr_t, uintptr_t> range_of(const void* p, uint64_t bytes) {
+    const uintptr_t a = reinterpret_cast<uintptr_t>(p);
+    return {a, a + (uintptr_t)bytes};
+}
+// Whether the ranges that `collect` lists are disjoint; false without a look where the plan is too large for the answer
+// to matter (replicas_side_by_side), or where memory for the list runs out.
+template <class Collect>
+bool on_small_plan_disjoint(const sparseloco_plan* plan, Collect collect) {
+    if (plan->n_chunks > splc::kFewChunks) return false;
+    try {
+        std::vector<std::pair<uintptr_t, uintptr_t>> ranges;
+        collect(ranges);
+        return splc::disjoint(std::move(ranges));
+    } catch (const std::bad_alloc&) {
+        return false;
+    }
 }
 
 // Entries of the chunk table that take the element-wise path (they come first in the table).
@@ -1596,17 +1617,11 @@ void launch_aggregate(const sparseloco_plan* plan, int n_replicas, const uint16_
                            dbar, theta, eta, n_reset, (uint32_t)plan->n_tensors, reset);
 }
 
-// Up to this many chunks the batched calls give every replica of a chunk a workgroup of its own, and the one-launch step
-// becomes two launches with the same results: the walk over the replicas is a chain, some 5 us each (one chunk, 8
-// replicas: 30.6 us in one launch, 10.6 in two; 300 chunks, 4 replicas: 24.5 / 18.0; 512, 8: 48.5 / 41.5; 700, 8:
-// 56.6 / 61.6).
-constexpr int64_t kFewChunks = 512;
-
 template <int QUANT, bool STEP>
-void launch_compress_batch(const sparseloco_plan* plan, int n_replicas, float* const* to, float* const* tl,
-                           float* const* ef, float beta, uint16_t* const* pairs, float* const* aux, float eta,
-                           float* const* dbar, int reset, hipStream_t stream) {
-    if (plan->n_chunks <= kFewChunks) {
+void launch_compress_batch(const sparseloco_plan* plan, int n_replicas, bool disjoint, float* const* to,
+                           float* const* tl, float* const* ef, float beta, uint16_t* const* pairs, float* const* aux,
+                           float eta, float* const* dbar, int reset, hipStream_t stream) {
+    if (splc::replicas_side_by_side(plan->n_chunks, disjoint)) {
         hipLaunchKernelGGL((compress_each_kernel<QUANT>), dim3((unsigned)plan->n_chunks, (unsigned)n_replicas),
                            dim3(kThreads), 0, stream, plan->d_all, (unsigned)plan->n_all_gen, (uint32_t)plan->n_tensors,
                            reinterpret_cast<const void* const*>(to), reinterpret_cast<const void* const*>(tl), ef, beta,
@@ -1655,15 +1670,19 @@ int compress_batch_impl(const sparseloco_plan* plan, int n_replicas, const spars
     uint16_t* const* d_pairs = reinterpret_cast<uint16_t* const*>(messages_out->d_table);
     float* const* d_aux = reinterpret_cast<float* const*>(messages_out->d_table + messages_out->n_replicas);
     float* const* d_dbar = delta_bar_out ? set_table<float*>(delta_bar_out, 0) : nullptr;
-    const bool q2 = plan->quant == SPLC_QUANT_2BIT;
+    const bool q2 = plan->quant == SPLC_QUANT_2BIT, apart = ef->disjoint && messages_out->disjoint;
     if (q2 && !step)
-        launch_compress_batch<SPLC_QUANT_2BIT, false>(plan, n_replicas, d_to, d_tl, d_ef, beta, d_pairs, d_aux, 0.f, nullptr, 0, st);
+        launch_compress_batch<SPLC_QUANT_2BIT, false>(plan, n_replicas, apart, d_to, d_tl, d_ef, beta, d_pairs, d_aux,
+                                                      0.f, nullptr, 0, st);
     else if (q2)
-        launch_compress_batch<SPLC_QUANT_2BIT, true>(plan, n_replicas, d_to, d_tl, d_ef, beta, d_pairs, d_aux, outer_lr, d_dbar, reset, st);
+        launch_compress_batch<SPLC_QUANT_2BIT, true>(plan, n_replicas, apart, d_to, d_tl, d_ef, beta, d_pairs, d_aux,
+                                                     outer_lr, d_dbar, reset, st);
     else if (!step)
-        launch_compress_batch<SPLC_QUANT_NONE, false>(plan, n_replicas, d_to, d_tl, d_ef, beta, d_pairs, d_aux, 0.f, nullptr, 0, st);
+        launch_compress_batch<SPLC_QUANT_NONE, false>(plan, n_replicas, apart, d_to, d_tl, d_ef, beta, d_pairs, d_aux,
+                                                      0.f, nullptr, 0, st);
     else
-        launch_compress_batch<SPLC_QUANT_NONE, true>(plan, n_replicas, d_to, d_tl, d_ef, beta, d_pairs, d_aux, outer_lr, d_dbar, reset, st);
+        launch_compress_batch<SPLC_QUANT_NONE, true>(plan, n_replicas, apart, d_to, d_tl, d_ef, beta, d_pairs, d_aux,
+                                                     outer_lr, d_dbar, reset, st);
     return hipGetLastError() == hipSuccess ? SPLC_OK : SPLC_EHIP;
 }
 
@@ -1997,6 +2016,11 @@ int sparseloco_tensors_bind(sparseloco_tensors** out, const sparseloco_plan* pla
     t->n_tensors = plan->n_tensors;
     t->n_sets = n_sets;
     t->dtype = dtype;
+    t->disjoint = n_sets == 1 || on_small_plan_disjoint(plan, [&](auto& ranges) {
+        const uint64_t size = dtype == SPLC_BF16 ? 2 : 4;
+        for (size_t i = 0; i < n; ++i)
+            ranges.push_back(range_of(ptrs[i], (uint64_t)plan->numel[i % nt] * size));
+    });
     if ((rc = upload_table(n, &t->h_table, &t->d_table)) == SPLC_OK) {
         for (size_t i = 0; i < n; ++i) t->h_table[i] = plan->numel[i % nt] == 0 ? nullptr : const_cast<void*>(ptrs[i]);
         if (hipMemcpyAsync(t->d_table, t->h_table, n * sizeof(void*), hipMemcpyHostToDevice,
@@ -2038,6 +2062,13 @@ int sparseloco_messages_bind(sparseloco_messages** out, const sparseloco_plan* p
     m->kappa = plan->kappa;
     m->n_chunks = plan->n_chunks;
     const size_t nr = (size_t)n_replicas;
+    m->disjoint = n_replicas == 1 || on_small_plan_disjoint(plan, [&](auto& ranges) {
+        const uint64_t slots = (uint64_t)plan->n_chunks * (uint64_t)plan->kappa;
+        for (size_t r = 0; r < nr; ++r) {
+            ranges.push_back(range_of(pairs[r], 2 * slots));
+            ranges.push_back(range_of(aux[r], 4 * (plan->quant == SPLC_QUANT_2BIT ? 2 * (uint64_t)plan->n_chunks : slots)));
+        }
+    });
     if ((rc = upload_table(2 * nr, &m->h_table, &m->d_table)) == SPLC_OK) {
         for (size_t r = 0; r < nr; ++r) {
             m->h_table[r] = pairs[r];

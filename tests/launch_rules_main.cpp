@@ -26,8 +26,23 @@ static int check_unguarded_tiles() {
     return 0;
 }
 
+// Replicas go side by side only where nothing one of them writes is another one's.
+static int check_side_by_side() {
+    using Ranges = std::vector<std::pair<uintptr_t, uintptr_t>>;
+    const struct { Ranges r; bool apart; } cases[] = {
+        {{}, true}, {{{100, 200}}, true}, {{{100, 200}, {200, 300}}, true}, {{{200, 300}, {100, 200}}, true},
+        {{{100, 200}, {100, 200}}, false}, {{{150, 250}, {100, 200}}, false}, {{{100, 400}, {150, 200}, {300, 301}}, false},
+        {{{100, 400}, {400, 500}, {499, 600}}, false}, {{{100, 100}, {100, 200}, {150, 150}}, true}, {{{0, 0}, {0, 0}}, true}};
+    for (const auto& c : cases)
+        if (splc::disjoint(c.r) != c.apart) { printf("disjoint: wrong answer\n"); return 1; }
+    for (int64_t chunks : {1, 100, 512, 513, 100000})
+        if (splc::replicas_side_by_side(chunks, false)) { printf("%ld chunks: shared buffers\n", (long)chunks); return 1; }
+    if (!splc::replicas_side_by_side(512, true) || splc::replicas_side_by_side(513, true)) { printf("line\n"); return 1; }
+    return 0;
+}
+
 int main() {
-    if (check_unguarded_tiles()) return 1;
+    if (check_unguarded_tiles() || check_side_by_side()) return 1;
     printf("ok\n");
     return 0;
 }

@@ -678,3 +678,41 @@ def test_batched_calls_on_both_sides_of_the_few_chunks_line(chunk_rows, tiled):
         assert torch.equal(th[i], th1[i]) and torch.equal(mean[i], mean1[i])
         for r in range(R):
             assert torch.equal(ef[r][i], ef1[r][i]) and torch.equal(tl[r][i], th1[i])
+
+
+@pytest.mark.parametrize("quant", [True, False])
+@pytest.mark.parametrize("chunks", [4, 600])
+def test_batched_calls_with_buffers_shared_by_the_replicas(chunks, quant):
+    """A caller with no use for the messages (or, at beta = 0, for the error feedback) may give all replicas the same
+    buffers: the parameters and the mean are those of separate buffers, and what remains in a shared buffer is the last
+    replica's, on small plans (whose replicas otherwise run side by side) as on large ones."""
+    R, numels = 5, [4096 * (chunks - 2) + 33, 50]
+    g = torch.Generator(device="cuda").manual_seed(chunks)
+    rn = lambda std: [torch.randn(n, generator=g, device="cuda") * std for n in numels]
+    plan = B.Plan(numels, 32, quant)
+    assert plan.num_chunks == chunks
+    th0, ef0 = rn(0.02), [rn(1e-4) for _ in range(R)]
+    tl = [[t - d for t, d in zip(th0, rn(1e-3))] for _ in range(R)]
+    messages = [plan.message_buffers() for _ in range(R)]
+
+    def run(share_messages, share_ef, beta, step):
+        th, mean = [t.clone() for t in th0], [torch.zeros_like(t) for t in th0]
+        ef = [[e.clone() for e in r] for r in ef0]
+        ef = [ef[0]] * R if share_ef else ef
+        out = [messages[0]] * R if share_messages else messages
+        for p, a in out:
+            p.fill_(0x5A5A), a.fill_(float("nan"))
+        pairs, aux = [p for p, _ in out], [a for _, a in out]
+        if step:
+            B.sparseloco_outer_step_batch(plan, th, tl, ef, pairs, beta, 0.8, aux_out=aux, delta_bar_out=mean)
+        else:
+            B.sparseloco_compress_batch(plan, th, tl, ef, pairs, beta, aux_out=aux)
+        torch.cuda.synchronize()
+        return [x.clone() for x in th + mean + ef[-1] + list(out[-1])]
+
+    for step in (True, False):
+        for share_ef, beta in ((False, 0.95), (True, 0.0)):
+            want = run(False, False, beta, step)
+            assert all(torch.equal(x, y) for x, y in zip(run(True, share_ef, beta, step), want))
+            assert all(torch.equal(x, y) for x, y in zip(run(False, share_ef, beta, step), want))
+    plan.close()
