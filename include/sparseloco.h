@@ -249,8 +249,8 @@ int sparseloco_aggregate_update(const sparseloco_plan* plan, const sparseloco_me
  * n_replicas sets of theta_local / ef as in sparseloco_compress_batch, then line 5 as in
  * sparseloco_aggregate_update over exactly those replicas' messages.  Results are bit-identical to
  * the two calls in sequence (the messages are still written: they are outputs).  A plan of up to 512
- * chunks is taken in two launches, every replica of a chunk by a workgroup of its own; in a larger one every chunk is
- * handled by one workgroup from its first read to the update of theta_outer, so the sent values
+ * chunks, with two replicas or more, is taken in two launches, every replica of a chunk by a workgroup of its own; else
+ * every chunk is handled by one workgroup from its first read to the update of theta_outer, so the sent values
  * are averaged where they are produced and theta_outer is read once and written once.
  *   theta_outer: one set, updated in place.  delta_bar_out: may be NULL; if given (one set), the
  *   dense mean is written.  reset_theta_local != 0: the new theta_outer is also written into

@@ -20,16 +20,20 @@ constexpr int unguarded_tiles(int rows, int width, int floats, int tile_rows) {
     return rows > spare ? (rows - spare) / tile_rows : 0;
 }
 
-// Batched calls (compress of several replicas, one-launch step): up to this many chunks every replica of a chunk gets a
+// Batched calls (compress of several replicas, one-launch step): on plans of few chunks every replica of a chunk gets a
 // workgroup of its own, and the one-launch step becomes two launches with the same results: the walk over the replicas
-// is a chain, some 5 us each (one chunk, 8 replicas: 30.6 us in one launch, 10.6 in two; 300 chunks, 4 replicas: 24.5 /
-// 18.0; 512, 8: 48.5 / 41.5; 700, 8: 56.6 / 61.6).
-// Workgroups of different replicas then run in any order, and the second launch reads the messages back.  Where the
+// is a chain, some 4 us each.  Measured, kappa 32, walk / side by side, in us:
+//   compress alone: 1 chunk, 1 replica 5.7 / 5.4, 8: 29.4 / 5.5; 300 chunks, 1: 7.9 / 7.6, 4: 23.2 / 13.3; 512, 1: 8.8 /
+//     8.7, 8: 46.7 / 37.1, 64: 328 / 296; 700, 8: 54.5 / 56.3, 64: 400 / 461;
+//   the step: 1 chunk, 2: 10.2 / 8.9, 8: 31.0 / 10.8; 300, 2: 14.5 / 14.1, 4: 24.0 / 20.0; 512, 2: 16.3 / 15.6, 8: 48.7 /
+//     41.6, 64: 332 / 305; 600, 3: 24.1 / 25.4; 700, 8: 56.7 / 61.6;
+//   the step with 1 replica, where there is no walk to split: 1 chunk 6.4 / 7.7; 300: 9.0 / 11.0; 512: 10.1 / 12.5.
+// Workgroups of different replicas run in any order, and the second launch reads the messages back.  Where the
 // replicas' message buffers or error-feedback sets share memory (a caller may have no use for them), the walk, which
 // takes the replicas in order and keeps their sum on chip, is what gives the documented result.
 constexpr int64_t kFewChunks = 512;
-constexpr bool replicas_side_by_side(int64_t chunks, bool buffers_disjoint) {
-    return chunks <= kFewChunks && buffers_disjoint;
+constexpr bool replicas_side_by_side(int64_t chunks, int replicas, bool step, bool buffers_disjoint) {
+    return chunks <= kFewChunks && !(step && replicas == 1) && buffers_disjoint;
 }
 
 // Whether no two of these address ranges [first, second) share a byte; empty ranges share none.

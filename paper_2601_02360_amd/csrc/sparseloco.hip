@@ -1621,7 +1621,7 @@ template <int QUANT, bool STEP>
 void launch_compress_batch(const sparseloco_plan* plan, int n_replicas, bool disjoint, float* const* to,
                            float* const* tl, float* const* ef, float beta, uint16_t* const* pairs, float* const* aux,
                            float eta, float* const* dbar, int reset, hipStream_t stream) {
-    if (splc::replicas_side_by_side(plan->n_chunks, disjoint)) {
+    if (splc::replicas_side_by_side(plan->n_chunks, n_replicas, STEP, disjoint)) {
         hipLaunchKernelGGL((compress_each_kernel<QUANT>), dim3((unsigned)plan->n_chunks, (unsigned)n_replicas),
                            dim3(kThreads), 0, stream, plan->d_all, (unsigned)plan->n_all_gen, (uint32_t)plan->n_tensors,
                            reinterpret_cast<const void* const*>(to), reinterpret_cast<const void* const*>(tl), ef, beta,

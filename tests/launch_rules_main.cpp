@@ -36,8 +36,21 @@ static int check_side_by_side() {
     for (const auto& c : cases)
         if (splc::disjoint(c.r) != c.apart) { printf("disjoint: wrong answer\n"); return 1; }
     for (int64_t chunks : {1, 100, 512, 513, 100000})
-        if (splc::replicas_side_by_side(chunks, false)) { printf("%ld chunks: shared buffers\n", (long)chunks); return 1; }
-    if (!splc::replicas_side_by_side(512, true) || splc::replicas_side_by_side(513, true)) { printf("line\n"); return 1; }
+        for (int replicas : {1, 2, 3, 1024})
+            for (bool step : {false, true})
+                if (splc::replicas_side_by_side(chunks, replicas, step, false)) {
+                    printf("%ld chunks: shared buffers\n", (long)chunks);
+                    return 1;
+                }
+    // the largest plan each number of replicas is taken side by side on (0: none)
+    const struct { int replicas; bool step; int64_t most; } lines[] = {
+        {1, false, 512}, {2, false, 512}, {1024, false, 512}, {1, true, 0}, {2, true, 512}, {3, true, 512}, {1024, true, 512}};
+    for (const auto& l : lines)
+        if ((l.most > 0 && !splc::replicas_side_by_side(l.most, l.replicas, l.step, true)) ||
+            splc::replicas_side_by_side(l.most + 1, l.replicas, l.step, true)) {
+            printf("line of %d replicas%s\n", l.replicas, l.step ? ", step" : "");
+            return 1;
+        }
     return 0;
 }
 
