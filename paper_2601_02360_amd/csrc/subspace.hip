@@ -1030,8 +1030,11 @@ void launch_gemm_tile(const float* A, int64_t lda, const float* B, int64_t ldb, 
 //            the re-projection at 32000 x 2048, k = 256 has 500 and takes 272 us so, 288 us with 64 rows --, else 64;
 //   a product with the basis as the N x K operand has K = k: up to K = 192 the K loop is so short that
 //            64 x 64 tiles win (more, smaller workgroups per compute unit overlap one group's epilogue
-//            with another's products); beyond that the reconstruction (light_epilogue: one store per
-//            output) still prefers 64 rows;
+//            with another's products) -- except a reconstruction (light_epilogue: one store per output) from 129 to 192
+//            columns with at least 2048 tiles of 64 x 128, eight per compute unit (16384 x 1536 from 192, 3072 tiles:
+//            101 / 94 us; 8192 x 2048 from 160, 2048: 59 / 57; but 16384 x 768 from 160, 1536: 46 / 48; 2048 x 1536
+//            from 192, 384: 14.6 / 17.2; 256 to 1024 rows: 6.3 / 9.3); beyond K = 192 the reconstruction still
+//            prefers 64 rows;
 //   with split-bf16 products (measured separately): see below.
 struct GemmTile { bool tall, wide; };
 GemmTile choose_gemm_tile(bool b_nk, int M, int N, int K, bool light_epilogue, int matmul) {
@@ -1046,8 +1049,7 @@ GemmTile choose_gemm_tile(bool b_nk, int M, int N, int K, bool light_epilogue, i
         // (re-projection 32001 x 2050, k = 170: 505 -> 470 us)
         if (b_nk && N > 16 * 64) wide = true;
         tall = b_nk || groups(128, wide ? 128 : 64) >= 448;
-    } else if (light_epilogue && K > 128 && K <= 192) {
-        // reconstruction, 16384 x 1536 from 192 columns: 101 us with 64 columns, 95 with 128 (from 64: 49.3 / 50.7)
+    } else if (light_epilogue && K > 128 && K <= 192 && groups(64, 128) >= 2048) {
         tall = false;
     } else if (b_nk && K <= 192) {
         wide = tall = false;

@@ -96,3 +96,14 @@ def test_kernel_choice_follows_the_documented_rule():
         c(9, 100, 64, 8)
     with pytest.raises(B.SparseLoCoError):
         c(B.SPLC_OP_PROJECT, 100, 64, 65)
+
+
+@pytest.mark.parametrize("op,rows,d,k,tables,matmul,tile", [
+    # fp32 reconstruction from 129 to 192 columns: 128 columns from eight 64 x 128 tiles per compute unit on
+    ("RECONSTRUCT", 1024, 1536, 160, 2, "FP32", (64, 64)), ("RECONSTRUCT", 4096, 1536, 192, 2, "FP32", (64, 64)),
+    ("RECONSTRUCT", 8191, 2048, 160, 0, "FP32", (64, 128)), ("RECONSTRUCT", 8128, 2048, 160, 0, "FP32", (64, 64)),
+    ("RECONSTRUCT", 16384, 1536, 192, 2, "FP32", (64, 128)), ("RECONSTRUCT", 16384, 1536, 128, 2, "FP32", (64, 64)),
+    ("REPROJECT_PASS2", 50304, 2048, 192, 0, "FP32", (64, 64))])
+def test_kernel_choice_at_its_lines(op, rows, d, k, tables, matmul, tile):
+    """Where the launcher's tile rules change, on both sides of each line."""
+    assert B.subspace_kernel_choice(getattr(B, "SPLC_OP_" + op), rows, d, k, tables, getattr(B, "SPLC_MATMUL_" + matmul)) == tile
