@@ -101,6 +101,7 @@ __device__ __forceinline__ void row_load(const float* __restrict__ row, int col,
 
 // Pass 1: store the coefficients.
 struct StoreCoeff {
+    static constexpr int kTables = 0;
     static constexpr bool kStaggeredStart = false;
     float* c;
     int64_t ld;
@@ -125,6 +126,7 @@ struct UpdateEmbedding {
     // This epilogue moves four arrays; a kernel that carries it is as much bound by memory as by the matrix
     // pipe, and gains when the workgroups that share a compute unit are not all in their epilogue at once.
     static constexpr bool kStaggeredStart = true;
+    static constexpr int kTables = 0;
     float* t_s;
     float* t_perp;
     int64_t ld;
@@ -224,6 +226,7 @@ struct SubtractHighRank {
 // Epilogue of reconstruct: out <- fl(fl(v + T_perp[x]) + PosEmbed); TP / PE: which tables exist.
 template <bool TP, bool PE>
 struct AddHighRank {
+    static constexpr int kTables = (TP ? 1 : 0) + (PE ? 1 : 0);
     static constexpr bool kStaggeredStart = false;     // measured: no gain for the reconstruction
     HighRank h;
     float* out;
@@ -1037,7 +1040,7 @@ void launch_gemm_tile(const float* A, int64_t lda, const float* B, int64_t ldb, 
 //            prefers 64 rows;
 //   with split-bf16 products (measured separately): see below.
 struct GemmTile { bool tall, wide; };
-GemmTile choose_gemm_tile(bool b_nk, int M, int N, int K, bool light_epilogue, int matmul) {
+GemmTile choose_gemm_tile(bool b_nk, int M, int N, int K, int tables, bool light_epilogue, int matmul) {
     auto groups = [&](int tm, int tn) { return (int64_t)((M + tm - 1) / tm) * ((N + tn - 1) / tn); };
     bool wide = ((N + 63) / 64) % 2 == 0 && (b_nk || groups(64, 128) > 128);
     bool tall;
@@ -1045,9 +1048,18 @@ GemmTile choose_gemm_tile(bool b_nk, int M, int N, int K, bool light_epilogue, i
         // split operands: a tile's matrix work is a third as long and splitting costs per staged value, so the
         // large tile, which stages fewest values per product, wins wherever it leaves 1.75 groups per compute unit
         // (16384 x 1536 onto 192 columns has 384: 94 us with 64 rows, 100 with 128; the first pass at 32000 rows 750).
-        // With many column blocks an odd one does not count: 128 columns take 2050 of them in 17 tiles instead of 33
-        // (re-projection 32001 x 2050, k = 170: 505 -> 470 us)
-        if (b_nk && N > 16 * 64) wide = true;
+        // An odd number of column blocks, above 16, does not count in an N x K product where that measured faster:
+        // the re-projection when a row is no whole number of 128-byte lines, so that longer row pieces share fewer of
+        // them, from 900 tiles of 128 x 128 on (32000 x 2050, k 32 / 170 / 224: 0.80 / 0.90 / 0.92 of the time; 8192 x
+        // 1930, 1024 tiles: 0.96 ... 1.00; 10263 x 1470, 972: 0.93; 6000 x 2050, 799: 1.01 ... 1.05; 1000 to 2048 rows:
+        // 1.0 ... 1.2; whole lines, x 1984: 1.0 ... 1.1); a reconstruction without tables from 1536 tiles on (from 64
+        // columns on 0.85 ... 1.00; from 8 ... 48, with whole lines 0.99 ... 1.07, else 0.84 ... 0.92).  With tables it
+        // does not pay (0.95 ... 1.3; 256 rows: 1.7)
+        const bool whole_lines = N % 32 == 0;
+        const int64_t tiles = groups(128, 128);
+        if (b_nk && N > 16 * 64 && (light_epilogue ? tables == 0 && tiles >= 1536 && (K >= 64 || !whole_lines)
+                                                   : !whole_lines && tiles >= 900))
+            wide = true;
         tall = b_nk || groups(128, wide ? 128 : 64) >= 448;
     } else if (light_epilogue && K > 128 && K <= 192 && groups(64, 128) >= 2048) {
         tall = false;
@@ -1063,7 +1075,7 @@ GemmTile choose_gemm_tile(bool b_nk, int M, int N, int K, bool light_epilogue, i
 template <bool B_NK, class Pro, class Epi>
 void launch_gemm(const float* A, int64_t lda, const float* B, int64_t ldb, int M, int N, int K, Pro pro, Epi epi,
                  int matmul, hipStream_t st, bool light_epilogue = false) {
-    const GemmTile t = choose_gemm_tile(B_NK, M, N, K, light_epilogue, matmul);
+    const GemmTile t = choose_gemm_tile(B_NK, M, N, K, Pro::kTables + Epi::kTables, light_epilogue, matmul);
     if (t.tall && t.wide) launch_gemm_tile<128, 128, B_NK>(A, lda, B, ldb, M, N, K, pro, epi, matmul, st);
     else if (t.tall) launch_gemm_tile<128, 64, B_NK>(A, lda, B, ldb, M, N, K, pro, epi, matmul, st);
     else if (t.wide) launch_gemm_tile<64, 128, B_NK>(A, lda, B, ldb, M, N, K, pro, epi, matmul, st);
@@ -1185,11 +1197,11 @@ extern "C" int sparseloco_subspace_kernel_choice(int op, int64_t rows, int d, in
             const HighRank h{n_tab >= 1 ? some : nullptr, nullptr, 0, n_tab >= 2 ? some : nullptr, 1, (int64_t)d};
             if (narrow_applies(d, k, h)) return 16 * 256 + (k <= 16 ? 16 : 32);
             if (rows_apply(M, d, k)) return 16 * 256 + (rows_wide(M, k) ? 64 : 32);
-            t = choose_gemm_tile(false, M, k, d, false, matmul);
+            t = choose_gemm_tile(false, M, k, d, n_tab, false, matmul);
             break;
         }
-        case SPLC_OP_RECONSTRUCT: t = choose_gemm_tile(true, M, d, k, true, matmul); break;
-        case SPLC_OP_REPROJECT_PASS2: t = choose_gemm_tile(true, M, d, k, false, matmul); break;
+        case SPLC_OP_RECONSTRUCT: t = choose_gemm_tile(true, M, d, k, tables, true, matmul); break;
+        case SPLC_OP_REPROJECT_PASS2: t = choose_gemm_tile(true, M, d, k, 0, false, matmul); break;
         default: return SPLC_EINVAL;
     }
     return (t.tall ? 128 : 64) * 256 + (t.wide ? 128 : 64);

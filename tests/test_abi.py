@@ -103,7 +103,15 @@ def test_kernel_choice_follows_the_documented_rule():
     ("RECONSTRUCT", 1024, 1536, 160, 2, "FP32", (64, 64)), ("RECONSTRUCT", 4096, 1536, 192, 2, "FP32", (64, 64)),
     ("RECONSTRUCT", 8191, 2048, 160, 0, "FP32", (64, 128)), ("RECONSTRUCT", 8128, 2048, 160, 0, "FP32", (64, 64)),
     ("RECONSTRUCT", 16384, 1536, 192, 2, "FP32", (64, 128)), ("RECONSTRUCT", 16384, 1536, 128, 2, "FP32", (64, 64)),
-    ("REPROJECT_PASS2", 50304, 2048, 192, 0, "FP32", (64, 64))])
+    ("REPROJECT_PASS2", 50304, 2048, 192, 0, "FP32", (64, 64)),
+    # split operands, N x K, an odd number of column blocks
+    ("RECONSTRUCT", 1024, 2050, 170, 2, "BF16X3", (128, 64)), ("RECONSTRUCT", 32768, 2050, 170, 2, "BF16X3", (128, 64)),
+    ("RECONSTRUCT", 16384, 1472, 170, 0, "BF16X3", (128, 128)), ("RECONSTRUCT", 16256, 1472, 170, 0, "BF16X3", (128, 64)),
+    ("RECONSTRUCT", 16384, 1472, 48, 0, "BF16X3", (128, 64)), ("RECONSTRUCT", 16384, 2050, 48, 0, "BF16X3", (128, 128)),
+    ("RECONSTRUCT", 16384, 1536, 48, 2, "BF16X3", (128, 128)), ("RECONSTRUCT", 50000, 960, 170, 0, "BF16X3", (128, 64)),
+    ("REPROJECT_PASS2", 32001, 2050, 170, 0, "BF16X3", (128, 128)), ("REPROJECT_PASS2", 32000, 1984, 170, 0, "BF16X3", (128, 64)),
+    ("REPROJECT_PASS2", 6000, 2050, 170, 0, "BF16X3", (128, 64)), ("REPROJECT_PASS2", 9600, 1470, 170, 0, "BF16X3", (128, 128)),
+    ("REPROJECT_PASS2", 9472, 1470, 170, 0, "BF16X3", (128, 64))])
 def test_kernel_choice_at_its_lines(op, rows, d, k, tables, matmul, tile):
     """Where the launcher's tile rules change, on both sides of each line."""
     assert B.subspace_kernel_choice(getattr(B, "SPLC_OP_" + op), rows, d, k, tables, getattr(B, "SPLC_MATMUL_" + matmul)) == tile
