@@ -1024,7 +1024,7 @@ void launch_gemm_tile(const float* A, int64_t lda, const float* B, int64_t ldb, 
         hipLaunchKernelGGL((gemm_kernel<MATH_F32, TM_, TN_, B_NK, Pro, Epi>), grid, dim3(kThreads), 0, st, A, lda, B,
                            ldb, M, N, K, pro, epi);
 }
-// Tile choice (measured on the shapes of sections 2.2 and 2.4 at d 1536 / 2048, k = d/8 ... d/16):
+// Tile choice (measured on the shapes of sections 2.2 and 2.4 at d 512 ... 3008, k 8 ... 384, 256 to 65536 rows):
 //   columns: 64 wide when N spans an odd number of 64-column blocks (the last 128-wide tile would be at
 //            most half used), else 128 wide -- unless a projection then has at most 128 tiles, where the time is one
 //            tile's serial reduction (4096 x 2048 onto 256: 87 us with 128 columns, 55 with 64; 8192 x 768 onto 96:
@@ -1038,39 +1038,39 @@ void launch_gemm_tile(const float* A, int64_t lda, const float* B, int64_t ldb, 
 //            101 / 94 us; 8192 x 2048 from 160, 2048: 59 / 57; but 16384 x 768 from 160, 1536: 46 / 48; 2048 x 1536
 //            from 192, 384: 14.6 / 17.2; 256 to 1024 rows: 6.3 / 9.3); beyond K = 192 the reconstruction still
 //            prefers 64 rows;
-//   with split-bf16 products (measured separately): see below.
+//   with split-bf16 products a tile's matrix work is a third as long and splitting costs per staged value, so the large
+//            tile, which stages fewest values per product, wins earlier:
+//     an N x K product takes 128 rows always, and 128 columns also for an odd number of column blocks above 16 where
+//            that measured faster: the re-projection when a row is no whole number of 128-byte lines, so that longer row
+//            pieces share fewer of them, from 900 tiles of 128 x 128 on (32000 x 2050, k 32 / 170 / 224: 0.80 / 0.90 /
+//            0.92 of the time; 8192 x 1930, 1024 tiles: 0.96 ... 1.00; 10263 x 1470, 972: 0.93; 6000 x 2050, 799: 1.01
+//            ... 1.05; 1000 to 2048 rows: 1.0 ... 1.2; whole lines, x 1984: 1.0 ... 1.1); a reconstruction without
+//            tables from 1536 tiles on (from 64 columns on 0.85 ... 1.00; from 8 ... 48, with whole lines 0.99 ...
+//            1.07, else 0.84 ... 0.92).  With tables it does not pay (0.95 ... 1.3; 256 rows: 1.7);
+//     a K x N product takes 128 rows from 1.5 workgroups per compute unit on, unless its 64-row tiles all run at once:
+//            three to a compute unit, 96 to an XCD (16384 x 1536 onto 192, 768 of them: 96 us with 64 rows, 104 with
+//            128; 18000 rows: 115 / 108).  128 columns without tables to gather do not gain by that (24576 x 1536 onto
+//            256: 135 / 127).
 struct GemmTile { bool tall, wide; };
 GemmTile choose_gemm_tile(bool b_nk, int M, int N, int K, int tables, bool light_epilogue, int matmul) {
-    auto groups = [&](int tm, int tn) { return (int64_t)((M + tm - 1) / tm) * ((N + tn - 1) / tn); };
-    bool wide = ((N + 63) / 64) % 2 == 0 && (b_nk || groups(64, 128) > 128);
-    bool tall;
+    auto blocks = [](int n, int t) { return (int64_t)((n + t - 1) / t); };
+    auto groups = [&](int tm, int tn) { return blocks(M, tm) * blocks(N, tn); };
+    bool wide = blocks(N, 64) % 2 == 0 && (b_nk || groups(64, 128) > 128);
     if (matmul == SPLC_MATMUL_BF16X3) {
-        // split operands: a tile's matrix work is a third as long and splitting costs per staged value, so the
-        // large tile, which stages fewest values per product, wins wherever it leaves 1.75 groups per compute unit
-        // (16384 x 1536 onto 192 columns has 384: 94 us with 64 rows, 100 with 128; the first pass at 32000 rows 750).
-        // An odd number of column blocks, above 16, does not count in an N x K product where that measured faster:
-        // the re-projection when a row is no whole number of 128-byte lines, so that longer row pieces share fewer of
-        // them, from 900 tiles of 128 x 128 on (32000 x 2050, k 32 / 170 / 224: 0.80 / 0.90 / 0.92 of the time; 8192 x
-        // 1930, 1024 tiles: 0.96 ... 1.00; 10263 x 1470, 972: 0.93; 6000 x 2050, 799: 1.01 ... 1.05; 1000 to 2048 rows:
-        // 1.0 ... 1.2; whole lines, x 1984: 1.0 ... 1.1); a reconstruction without tables from 1536 tiles on (from 64
-        // columns on 0.85 ... 1.00; from 8 ... 48, with whole lines 0.99 ... 1.07, else 0.84 ... 0.92).  With tables it
-        // does not pay (0.95 ... 1.3; 256 rows: 1.7)
-        const bool whole_lines = N % 32 == 0;
-        const int64_t tiles = groups(128, 128);
-        if (b_nk && N > 16 * 64 && (light_epilogue ? tables == 0 && tiles >= 1536 && (K >= 64 || !whole_lines)
-                                                   : !whole_lines && tiles >= 900))
-            wide = true;
-        tall = b_nk || groups(128, wide ? 128 : 64) >= 448;
-    } else if (light_epilogue && K > 128 && K <= 192 && groups(64, 128) >= 2048) {
-        tall = false;
-    } else if (b_nk && K <= 192) {
-        wide = tall = false;
-    } else if (light_epilogue) {
-        tall = false;
-    } else {
-        tall = groups(128, wide ? 128 : 64) >= 480;
+        if (b_nk) {
+            const bool whole_lines = N % 32 == 0;
+            const int64_t tiles = groups(128, 128);
+            if (N > 16 * 64 && (light_epilogue ? tables == 0 && tiles >= 1536 && (K >= 64 || !whole_lines)
+                                               : !whole_lines && tiles >= 900))
+                wide = true;
+            return GemmTile{true, wide};
+        }
+        const int tn = wide ? 128 : 64;
+        const bool at_once = (blocks(M, 64) + 7) / 8 * blocks(N, tn) <= 96;       // (an XCD takes whole row blocks)
+        return GemmTile{groups(128, tn) >= 384 && !(at_once && (tables > 0 || !wide)), wide};
     }
-    return GemmTile{tall, wide};
+    if (b_nk && K <= 192) return GemmTile{false, wide && light_epilogue && K > 128 && groups(64, 128) >= 2048};
+    return GemmTile{!light_epilogue && groups(128, wide ? 128 : 64) >= 480, wide};
 }
 template <bool B_NK, class Pro, class Epi>
 void launch_gemm(const float* A, int64_t lda, const float* B, int64_t ldb, int M, int N, int K, Pro pro, Epi epi,

@@ -111,7 +111,12 @@ def test_kernel_choice_follows_the_documented_rule():
     ("RECONSTRUCT", 16384, 1536, 48, 2, "BF16X3", (128, 128)), ("RECONSTRUCT", 50000, 960, 170, 0, "BF16X3", (128, 64)),
     ("REPROJECT_PASS2", 32001, 2050, 170, 0, "BF16X3", (128, 128)), ("REPROJECT_PASS2", 32000, 1984, 170, 0, "BF16X3", (128, 64)),
     ("REPROJECT_PASS2", 6000, 2050, 170, 0, "BF16X3", (128, 64)), ("REPROJECT_PASS2", 9600, 1470, 170, 0, "BF16X3", (128, 128)),
-    ("REPROJECT_PASS2", 9472, 1470, 170, 0, "BF16X3", (128, 64))])
+    ("REPROJECT_PASS2", 9472, 1470, 170, 0, "BF16X3", (128, 64)),
+    # split operands, K x N: 64 rows while all those tiles run at once
+    ("PROJECT", 16384, 1536, 192, 2, "BF16X3", (64, 64)), ("PROJECT", 16385, 1536, 192, 2, "BF16X3", (128, 64)),
+    ("PROJECT", 24576, 1536, 256, 1, "BF16X3", (64, 128)), ("PROJECT", 24576, 1536, 256, 0, "BF16X3", (128, 128)),
+    ("PROJECT", 24448, 1536, 256, 0, "BF16X3", (64, 128)), ("REPROJECT_PASS1", 32001, 2050, 170, 0, "BF16X3", (128, 64)),
+    ("PROJECT", 9796, 1536, 320, 0, "BF16X3", (128, 64))])
 def test_kernel_choice_at_its_lines(op, rows, d, k, tables, matmul, tile):
     """Where the launcher's tile rules change, on both sides of each line."""
     assert B.subspace_kernel_choice(getattr(B, "SPLC_OP_" + op), rows, d, k, tables, getattr(B, "SPLC_MATMUL_" + matmul)) == tile
