@@ -716,3 +716,58 @@ def test_batched_calls_with_buffers_shared_by_the_replicas(chunks, quant):
             assert all(torch.equal(x, y) for x, y in zip(run(True, share_ef, beta, step), want))
             assert all(torch.equal(x, y) for x, y in zip(run(False, share_ef, beta, step), want))
     plan.close()
+
+
+@pytest.mark.parametrize("tiled", [False, True])
+@pytest.mark.parametrize("select", [B.SPLC_SELECT_AUTO, B.SPLC_SELECT_RADIX])
+@pytest.mark.parametrize("quant", [True, False])
+@pytest.mark.parametrize("kappa", [1, 32, 128, 256, 257, 1000])
+def test_batched_calls_on_large_plans(kappa, quant, select, tiled):
+    """Beyond 512 chunks one workgroup walks a chunk's replicas: both batched calls against the single calls (which the
+    oracle checks), bit for bit, with messages beyond the candidate filter, the general path, ties at every cut, a
+    constant chunk, an all-zero one, more zeros than kappa leaves, edge chunks, and the reset."""
+    R, shapes = 3, [(64 * 100, 390), (130, 70), (63, 65), (1, 5000), (70, 520), (3, 2)] if tiled else \
+        [4096 * 515, 4096 * 3 + 17, 100, 0, 4095, 1]
+    numels = [s if isinstance(s, int) else s[0] * s[1] for s in shapes]
+    g = torch.Generator(device="cuda").manual_seed(kappa)
+    rn = lambda n: torch.randn(n, generator=g, device="cuda")
+    plan = B.Plan(shapes, kappa, quant, tiled=tiled)
+    plan.set_select(select)
+    assert plan.num_chunks > 512
+    th = [torch.round(rn(n) * 64) * 2.0 ** -12 for n in numels]               # on a grid, so that differences are exact
+    delta = [[torch.round(rn(n) * 3) * 2.0 ** -12 for n in numels] for _ in range(R - 1)] + [[rn(n) * 1e-3 for n in numels]]
+    for r in range(R):
+        first = delta[r][0].view(shapes[0]) if tiled else delta[r][0].view(-1, 64)
+        first[:64, :64] = -0.25                                            # one chunk constant
+        second = first[:64, 64:128] if tiled else first[64:128]
+        second.zero_()
+        third = first[64:128, :64] if tiled else first[128:192]
+        third.mul_((torch.rand(third.shape, generator=g, device="cuda") < 0.01).to(third.dtype))
+    tl = [[t - x for t, x in zip(th, r)] for r in delta]
+    ef = [[torch.zeros_like(t) for t in th] for _ in range(R - 1)] + [[rn(n) * 1e-4 for n in numels]]
+
+    def state():
+        messages = [plan.message_buffers() for _ in range(R)]
+        for p, a in messages:
+            p.fill_(0x5A5A), a.fill_(float("nan"))
+        return ([t.clone() for t in th], [[x.clone() for x in r] for r in tl], [[x.clone() for x in r] for r in ef],
+                [p for p, _ in messages], [a for _, a in messages], [torch.full_like(t, float("nan")) for t in th])
+
+    def equal(x, y):
+        return all(torch.equal(a.view(torch.int32) if a.dtype == torch.float32 else a,
+                               b.view(torch.int32) if b.dtype == torch.float32 else b) for a, b in zip(x, y))
+
+    th1, tl1, ef1, pairs1, aux1, mean1 = state()
+    for r in range(R):
+        B.sparseloco_compress(plan, ef1[r], pairs1[r], aux1[r], 0.95, theta_outer=th1, theta_local=tl1[r])
+    B.sparseloco_aggregate_update(plan, pairs1, th1, 0.75, aux=aux1, delta_bar_out=mean1, reset=tl1)
+    th2, tl2, ef2, pairs2, aux2, _ = state()
+    B.sparseloco_compress_batch(plan, th2, tl2, ef2, pairs2, 0.95, aux_out=aux2)
+    th3, tl3, ef3, pairs3, aux3, mean3 = state()
+    B.sparseloco_outer_step_batch(plan, th3, tl3, ef3, pairs3, 0.95, 0.75, aux_out=aux3, delta_bar_out=mean3, reset=True)
+    torch.cuda.synchronize()
+    for r in range(R):
+        assert equal([pairs2[r], aux2[r]] + ef2[r], [pairs1[r], aux1[r]] + ef1[r]), "batched compress, replica %d" % r
+        assert equal([pairs3[r], aux3[r]] + ef3[r] + tl3[r], [pairs1[r], aux1[r]] + ef1[r] + tl1[r]), "step, replica %d" % r
+    assert equal(th2, th) and equal(th3 + mean3, th1 + mean1)
+    plan.close()
