@@ -192,8 +192,8 @@ STAGE_SHAPES = [
     (77, 11, 64, 3, 9, True, False), (200, 40, 96, 5, 50, False, False), (333, 37, 256, 24, 100, True, True),
     (50, 50, 32, 12, 5, False, True), (1, 1, 32, 4, 2, True, True), (130, 13, 160, 1, 7, True, True),
     (1000, 100, 1024, 20, 300, True, False),
-    # the GEMM kernel with a basis whose width is no multiple of four: its loads run past column k into the next
-    # row of U, except in the guarded last tiles
+    # a basis whose width is no multiple of four: loads run past column k into the next row of U, except in the
+    # guarded last tiles (d >= 256: the projection of few rows; the GEMM kernel's long ones are GEMM_PROJECTIONS below)
     (700, 70, 512, 42, 60, True, True), (300, 30, 1024, 21, 10, True, True), (90, 9, 64, 63, 5, False, True),
     (64, 8, 48, 1, 3, True, True), (2000, 200, 2048, 170, 100, True, False),
     # 128-row tiles of the projection: 128 x 128 (k = 256, 32768 rows) and 128 x 64 (k = 192), with and without tables
@@ -231,6 +231,37 @@ def test_projection_of_few_rows_matches_the_oracle(rows, seq, d, k, vocab, use_p
     tables = int(use_perp) + int(use_pos)
     assert B.subspace_kernel_choice(B.SPLC_OP_PROJECT, rows, d, k, tables, matmul_mode) == (16, columns)
     check_stage_boundary(rows, seq, d, k, vocab, use_perp, use_pos, seed=rows + d + k, mode=matmul_mode)
+
+
+# The GEMM kernel's 64-row tiles on long reductions (more than 128 tiles of 64 x 64: fewer go to the kernel for few
+# rows), with both tables, either and none: widths that are and are not multiples of four, reductions that end inside
+# a K tile, row counts off the 64-row grid.
+GEMM_PROJECTIONS = [
+    (2800, 700, 1536, 192, 100, True, True, 64), (2753, 300, 1023, 170, 64, True, False, 64),
+    (8300, 830, 513, 42, 300, False, True, 64), (8257, 1000, 512, 21, 77, True, True, 64),
+    (4100, 512, 768, 96, 9, False, False, 64), (2800, 100, 2050, 130, 50, False, False, 64),
+    (8300, 830, 704, 128, 200, True, True, 128), (8257, 415, 513, 126, 33, True, False, 128),
+    (4200, 1050, 770, 255, 20, False, True, 128), (8300, 83, 1025, 65, 5, False, False, 128)]
+
+
+@pytest.mark.parametrize("rows,seq,d,k,vocab,use_perp,use_pos,columns", GEMM_PROJECTIONS)
+def test_long_projections_on_64_row_tiles(rows, seq, d, k, vocab, use_perp, use_pos, columns, matmul_mode):
+    tables = int(use_perp) + int(use_pos)
+    assert B.subspace_kernel_choice(B.SPLC_OP_PROJECT, rows, d, k, tables, matmul_mode) == (64, columns)
+    check_stage_boundary(rows, seq, d, k, vocab, use_perp, use_pos, seed=rows + d + k, mode=matmul_mode)
+
+
+# Reconstructions and re-projections on both sides of the lines of the tile choice that depend on the number of tiles
+LINE_SHAPES = [("x", 1024, 1536, 160, True), ("x", 8191, 2048, 160, False), ("x", 1000, 2050, 170, True),
+               ("x", 12300, 2050, 40, False), ("r", 7000, 2050, 30, False), ("r", 6000, 1984, 50, False)]
+
+
+@pytest.mark.parametrize("op,rows,d,k,tables", LINE_SHAPES)
+def test_reconstruction_and_reprojection_at_the_lines_of_the_tile_choice(op, rows, d, k, tables, matmul_mode):
+    if op == "r":
+        check_reproject(rows, d, k, seed=rows + d + k, mode=matmul_mode)
+    else:
+        check_stage_boundary(rows, 500, d, k, 100, tables, tables, seed=rows + d + k, mode=matmul_mode)
 
 
 def test_every_kernel_variant_is_reached(matmul_mode):
