@@ -122,15 +122,6 @@ __device__ __forceinline__ uint32_t lanes_below(uint64_t mask) {
     return __builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u));
 }
 
-__device__ __forceinline__ uint32_t wave_max_u32(uint32_t v) {
-#pragma unroll
-    for (int o = 32; o >= 1; o >>= 1) {
-        uint32_t other = (uint32_t)__shfl_xor((int)v, o);
-        v = other > v ? other : v;
-    }
-    return v;
-}
-
 // e' = fl(fl(beta * e) + delta), delta = fl(theta_outer - theta_local) or given (section 2.1, lines 1-2).
 __device__ __forceinline__ float fold(float beta, float e, float delta) {
     return __fadd_rn(__fmul_rn(beta, e), delta);
@@ -396,7 +387,9 @@ __device__ __forceinline__ void solve_candidates(const SelectShared& sh, int lan
     if (top < 0) X = T0;
     bool exact = n == kappa_c;
     if constexpr (NJ <= 2) {
-        for (int b = top; b >= 0 && !exact; b -= 2) {         // two bits a step (t2, t3 exceed every key if one is left)
+        // two bits a step; at least kappa_c candidates are >= X, fewer are >= X + 2^(b+1): with one bit left (b = 0)
+        // t2 and t3 can neither be taken nor end the loop
+        for (int b = top; b >= 0 && !exact; b -= 2) {
             const int sh2 = b > 0 ? b - 1 : 0;
             const uint32_t t1 = X + (1u << sh2), t2 = X + (2u << sh2), t3 = X + (3u << sh2);
             uint32_t c1 = 0, c2 = 0, c3 = 0;
@@ -804,14 +797,15 @@ __global__ __launch_bounds__(kThreads) void compress_kernel(const ChunkDesc* __r
 // one-tile kernels.
 constexpr int kStripTiles = 4;
 constexpr int kStripThreads = kStripTiles * kThreads;
-// Two strip workgroups per compute unit (8 waves per SIMD, 64 registers per lane, 2 x 77 KB of LDS): one of
-// them selects while the other one's rows are in flight.
+// Two strip workgroups per compute unit (8 waves per SIMD, 64 registers per lane, half of the 160 KB of LDS each): one
+// of them selects while the other one's rows are in flight.
 
 struct StripShared {
     float tile[kStripTiles][kChunk];     // local index order: [row * 64 + column]
     SelectShared sel[kStripTiles];
     uint32_t group_ok[kStripTiles];
 };
+static_assert(sizeof(StripShared) <= 160 * 1024 / 2, "two strip workgroups share a compute unit's LDS");
 
 // Row-wise position of lane `lane` of wave `wave` (0..15) in round i (0..3): local row 16 i + wave of the strip,
 // floats 4 lane .. 4 lane + 3 of that row, i.e. tile lane / 16, local columns 4 (lane % 16) ...
@@ -1087,7 +1081,7 @@ __device__ __forceinline__ void compress_batch_body(SelectShared& sh, float* so,
     }
 }
 
-// Four workgroups per compute unit: the register allocation is held to 128.
+// Four workgroups per compute unit (three on large plans, see reserve_lds): the register allocation is held to 128.
 template <int QUANT, bool STEP>
 __global__ __launch_bounds__(kThreads, 4) void compress_batch_kernel(const ChunkDesc* __restrict__ chunks, uint32_t n_gen,
                                                                   int n_replicas, uint32_t n_tensors,
@@ -1576,12 +1570,13 @@ unsigned gen_entries(const sparseloco_plan* plan, bool bf16_source) {
 
 // Large plans stream far more than the last-level cache holds, and there fewer workgroups per compute unit than would
 // fit keep the memory busier (fewer streams in flight at once).  Their launches reserve LDS so that only
-// `groups_per_unit` fit.  Measured, all that fit -> reserved:
-//   compress, 3: 16,384 chunks, kappa 32 / 128: 173.3 / 174.4 -> 166.4 / 169.2 us; 37,105: 396.8 / 395.5 -> 377.5 /
-//     376.6; 8192: 86.8 / 86.9 -> 84.9 / 87.0; but 4096: 43.3 / 43.7 -> 44.1 / 46.1 (a few rounds of workgroups only, where
-//     latency counts).  With 2, 4: slower (0.9B model, one compress + aggregate + update: 5.15, 4.86 ms; 3: 4.72).
-//   one-launch step, 3: 150M parameters, 8 replicas: 2938 -> 2889 us; with 2: 3138.
-//   outer update, 2: 0.9B model, whole step 4.72 -> 4.65 ms; 24,000 chunks: 184.2 -> 182.7 us; 8192: 61.9 -> 62.3.
+// `groups_per_unit` fit.  Measured, all that fit -> reserved, in us:
+//   compress, 3: 16,384 chunks, kappa 32 / 128: 175.8 / 175.1 -> 169.1 / 171.5; 37,105: 402.5 / 397.9 -> 384.1 / 386.2;
+//     120,000: 1319 / 1319 -> 1228 / 1218; 8192: 93.0 / 92.1 -> 90.8 / 91.5; but 4096: 43.3 / 43.7 -> 44.1 / 46.1 (a few
+//     rounds of workgroups only, where latency counts).  4 changes little, 2 loses 7 to 25 %.
+//   one-launch step, 3: 37,105 chunks (150M parameters), kappa 32, 8 replicas: 2862 -> 2833, 2: 832 -> 799; 8192, 8: 625
+//     -> 601, 2: 179 -> 179; but 2000 chunks, 2: 48.4 -> 51.6.
+//   outer update, 2: 228,000 chunks (0.9B model): 1866 -> 1803, 120,000: 959 -> 945; 24,000 to 37,105: no difference.
 constexpr int64_t kStreamingChunks = 8192, kStreamingChunksUpdate = 24000;
 unsigned reserve_lds(int64_t chunks, int64_t from, int groups_per_unit, size_t used) {
     const size_t share = 160 * 1024 / (size_t)groups_per_unit / 1280 * 1280;       // LDS is handed out in 1280-byte units
