@@ -386,10 +386,16 @@ __device__ __forceinline__ void solve_candidates(const SelectShared& sh, int lan
     uint32_t X = T0 & ~((2u << (top < 0 ? 0 : top)) - 1u);
     if (top < 0) X = T0;
     bool exact = n == kappa_c;
+    // bf16 pseudo-gradients and other coarse values leave the lower half of every key empty: nothing to decide there
+    // (one chunk of bf16 values at kappa 16 / 32: 6.1 / 6.3 -> 5.2 / 5.4 us; 1024 chunks, 16: 11.4 -> 9.8)
+    uint32_t used = 0;
+#pragma unroll
+    for (int j = 0; j < NJ; ++j) used |= key[j];
+    const int low = __ballot((used & 0xFFFFu) != 0) ? 0 : 16;
     if constexpr (NJ <= 2) {
         // two bits a step; at least kappa_c candidates are >= X, fewer are >= X + 2^(b+1): with one bit left (b = 0)
         // t2 and t3 can neither be taken nor end the loop
-        for (int b = top; b >= 0 && !exact; b -= 2) {
+        for (int b = top; b >= low && !exact; b -= 2) {
             const int sh2 = b > 0 ? b - 1 : 0;
             const uint32_t t1 = X + (1u << sh2), t2 = X + (2u << sh2), t3 = X + (3u << sh2);
             uint32_t c1 = 0, c2 = 0, c3 = 0;
@@ -403,7 +409,7 @@ __device__ __forceinline__ void solve_candidates(const SelectShared& sh, int lan
             exact = c1 == kappa_c || c2 == kappa_c || c3 == kappa_c;
         }
     } else {
-        for (int b = top; b >= 0 && !exact; --b) {            // one bit: a step has enough independent work, and fewer
+        for (int b = top; b >= low && !exact; --b) {            // one bit: a step has enough independent work, and fewer
             const uint32_t t = X + (1u << b);                 // instructions count where memory is what bounds
             uint32_t c = 0;
 #pragma unroll
