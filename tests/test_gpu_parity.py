@@ -771,3 +771,29 @@ def test_batched_calls_on_large_plans(kappa, quant, select, tiled):
         assert equal([pairs3[r], aux3[r]] + ef3[r] + tl3[r], [pairs1[r], aux1[r]] + ef1[r] + tl1[r]), "step, replica %d" % r
     assert equal(th2, th) and equal(th3 + mean3, th1 + mean1)
     plan.close()
+
+
+@pytest.mark.parametrize("select", [B.SPLC_SELECT_AUTO, B.SPLC_SELECT_RADIX])
+@pytest.mark.parametrize("kappa", [1, 32, 300, 1000])
+def test_general_path_with_few_nonzeros(kappa, select):
+    """The general path leaves zeros out of its counts: chunks with none, one fewer than kappa, kappa and one more
+    nonzeros (subnormals among them, and many of one magnitude), whole and short, against the oracle."""
+    rng = np.random.default_rng(kappa)
+    sizes = [4096] * 8 + [4095, 2000, 1500, 1001, 1000]
+    x = []
+    for i, n in enumerate(sizes):
+        v = np.zeros(n, np.float32)
+        count = [0, kappa - 1, kappa, kappa + 1, 1, 2 * kappa][i % 6]
+        at = rng.permutation(n)[:min(count, n)]
+        v[at] = rng.standard_normal(at.size).astype(np.float32)
+        if i % 4 == 1:
+            v[at] = np.float32(0.75) * np.sign(v[at])                    # one magnitude
+        if i % 4 == 2 and at.size:
+            v[at[0]] = np.uint32(1).view(np.float32)                     # the smallest subnormal
+        v[rng.integers(0, n, n // 8)] *= np.float32(-1.0)                # zeros of both signs
+        x.append(v)
+    th = [np.zeros(n, np.float32) for n in sizes]
+    ef = [[np.zeros(n, np.float32) for n in sizes]]
+    parity.check(parity.HostCase(th, ef, delta=[x]), kappa, beta=1.0, select=select, what="few nonzeros, kappa %d" % kappa)
+    parity.check(parity.HostCase(th, ef, delta=[x]), kappa, beta=1.0, quant=False, select=select,
+                 what="few nonzeros, identity, kappa %d" % kappa)
