@@ -590,7 +590,9 @@ __device__ __forceinline__ Threshold find_threshold(SelectShared& sh, const floa
         __syncthreads();
         if (FROM_LDS && (group_ok[0] & group_ok[1] & group_ok[2] & group_ok[3]) == 0) th.n_cand = 0;
         if (th.n_cand != 0) {
-            if (n <= 128) solve_candidates<2>(sh, lane, n, kappa_c, T0, th);
+            // (one register of candidates where they fit: kappa 16 and less, 1024 chunks 9.56 -> 9.30 us)
+            if (n <= 64) solve_candidates<1>(sh, lane, n, kappa_c, T0, th);
+            else if (n <= 128) solve_candidates<2>(sh, lane, n, kappa_c, T0, th);
             else if (n <= 256) solve_candidates<4>(sh, lane, n, kappa_c, T0, th);
             else solve_candidates<7>(sh, lane, n, kappa_c, T0, th);
         }
