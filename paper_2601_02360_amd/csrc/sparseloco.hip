@@ -155,6 +155,7 @@ __device__ __forceinline__ void load_fold_full(const void* __restrict__ a, const
         float4 dv[4];
 #pragma unroll
         for (int s = 0; s < 4; ++s) dv[s] = stream_load4(vec_at(pd, d, tid, s));
+        __builtin_amdgcn_sched_barrier(0);            // all eight in flight before the first is waited for
 #pragma unroll
         for (int s = 0; s < 4; ++s) {
             x[4 * s + 0] = fold(beta, ev[s].x, dv[s].x);
@@ -168,6 +169,7 @@ __device__ __forceinline__ void load_fold_full(const void* __restrict__ a, const
         uint2 dv[4];
 #pragma unroll
         for (int s = 0; s < 4; ++s) dv[s] = stream_load4(vec_at(pd, d, tid, s));
+        __builtin_amdgcn_sched_barrier(0);            // all eight in flight before the first is waited for
 #pragma unroll
         for (int s = 0; s < 4; ++s) {
             x[4 * s + 0] = fold(beta, ev[s].x, __uint_as_float(dv[s].x << 16));
