@@ -65,6 +65,10 @@ __device__ __forceinline__ uint32_t elem_of(const ChunkDesc& d, uint32_t idx) {
 __device__ __forceinline__ uint32_t present_or_first(const ChunkDesc& d, uint32_t idx) {
     return present(d, idx) ? elem_of(d, idx) : 0u;
 }
+// Whether round i (kThreads indices, four rows) of an edge chunk's walk can hold anything, looked at four rounds at a
+// time: short chunks (the tail of a tensor, mostly) skip the address arithmetic of the rest, tall ones branch rarely
+// (outer update of a tail of 17 / 4095 elements: 2.78 / 4.17 -> 1.90 / 3.62 us).
+__device__ __forceinline__ bool round_used(const ChunkDesc& d, int i) { return 16 * (i >> 2) < (int)d.h; }
 // Address of lane tid's 4-element vector in slot s (local rows 16 s + tid / 16, columns 4 (tid % 16)...).
 // The slot part is uniform and stays in scalar registers; the per-lane part is one 32-bit byte
 // offset shared by all slots and arrays (a chunk spans less than 4 GiB: stride < 2^24).
@@ -1325,10 +1329,12 @@ __device__ __forceinline__ void aggregate_body(float* acc, const ChunkDesc* __re
         float te[16];
         if (UPDATE) {
 #pragma unroll
-            for (int i = 0; i < 16; ++i) te[i] = *elem_at(th, present_or_first(d, tid + kThreads * i));
+            for (int i = 0; i < 16; ++i)
+                if (round_used(d, i)) te[i] = *elem_at(th, present_or_first(d, tid + kThreads * i));
         }
 #pragma unroll
         for (int i = 0; i < 16; ++i) {
+            if (!round_used(d, i)) break;
             const uint32_t idx = tid + kThreads * i;
             if (!present(d, idx)) continue;
             const uint32_t at = elem_of(d, idx);
@@ -1453,12 +1459,14 @@ __device__ __forceinline__ void outer_update_body(const ChunkDesc* __restrict__ 
         float t[16], g[16];
 #pragma unroll
         for (int i = 0; i < 16; ++i) {
+            if (!round_used(d, i)) break;
             const uint32_t at = present_or_first(d, tid + kThreads * i);
             t[i] = *elem_at(th, at);
             g[i] = *elem_at(db, at);
         }
 #pragma unroll
         for (int i = 0; i < 16; ++i) {
+            if (!round_used(d, i)) break;
             const uint32_t idx = tid + kThreads * i;
             if (present(d, idx)) th[elem_of(d, idx)] = __fsub_rn(t[i], __fmul_rn(eta, g[i]));
         }

@@ -797,3 +797,13 @@ def test_general_path_with_few_nonzeros(kappa, select):
     parity.check(parity.HostCase(th, ef, delta=[x]), kappa, beta=1.0, select=select, what="few nonzeros, kappa %d" % kappa)
     parity.check(parity.HostCase(th, ef, delta=[x]), kappa, beta=1.0, quant=False, select=select,
                  what="few nonzeros, identity, kappa %d" % kappa)
+
+
+@pytest.mark.parametrize("fused", [None, "with_mean", "no_mean"])
+@pytest.mark.parametrize("tiled", [False, True])
+def test_edge_chunks_around_the_groups_of_rounds(tiled, fused):
+    """Edge chunks whose rows end just before, at and after the sixteen rows that the update's walk looks at together."""
+    rows = [1, 3, 4, 15, 16, 17, 31, 32, 33, 47, 48, 49, 63]
+    shapes = [(r, 70) for r in rows] if tiled else None
+    case = gaussian_case(None if tiled else [64 * r + e for r in rows for e in (-1, 0, 1)], R=3, seed=61, shapes=shapes)
+    parity.check(case, 32, lr=0.8, fused=fused, what="rounds of edge chunks")
