@@ -39,6 +39,23 @@ constexpr bool replicas_side_by_side(int64_t chunks, int replicas, bool step, bo
     return chunks <= kFewChunks && !(step && replicas == 1) && buffers_disjoint;
 }
 
+// Large plans stream far more than the last-level cache holds, and there fewer workgroups per compute unit than would fit
+// keep the memory busier (fewer streams in flight at once) -- as long as memory is what bounds: with other sources, which
+// move less per chunk, and with messages or data that need the general path of the selection, the workgroups left out are
+// missed.  Measured, all that fit / three per compute unit, in us:
+//   compress from parameters: 9000 chunks, kappa 32 / 128: 96.7 / 97.5 -> 94.6 / 96.5; 37,105: 400 / 395 -> 381 / 380;
+//     120,000: 1319 / 1319 -> 1228 / 1218; coarse values, 32: 394 -> 378; 1 % nonzeros, 32: 421 -> 521 (that data took 702
+//     before the general path left zeros out); kappa 200: 408 -> 477, 256: 407 -> 661, 1000: 419 -> 608; 4096 chunks, 32:
+//     43.3 -> 44.1 (a few rounds of workgroups only).  Four per unit change little, two lose 7 to 25 %;
+//   compress from bf16: 9000 chunks, kappa 32 / 128: 62.9 / 63.5 -> 73.9 / 81.9; from fp32 differences 72 -> 77;
+//   one-launch step: 37,105 chunks (150M parameters), kappa 32, 8 replicas: 2862 -> 2833, 2: 832 -> 799; 8192, 8: 625 ->
+//     601, 2: 179 -> 179; 2000, 2: 48.4 -> 51.6;
+//   outer update, two per unit: 228,000 chunks (0.9B model): 1866 -> 1803, 120,000: 959 -> 945; 24,000 to 37,105: the same.
+constexpr int64_t kFewStreams = 8192, kFewStreamsUpdate = 24000;
+constexpr bool few_streams(int64_t chunks, int kappa, bool from_params, bool general_path) {
+    return chunks >= kFewStreams && kappa <= 128 && from_params && !general_path;
+}
+
 // Whether no two of these address ranges [first, second) share a byte; empty ranges share none.
 inline bool disjoint(std::vector<std::pair<uintptr_t, uintptr_t>> ranges) {
     std::sort(ranges.begin(), ranges.end());

@@ -1599,19 +1599,14 @@ unsigned gen_entries(const sparseloco_plan* plan, bool bf16_source) {
     return (unsigned)(bf16_source ? plan->n_gen_bf16 : plan->n_gen_f32);
 }
 
-// Large plans stream far more than the last-level cache holds, and there fewer workgroups per compute unit than would
-// fit keep the memory busier (fewer streams in flight at once).  Their launches reserve LDS so that only
-// `groups_per_unit` fit.  Measured, all that fit -> reserved, in us:
-//   compress, 3: 16,384 chunks, kappa 32 / 128: 175.8 / 175.1 -> 169.1 / 171.5; 37,105: 402.5 / 397.9 -> 384.1 / 386.2;
-//     120,000: 1319 / 1319 -> 1228 / 1218; 8192: 93.0 / 92.1 -> 90.8 / 91.5; but 4096: 43.3 / 43.7 -> 44.1 / 46.1 (a few
-//     rounds of workgroups only, where latency counts).  4 changes little, 2 loses 7 to 25 %.
-//   one-launch step, 3: 37,105 chunks (150M parameters), kappa 32, 8 replicas: 2862 -> 2833, 2: 832 -> 799; 8192, 8: 625
-//     -> 601, 2: 179 -> 179; but 2000 chunks, 2: 48.4 -> 51.6.
-//   outer update, 2: 228,000 chunks (0.9B model): 1866 -> 1803, 120,000: 959 -> 945; 24,000 to 37,105: no difference.
-constexpr int64_t kStreamingChunks = 8192, kStreamingChunksUpdate = 24000;
-unsigned reserve_lds(int64_t chunks, int64_t from, int groups_per_unit, size_t used) {
-    const size_t share = 160 * 1024 / (size_t)groups_per_unit / 1280 * 1280;       // LDS is handed out in 1280-byte units
-    return chunks >= from && used < share ? (unsigned)(share - used) : 0u;
+// LDS that a launch on a large plan reserves so that only `groups_per_unit` of its workgroups, which use `used` bytes
+// each, fit on a compute unit (splc::few_streams).  LDS is handed out in 1280-byte units.
+unsigned reserve_lds(int groups_per_unit, size_t used) {
+    const size_t share = 160 * 1024 / (size_t)groups_per_unit / 1280 * 1280;
+    return used < share ? (unsigned)(share - used) : 0u;
+}
+unsigned reserve_lds_compress(const sparseloco_plan* plan, int64_t entries, bool from_params, size_t used) {
+    return splc::few_streams(entries, plan->kappa, from_params, plan->select == SPLC_SELECT_RADIX) ? reserve_lds(3, used) : 0u;
 }
 
 template <int MODE, int QUANT>
@@ -1624,7 +1619,7 @@ void launch_compress(const sparseloco_plan* plan, const void* const* a, const vo
                            plan->radix_counter, pairs_out, aux_out);
     if (plan->n_entries > 0)
         hipLaunchKernelGGL((compress_kernel<MODE, QUANT>), dim3((unsigned)plan->n_entries), dim3(kThreads),
-                           reserve_lds(plan->n_entries, kStreamingChunks, 3, sizeof(SelectShared)), stream, plan->d_chunks,
+                           reserve_lds_compress(plan, plan->n_entries, MODE == MODE_PARAMS_F32, sizeof(SelectShared)), stream, plan->d_chunks,
                            gen_entries(plan, MODE == MODE_DIRECT_BF16), a, b, ef, beta, (uint32_t)plan->kappa,
                            force_radix, plan->radix_counter, pairs_out, aux_out);
 }
@@ -1663,7 +1658,7 @@ void launch_compress_batch(const sparseloco_plan* plan, int n_replicas, bool dis
     // could use, so the batched path walks the per-chunk view kept behind the update table.
     const size_t used = sizeof(SelectShared) + sizeof(float) * (kChunk + (STEP ? kChunk : 4));
     hipLaunchKernelGGL((compress_batch_kernel<QUANT, STEP>), dim3((unsigned)plan->n_chunks), dim3(kThreads),
-                       reserve_lds(plan->n_chunks, kStreamingChunks, 3, used), stream,
+                       reserve_lds_compress(plan, plan->n_chunks, true, used), stream,
                        plan->d_all, (unsigned)plan->n_all_gen, n_replicas, (uint32_t)plan->n_tensors, to, tl, ef,
                        beta, (uint32_t)plan->kappa, plan->select == SPLC_SELECT_RADIX ? 1 : 0, plan->radix_counter, pairs,
                        aux, eta, dbar, reset);
@@ -2203,7 +2198,8 @@ int sparseloco_outer_update(const sparseloco_plan* plan, const sparseloco_tensor
     if ((rc = current_device_is(plan->device)) != SPLC_OK) return rc;
     if (plan->n_chunks == 0) return SPLC_OK;
     hipLaunchKernelGGL(outer_update_kernel, dim3((unsigned)plan->n_update), dim3(kThreads),
-                       reserve_lds(plan->n_update, kStreamingChunksUpdate, 2, 0), static_cast<hipStream_t>(stream), plan->d_update, (unsigned)plan->n_update_gen,
+                       plan->n_update >= splc::kFewStreamsUpdate ? reserve_lds(2, 0) : 0u, static_cast<hipStream_t>(stream),
+                       plan->d_update, (unsigned)plan->n_update_gen,
                        set_table<float*>(theta_outer, 0), set_table<const float*>(delta_bar, 0), outer_lr);
     return hipGetLastError() == hipSuccess ? SPLC_OK : SPLC_EHIP;
 }

@@ -54,8 +54,22 @@ static int check_side_by_side() {
     return 0;
 }
 
+// Fewer workgroups per compute unit only where memory bounds the launch.
+static int check_few_streams() {
+    const struct { int64_t chunks; int kappa; bool params, general, want; } cases[] = {
+        {8192, 32, true, false, true}, {8191, 32, true, false, false}, {220000, 128, true, false, true},
+        {220000, 129, true, false, false}, {220000, 1000, true, false, false}, {220000, 32, false, false, false},
+        {220000, 32, true, true, false}};
+    for (const auto& c : cases)
+        if (splc::few_streams(c.chunks, c.kappa, c.params, c.general) != c.want) {
+            printf("few_streams: %ld chunks, kappa %d\n", (long)c.chunks, c.kappa);
+            return 1;
+        }
+    return 0;
+}
+
 int main() {
-    if (check_unguarded_tiles() || check_side_by_side()) return 1;
+    if (check_unguarded_tiles() || check_side_by_side() || check_few_streams()) return 1;
     printf("ok\n");
     return 0;
 }
