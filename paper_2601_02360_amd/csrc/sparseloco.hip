@@ -474,7 +474,8 @@ __device__ __forceinline__ void solve_candidates(const SelectShared& sh, int lan
 // group_ok: four flags in LDS when four 256-lane groups of one workgroup each select a chunk of their own side
 // by side (tid, lane, wave are then group-local and `sh` is the group's own).  Workgroup barriers must be
 // reached by all groups alike, so the groups agree on the path: if one needs the general path, all take it.
-template <bool FROM_LDS = false>
+// WALK: the caller walks replicas in one workgroup.
+template <bool FROM_LDS = false, bool WALK = false>
 __device__ __forceinline__ Threshold find_threshold(SelectShared& sh, const float (&x)[16], int tid, int lane, int wave,
                                                     uint32_t kappa_c, uint32_t kappa, uint32_t pmask, bool edge,
                                                     int force_radix, uint32_t* radix_counter, const float* lds_chunk = nullptr,
@@ -596,8 +597,9 @@ __device__ __forceinline__ Threshold find_threshold(SelectShared& sh, const floa
         __syncthreads();
         if (FROM_LDS && (group_ok[0] & group_ok[1] & group_ok[2] & group_ok[3]) == 0) th.n_cand = 0;
         if (th.n_cand != 0) {
-            // (one register of candidates where they fit: kappa 16 and less, 1024 chunks 9.56 -> 9.30 us)
-            if (n <= 64) solve_candidates<1>(sh, lane, n, kappa_c, T0, th);
+            // (one register of candidates where they fit: kappa 16 and less, 1024 chunks 9.56 -> 9.30 us; in the walk over
+            // replicas it lost: 150M parameters, 8 replicas 2865 -> 2890 us, 720 chunks, 5 replicas 40.1 -> 41.3)
+            if (!WALK && n <= 64) solve_candidates<1>(sh, lane, n, kappa_c, T0, th);
             else if (n <= 128) solve_candidates<2>(sh, lane, n, kappa_c, T0, th);
             else if (n <= 256) solve_candidates<4>(sh, lane, n, kappa_c, T0, th);
             else solve_candidates<7>(sh, lane, n, kappa_c, T0, th);
@@ -1066,8 +1068,8 @@ __device__ __forceinline__ void compress_batch_body(SelectShared& sh, float* so,
             }
         }
         float* aux_r = aux_tab[r];
-        const Threshold th = find_threshold(sh, x, t, t & 63, wave, kappa_c, kappa, pmask, !VEC, force_radix,
-                                            radix_counter);
+        const Threshold th = find_threshold<false, true>(sh, x, t, t & 63, wave, kappa_c, kappa, pmask, !VEC, force_radix,
+                                                         radix_counter);
         quantise_pack_sum<QUANT, STEP>(sh, th, x, sum, t, t & 63, wave, kappa_c, kappa, pmask, pairs_tab[r] + c * kappa,
                                        aux_r + c * kappa, aux_r + 2 * c);
         store_ef<VEC>(pe, d, t, pmask, x);
