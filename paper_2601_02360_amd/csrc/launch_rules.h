@@ -23,6 +23,47 @@ constexpr int unguarded_tiles(int rows, int width, int floats, int tile_rows) {
     return (rows - spare) / tile_rows;
 }
 
+// Second product of the subspace calls (out [rows, width] = coefficients [rows, k] U^T): expand_kernel, which keeps rows of
+// coefficients in registers and walks along the columns, instead of the GEMM kernel's tile per workgroup.  It needs whole
+// 128-byte lines in a row (with rows of 1100 or 1300 floats it takes 1.2 to 1.6 times as long), k above 32 (below, memory
+// bounds both) and what fits its registers and LDS: k <= 256, split products 224.  tiles: of 128 rows x 32 columns.
+// Time of the GEMM kernel over time of expand_kernel, MI355X:
+//   update (re-projection, both passes): split 128 x 512 ... 45056 x 1536, k 33 ... 214: 1.02 ... 1.5 (width 320 on 24,064
+//     rows 0.97); fp32 from 3072 tiles on 1.01 ... 1.15, 1248 ... 2760 tiles 0.90 ... 1.06, fewer 0.73 ... 1.0;
+//   reconstruction, split: k from 65 on, an even number of 64-column blocks: 1.03 ... 1.98; an odd number (the GEMM tile is
+//     64 columns wide there): 0.95 ... 1.1 up to 700 tiles, 1.1 ... 1.44 from 1200 on; k to 64: with tables 1.01 ... 1.31 (odd
+//     blocks 0.95 ... 1.15), without 0.83 ... 1.3 with no clear line;
+//   reconstruction, fp32: with tables from 3072 tiles on and k from 80 on 1.03 ... 1.22 (k above 224: 8192 rows x 2048, 4096
+//     tiles, 1.02; without tables 0.98), without tables from 4096 tiles and k 128 on 1.02 ... 1.11; fewer tiles 0.77 ... 1.06.
+constexpr bool expand_applies(int64_t rows, int width, int k, int tables, bool update, bool split) {
+    if (width % 32 != 0 || width >= 1 << 20 || k <= 32 || k > (split ? 224 : 256)) return false;
+    const int64_t tiles = (rows + 127) / 128 * (width / 32);
+    if (tiles >= int64_t(1) << 31) return false;
+    if (update) return split ? width > 320 || tiles < 1024 : tiles >= 3072;
+    if (split) return (k > 64 || tables > 0) && (width % 128 == 0 || tiles >= 1200);
+    return tables > 0 ? k >= 80 && tiles >= 3072 : k >= 128 && tiles >= (k > 224 ? 8192 : 4096);
+}
+
+// How expand_kernel's workgroups share the tiles: `parts` of them each take an equal part of one row block's column tiles,
+// or (parts 0) each takes an equal run of all tiles, row block after row block, and new rows on the way.
+struct TileRun { int row_block, col_tile, tiles; };
+constexpr TileRun tile_run(int place, int groups, int row_blocks, int col_tiles, int parts) {
+    if (parts > 0) {
+        const int part = place % parts, each = col_tiles / parts, more = col_tiles % parts;
+        return TileRun{place / parts, part * each + (part < more ? part : more), each + (part < more ? 1 : 0)};
+    }
+    const int tiles = row_blocks * col_tiles, each = tiles / groups, more = tiles % groups;
+    const int first = place * each + (place < more ? place : more);
+    return TileRun{first / col_tiles, first % col_tiles, each + (place < more ? 1 : 0)};
+}
+// Parts of a row block, unless equal runs are shorter by more than the two tiles that taking new rows costs (their loads,
+// 3 to 4 us, and the two tiles in flight, which are finished first).
+constexpr int parts_of_row_block(int row_blocks, int col_tiles, int units) {
+    const int parts = units / row_blocks < col_tiles ? units / row_blocks : col_tiles;
+    const int64_t run = ((int64_t)row_blocks * col_tiles + units - 1) / units;
+    return parts > 0 && (col_tiles + parts - 1) / parts <= run + 2 ? parts : 0;
+}
+
 // Batched calls (compress of several replicas, one-launch step): on plans of few chunks every replica of a chunk gets a
 // workgroup of its own, and the one-launch step becomes two launches with the same results: the walk over the replicas
 // is a chain, some 4 us each.  Measured, kappa 32, walk / side by side, in us:

@@ -1082,6 +1082,14 @@ void launch_gemm(const float* A, int64_t lda, const float* B, int64_t ldb, int M
     else launch_gemm_tile<64, 64, B_NK>(A, lda, B, ldb, M, N, K, pro, epi, matmul, st);
 }
 
+#include "subspace_expand.h"
+
+// expand_kernel addresses the tables by 32-bit byte offsets
+bool tables_in_32_bits(const HighRank& h, int rows) {
+    const int64_t positions = h.seq_len < rows ? h.seq_len : rows;
+    return (!h.t_perp || h.vocab * h.ld < (int64_t)1 << 30) && (!h.pos || positions * h.ld < (int64_t)1 << 30);
+}
+
 bool valid_matmul(int matmul) { return matmul == SPLC_MATMUL_FP32 || matmul == SPLC_MATMUL_BF16X3; }
 
 bool aligned4(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 3) == 0; }
@@ -1112,9 +1120,12 @@ int reproject_impl(float* t_s, float* t_perp, const float* u, float* coeff_ws, i
         launch_gemm<false>(t_s, (int64_t)d, u, (int64_t)k, M, k, d, NoPrologue{}, StoreCoeff{coeff_ws, (int64_t)k}, matmul,
                            st);
     // pass 2: Pi = coeff U^T           (M x d) = (M x k)(k x d), U given as d x k = the N x K form
-    launch_gemm<true>(coeff_ws, (int64_t)k, u, (int64_t)k, M, d, k, NoPrologue{},
-                      UpdateEmbedding{t_s, t_perp, (int64_t)d, compute_units()},
-                      matmul, st);
+    if (splc::expand_applies(M, d, k, 0, true, matmul == SPLC_MATMUL_BF16X3))
+        launch_expand<EPI_UPDATE>(ExpandArgs{coeff_ws, u, t_s, t_perp, HighRank{}, M, d, k, 0, 0}, matmul, compute_units(),
+                                  st);
+    else
+        launch_gemm<true>(coeff_ws, (int64_t)k, u, (int64_t)k, M, d, k, NoPrologue{},
+                          UpdateEmbedding{t_s, t_perp, (int64_t)d, compute_units()}, matmul, st);
     return hipGetLastError() == hipSuccess ? SPLC_OK : SPLC_EHIP;
 }
 
@@ -1249,6 +1260,16 @@ extern "C" int sparseloco_subspace_reconstruct(const float* x_tilde, const float
     const int M = (int)rows;
     const HighRank h{t_perp, token_ids, vocab, pos_embed, seq_len > 0 ? seq_len : 1, (int64_t)d};
     hipStream_t st = static_cast<hipStream_t>(stream);
+    const int tables = (t_perp ? 1 : 0) + (pos_embed ? 1 : 0);
+    if (splc::expand_applies(M, d, k, tables, false, matmul == SPLC_MATMUL_BF16X3) && tables_in_32_bits(h, M)) {
+        const ExpandArgs g{x_tilde, u, x_hat, nullptr, h, M, d, k, 0, 0};
+        const int units = compute_units();
+        if (t_perp && pos_embed) launch_expand<EPI_PERP | EPI_POS>(g, matmul, units, st);
+        else if (t_perp) launch_expand<EPI_PERP>(g, matmul, units, st);
+        else if (pos_embed) launch_expand<EPI_POS>(g, matmul, units, st);
+        else launch_expand<0>(g, matmul, units, st);
+        return hipGetLastError() == hipSuccess ? SPLC_OK : SPLC_EHIP;
+    }
     if (t_perp && pos_embed)
         launch_gemm<true>(x_tilde, (int64_t)k, u, (int64_t)k, M, d, k, NoPrologue{}, AddHighRank<true, true>{h, x_hat},
                           matmul, st, true);

@@ -1,0 +1,51 @@
+// How expand_kernel's workgroups share the output tiles (csrc/launch_rules.h), on the CPU: every tile exactly once.
+#include <algorithm>
+#include <cstdio>
+#include <initializer_list>
+#include <vector>
+
+#include "launch_rules.h"
+
+static int check(int row_blocks, int col_tiles, int units) {
+    const int parts = splc::parts_of_row_block(row_blocks, col_tiles, units);
+    const int tiles = row_blocks * col_tiles, groups = parts ? parts * row_blocks : std::min(tiles, units);
+    std::vector<char> seen(tiles, 0);
+    int most = 0;
+    for (int place = 0; place < groups; ++place) {
+        const splc::TileRun r = splc::tile_run(place, groups, row_blocks, col_tiles, parts);
+        const int first = r.row_block * col_tiles + r.col_tile;
+        if (r.tiles < 0 || (r.tiles > 0 && (r.row_block < 0 || r.col_tile < 0 || r.col_tile >= col_tiles))) return 1;
+        if (parts && r.col_tile + r.tiles > col_tiles) return 2;         // a part stays in its row block
+        most = std::max(most, r.tiles);
+        for (int t = first; t < first + r.tiles; ++t) {
+            if (t >= tiles || seen[t]) return 3;
+            seen[t] = 1;
+        }
+    }
+    if (std::count(seen.begin(), seen.end(), 1) != tiles) return 4;
+    if (groups > units || most > (tiles + units - 1) / units + 2) return 5;
+    return 0;
+}
+
+int main() {
+    for (int units : {1, 8, 104, 256})
+        for (int row_blocks : {1, 2, 3, 5, 16, 100, 127, 128, 129, 200, 250, 255, 256, 257, 300, 393, 513})
+            for (int col_tiles = 1; col_tiles <= 64; ++col_tiles)
+                if (const int rc = check(row_blocks, col_tiles, units)) {
+                    printf("%d row blocks x %d tiles on %d units: %d\n", row_blocks, col_tiles, units, rc);
+                    return 1;
+                }
+    // what the kernel cannot take is never sent to it
+    for (int k : {1, 16, 32, 33, 80, 224, 225, 256, 257, 512})
+        for (int width : {512, 520, 2048, 2050, 1 << 20})
+            for (bool split : {false, true})
+                for (bool update : {false, true})
+                    for (int tables : {0, 1, 2})
+                        if (splc::expand_applies(1 << 20, width, k, tables, update, split) &&
+                            (width % 32 || width >= 1 << 20 || k <= 32 || k > (split ? 224 : 256))) {
+                            printf("width %d k %d\n", width, k);
+                            return 1;
+                        }
+    printf("ok\n");
+    return 0;
+}
