@@ -64,6 +64,21 @@ constexpr int parts_of_row_block(int row_blocks, int col_tiles, int units) {
     return parts > 0 && (col_tiles + parts - 1) / parts <= run + 2 ? parts : 0;
 }
 
+// First product of the subspace calls, split products: contract_kernel, one workgroup per compute unit and 64 rows with all
+// columns, instead of the GEMM kernel.  Time of the GEMM kernel over its time, MI355X, by blocks of 64 rows:
+//   k 129 ... 192: 85 to 256 blocks 1.04 ... 1.7; then a second round begins: 262 to 336 blocks 0.84 ... 1.12, 352 to 512
+//     1.18 ... 1.83, 516 blocks 0.96, 551 to 730 1.02 ... 1.6 -- so at least 68 % of the units in the rounds' average;
+//   k 65 ... 128, no table: 66 to 768 blocks 1.04 ... 1.8; with tables 72 to 256 blocks 1.03 ... 1.54, beyond 0.91 ... 1.11
+//     (rows that are no whole number of 16 bytes, both tables, 83 to 125 blocks: 0.90 ... 0.98).
+// Fewer blocks go to the projection of few rows or, some of them, to the GEMM kernel (0.5 ... 0.9).
+constexpr bool contract_applies(int64_t rows, int d, int k, int tables, int units) {
+    if (k <= 64 || k > 192 || d < 512) return false;
+    const int64_t blocks = (rows + 63) / 64, rounds = (blocks + units - 1) / units;
+    if (k > 128) return blocks * 3 >= units && (rounds == 1 || blocks * 100 >= rounds * units * 68);
+    if (tables == 0) return blocks * 4 > units;
+    return rounds == 1 && blocks * 32 >= units * 9 && (tables < 2 || d % 4 == 0 || blocks * 2 > units);
+}
+
 // Batched calls (compress of several replicas, one-launch step): on plans of few chunks every replica of a chunk gets a
 // workgroup of its own, and the one-launch step becomes two launches with the same results: the walk over the replicas
 // is a chain, some 4 us each.  Measured, kappa 32, walk / side by side, in us:
