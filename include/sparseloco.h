@@ -349,9 +349,9 @@ int sparseloco_subspace_reconstruct(const float* x_tilde, const float* t_perp, c
  * rows -- or a negative status.
  * For the products with U^T (SPLC_OP_RECONSTRUCT, SPLC_OP_REPROJECT_PASS2) the answer is the GEMM kernel's tile also
  * where the call prefers the kernel that keeps 128 rows of coefficients in registers: rows of whole 128-byte lines
- * (d a multiple of 32), 32 < k <= 256 (split products 224) and enough tiles; likewise for the first product with split
- * products, 64 < k <= 192 and enough rows, where a workgroup takes 64 rows with all columns.  csrc/launch_rules.h has
- * both lines.
+ * (d a multiple of 32), 32 < k <= 256 (split products 224) and enough tiles; likewise for the first product with enough rows
+ * and 64 < k <= 192 (split products) or 128 < k <= 256 (fp32), where a workgroup takes 64 rows with all columns.
+ * csrc/launch_rules.h has both lines.
  */
 enum { SPLC_OP_PROJECT = 0, SPLC_OP_RECONSTRUCT = 1, SPLC_OP_REPROJECT_PASS1 = 2, SPLC_OP_REPROJECT_PASS2 = 3 };
 int sparseloco_subspace_kernel_choice(int op, int64_t rows, int d, int k, int tables, int matmul);

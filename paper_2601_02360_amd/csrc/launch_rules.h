@@ -64,17 +64,32 @@ constexpr int parts_of_row_block(int row_blocks, int col_tiles, int units) {
     return parts > 0 && (col_tiles + parts - 1) / parts <= run + 2 ? parts : 0;
 }
 
-// First product of the subspace calls, split products: contract_kernel, one workgroup per compute unit and 64 rows with all
-// columns, instead of the GEMM kernel.  Time of the GEMM kernel over its time, MI355X, by blocks of 64 rows:
-//   k 129 ... 192: 85 to 256 blocks 1.04 ... 1.7; then a second round begins: 262 to 336 blocks 0.84 ... 1.12, 352 to 512
-//     1.18 ... 1.83, 516 blocks 0.96, 551 to 730 1.02 ... 1.6 -- so at least 68 % of the units in the rounds' average;
-//   k 65 ... 128, no table: 66 to 768 blocks 1.04 ... 1.8; with tables 72 to 256 blocks 1.03 ... 1.54, beyond 0.91 ... 1.11
-//     (rows that are no whole number of 16 bytes, both tables, 83 to 125 blocks: 0.90 ... 0.98).
-// Fewer blocks go to the projection of few rows or, some of them, to the GEMM kernel (0.5 ... 0.9).
-constexpr bool contract_applies(int64_t rows, int d, int k, int tables, int units) {
-    if (k <= 64 || k > 192 || d < 512) return false;
+// First product of the subspace calls: contract_kernel (split products) and contract_fp32_kernel, one workgroup per compute
+// unit and 64 rows with all columns, instead of the GEMM kernel.  Time of the GEMM kernel over theirs, MI355X, by blocks of
+// 64 rows (256 units; a second round of workgroups begins with block 257):
+//   split, k 129 ... 192: 85 to 256 blocks 1.04 ... 1.7; 262 to 336 0.84 ... 1.12, 352 to 512 1.18 ... 1.83, 516 0.96, 551 to
+//     730 1.02 ... 1.6 -- so at least 68 % of the units in the rounds' average;
+//   split, k 65 ... 128, no table: 66 to 768 blocks 1.04 ... 1.8; with tables 72 to 256 blocks 1.03 ... 1.54, beyond 0.91 ...
+//     1.11 (rows that are no whole number of 16 bytes, both tables, 83 to 125 blocks: 0.90 ... 0.98);
+//   fp32, k 129 ... 192 (the GEMM tile pads them to 256): with tables 86 to 160 blocks 0.70 ... 0.88, 173 to 256 1.01 ...
+//     1.26, 288 to 326 0.77 ... 0.96, 352 to 524 1.02 ... 1.68; no table, k from 160 on 192 to 256 0.99 ... 1.11, 288 to
+//     320 0.72 ... 0.79, 352 to 512 1.03 ... 1.11, k below 160 0.92 ... 1.05;
+//   fp32, k 193 ... 256: with tables 86 to 131 blocks 0.57 ... 1.00, 147 to 256 1.02 ... 1.13, 288 to 384 0.82 ... 0.95, 416 to
+//     522 1.12 ... 1.19 (one card of several; 1.07 at the least), 786 0.97; no table 0.95 ... 1.06 with no clear line;
+//   fp32, k to 128: 0.85 ... 1.07; d 512 to 1023: 0.63 ... 1.19.
+// Fewer blocks go to the projection of few rows or, some of them, to the GEMM kernel (0.5 ... 0.9).  d is bounded because the
+// kernels address U and 64 rows of x by 32-bit byte offsets.
+constexpr bool contract_applies(int64_t rows, int d, int k, int tables, bool split, int units) {
     const int64_t blocks = (rows + 63) / 64, rounds = (blocks + units - 1) / units;
-    if (k > 128) return blocks * 3 >= units && (rounds == 1 || blocks * 100 >= rounds * units * 68);
+    const int64_t percent = rounds > 0 ? blocks * 100 / (rounds * units) : 0;       // of the units, in the rounds' average
+    if (d >= 1 << 20) return false;
+    if (!split) {
+        if (k <= 128 || k > 256 || d < 1024) return false;
+        if (k <= 192) return (tables > 0 || k >= 160) && percent >= 67;
+        return tables > 0 && percent >= (rounds == 1 ? 60 : 80);
+    }
+    if (k <= 64 || k > 192 || d < 512) return false;
+    if (k > 128) return blocks * 3 >= units && (rounds == 1 || percent >= 68);
     if (tables == 0) return blocks * 4 > units;
     return rounds == 1 && blocks * 32 >= units * 9 && (tables < 2 || d % 4 == 0 || blocks * 2 > units);
 }

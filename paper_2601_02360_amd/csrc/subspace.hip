@@ -1112,18 +1112,19 @@ int compute_units() {
 int reproject_impl(float* t_s, float* t_perp, const float* u, float* coeff_ws, int64_t vocab, int d, int k,
                    int matmul, hipStream_t st) {
     const int M = (int)vocab, units = compute_units();
+    const bool split = matmul == SPLC_MATMUL_BF16X3;
     // pass 1: coeff = T_S U            (M x k) = (M x d)(d x k)
     if (narrow_applies(d, k, HighRank{nullptr, nullptr, 0, nullptr, 1, (int64_t)d}))
         launch_project_narrow(t_s, HighRank{nullptr, nullptr, 0, nullptr, 1, (int64_t)d}, u, coeff_ws, M, d, k, st);
-    else if (matmul == SPLC_MATMUL_BF16X3 && splc::contract_applies(M, d, k, 0, units))
-        launch_contract(ContractArgs{t_s, u, coeff_ws, HighRank{}, M, d, k}, st);
+    else if (splc::contract_applies(M, d, k, 0, split, units))
+        launch_contract(ContractArgs{t_s, u, coeff_ws, HighRank{}, M, d, k}, split, st);
     else if (rows_apply(M, d, k))
         launch_project_rows(t_s, HighRank{nullptr, nullptr, 0, nullptr, 1, (int64_t)d}, u, coeff_ws, M, d, k, st);
     else
         launch_gemm<false>(t_s, (int64_t)d, u, (int64_t)k, M, k, d, NoPrologue{}, StoreCoeff{coeff_ws, (int64_t)k}, matmul,
                            st);
     // pass 2: Pi = coeff U^T           (M x d) = (M x k)(k x d), U given as d x k = the N x K form
-    if (splc::expand_applies(M, d, k, 0, true, matmul == SPLC_MATMUL_BF16X3))
+    if (splc::expand_applies(M, d, k, 0, true, split))
         launch_expand<EPI_UPDATE>(ExpandArgs{coeff_ws, u, t_s, t_perp, HighRank{}, M, d, k, 0, 0}, matmul, units, st);
     else
         launch_gemm<true>(coeff_ws, (int64_t)k, u, (int64_t)k, M, d, k, NoPrologue{},
@@ -1233,11 +1234,11 @@ extern "C" int sparseloco_subspace_project(const float* x, const float* t_perp, 
     const HighRank h{t_perp, token_ids, vocab, pos_embed, seq_len > 0 ? seq_len : 1, (int64_t)d};
     hipStream_t st = static_cast<hipStream_t>(stream);
     const int tables = (t_perp ? 1 : 0) + (pos_embed ? 1 : 0);
+    const bool split = matmul == SPLC_MATMUL_BF16X3;
     if (narrow_applies(d, k, h)) {
         launch_project_narrow(x, h, u, x_tilde, M, d, k, st);
-    } else if (matmul == SPLC_MATMUL_BF16X3 && splc::contract_applies(M, d, k, tables, compute_units()) &&
-               tables_in_32_bits(h, M)) {
-        launch_contract(ContractArgs{x, u, x_tilde, h, M, d, k}, st);
+    } else if (splc::contract_applies(M, d, k, tables, split, compute_units()) && tables_in_32_bits(h, M)) {
+        launch_contract(ContractArgs{x, u, x_tilde, h, M, d, k}, split, st);
     } else if (rows_apply(M, d, k)) {
         launch_project_rows(x, h, u, x_tilde, M, d, k, st);
     } else if (t_perp && pos_embed)

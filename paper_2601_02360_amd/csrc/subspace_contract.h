@@ -1,4 +1,4 @@
-// The first product of the subspace calls, split products, for blocks of 64 rows; included by subspace.hip, inside its
+// The first product of the subspace calls for blocks of 64 rows, split products and fp32; included by subspace.hip, inside its
 // anonymous namespace, after subspace_expand.h.
 #pragma once
 
@@ -24,6 +24,34 @@ struct ContractArgs {
     HighRank h;
     int rows, d, k;
 };
+
+// The four partial sums of each element meet in LDS, 32 rows at a time, and are added in the order of the shares.
+template <int NJ>
+__device__ __forceinline__ void add_shares(float (&sums)[8][32][32 * NJ], const v16f (&acc)[2][NJ], const ContractArgs& g,
+                                           int m0, int rows, int wave, int h, int col, int tid) {
+    constexpr int KG = 4, WIDE = 32 * NJ;
+    const int first = WIDE * (wave & 1);
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+        __syncthreads();
+#pragma unroll
+        for (int v = 0; v < 16; ++v) {
+            float* const at = &sums[wave][8 * (v >> 2) + 4 * h + (v & 3)][0];
+#pragma unroll
+            for (int j = 0; j < NJ; ++j)
+                if (col + j >= first) at[col + j - first] = acc[i][j][v];
+        }
+        __syncthreads();
+#pragma unroll
+        for (int e = 0; e < 32 * 2 * WIDE / 512; ++e) {
+            const int f = tid + 512 * e, row = f / (2 * WIDE), cc = f % (2 * WIDE), side = cc / WIDE;
+            float sum = sums[side][row][cc - WIDE * side];
+#pragma unroll
+            for (int p = 1; p < KG; ++p) sum = __fadd_rn(sum, sums[2 * p + side][row][cc - WIDE * side]);
+            if (32 * i + row < rows && cc < g.k) g.out[(int64_t)(m0 + 32 * i + row) * g.k + cc] = sum;
+        }
+    }
+}
 
 template <int NJ, bool TP, bool PE>
 __global__ __launch_bounds__(512, 2) void contract_kernel(ContractArgs g) {
@@ -213,39 +241,192 @@ __global__ __launch_bounds__(512, 2) void contract_kernel(ContractArgs g) {
         one_round(any, r, even, b0, b1);
         if (r + 1 < rounds) one_round(any, r + 1, odd, b1, b0);
     }
-
-    // The four partial sums of each element meet in LDS, 32 rows at a time, and are added in the order of k steps.
-#pragma unroll
-    for (int i = 0; i < 2; ++i) {
-        __syncthreads();
-#pragma unroll
-        for (int v = 0; v < 16; ++v) {
-            float* const at = &sm.sums[wave][8 * (v >> 2) + 4 * h + (v & 3)][0];
-#pragma unroll
-            for (int j = 0; j < NJ; ++j)
-                if (col + j >= WIDE * cg) at[col + j - WIDE * cg] = acc[i][j][v];
-        }
-        __syncthreads();
-#pragma unroll
-        for (int e = 0; e < 32 * 2 * WIDE / 512; ++e) {
-            const int f = tid + 512 * e, row = f / (2 * WIDE), cc = f % (2 * WIDE), side = cc / WIDE;
-            float sum = sm.sums[side][row][cc - WIDE * side];
-#pragma unroll
-            for (int p = 1; p < KG; ++p) sum = __fadd_rn(sum, sm.sums[2 * p + side][row][cc - WIDE * side]);
-            if (32 * i + row < rows && cc < N) g.out[(int64_t)(m0 + 32 * i + row) * N + cc] = sum;
-        }
-    }
+    add_shares<NJ>(sm.sums, acc, g, m0, rows, wave, h, col, tid);
 }
 
-template <int NJ>
+// The same with fp32 products, 128 < k <= 256: the row blocks, column halves and shares of the reduction are those of
+// contract_kernel, a round is 64 k, a share two groups of 8.  Lane half h takes k 4 h .. 4 h + 3 of a group, and product t
+// multiplies the set {t, 4 + t}, so that a lane reads its row of A as 16 bytes and needs four rows of U.  A row of U is
+// requested anew as soon as its products are issued, x and its tables a round ahead, 256 bytes of a row at a time.
+//
+// Bound: the fp32 matrix pipe (at 16384 x 2048 onto 256 no tables 133 us of at least 109).  The GEMM kernel gathers and
+// subtracts a row twice and pads 129 ... 192 columns to 256.  GEMM kernel / this, us, one card: 16384 x 2048 onto 256, both tables
+// 168 / 146; 16384 x 1536 onto 192: 97 / 85; 32768 x 2048 onto 256: 309 / 293; without tables 132 / 133.  128 bytes of a row
+// at a time: 156; the order of all instructions fixed: 169; free over a whole group instead of half a group: 151 to 146.
+template <int NJ, bool TP, bool PE>
+__global__ __launch_bounds__(512, 2) void contract_fp32_kernel(ContractArgs g) {
+    constexpr int KG = 4, DEEP = 16 * KG;        // a round: 16 k for every pair of waves
+    constexpr int WIDE = 32 * NJ;                // columns of a wave
+    typedef float v4f __attribute__((ext_vector_type(4)));
+    typedef float vcols __attribute__((ext_vector_type(NJ), aligned(4)));
+    union Shared {
+        v4f a[2][4 * KG][65];                    // [four k][row]; the pitch spreads writes and reads over all banks
+        float sums[8][32][WIDE];
+    };
+    __shared__ __attribute__((aligned(16))) Shared sm;
+    const int tid = threadIdx.x, lane = tid & 63, c = lane & 31, h = lane >> 5;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int cg = wave & 1, kg = wave >> 1;
+    const int d = g.d, N = g.k;
+    const int m0 = blockIdx.x * 64, rows = g.rows - m0 < 64 ? g.rows - m0 : 64;
+
+    // A: sixteen threads take 256 bytes of a row, four k each, of two rows
+    const int ar = tid >> 4, aq = tid & 15;
+    const char* const xb = reinterpret_cast<const char*>(g.x + (int64_t)m0 * d);
+    uint32_t x_off[2], t_off[2], p_off[2];
+#pragma unroll
+    for (int e = 0; e < 2; ++e) {
+        const int row = ar + 32 * e < rows ? ar + 32 * e : rows - 1;
+        x_off[e] = 4u * ((uint32_t)row * (uint32_t)d + 4u * (uint32_t)aq);
+        if (TP) {
+            int t = g.h.token[m0 + row];
+            t = t < 0 ? 0 : (t >= g.h.vocab ? g.h.vocab - 1 : t);
+            t_off[e] = 4u * ((uint32_t)t * (uint32_t)d + 4u * (uint32_t)aq);
+        }
+        if (PE) p_off[e] = 4u * ((uint32_t)((m0 + row) % g.h.seq_len) * (uint32_t)d + 4u * (uint32_t)aq);
+    }
+    // B: columns as in contract_kernel
+    const int col = WIDE * cg + NJ * c < N - NJ ? WIDE * cg + NJ * c : N - NJ;
+    const uint32_t u_off = 4u * (uint32_t)(4 * h * N + col);
+
+    struct StageA { vfloat4 x, t, p; };
+    StageA sa[2];
+    vcols b[2][4];
+    const int rounds = (d + DEEP - 1) / DEEP, plain_rounds = d / DEEP;
+    auto fetch_a = [&](auto plain, int r) {
+        const int k0 = r * DEEP;
+#pragma unroll
+        for (int e = 0; e < 2; ++e) {
+            StageA& s = sa[e];
+            if (decltype(plain)::value || k0 + DEEP <= d) {
+                const uint32_t at = 4u * (uint32_t)k0;
+                s.x = *(const SPLC_GLOBAL vfloat4*)(xb + at + x_off[e]);
+                if (TP) s.t = *(const SPLC_GLOBAL vfloat4*)((const char*)g.h.t_perp + at + t_off[e]);
+                if (PE) s.p = *(const SPLC_GLOBAL vfloat4*)((const char*)g.h.pos + at + p_off[e]);
+            } else {                             // zeros from k = d on
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    const bool there = k0 + 4 * aq + i < d;
+                    const uint32_t at = there ? 4u * (uint32_t)(k0 + i) : 0u - 16u * (uint32_t)aq;
+                    const float vx = *(const SPLC_GLOBAL float*)(xb + (x_off[e] + at));
+                    s.x[i] = there ? vx : 0.f;
+                    if (TP) {
+                        const float vt = *(const SPLC_GLOBAL float*)((const char*)g.h.t_perp + (t_off[e] + at));
+                        s.t[i] = there ? vt : 0.f;
+                    }
+                    if (PE) {
+                        const float vp = *(const SPLC_GLOBAL float*)((const char*)g.h.pos + (p_off[e] + at));
+                        s.p[i] = there ? vp : 0.f;
+                    }
+                }
+            }
+        }
+    };
+    auto fetch_b = [&](auto plain, int r, int q, int t) {         // row 4 h + t of group q of this wave's share
+        const int k0 = r * DEEP + 16 * kg + 8 * q + t;
+        if (decltype(plain)::value) {
+            b[q][t] = *(const SPLC_GLOBAL vcols*)((const char*)(g.u + (int64_t)k0 * N) + u_off);
+        } else {                                 // zeros from row d on
+            const bool there = k0 + 4 * h < d;
+            b[q][t] = *(const SPLC_GLOBAL vcols*)(g.u + ((int64_t)(there ? k0 + 4 * h : d - 1) * N + col));
+#pragma unroll
+            for (int j = 0; j < NJ; ++j) b[q][t][j] = there ? b[q][t][j] : 0.f;
+        }
+    };
+    auto stash = [&](int e, int buf) {
+        v4f v;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            v[i] = sa[e].x[i];
+            if (TP) v[i] = __fsub_rn(v[i], sa[e].t[i]);
+            if (PE) v[i] = __fsub_rn(v[i], sa[e].p[i]);
+        }
+        sm.a[buf][aq][ar + 32 * e] = v;
+    };
+
+    v16f acc[2][NJ];
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int j = 0; j < NJ; ++j)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.f;
+    v4f fa[2][2];                                // [group][half of the rows]
+    auto rows_of = [&](int buf, int q) {
+#pragma unroll
+        for (int i = 0; i < 2; ++i) fa[q][i] = sm.a[buf][4 * kg + 2 * q + h][32 * i + c];
+    };
+
+    // One round.  With its first group A of round r + 1 goes to LDS and that of round r + 2 is requested; the barrier comes
+    // between the groups, and behind it the first group of round r + 1 is read.
+    auto one_round = [&](auto plain, int r, auto parity) {
+        constexpr int buf = decltype(parity)::value;
+        rows_of(buf, 1);
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {
+            if (q == 1) {
+                __syncthreads();
+                rows_of(buf ^ 1, 0);
+            }
+#pragma unroll
+            for (int t = 0; t < 4; ++t) {
+#pragma unroll
+                for (int j = 0; j < NJ; ++j)
+#pragma unroll
+                    for (int i = 0; i < 2; ++i) {
+                        acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(fa[q][i][t], b[q][t][j], acc[i][j], 0, 0, 0);
+                        if (q == 0 && t == 0 && j == 0) stash(i, buf ^ 1);
+                        if (q == 0 && t == 0 && j == 1 && i == 0 && (decltype(plain)::value || r + 2 < rounds))
+                            fetch_a(plain, r + 2);
+                    }
+                if (decltype(plain)::value || r + 1 < rounds) fetch_b(plain, r + 1, q, t);
+                if (t & 1) __builtin_amdgcn_sched_barrier(0);    // the compiler orders half a group
+            }
+        }
+    };
+    const std::integral_constant<bool, true> plain;
+    const std::integral_constant<bool, false> any;
+    fetch_a(any, 0);
+#pragma unroll
+    for (int t = 0; t < 8; ++t) fetch_b(any, 0, t >> 2, t & 3);
+    stash(0, 0);
+    stash(1, 0);
+    fetch_a(any, 1);                             // (zeros if there is no second round)
+    __syncthreads();
+    rows_of(0, 0);
+    const std::integral_constant<int, 0> even;
+    const std::integral_constant<int, 1> odd;
+    int r = 0;
+    for (; r + 3 < plain_rounds; r += 2) {
+        one_round(plain, r, even);
+        one_round(plain, r + 1, odd);
+    }
+    for (; r < rounds; r += 2) {
+        one_round(any, r, even);
+        if (r + 1 < rounds) one_round(any, r + 1, odd);
+    }
+    add_shares<NJ>(sm.sums, acc, g, m0, rows, wave, h, col, tid);
+}
+
+template <int NJ, bool SPLIT>
 void launch_contract(const ContractArgs& g, hipStream_t st) {
     const dim3 grid((unsigned)((g.rows + 63) / 64)), block(512);
-    if (g.h.t_perp && g.h.pos) hipLaunchKernelGGL((contract_kernel<NJ, true, true>), grid, block, 0, st, g);
-    else if (g.h.t_perp) hipLaunchKernelGGL((contract_kernel<NJ, true, false>), grid, block, 0, st, g);
-    else if (g.h.pos) hipLaunchKernelGGL((contract_kernel<NJ, false, true>), grid, block, 0, st, g);
-    else hipLaunchKernelGGL((contract_kernel<NJ, false, false>), grid, block, 0, st, g);
+    auto run = [&](auto tp, auto pe) {
+        constexpr bool TP = decltype(tp)::value, PE = decltype(pe)::value;
+        if constexpr (SPLIT) hipLaunchKernelGGL((contract_kernel<NJ, TP, PE>), grid, block, 0, st, g);
+        else hipLaunchKernelGGL((contract_fp32_kernel<NJ, TP, PE>), grid, block, 0, st, g);
+    };
+    const std::true_type yes;
+    const std::false_type no;
+    if (g.h.t_perp && g.h.pos) run(yes, yes);
+    else if (g.h.t_perp) run(yes, no);
+    else if (g.h.pos) run(no, yes);
+    else run(no, no);
 }
-void launch_contract(const ContractArgs& g, hipStream_t st) {
-    if (g.k <= 128) launch_contract<2>(g, st);
-    else launch_contract<3>(g, st);
+void launch_contract(const ContractArgs& g, bool split, hipStream_t st) {
+    if (split) {
+        if (g.k <= 128) launch_contract<2, true>(g, st);
+        else launch_contract<3, true>(g, st);
+    } else if (g.k <= 192) launch_contract<3, false>(g, st);
+    else launch_contract<4, false>(g, st);
 }

@@ -46,6 +46,17 @@ int main() {
                             printf("width %d k %d\n", width, k);
                             return 1;
                         }
+    for (int64_t rows : {0, 1, 5440, 11008, 16384, 16448, 32768, 1 << 24})
+        for (int k : {1, 64, 65, 128, 129, 192, 193, 256, 257, 600})
+            for (int d : {16, 511, 512, 1023, 1024, 2050, 1 << 20, 1 << 23})
+                for (bool split : {false, true})
+                    for (int tables : {0, 1, 2})
+                        for (int units : {1, 104, 256})
+                            if (splc::contract_applies(rows, d, k, tables, split, units) &&
+                                (rows == 0 || d < 512 || (int64_t)d * k * 4 >= int64_t(1) << 32 || k <= (split ? 64 : 128) || k > (split ? 192 : 256))) {
+                                printf("rows %d d %d k %d\n", (int)rows, d, k);
+                                return 1;
+                            }
     printf("ok\n");
     return 0;
 }

@@ -1,8 +1,9 @@
-"""The first product of the subspace calls where a workgroup takes 64 rows with all columns (contract_kernel, split
-products): both column counts of a wave, columns that end inside a lane's, reductions that end inside a step of 16, a round
+"""The first product of the subspace calls where a workgroup takes 64 rows with all columns (contract_kernel and
+contract_fp32_kernel): both column counts of a wave, columns that end inside a lane's, reductions that end inside a step of 16, a round
 of 64 and a pair of rounds, row blocks that end early, one and two rounds of workgroups, every set of tables.  Oracle and
 bars are those of test_gpu_subspace.py."""
 import pytest
+import torch
 
 from paper_2601_02360_amd import binding as B
 from test_gpu_subspace import check_reproject, check_stage_boundary
@@ -25,3 +26,40 @@ def test_projection(rows, d, k, use_perp, use_pos):
 def test_reprojection(vocab, d, k):
     rows = list(range(200)) + list(range(vocab - 300, vocab))
     check_reproject(vocab, d, k, seed=vocab + d + k, mode=B.SPLC_MATMUL_BF16X3, rows=rows)
+
+
+# fp32 products: reductions that end inside four k, a share of 16, a round of 64 and a pair of rounds
+FP32_PROJECT = [
+    (11008, 1024, 129, True, True), (10945, 1025, 160, False, False), (11000, 1055, 130, True, False), (11008, 1056, 161, False, False),
+    (11007, 1087, 191, False, True), (22600, 1088, 192, True, True), (9793, 1100, 193, True, False), (9800, 1151, 194, False, True),
+    (16384, 1152, 222, True, True), (26300, 1042, 223, True, False), (16383, 2050, 255, True, True), (16384, 2048, 256, True, True)]
+
+
+@pytest.mark.parametrize("rows,d,k,use_perp,use_pos", FP32_PROJECT)
+def test_projection_with_fp32_products(rows, d, k, use_perp, use_pos):
+    check_stage_boundary(rows, 300, d, k, 77, use_perp, use_pos, seed=rows + d + k, mode=B.SPLC_MATMUL_FP32)
+
+
+@pytest.mark.parametrize("vocab,d,k", [(11000, 1090, 163), (32001, 1538, 192)])
+def test_reprojection_with_fp32_products(vocab, d, k):
+    rows = list(range(200)) + list(range(vocab - 300, vocab))
+    check_reproject(vocab, d, k, seed=vocab + d + k, mode=B.SPLC_MATMUL_FP32, rows=rows)
+
+
+@pytest.mark.parametrize("d,k", [(1088, 170), (1089, 160), (1027, 192)])
+def test_infinities_and_nan_stay_in_their_row_and_column(d, k):
+    """fp32 products: a NaN in x makes its row NaN; an infinite last entry of a column of U its column, nothing else."""
+    rows = 11008
+    g = torch.Generator(device="cuda").manual_seed(d)
+    x = torch.rand(rows, d, generator=g, device="cuda") + 0.5
+    u = torch.randn(d, k, generator=g, device="cuda")
+    x[5, d - 1] = float("nan")
+    x[130, 0] = float("inf")
+    u[d - 1, k - 1] = float("inf")
+    u[7, 64] = float("nan")
+    out = torch.empty(rows, k, device="cuda")
+    B.sparseloco_subspace_project(x, u, out, matmul=B.SPLC_MATMUL_FP32)
+    want = torch.zeros(rows, k, dtype=torch.bool, device="cuda")
+    want[5], want[130], want[:, k - 1], want[:, 64] = True, True, True, True
+    assert torch.equal(~torch.isfinite(out), want)
+    assert torch.isnan(out[5]).all() and torch.isinf(out[131:, k - 1]).all() and torch.isnan(out[:, 64]).all()
