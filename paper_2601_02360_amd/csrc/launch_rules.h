@@ -127,6 +127,29 @@ constexpr bool few_streams(int64_t chunks, int kappa, bool from_params, bool gen
     return chunks >= kFewStreams && kappa <= 128 && from_params && !general_path;
 }
 
+// Aggregation over a flat plan: the entry of the chunk table that a workgroup takes where every XCD (workgroups go to the
+// eight of them round-robin by number) is to get runs of kChunkRun consecutive ones; those behind the last whole round of
+// eight runs keep their place.  kChunkRun chunks' levels (8 bytes each) are one cache line, and so are two to four
+// chunks' pairs at kappa 32 ... 16: taken one by one, every XCD fetches each of these lines for itself.
+// Worth it where messages are a large part of the traffic and a small part of a line; otherwise the order of the table keeps
+// memory busier.  Time in the table's order / in runs, MI355X, quantised, 9000 to 100,000 chunks:
+//   aggregate_update, kappa 16 ... 48: 32 replicas 1.02 ... 1.24, 24: 1.02 ... 1.25, 20: 0.98 ... 1.18, 16: 0.95 ... 1.09, 2 to 8:
+//     0.93 ... 0.97, 64: 0.99 ... 1.03; kappa 64: 24 to 32 replicas 1.00 ... 1.15 from 12,000 chunks on, 0.99 at 9000, 64
+//     replicas 0.96 ... 0.98; kappa 96 and 128: 0.97 ... 1.17; 4096 chunks, 32 replicas: 0.97 ... 1.16, 1500: 0.93 ... 0.97;
+//   aggregate, kappa 16 ... 64: 24 to 32 replicas 1.00 ... 1.27, 64: 1.01 ... 1.14, 20: 0.94 ... 1.13, 4: 0.92 ... 1.05;
+//   without quantisation (the values are whole lines), 32, kappa 32: 0.95 ... 1.12; 128: 0.94 ... 1.01.
+constexpr uint32_t kChunkRun = 16;
+constexpr uint32_t entry_in_runs(uint32_t place, uint32_t entries) {
+    constexpr uint32_t kRound = 8 * kChunkRun;
+    if (place >= entries / kRound * kRound) return place;
+    const uint32_t slot = place / 8;
+    return (slot / kChunkRun * 8 + place % 8) * kChunkRun + slot % kChunkRun;
+}
+constexpr bool chunks_in_runs(int64_t entries, int replicas, int kappa, bool quantised) {
+    if (!quantised || replicas < 24 || entries < 9000) return false;
+    return kappa <= 48 || (kappa <= 64 && replicas <= 48 && entries >= 12000);
+}
+
 // Whether no two of these address ranges [first, second) share a byte; empty ranges share none.
 inline bool disjoint(std::vector<std::pair<uintptr_t, uintptr_t>> ranges) {
     std::sort(ranges.begin(), ranges.end());

@@ -1280,11 +1280,11 @@ __device__ __forceinline__ void aggregate_body(float* acc, const ChunkDesc* __re
                                                              const float* const* __restrict__ aux_tab,
                                                              float* const* __restrict__ dbar_tab,
                                                              float* const* __restrict__ theta_tab, float eta, int n_reset,
-                                               uint32_t n_tensors, float* const* __restrict__ reset_tab) {
+                                               uint32_t n_tensors, float* const* __restrict__ reset_tab, uint32_t entry) {
     const int tid = threadIdx.x;
     const int lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const ChunkDesc d = chunks[blockIdx.x];
+    const ChunkDesc d = chunks[entry];
     const uint64_t c = d.id;
     const uint32_t n_c = VEC ? (uint32_t)kChunk : d.n_c;
     const uint32_t kappa_c = kappa < n_c ? kappa : n_c;
@@ -1358,15 +1358,16 @@ __global__ __launch_bounds__(kThreads) void aggregate_kernel(const ChunkDesc* __
                                                              const float* const* __restrict__ aux_tab,
                                                              float* const* __restrict__ dbar_tab,
                                                              float* const* __restrict__ theta_tab, float eta,
-                                                             int n_reset, uint32_t n_tensors,
+                                                             int n_reset, uint32_t n_tensors, bool in_runs,
                                                              float* const* __restrict__ reset_tab) {
     __shared__ __align__(16) float acc[kChunk];
-    if (blockIdx.x >= n_gen)
+    const uint32_t entry = in_runs ? splc::entry_in_runs(blockIdx.x, gridDim.x) : blockIdx.x;
+    if (entry >= n_gen)
         aggregate_body<QUANT, UPDATE, true>(acc, chunks, n_replicas, kappa, pairs_tab, aux_tab, dbar_tab, theta_tab, eta,
-                                            n_reset, n_tensors, reset_tab);
+                                            n_reset, n_tensors, reset_tab, entry);
     else
         aggregate_body<QUANT, UPDATE, false>(acc, chunks, n_replicas, kappa, pairs_tab, aux_tab, dbar_tab, theta_tab,
-                                             eta, n_reset, n_tensors, reset_tab);
+                                             eta, n_reset, n_tensors, reset_tab, entry);
 }
 
 // Line 5 for a strip of four complete 64 x 64 tiles (see compress_strip_kernel): the four 256-lane groups
@@ -1637,7 +1638,9 @@ void launch_aggregate(const sparseloco_plan* plan, int n_replicas, const uint16_
     if (plan->n_entries > 0)
         hipLaunchKernelGGL((aggregate_kernel<QUANT, UPDATE>), dim3((unsigned)plan->n_entries), dim3(kThreads), 0, stream,
                            plan->d_chunks, gen_entries(plan, false), n_replicas, (uint32_t)plan->kappa, pairs, aux,
-                           dbar, theta, eta, n_reset, (uint32_t)plan->n_tensors, reset);
+                           dbar, theta, eta, n_reset, (uint32_t)plan->n_tensors,
+                           plan->layout == SPLC_LAYOUT_FLAT && splc::chunks_in_runs(plan->n_entries, n_replicas, plan->kappa,
+                                                                                    QUANT == SPLC_QUANT_2BIT), reset);
 }
 
 template <int QUANT, bool STEP>

@@ -1,4 +1,5 @@
-// How expand_kernel's workgroups share the output tiles (csrc/launch_rules.h), on the CPU: every tile exactly once.
+// How expand_kernel's workgroups share the output tiles and the aggregation's the chunks (csrc/launch_rules.h), on the CPU:
+// every one exactly once.
 #include <algorithm>
 #include <cstdio>
 #include <initializer_list>
@@ -57,6 +58,16 @@ int main() {
                                 printf("rows %d d %d k %d\n", (int)rows, d, k);
                                 return 1;
                             }
+    for (uint32_t entries : {1u, 127u, 128u, 129u, 255u, 256u, 9000u, 9087u, 9088u, 37105u}) {
+        std::vector<char> seen(entries, 0);
+        for (uint32_t place = 0; place < entries; ++place) {
+            const uint32_t e = splc::entry_in_runs(place, entries);
+            if (e >= entries || seen[e]++) {
+                printf("%u of %u entries\n", place, entries);
+                return 1;
+            }
+        }
+    }
     printf("ok\n");
     return 0;
 }
