@@ -346,12 +346,10 @@ int sparseloco_subspace_reconstruct(const float* x_tilde, const float* t_perp, c
  * tables: how many of the two tables of section 2.2 are present (0..2; ignored for the re-projection).
  * Returns tile_rows * 256 + tile_cols of a workgroup's output tile -- 128 or 64 by 128 or 64 for the GEMM
  * kernel, 16 by 16 or 16 by 32 for the narrow projection kernel, 16 by 32 or 16 by 64 for the projection of few
- * rows -- or a negative status.
- * For the products with U^T (SPLC_OP_RECONSTRUCT, SPLC_OP_REPROJECT_PASS2) the answer is the GEMM kernel's tile also
- * where the call prefers the kernel that keeps 128 rows of coefficients in registers: rows of whole 128-byte lines
- * (d a multiple of 32), 32 < k <= 256 (split products 224) and enough tiles; likewise for the first product with enough rows
- * and 64 < k <= 192 (split products) or 128 < k <= 256 (fp32), where a workgroup takes 64 rows with all columns.
- * csrc/launch_rules.h has both lines.
+ * rows, 64 by 0 for the first product with all columns of 64 rows per workgroup, 128 by 32 for the second product
+ * with 128 rows of coefficients in registers -- or a negative status.  The answer is that of the launch on the current
+ * device (without one: for 256 compute units), except that the last two leave tables of 2^30 floats and more, whose
+ * size is not asked here, to the GEMM kernel.
  */
 enum { SPLC_OP_PROJECT = 0, SPLC_OP_RECONSTRUCT = 1, SPLC_OP_REPROJECT_PASS1 = 2, SPLC_OP_REPROJECT_PASS2 = 3 };
 int sparseloco_subspace_kernel_choice(int op, int64_t rows, int d, int k, int tables, int matmul);

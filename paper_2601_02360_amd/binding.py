@@ -520,7 +520,8 @@ def sparseloco_reproject_embedding_noalloc(t_s: torch.Tensor, t_perp: torch.Tens
 
 
 def subspace_kernel_choice(op: int, rows: int, d: int, k: int, tables: int = 0, matmul: int = SPLC_MATMUL_FP32):
-    """(tile_rows, tile_cols) of the kernel variant a matrix call takes for this shape (host logic only)."""
+    """(tile_rows, tile_cols) of the kernel variant a matrix call takes for this shape (host logic only); (64, 0): all
+    columns of 64 rows per workgroup."""
     rc = lib().sparseloco_subspace_kernel_choice(int(op), int(rows), int(d), int(k), int(tables), int(matmul))
     if rc < 0:
         raise SparseLoCoError(rc, "sparseloco_subspace_kernel_choice")

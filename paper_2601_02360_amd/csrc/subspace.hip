@@ -1085,10 +1085,34 @@ void launch_gemm(const float* A, int64_t lda, const float* B, int64_t ldb, int M
 #include "subspace_expand.h"
 #include "subspace_contract.h"
 
-// expand_kernel addresses the tables by 32-bit byte offsets
+// Compute units of the current device (256 on an MI355X).
+int compute_units() {
+    int dev = 0, n = 0;
+    if (hipGetDevice(&dev) != hipSuccess ||
+        hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || n <= 0)
+        return 256;
+    return n;
+}
+
+// expand_kernel and the contract kernels address the tables by 32-bit byte offsets
 bool tables_in_32_bits(const HighRank& h, int rows) {
     const int64_t positions = h.seq_len < rows ? h.seq_len : rows;
     return (!h.t_perp || h.vocab * h.ld < (int64_t)1 << 30) && (!h.pos || positions * h.ld < (int64_t)1 << 30);
+}
+
+// The kernel of a first product (projection, first pass of the re-projection) and of a second one (reconstruction; update:
+// second pass of the re-projection).  The calls launch by these, and sparseloco_subspace_kernel_choice answers by them.
+enum class First { narrow, contract, rows, gemm };
+First first_product(const HighRank& h, int rows, int d, int k, bool split) {
+    if (narrow_applies(d, k, h)) return First::narrow;
+    const int tables = (h.t_perp ? 1 : 0) + (h.pos ? 1 : 0);
+    if (splc::contract_applies(rows, d, k, tables, split, compute_units()) && tables_in_32_bits(h, rows)) return First::contract;
+    return rows_apply(rows, d, k) ? First::rows : First::gemm;
+}
+enum class Second { expand, gemm };
+Second second_product(const HighRank& h, int rows, int d, int k, bool update, bool split) {
+    const int tables = (h.t_perp ? 1 : 0) + (h.pos ? 1 : 0);
+    return splc::expand_applies(rows, d, k, tables, update, split) && tables_in_32_bits(h, rows) ? Second::expand : Second::gemm;
 }
 
 bool valid_matmul(int matmul) { return matmul == SPLC_MATMUL_FP32 || matmul == SPLC_MATMUL_BF16X3; }
@@ -1099,33 +1123,25 @@ bool aligned4(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 3) == 0;
 
 namespace {
 
-// Compute units of the current device (256 on an MI355X).
-int compute_units() {
-    int dev = 0, n = 0;
-    if (hipGetDevice(&dev) != hipSuccess ||
-        hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || n <= 0)
-        return 256;
-    return n;
-}
-
 // Both passes of the re-projection with the coefficients in `coeff_ws` (vocab * k floats of device memory).
 int reproject_impl(float* t_s, float* t_perp, const float* u, float* coeff_ws, int64_t vocab, int d, int k,
                    int matmul, hipStream_t st) {
     const int M = (int)vocab, units = compute_units();
     const bool split = matmul == SPLC_MATMUL_BF16X3;
+    const HighRank none{nullptr, nullptr, 0, nullptr, 1, (int64_t)d};
     // pass 1: coeff = T_S U            (M x k) = (M x d)(d x k)
-    if (narrow_applies(d, k, HighRank{nullptr, nullptr, 0, nullptr, 1, (int64_t)d}))
-        launch_project_narrow(t_s, HighRank{nullptr, nullptr, 0, nullptr, 1, (int64_t)d}, u, coeff_ws, M, d, k, st);
-    else if (splc::contract_applies(M, d, k, 0, split, units))
-        launch_contract(ContractArgs{t_s, u, coeff_ws, HighRank{}, M, d, k}, split, st);
-    else if (rows_apply(M, d, k))
-        launch_project_rows(t_s, HighRank{nullptr, nullptr, 0, nullptr, 1, (int64_t)d}, u, coeff_ws, M, d, k, st);
-    else
-        launch_gemm<false>(t_s, (int64_t)d, u, (int64_t)k, M, k, d, NoPrologue{}, StoreCoeff{coeff_ws, (int64_t)k}, matmul,
-                           st);
+    switch (first_product(none, M, d, k, split)) {
+        case First::narrow: launch_project_narrow(t_s, none, u, coeff_ws, M, d, k, st); break;
+        case First::contract: launch_contract(ContractArgs{t_s, u, coeff_ws, none, M, d, k}, split, st); break;
+        case First::rows: launch_project_rows(t_s, none, u, coeff_ws, M, d, k, st); break;
+        case First::gemm:
+            launch_gemm<false>(t_s, (int64_t)d, u, (int64_t)k, M, k, d, NoPrologue{}, StoreCoeff{coeff_ws, (int64_t)k},
+                               matmul, st);
+            break;
+    }
     // pass 2: Pi = coeff U^T           (M x d) = (M x k)(k x d), U given as d x k = the N x K form
-    if (splc::expand_applies(M, d, k, 0, true, split))
-        launch_expand<EPI_UPDATE>(ExpandArgs{coeff_ws, u, t_s, t_perp, HighRank{}, M, d, k, 0, 0}, matmul, units, st);
+    if (second_product(none, M, d, k, true, split) == Second::expand)
+        launch_expand<EPI_UPDATE>(ExpandArgs{coeff_ws, u, t_s, t_perp, none, M, d, k, 0, 0}, matmul, units, st);
     else
         launch_gemm<true>(coeff_ws, (int64_t)k, u, (int64_t)k, M, d, k, NoPrologue{},
                           UpdateEmbedding{t_s, t_perp, (int64_t)d, units}, matmul, st);
@@ -1202,20 +1218,29 @@ extern "C" int sparseloco_subspace_kernel_choice(int op, int64_t rows, int d, in
     if (rows < 1 || rows > 0x7FFFFFFF - TM || d < 1 || k < 1 || k > d || tables < 0 || tables > 2 || !valid_matmul(matmul))
         return SPLC_EINVAL;
     const int M = (int)rows;
+    const bool split = matmul == SPLC_MATMUL_BF16X3;
     const float* const some = reinterpret_cast<const float*>(&op);      // only tested for being non-null
+    const int n_tab = op == SPLC_OP_PROJECT || op == SPLC_OP_RECONSTRUCT ? tables : 0;
+    const HighRank h{n_tab >= 1 ? some : nullptr, nullptr, 0, n_tab >= 2 ? some : nullptr, 1, (int64_t)d};
     GemmTile t;
     switch (op) {
         case SPLC_OP_PROJECT:
-        case SPLC_OP_REPROJECT_PASS1: {
-            const int n_tab = op == SPLC_OP_PROJECT ? tables : 0;
-            const HighRank h{n_tab >= 1 ? some : nullptr, nullptr, 0, n_tab >= 2 ? some : nullptr, 1, (int64_t)d};
-            if (narrow_applies(d, k, h)) return 16 * 256 + (k <= 16 ? 16 : 32);
-            if (rows_apply(M, d, k)) return 16 * 256 + (rows_wide(M, k) ? 64 : 32);
+        case SPLC_OP_REPROJECT_PASS1:
+            switch (first_product(h, M, d, k, split)) {
+                case First::narrow: return 16 * 256 + (k <= 16 ? 16 : 32);
+                case First::contract: return 64 * 256;
+                case First::rows: return 16 * 256 + (rows_wide(M, k) ? 64 : 32);
+                case First::gemm: break;
+            }
             t = choose_gemm_tile(false, M, k, d, n_tab, false, matmul);
             break;
+        case SPLC_OP_RECONSTRUCT:
+        case SPLC_OP_REPROJECT_PASS2: {
+            const bool update = op == SPLC_OP_REPROJECT_PASS2;
+            if (second_product(h, M, d, k, update, split) == Second::expand) return 128 * 256 + 32;
+            t = choose_gemm_tile(true, M, d, k, n_tab, !update, matmul);
+            break;
         }
-        case SPLC_OP_RECONSTRUCT: t = choose_gemm_tile(true, M, d, k, tables, true, matmul); break;
-        case SPLC_OP_REPROJECT_PASS2: t = choose_gemm_tile(true, M, d, k, 0, false, matmul); break;
         default: return SPLC_EINVAL;
     }
     return (t.tall ? 128 : 64) * 256 + (t.wide ? 128 : 64);
@@ -1233,15 +1258,15 @@ extern "C" int sparseloco_subspace_project(const float* x, const float* t_perp, 
     const int M = (int)rows;
     const HighRank h{t_perp, token_ids, vocab, pos_embed, seq_len > 0 ? seq_len : 1, (int64_t)d};
     hipStream_t st = static_cast<hipStream_t>(stream);
-    const int tables = (t_perp ? 1 : 0) + (pos_embed ? 1 : 0);
     const bool split = matmul == SPLC_MATMUL_BF16X3;
-    if (narrow_applies(d, k, h)) {
+    const First kernel = first_product(h, M, d, k, split);
+    if (kernel == First::narrow)
         launch_project_narrow(x, h, u, x_tilde, M, d, k, st);
-    } else if (splc::contract_applies(M, d, k, tables, split, compute_units()) && tables_in_32_bits(h, M)) {
+    else if (kernel == First::contract)
         launch_contract(ContractArgs{x, u, x_tilde, h, M, d, k}, split, st);
-    } else if (rows_apply(M, d, k)) {
+    else if (kernel == First::rows)
         launch_project_rows(x, h, u, x_tilde, M, d, k, st);
-    } else if (t_perp && pos_embed)
+    else if (t_perp && pos_embed)
         launch_gemm<false>(x, (int64_t)d, u, (int64_t)k, M, k, d, SubtractHighRank<true, true>{h, {nullptr, nullptr}},
                            StoreCoeff{x_tilde, (int64_t)k}, matmul, st);
     else if (t_perp)
@@ -1267,8 +1292,7 @@ extern "C" int sparseloco_subspace_reconstruct(const float* x_tilde, const float
     const int M = (int)rows;
     const HighRank h{t_perp, token_ids, vocab, pos_embed, seq_len > 0 ? seq_len : 1, (int64_t)d};
     hipStream_t st = static_cast<hipStream_t>(stream);
-    const int tables = (t_perp ? 1 : 0) + (pos_embed ? 1 : 0);
-    if (splc::expand_applies(M, d, k, tables, false, matmul == SPLC_MATMUL_BF16X3) && tables_in_32_bits(h, M)) {
+    if (second_product(h, M, d, k, false, matmul == SPLC_MATMUL_BF16X3) == Second::expand) {
         const ExpandArgs g{x_tilde, u, x_hat, nullptr, h, M, d, k, 0, 0};
         const int units = compute_units();
         if (t_perp && pos_embed) launch_expand<EPI_PERP | EPI_POS>(g, matmul, units, st);

@@ -85,13 +85,13 @@ def test_kernel_choice_follows_the_documented_rule():
     assert c(B.SPLC_OP_PROJECT, 16384, 2048, 32, 2) == (64, 64)
     assert c(B.SPLC_OP_PROJECT, 16384, 2048, 32, 1) == (16, 32)
     assert c(B.SPLC_OP_PROJECT, 16384, 2050, 16, 0) == (64, 64)              # d not a multiple of 32
-    assert c(B.SPLC_OP_PROJECT, 16384, 2048, 256, 2) == (64, 128)
-    assert c(B.SPLC_OP_PROJECT, 32768, 2048, 256, 2) == (128, 128)
-    assert c(B.SPLC_OP_REPROJECT_PASS1, 32000, 2048, 192) == (128, 64)
-    assert c(B.SPLC_OP_REPROJECT_PASS2, 32000, 2048, 256) == (128, 128)
-    assert c(B.SPLC_OP_REPROJECT_PASS2, 32000, 2048, 192) == (64, 64)
-    assert c(B.SPLC_OP_RECONSTRUCT, 16384, 2048, 256, 2) == (64, 128)
-    assert c(B.SPLC_OP_REPROJECT_PASS2, 32000, 2048, 256, 0, B.SPLC_MATMUL_BF16X3) == (128, 128)
+    assert c(B.SPLC_OP_PROJECT, 16384, 2048, 256, 0) == (64, 128)
+    assert c(B.SPLC_OP_PROJECT, 32768, 2048, 256, 0) == (128, 128)
+    assert c(B.SPLC_OP_REPROJECT_PASS1, 32000, 1000, 192) == (128, 64)
+    assert c(B.SPLC_OP_REPROJECT_PASS2, 32000, 2040, 256) == (128, 128)
+    assert c(B.SPLC_OP_REPROJECT_PASS2, 32000, 2040, 192) == (64, 64)
+    assert c(B.SPLC_OP_RECONSTRUCT, 16384, 2040, 256, 2) == (64, 128)
+    assert c(B.SPLC_OP_REPROJECT_PASS2, 32000, 2040, 256, 0, B.SPLC_MATMUL_BF16X3) == (128, 128)
     with pytest.raises(B.SparseLoCoError):
         c(9, 100, 64, 8)
     with pytest.raises(B.SparseLoCoError):
@@ -101,22 +101,46 @@ def test_kernel_choice_follows_the_documented_rule():
 @pytest.mark.parametrize("op,rows,d,k,tables,matmul,tile", [
     # fp32 reconstruction from 129 to 192 columns: 128 columns from eight 64 x 128 tiles per compute unit on
     ("RECONSTRUCT", 1024, 1536, 160, 2, "FP32", (64, 64)), ("RECONSTRUCT", 4096, 1536, 192, 2, "FP32", (64, 64)),
-    ("RECONSTRUCT", 8191, 2048, 160, 0, "FP32", (64, 128)), ("RECONSTRUCT", 8128, 2048, 160, 0, "FP32", (64, 64)),
-    ("RECONSTRUCT", 16384, 1536, 192, 2, "FP32", (64, 128)), ("RECONSTRUCT", 16384, 1536, 128, 2, "FP32", (64, 64)),
-    ("REPROJECT_PASS2", 50304, 2048, 192, 0, "FP32", (64, 64)),
+    ("RECONSTRUCT", 8191, 2040, 160, 0, "FP32", (64, 128)), ("RECONSTRUCT", 8128, 2040, 160, 0, "FP32", (64, 64)),
+    ("RECONSTRUCT", 16384, 1530, 192, 2, "FP32", (64, 128)), ("RECONSTRUCT", 16384, 1530, 128, 2, "FP32", (64, 64)),
+    ("REPROJECT_PASS2", 50304, 2040, 192, 0, "FP32", (64, 64)),
     # split operands, N x K, an odd number of column blocks
     ("RECONSTRUCT", 1024, 2050, 170, 2, "BF16X3", (128, 64)), ("RECONSTRUCT", 32768, 2050, 170, 2, "BF16X3", (128, 64)),
-    ("RECONSTRUCT", 16384, 1472, 170, 0, "BF16X3", (128, 128)), ("RECONSTRUCT", 16256, 1472, 170, 0, "BF16X3", (128, 64)),
+    ("RECONSTRUCT", 16384, 1470, 170, 0, "BF16X3", (128, 128)), ("RECONSTRUCT", 16256, 1470, 170, 0, "BF16X3", (128, 64)),
+    ("RECONSTRUCT", 16384, 1472, 64, 0, "BF16X3", (128, 128)), ("RECONSTRUCT", 16256, 1472, 64, 0, "BF16X3", (128, 64)),
     ("RECONSTRUCT", 16384, 1472, 48, 0, "BF16X3", (128, 64)), ("RECONSTRUCT", 16384, 2050, 48, 0, "BF16X3", (128, 128)),
-    ("RECONSTRUCT", 16384, 1536, 48, 2, "BF16X3", (128, 128)), ("RECONSTRUCT", 50000, 960, 170, 0, "BF16X3", (128, 64)),
-    ("REPROJECT_PASS2", 32001, 2050, 170, 0, "BF16X3", (128, 128)), ("REPROJECT_PASS2", 32000, 1984, 170, 0, "BF16X3", (128, 64)),
+    ("RECONSTRUCT", 16384, 1530, 48, 2, "BF16X3", (128, 128)), ("RECONSTRUCT", 50000, 950, 170, 0, "BF16X3", (128, 64)),
+    ("REPROJECT_PASS2", 32001, 2050, 170, 0, "BF16X3", (128, 128)), ("REPROJECT_PASS2", 32000, 1984, 230, 0, "BF16X3", (128, 64)),
     ("REPROJECT_PASS2", 6000, 2050, 170, 0, "BF16X3", (128, 64)), ("REPROJECT_PASS2", 9600, 1470, 170, 0, "BF16X3", (128, 128)),
     ("REPROJECT_PASS2", 9472, 1470, 170, 0, "BF16X3", (128, 64)),
     # split operands, K x N: 64 rows while all those tiles run at once
-    ("PROJECT", 16384, 1536, 192, 2, "BF16X3", (64, 64)), ("PROJECT", 16385, 1536, 192, 2, "BF16X3", (128, 64)),
+    ("PROJECT", 16384, 510, 192, 2, "BF16X3", (64, 64)), ("PROJECT", 16385, 510, 192, 2, "BF16X3", (128, 64)),
     ("PROJECT", 24576, 1536, 256, 1, "BF16X3", (64, 128)), ("PROJECT", 24576, 1536, 256, 0, "BF16X3", (128, 128)),
-    ("PROJECT", 24448, 1536, 256, 0, "BF16X3", (64, 128)), ("REPROJECT_PASS1", 32001, 2050, 170, 0, "BF16X3", (128, 64)),
+    ("PROJECT", 24448, 1536, 256, 0, "BF16X3", (64, 128)), ("REPROJECT_PASS1", 32001, 510, 170, 0, "BF16X3", (128, 64)),
     ("PROJECT", 9796, 1536, 320, 0, "BF16X3", (128, 64))])
 def test_kernel_choice_at_its_lines(op, rows, d, k, tables, matmul, tile):
     """Where the launcher's tile rules change, on both sides of each line."""
     assert B.subspace_kernel_choice(getattr(B, "SPLC_OP_" + op), rows, d, k, tables, getattr(B, "SPLC_MATMUL_" + matmul)) == tile
+
+
+ALL_COLUMNS, ROWS_IN_REGISTERS = (64, 0), (128, 32)
+
+
+@pytest.mark.parametrize("op,rows,d,k,tables,matmul,kernel", [
+    # first product: all columns of 64 rows per workgroup
+    ("PROJECT", 16384, 2048, 256, 2, "FP32", ALL_COLUMNS), ("PROJECT", 16385, 2048, 256, 2, "FP32", (64, 128)),
+    ("PROJECT", 16384, 1023, 256, 2, "FP32", (64, 128)), ("PROJECT", 32768, 2048, 257, 2, "FP32", (128, 64)),
+    ("REPROJECT_PASS1", 32000, 2048, 192, 2, "FP32", ALL_COLUMNS), ("REPROJECT_PASS1", 32000, 2048, 256, 2, "FP32", (128, 128)),
+    ("PROJECT", 16384, 1536, 192, 2, "BF16X3", ALL_COLUMNS), ("PROJECT", 16385, 1536, 192, 2, "BF16X3", (128, 64)),
+    ("PROJECT", 8300, 513, 65, 0, "BF16X3", ALL_COLUMNS), ("PROJECT", 4096, 1536, 65, 0, "BF16X3", (16, 64)),
+    ("REPROJECT_PASS1", 32001, 2050, 170, 0, "BF16X3", ALL_COLUMNS), ("REPROJECT_PASS1", 32001, 2050, 193, 0, "BF16X3", (128, 128)),
+    # second product: 128 rows of coefficients in registers
+    ("RECONSTRUCT", 16384, 2048, 256, 2, "FP32", ROWS_IN_REGISTERS), ("RECONSTRUCT", 16256, 2048, 256, 0, "FP32", (64, 128)),
+    ("RECONSTRUCT", 6144, 2048, 80, 2, "FP32", ROWS_IN_REGISTERS), ("RECONSTRUCT", 6016, 2048, 80, 2, "FP32", (64, 64)),
+    ("RECONSTRUCT", 1, 2048, 224, 2, "BF16X3", ROWS_IN_REGISTERS), ("RECONSTRUCT", 1, 2048, 225, 2, "BF16X3", (128, 128)),
+    ("RECONSTRUCT", 15361, 320, 131, 1, "BF16X3", ROWS_IN_REGISTERS), ("RECONSTRUCT", 9800, 320, 131, 1, "BF16X3", (128, 64)),
+    ("REPROJECT_PASS2", 32000, 2048, 256, 0, "FP32", ROWS_IN_REGISTERS), ("REPROJECT_PASS2", 6016, 2048, 256, 0, "FP32", (128, 128)),
+    ("REPROJECT_PASS2", 32000, 1984, 170, 0, "BF16X3", ROWS_IN_REGISTERS), ("REPROJECT_PASS2", 32001, 2050, 170, 0, "BF16X3", (128, 128))])
+def test_kernel_choice_names_the_kernel_that_runs(op, rows, d, k, tables, matmul, kernel):
+    """The two kernels that take a call before the GEMM kernel does, and their neighbours that it keeps."""
+    assert B.subspace_kernel_choice(getattr(B, "SPLC_OP_" + op), rows, d, k, tables, getattr(B, "SPLC_MATMUL_" + matmul)) == kernel

@@ -239,9 +239,9 @@ def test_projection_of_few_rows_matches_the_oracle(rows, seq, d, k, vocab, use_p
 GEMM_PROJECTIONS = [
     (2800, 700, 1536, 192, 100, True, True, 64), (2753, 300, 1023, 170, 64, True, False, 64),
     (8300, 830, 513, 42, 300, False, True, 64), (8257, 1000, 512, 21, 77, True, True, 64),
-    (4100, 512, 768, 96, 9, False, False, 64), (2800, 100, 2050, 130, 50, False, False, 64),
-    (8300, 830, 704, 128, 200, True, True, 128), (8257, 415, 513, 126, 33, True, False, 128),
-    (4200, 1050, 770, 255, 20, False, True, 128), (8300, 83, 1025, 65, 5, False, False, 128)]
+    (4100, 512, 768, 260, 9, False, False, 64), (2800, 100, 2050, 130, 50, False, False, 64),
+    (8300, 830, 704, 250, 200, True, True, 128), (8257, 415, 513, 254, 33, True, False, 128),
+    (4200, 1050, 770, 255, 20, False, True, 128), (8300, 83, 1025, 194, 5, False, False, 128)]
 
 
 @pytest.mark.parametrize("rows,seq,d,k,vocab,use_perp,use_pos,columns", GEMM_PROJECTIONS)
@@ -252,12 +252,14 @@ def test_long_projections_on_64_row_tiles(rows, seq, d, k, vocab, use_perp, use_
 
 
 # Reconstructions and re-projections on both sides of the lines of the tile choice that depend on the number of tiles
-LINE_SHAPES = [("x", 1024, 1536, 160, True), ("x", 8191, 2048, 160, False), ("x", 1000, 2050, 170, True),
-               ("x", 12300, 2050, 40, False), ("r", 7000, 2050, 30, False), ("r", 6000, 1984, 50, False)]
+LINE_SHAPES = [("x", 1024, 1530, 160, True), ("x", 8191, 2040, 160, False), ("x", 8191, 2040, 160, True), ("x", 1000, 2050, 170, True),
+               ("x", 12300, 2050, 40, False), ("r", 7000, 2050, 30, False), ("r", 6000, 1980, 50, False)]
 
 
 @pytest.mark.parametrize("op,rows,d,k,tables", LINE_SHAPES)
 def test_reconstruction_and_reprojection_at_the_lines_of_the_tile_choice(op, rows, d, k, tables, matmul_mode):
+    second = B.SPLC_OP_REPROJECT_PASS2 if op == "r" else B.SPLC_OP_RECONSTRUCT
+    assert B.subspace_kernel_choice(second, rows, d, k, 2 * tables, matmul_mode) != (128, 32)     # the GEMM kernel
     if op == "r":
         check_reproject(rows, d, k, seed=rows + d + k, mode=matmul_mode)
     else:
@@ -266,7 +268,8 @@ def test_reconstruction_and_reprojection_at_the_lines_of_the_tile_choice(op, row
 
 def test_every_kernel_variant_is_reached(matmul_mode):
     """The shapes above, run through the library's own launch rule, cover all eight tile shapes of the GEMM
-    kernel (rows x columns x operand form) and both narrow kernels, in this matmul mode."""
+    kernel (rows x columns x operand form), both narrow kernels, the first product with all columns per workgroup and the
+    second one with rows in registers, in this matmul mode."""
     reached = set()
     for vocab, d, k in REPROJECT_SHAPES + [(32000, 2048, 256), (32000, 2048, 192)]:
         reached.add(("KxN",) + B.subspace_kernel_choice(B.SPLC_OP_REPROJECT_PASS1, vocab, d, k, 0, matmul_mode))
@@ -278,7 +281,7 @@ def test_every_kernel_variant_is_reached(matmul_mode):
     want = {(form, tm, tn) for form in ("KxN", "NxK") for tm in (64, 128) for tn in (64, 128)}
     if matmul_mode == B.SPLC_MATMUL_BF16X3:          # with split operands an N x K product always takes 128 rows
         want -= {("NxK", 64, 64), ("NxK", 64, 128)}
-    want |= {("KxN", 16, 16), ("KxN", 16, 32)}
+    want |= {("KxN", 16, 16), ("KxN", 16, 32), ("KxN", 64, 0), ("NxK", 128, 32)}
     assert want <= reached, "not reached: %r" % sorted(want - reached)
 
 
