@@ -78,17 +78,18 @@ constexpr int parts_of_row_block(int row_blocks, int col_tiles, int units) {
 //     522 1.12 ... 1.19 (one card of several; 1.07 at the least), 786 0.97; no table 0.95 ... 1.06 with no clear line;
 //   fp32, k to 128: 0.85 ... 1.07; d 512 to 1023: 0.63 ... 1.19.
 // Fewer blocks go to the projection of few rows or, some of them, to the GEMM kernel (0.5 ... 0.9).  d is bounded because the
-// kernels address U and 64 rows of x by 32-bit byte offsets.
-constexpr bool contract_applies(int64_t rows, int d, int k, int tables, bool split, int units) {
+// kernels address U and 64 rows of x by 32-bit byte offsets.  units_of_device(): compute units, asked of the runtime only where
+// d and k do not refuse by themselves.
+template <class Units>
+constexpr bool contract_applies(int64_t rows, int d, int k, int tables, bool split, Units units_of_device) {
+    if (k <= (split ? 64 : 128) || k > (split ? 192 : 256) || d < (split ? 512 : 1024) || d >= 1 << 20) return false;
+    const int64_t units = units_of_device();
     const int64_t blocks = (rows + 63) / 64, rounds = (blocks + units - 1) / units;
     const int64_t percent = rounds > 0 ? blocks * 100 / (rounds * units) : 0;       // of the units, in the rounds' average
-    if (d >= 1 << 20) return false;
     if (!split) {
-        if (k <= 128 || k > 256 || d < 1024) return false;
         if (k <= 192) return (tables > 0 || k >= 160) && percent >= 67;
         return tables > 0 && percent >= (rounds == 1 ? 60 : 80);
     }
-    if (k <= 64 || k > 192 || d < 512) return false;
     if (k > 128) return blocks * 3 >= units && (rounds == 1 || percent >= 68);
     if (tables == 0) return blocks * 4 > units;
     return rounds == 1 && blocks * 32 >= units * 9 && (tables < 2 || d % 4 == 0 || blocks * 2 > units);

@@ -1103,10 +1103,11 @@ bool tables_in_32_bits(const HighRank& h, int rows) {
 // The kernel of a first product (projection, first pass of the re-projection) and of a second one (reconstruction; update:
 // second pass of the re-projection).  The calls launch by these, and sparseloco_subspace_kernel_choice answers by them.
 enum class First { narrow, contract, rows, gemm };
-First first_product(const HighRank& h, int rows, int d, int k, bool split) {
+template <class Units>
+First first_product(const HighRank& h, int rows, int d, int k, bool split, Units units) {
     if (narrow_applies(d, k, h)) return First::narrow;
     const int tables = (h.t_perp ? 1 : 0) + (h.pos ? 1 : 0);
-    if (splc::contract_applies(rows, d, k, tables, split, compute_units()) && tables_in_32_bits(h, rows)) return First::contract;
+    if (splc::contract_applies(rows, d, k, tables, split, units) && tables_in_32_bits(h, rows)) return First::contract;
     return rows_apply(rows, d, k) ? First::rows : First::gemm;
 }
 enum class Second { expand, gemm };
@@ -1130,7 +1131,7 @@ int reproject_impl(float* t_s, float* t_perp, const float* u, float* coeff_ws, i
     const bool split = matmul == SPLC_MATMUL_BF16X3;
     const HighRank none{nullptr, nullptr, 0, nullptr, 1, (int64_t)d};
     // pass 1: coeff = T_S U            (M x k) = (M x d)(d x k)
-    switch (first_product(none, M, d, k, split)) {
+    switch (first_product(none, M, d, k, split, [&] { return units; })) {
         case First::narrow: launch_project_narrow(t_s, none, u, coeff_ws, M, d, k, st); break;
         case First::contract: launch_contract(ContractArgs{t_s, u, coeff_ws, none, M, d, k}, split, st); break;
         case First::rows: launch_project_rows(t_s, none, u, coeff_ws, M, d, k, st); break;
@@ -1226,7 +1227,7 @@ extern "C" int sparseloco_subspace_kernel_choice(int op, int64_t rows, int d, in
     switch (op) {
         case SPLC_OP_PROJECT:
         case SPLC_OP_REPROJECT_PASS1:
-            switch (first_product(h, M, d, k, split)) {
+            switch (first_product(h, M, d, k, split, compute_units)) {
                 case First::narrow: return 16 * 256 + (k <= 16 ? 16 : 32);
                 case First::contract: return 64 * 256;
                 case First::rows: return 16 * 256 + (rows_wide(M, k) ? 64 : 32);
@@ -1259,7 +1260,7 @@ extern "C" int sparseloco_subspace_project(const float* x, const float* t_perp, 
     const HighRank h{t_perp, token_ids, vocab, pos_embed, seq_len > 0 ? seq_len : 1, (int64_t)d};
     hipStream_t st = static_cast<hipStream_t>(stream);
     const bool split = matmul == SPLC_MATMUL_BF16X3;
-    const First kernel = first_product(h, M, d, k, split);
+    const First kernel = first_product(h, M, d, k, split, compute_units);
     if (kernel == First::narrow)
         launch_project_narrow(x, h, u, x_tilde, M, d, k, st);
     else if (kernel == First::contract)

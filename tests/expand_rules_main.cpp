@@ -52,12 +52,16 @@ int main() {
             for (int d : {16, 511, 512, 1023, 1024, 2050, 1 << 20, 1 << 23})
                 for (bool split : {false, true})
                     for (int tables : {0, 1, 2})
-                        for (int units : {1, 104, 256})
-                            if (splc::contract_applies(rows, d, k, tables, split, units) &&
-                                (rows == 0 || d < 512 || (int64_t)d * k * 4 >= int64_t(1) << 32 || k <= (split ? 64 : 128) || k > (split ? 192 : 256))) {
-                                printf("rows %d d %d k %d\n", (int)rows, d, k);
+                        for (int units : {1, 104, 256}) {
+                            int asked = 0;
+                            const bool applies = splc::contract_applies(rows, d, k, tables, split, [&] { return ++asked, units; });
+                            const bool refused = d < (split ? 512 : 1024) || (int64_t)d * k * 4 >= int64_t(1) << 32 || k <= (split ? 64 : 128) ||
+                                                 k > (split ? 192 : 256);
+                            if ((applies && (rows == 0 || refused)) || (refused && asked) || asked > 1) {      // asking takes runtime calls
+                                printf("rows %d d %d k %d, units asked for %d times\n", (int)rows, d, k, asked);
                                 return 1;
                             }
+                        }
     for (uint32_t entries : {1u, 127u, 128u, 129u, 255u, 256u, 9000u, 9087u, 9088u, 37105u}) {
         std::vector<char> seen(entries, 0);
         for (uint32_t place = 0; place < entries; ++place) {
