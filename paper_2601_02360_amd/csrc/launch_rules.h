@@ -71,11 +71,15 @@ constexpr int parts_of_row_block(int row_blocks, int col_tiles, int units) {
 //     730 1.02 ... 1.6 -- so at least 68 % of the units in the rounds' average;
 //   split, k 65 ... 128, no table: 66 to 768 blocks 1.04 ... 1.8; with tables 72 to 256 blocks 1.03 ... 1.54, beyond 0.91 ...
 //     1.11 (rows that are no whole number of 16 bytes, both tables, 83 to 125 blocks: 0.90 ... 0.98);
-//   fp32, k 129 ... 192 (the GEMM tile pads them to 256): with tables 86 to 160 blocks 0.70 ... 0.88, 173 to 256 1.01 ...
-//     1.26, 288 to 326 0.77 ... 0.96, 352 to 524 1.02 ... 1.68; no table, k from 160 on 192 to 256 0.99 ... 1.11, 288 to
-//     320 0.72 ... 0.79, 352 to 512 1.03 ... 1.11, k below 160 0.92 ... 1.05;
-//   fp32, k 193 ... 256: with tables 86 to 131 blocks 0.57 ... 1.00, 147 to 256 1.02 ... 1.13, 288 to 384 0.82 ... 0.95, 416 to
-//     522 1.12 ... 1.19 (one card of several; 1.07 at the least), 786 0.97; no table 0.95 ... 1.06 with no clear line;
+//   fp32 (rounds of workgroups, and percent of the units that have one on average over them; lines: rows of whole 128-byte
+//   lines, which the GEMM kernel reads faster; inputs that the call before did not leave in a cache):
+//     k 129 ... 192 (the GEMM tile pads them to 256), both tables, from 67 % on 1.00 ... 1.81, below 0.70 ... 1.0; one table, one
+//       and two rounds 0.95 ... 1.66, three and four on lines 0.87 ... 1.07 below 88 % and 0.99 ... 1.25 above, more rounds
+//       0.90 ... 1.14, other rows 1.00 ... 1.53; no table, one and two rounds 0.97 ... 1.07 from d 1536 (on lines 1280) on and
+//       0.93 ... 1.02 below, three and four 0.84 ... 0.94 below 88 % and 1.01 ... 1.17 above; no table, k to 159: 0.92 ... 1.05;
+//     k 193 ... 256 with tables: one round from 60 % and d 1536 on 0.95 ... 1.04, of smaller d 0.93 ... 1.03 (median 0.98), two
+//       rounds from d 1280 on 0.97 ... 1.14, below 0.94 ... 1.02, three 0.97 ... 1.31, four and more 0.97 ... 1.11, below d 1280
+//       0.95 ... 1.07; fewer percent 0.57 ... 1.0; no table 0.95 ... 1.06 with no clear line;
 //   fp32, k to 128: 0.85 ... 1.07; d 512 to 1023: 0.63 ... 1.19.
 // Fewer blocks go to the projection of few rows or, some of them, to the GEMM kernel (0.5 ... 0.9).  d is bounded because the
 // kernels address U and 64 rows of x by 32-bit byte offsets.  units_of_device(): compute units, asked of the runtime only where
@@ -86,9 +90,13 @@ constexpr bool contract_applies(int64_t rows, int d, int k, int tables, bool spl
     const int64_t units = units_of_device();
     const int64_t blocks = (rows + 63) / 64, rounds = (blocks + units - 1) / units;
     const int64_t percent = rounds > 0 ? blocks * 100 / (rounds * units) : 0;       // of the units, in the rounds' average
+    const bool lines = d % 32 == 0;              // rows of whole 128-byte lines
     if (!split) {
-        if (k <= 192) return (tables > 0 || k >= 160) && percent >= 67;
-        return tables > 0 && percent >= (rounds == 1 ? 60 : 80);
+        if (k > 192) return tables > 0 && percent >= (rounds == 1 ? 60 : 80) && d >= (rounds == 1 ? 1536 : rounds == 3 ? 1024 : 1280);
+        if (percent < 67) return false;
+        const bool full = rounds <= 2 || (rounds <= 4 && percent >= 88);
+        if (tables == 0) return k >= 160 && full && d >= (lines ? 1280 : 1536);
+        return tables == 2 || full || !lines;
     }
     if (k > 128) return blocks * 3 >= units && (rounds == 1 || percent >= 68);
     if (tables == 0) return blocks * 4 > units;

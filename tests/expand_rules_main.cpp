@@ -62,6 +62,20 @@ int main() {
                                 return 1;
                             }
                         }
+    // where the GEMM kernel was measured to be faster, and neighbours of these shapes where it was not
+    const auto card = [] { return 256; };
+    const struct { int64_t rows; int d, k, tables; bool split, taken; } first[] = {
+        {50304, 1728, 161, 0, false, false}, {36864, 1393, 190, 0, false, false}, {47104, 1984, 175, 0, false, true},
+        {14336, 1059, 167, 0, false, false}, {16384, 1536, 167, 0, false, true}, {16384, 1280, 160, 0, false, true},
+        {16384, 1279, 160, 0, false, false}, {37888, 1088, 170, 1, false, false}, {37532, 1059, 173, 1, false, true},
+        {45056, 1216, 137, 1, false, true}, {84992, 1344, 170, 1, false, false}, {36864, 1088, 170, 2, false, true},
+        {14336, 1297, 247, 2, false, false}, {16384, 1536, 247, 2, false, true}, {30720, 1088, 200, 2, false, false},
+        {30720, 1280, 200, 2, false, true}, {45056, 1088, 200, 2, false, true}};
+    for (const auto& c : first)
+        if (splc::contract_applies(c.rows, c.d, c.k, c.tables, c.split, card) != c.taken) {
+            printf("first product %d x %d onto %d, %d tables\n", (int)c.rows, c.d, c.k, c.tables);
+            return 1;
+        }
     for (uint32_t entries : {1u, 127u, 128u, 129u, 255u, 256u, 9000u, 9087u, 9088u, 37105u}) {
         std::vector<char> seen(entries, 0);
         for (uint32_t place = 0; place < entries; ++place) {
