@@ -67,12 +67,17 @@ constexpr int parts_of_row_block(int row_blocks, int col_tiles, int units) {
 // First product of the subspace calls: contract_kernel (split products) and contract_fp32_kernel, one workgroup per compute
 // unit and 64 rows with all columns, instead of the GEMM kernel.  Time of the GEMM kernel over theirs, MI355X, by blocks of
 // 64 rows (256 units; a second round of workgroups begins with block 257):
-//   split, k 129 ... 192: 85 to 256 blocks 1.04 ... 1.7; 262 to 336 0.84 ... 1.12, 352 to 512 1.18 ... 1.83, 516 0.96, 551 to
-//     730 1.02 ... 1.6 -- so at least 68 % of the units in the rounds' average;
-//   split, k 65 ... 128, no table: 66 to 768 blocks 1.04 ... 1.8; with tables 72 to 256 blocks 1.03 ... 1.54, beyond 0.91 ...
-//     1.11 (rows that are no whole number of 16 bytes, both tables, 83 to 125 blocks: 0.90 ... 0.98);
-//   fp32 (rounds of workgroups, and percent of the units that have one on average over them; lines: rows of whole 128-byte
+//   split (rounds of workgroups, and percent of the units that have one on average over them; lines: rows of whole 128-byte
 //   lines, which the GEMM kernel reads faster; inputs that the call before did not leave in a cache):
+//     k 129 ... 192, one round from a third of the units on 0.97 ... 1.71, but with tables on other rows than lines, d below 768
+//       and less than half of the units 0.94 ... 1.1; more rounds from 68 % on 0.97 ... 1.87, below 0.84 ... 1.12; there without
+//       tables below d 640 0.87 ... 1.1 (four rounds and more, below d 768: 0.87 ... 1.07), and with one table on lines, d
+//       below 640 and less than 88 % 0.91 ... 1.09;
+//     k 65 ... 128, no table, from a quarter of the units on: one and two rounds 0.95 ... 1.78 (31456 x 512 onto 118: 0.89), three
+//       1.0 ... 1.18 from d 640 on (below 0.94 ... 1.04), more 0.91 ... 1.2 from d 1024 on (below 0.84 ... 1.08);
+//     k 65 ... 128, tables, 72 to 256 blocks: one 0.95 ... 1.52, both from half of the units on 1.07 ... 1.35, fewer 1.0 ... 1.22 on
+//       lines from d 768 on and 0.90 ... 1.14 elsewhere; 257 blocks and more 0.91 ... 1.11;
+//   fp32, measured and told apart in the same way:
 //     k 129 ... 192 (the GEMM tile pads them to 256), both tables, from 67 % on 1.00 ... 1.81, below 0.70 ... 1.0; one table, one
 //       and two rounds 0.95 ... 1.66, three and four on lines 0.87 ... 1.07 below 88 % and 0.99 ... 1.25 above, more rounds
 //       0.90 ... 1.14, other rows 1.00 ... 1.53; no table, one and two rounds 0.97 ... 1.07 from d 1536 (on lines 1280) on and
@@ -98,9 +103,14 @@ constexpr bool contract_applies(int64_t rows, int d, int k, int tables, bool spl
         if (tables == 0) return k >= 160 && full && d >= (lines ? 1280 : 1536);
         return tables == 2 || full || !lines;
     }
-    if (k > 128) return blocks * 3 >= units && (rounds == 1 || percent >= 68);
-    if (tables == 0) return blocks * 4 > units;
-    return rounds == 1 && blocks * 32 >= units * 9 && (tables < 2 || d % 4 == 0 || blocks * 2 > units);
+    if (k > 128) {
+        if (rounds == 1) return blocks * 3 >= units && (tables == 0 || lines || d >= 768 || percent >= 50);
+        if (percent < 68) return false;
+        if (tables == 0) return d >= (rounds == 2 ? 512 : rounds == 3 ? 640 : 768);
+        return tables == 2 || rounds == 2 || !lines || d >= 640 || percent >= 88;
+    }
+    if (tables == 0) return blocks * 4 > units && d >= (rounds <= 2 ? 512 : rounds == 3 ? 640 : 1024);
+    return rounds == 1 && blocks * 32 >= units * 9 && (tables == 1 || blocks * 2 > units || (lines && d >= 768));
 }
 
 // Batched calls (compress of several replicas, one-launch step): on plans of few chunks every replica of a chunk gets a

@@ -70,7 +70,13 @@ int main() {
         {16384, 1279, 160, 0, false, false}, {37888, 1088, 170, 1, false, false}, {37532, 1059, 173, 1, false, true},
         {45056, 1216, 137, 1, false, true}, {84992, 1344, 170, 1, false, false}, {36864, 1088, 170, 2, false, true},
         {14336, 1297, 247, 2, false, false}, {16384, 1536, 247, 2, false, true}, {30720, 1088, 200, 2, false, false},
-        {30720, 1280, 200, 2, false, true}, {45056, 1088, 200, 2, false, true}};
+        {30720, 1280, 200, 2, false, true}, {45056, 1088, 200, 2, false, true},
+        {54245, 512, 115, 0, true, false}, {54272, 799, 120, 0, true, false}, {54272, 1024, 120, 0, true, true},
+        {36622, 576, 97, 0, true, false}, {36622, 640, 97, 0, true, true}, {38912, 576, 160, 0, true, false},
+        {38912, 640, 160, 0, true, true}, {49743, 704, 180, 0, true, false}, {36072, 512, 132, 1, true, false},
+        {37060, 519, 136, 1, true, true}, {46859, 576, 148, 1, true, true}, {5876, 545, 151, 2, true, false},
+        {5876, 576, 151, 2, true, true}, {8597, 549, 135, 2, true, true}, {5120, 512, 78, 2, true, false},
+        {6144, 660, 116, 2, true, false}, {6052, 832, 91, 2, true, true}};
     for (const auto& c : first)
         if (splc::contract_applies(c.rows, c.d, c.k, c.tables, c.split, card) != c.taken) {
             printf("first product %d x %d onto %d, %d tables\n", (int)c.rows, c.d, c.k, c.tables);
