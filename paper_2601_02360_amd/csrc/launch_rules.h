@@ -23,27 +23,6 @@ constexpr int unguarded_tiles(int rows, int width, int floats, int tile_rows) {
     return (rows - spare) / tile_rows;
 }
 
-// Second product of the subspace calls (out [rows, width] = coefficients [rows, k] U^T): expand_kernel, which keeps rows of
-// coefficients in registers and walks along the columns, instead of the GEMM kernel's tile per workgroup.  It needs whole
-// 128-byte lines in a row (with rows of 1100 or 1300 floats it takes 1.2 to 1.6 times as long), k above 32 (below, memory
-// bounds both) and what fits its registers and LDS: k <= 256, split products 224.  tiles: of 128 rows x 32 columns.
-// Time of the GEMM kernel over time of expand_kernel, MI355X:
-//   update (re-projection, both passes): split 128 x 512 ... 45056 x 1536, k 33 ... 214: 1.02 ... 1.5 (width 320 on 24,064
-//     rows 0.97); fp32 from 3072 tiles on 1.01 ... 1.15, 1248 ... 2760 tiles 0.90 ... 1.06, fewer 0.73 ... 1.0;
-//   reconstruction, split: k from 65 on, an even number of 64-column blocks: 1.03 ... 1.98; an odd number (the GEMM tile is
-//     64 columns wide there): 0.95 ... 1.1 up to 700 tiles, 1.1 ... 1.44 from 1200 on; k to 64: with tables 1.01 ... 1.31 (odd
-//     blocks 0.95 ... 1.15), without 0.83 ... 1.3 with no clear line;
-//   reconstruction, fp32: with tables from 3072 tiles on and k from 80 on 1.03 ... 1.22 (k above 224: 8192 rows x 2048, 4096
-//     tiles, 1.02; without tables 0.98), without tables from 4096 tiles and k 128 on 1.02 ... 1.11; fewer tiles 0.77 ... 1.06.
-constexpr bool expand_applies(int64_t rows, int width, int k, int tables, bool update, bool split) {
-    if (width % 32 != 0 || width >= 1 << 20 || k <= 32 || k > (split ? 224 : 256)) return false;
-    const int64_t tiles = (rows + 127) / 128 * (width / 32);
-    if (tiles >= int64_t(1) << 31) return false;
-    if (update) return split ? width > 320 || tiles < 1024 : tiles >= 3072;
-    if (split) return (k > 64 || tables > 0) && (width % 128 == 0 || tiles >= 1200);
-    return tables > 0 ? k >= 80 && tiles >= 3072 : k >= 128 && tiles >= (k > 224 ? 8192 : 4096);
-}
-
 // How expand_kernel's workgroups share the tiles: `parts` of them each take an equal part of one row block's column tiles,
 // or (parts 0) each takes an equal run of all tiles, row block after row block, and new rows on the way.
 struct TileRun { int row_block, col_tile, tiles; };
@@ -62,6 +41,56 @@ constexpr int parts_of_row_block(int row_blocks, int col_tiles, int units) {
     const int parts = units / row_blocks < col_tiles ? units / row_blocks : col_tiles;
     const int64_t run = ((int64_t)row_blocks * col_tiles + units - 1) / units;
     return parts > 0 && (col_tiles + parts - 1) / parts <= run + 2 ? parts : 0;
+}
+
+// Whether expand_kernel's workgroups, one per compute unit, are at work nine tenths of the time of the longest.
+constexpr bool shared_evenly(int64_t rows, int width, int units) {
+    const int64_t tiles = (rows + 127) / 128 * (width / 32);
+    const int parts = parts_of_row_block((int)((rows + 127) / 128), width / 32, units);
+    const int64_t most = parts > 0 ? (width / 32 + parts - 1) / parts : (tiles + units - 1) / units;
+    return tiles * 10 >= most * units * 9;
+}
+
+// Second product of the subspace calls (out [rows, width] = coefficients [rows, k] U^T): expand_kernel, which keeps rows of
+// coefficients in registers and walks along the columns, instead of the GEMM kernel's tile per workgroup.  It needs whole
+// 128-byte lines in a row (with rows of 1100 or 1300 floats it takes 1.2 to 1.6 times as long), k above 32 (below, memory
+// bounds both) and what fits its registers and LDS: k <= 256, split products 224.  tiles: of 128 rows x 32 columns.
+// half: the last step of 32 k is at most half used.  Time of the GEMM kernel over time of expand_kernel, MI355X, inputs that the
+// call before did not leave in a cache:
+//   update (re-projection, both passes), split, width above 320: 0.94 ... 1.6 (median 1.12), but k to 48 from 19,000 tiles on
+//     0.93 ... 1.03; width to 320, an even number of 64-column blocks: 1.0 ... 1.6 up to 1024 tiles; an odd number, from 10 tiles
+//     and up to 3072 rows 0.91 ... 1.24, single rows of few tiles 0.91 ... 1.0, more rows 0.84 ... 1.17;
+//   update, fp32 from 3072 tiles on 1.01 ... 1.15, 1248 ... 2760 tiles 0.90 ... 1.06, fewer 0.73 ... 1.0;
+//   reconstruction, split, one table: 0.95 ... 2.4 (an odd number of 64-column blocks, whose GEMM tile is 64 columns wide, 0.95 ...
+//     1.1 up to 700 tiles, 1.0 ... 1.44 from 1200 on);
+//   reconstruction, split, no table: k from 65 on 1.1 ... 1.98 below 1024 tiles, from there 0.92 ... 1.45 (half and not shared
+//     evenly 0.81 ... 1.1), width to 256 0.89 ... 1.2; k to 64 0.83 ... 1.3 with no clear line;
+//   reconstruction, split, both tables: below 1024 tiles 1.2 ... 2.4; from there k from 73 on 0.92 ... 1.9; k 41 ... 72, where memory
+//     bounds it, 0.94 ... 1.48 where workgroups stay in a row block, or take up to 4096 tiles, but 0.77 ... 1.18 where more tiles
+//     are shared as equal runs and 0.86 ... 1.0 for four parts and more of an odd number of 64-column blocks; k to 40
+//     0.86 ... 1.32 (median 1.04);
+//   reconstruction, fp32: with tables from 3072 tiles on and k from 80 on 1.03 ... 1.22 (k above 224: 8192 rows x 2048, 4096
+//     tiles, 1.02; without tables 0.98), without tables from 4096 tiles and k 128 on 1.02 ... 1.11; fewer tiles 0.77 ... 1.06.
+template <class Units>
+constexpr bool expand_applies(int64_t rows, int width, int k, int tables, bool update, bool split, Units units) {
+    if (width % 32 != 0 || width >= 1 << 20 || k <= 32 || k > (split ? 224 : 256)) return false;
+    const int64_t tiles = (rows + 127) / 128 * (width / 32);
+    if (tiles >= int64_t(1) << 31) return false;
+    if (update && !split) return tiles >= 3072;
+    if (update) {
+        if (k <= 48 && tiles >= 19000) return false;
+        return width > 320 || (tiles < 1024 && (width % 128 == 0 || (tiles >= 10 && rows <= 3072)));
+    }
+    const bool half = (k - 1) % 32 < 16;
+    if (split) {
+        if ((k <= 64 && tables == 0) || (width % 128 != 0 && tiles < 1200)) return false;
+        if (tables == 1 || tiles < 1024) return true;
+        if (tables == 0) return width > 256 && (!half || shared_evenly(rows, width, units()));
+        if (k <= 40) return false;
+        const int parts = k > 72 ? 1 : parts_of_row_block((int)((rows + 127) / 128), width / 32, units());
+        return parts > 0 ? parts < 4 || width % 128 == 0 : tiles < 4096;
+    }
+    return tables > 0 ? k >= 80 && tiles >= 3072 : k >= 128 && tiles >= (k > 224 ? 8192 : 4096);
 }
 
 // First product of the subspace calls: contract_kernel (split products) and contract_fp32_kernel, one workgroup per compute

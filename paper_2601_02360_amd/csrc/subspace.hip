@@ -1113,7 +1113,7 @@ First first_product(const HighRank& h, int rows, int d, int k, bool split, Units
 enum class Second { expand, gemm };
 Second second_product(const HighRank& h, int rows, int d, int k, bool update, bool split) {
     const int tables = (h.t_perp ? 1 : 0) + (h.pos ? 1 : 0);
-    return splc::expand_applies(rows, d, k, tables, update, split) && tables_in_32_bits(h, rows) ? Second::expand : Second::gemm;
+    return splc::expand_applies(rows, d, k, tables, update, split, compute_units) && tables_in_32_bits(h, rows) ? Second::expand : Second::gemm;
 }
 
 bool valid_matmul(int matmul) { return matmul == SPLC_MATMUL_FP32 || matmul == SPLC_MATMUL_BF16X3; }

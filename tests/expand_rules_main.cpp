@@ -42,7 +42,7 @@ int main() {
             for (bool split : {false, true})
                 for (bool update : {false, true})
                     for (int tables : {0, 1, 2})
-                        if (splc::expand_applies(1 << 20, width, k, tables, update, split) &&
+                        if (splc::expand_applies(1 << 20, width, k, tables, update, split, [] { return 256; }) &&
                             (width % 32 || width >= 1 << 20 || k <= 32 || k > (split ? 224 : 256))) {
                             printf("width %d k %d\n", width, k);
                             return 1;
@@ -80,6 +80,19 @@ int main() {
     for (const auto& c : first)
         if (splc::contract_applies(c.rows, c.d, c.k, c.tables, c.split, card) != c.taken) {
             printf("first product %d x %d onto %d, %d tables\n", (int)c.rows, c.d, c.k, c.tables);
+            return 1;
+        }
+    const struct { int64_t rows; int width, k, tables; bool update, split, taken; } second[] = {
+        {43008, 960, 64, 2, false, true, false}, {30720, 896, 59, 2, false, true, true}, {22016, 448, 47, 2, false, true, true},
+        {6144, 1088, 48, 2, false, true, false}, {6144, 1024, 48, 2, false, true, true}, {82853, 1536, 44, 2, false, true, false},
+        {82853, 1536, 44, 1, false, true, true}, {82853, 1536, 73, 2, false, true, true}, {12288, 1024, 38, 2, false, true, false},
+        {1024, 1024, 38, 2, false, true, true}, {8529, 896, 97, 0, false, true, false}, {8529, 896, 113, 0, false, true, true},
+        {8192, 896, 97, 0, false, true, true}, {47046, 256, 130, 0, false, true, false}, {4096, 256, 130, 0, false, true, true},
+        {5840, 192, 163, 0, true, true, false}, {3072, 192, 134, 0, true, true, true}, {64, 192, 34, 0, true, true, false},
+        {4096, 256, 224, 0, true, true, true}, {59653, 1984, 41, 0, true, true, false}, {30000, 1984, 41, 0, true, true, true}};
+    for (const auto& c : second)
+        if (splc::expand_applies(c.rows, c.width, c.k, c.tables, c.update, c.split, card) != c.taken) {
+            printf("second product %d x %d from %d, %d tables\n", (int)c.rows, c.width, c.k, c.tables);
             return 1;
         }
     for (uint32_t entries : {1u, 127u, 128u, 129u, 255u, 256u, 9000u, 9087u, 9088u, 37105u}) {
