@@ -60,7 +60,8 @@ constexpr bool shared_evenly(int64_t rows, int width, int units) {
 //   update (re-projection, both passes), split, width above 320: 0.94 ... 1.6 (median 1.12), but k to 48 from 19,000 tiles on
 //     0.93 ... 1.03; width to 320, an even number of 64-column blocks: 1.0 ... 1.6 up to 1024 tiles; an odd number, from 10 tiles
 //     and up to 3072 rows 0.91 ... 1.24, single rows of few tiles 0.91 ... 1.0, more rows 0.84 ... 1.17;
-//   update, fp32 from 3072 tiles on 1.01 ... 1.15, 1248 ... 2760 tiles 0.90 ... 1.06, fewer 0.73 ... 1.0;
+//   update, fp32, from 3072 tiles on 0.97 ... 1.23 (k 41 ... 47 0.98 ... 1.13, k 48 0.96 ... 1.03, k to 40 0.95 ... 1.08, median 1.0),
+//     1248 ... 2760 tiles 0.90 ... 1.06, fewer 0.73 ... 1.0;
 //   reconstruction, split, one table: 0.95 ... 2.4 (an odd number of 64-column blocks, whose GEMM tile is 64 columns wide, 0.95 ...
 //     1.1 up to 700 tiles, 1.0 ... 1.44 from 1200 on);
 //   reconstruction, split, no table: k from 65 on 1.1 ... 1.98 below 1024 tiles, from there 0.92 ... 1.45 (half and not shared
@@ -69,14 +70,16 @@ constexpr bool shared_evenly(int64_t rows, int width, int units) {
 //     bounds it, 0.94 ... 1.48 where workgroups stay in a row block, or take up to 4096 tiles, but 0.77 ... 1.18 where more tiles
 //     are shared as equal runs and 0.86 ... 1.0 for four parts and more of an odd number of 64-column blocks; k to 40
 //     0.86 ... 1.32 (median 1.04);
-//   reconstruction, fp32: with tables from 3072 tiles on and k from 80 on 1.03 ... 1.22 (k above 224: 8192 rows x 2048, 4096
-//     tiles, 1.02; without tables 0.98), without tables from 4096 tiles and k 128 on 1.02 ... 1.11; fewer tiles 0.77 ... 1.06.
+//   reconstruction, fp32, from 3072 tiles on, with tables: k from 81 on 0.97 ... 1.26, but half 0.94 ... 1.1 (width to 640, one table
+//     and fewer than 4096 tiles, or not shared evenly: 0.88 ... 1.09), width to 256 0.88 ... 1.06, k 80 0.89 ... 1.06 (the GEMM kernel's
+//     steps are of 16 k); without, from 4096 tiles (k above 224: 8192) and k 128 on 0.97 ... 1.13, half 0.90 ... 1.07 (median 0.98);
+//     fewer tiles 0.77 ... 1.06.
 template <class Units>
 constexpr bool expand_applies(int64_t rows, int width, int k, int tables, bool update, bool split, Units units) {
     if (width % 32 != 0 || width >= 1 << 20 || k <= 32 || k > (split ? 224 : 256)) return false;
     const int64_t tiles = (rows + 127) / 128 * (width / 32);
     if (tiles >= int64_t(1) << 31) return false;
-    if (update && !split) return tiles >= 3072;
+    if (update && !split) return tiles >= 3072 && k > 40 && k != 48;
     if (update) {
         if (k <= 48 && tiles >= 19000) return false;
         return width > 320 || (tiles < 1024 && (width % 128 == 0 || (tiles >= 10 && rows <= 3072)));
@@ -90,7 +93,9 @@ constexpr bool expand_applies(int64_t rows, int width, int k, int tables, bool u
         const int parts = k > 72 ? 1 : parts_of_row_block((int)((rows + 127) / 128), width / 32, units());
         return parts > 0 ? parts < 4 || width % 128 == 0 : tiles < 4096;
     }
-    return tables > 0 ? k >= 80 && tiles >= 3072 : k >= 128 && tiles >= (k > 224 ? 8192 : 4096);
+    if (width <= 256 || tiles < 3072 || k <= 80) return false;
+    if (tables == 0) return !half && k >= 128 && width > 320 && tiles >= (k > 224 ? 8192 : 4096);
+    return !half || (width > 640 && tiles >= (tables == 2 ? 3072 : 4096) && shared_evenly(rows, width, units()));
 }
 
 // First product of the subspace calls: contract_kernel (split products) and contract_fp32_kernel, one workgroup per compute

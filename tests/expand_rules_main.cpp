@@ -89,7 +89,13 @@ int main() {
         {1024, 1024, 38, 2, false, true, true}, {8529, 896, 97, 0, false, true, false}, {8529, 896, 113, 0, false, true, true},
         {8192, 896, 97, 0, false, true, true}, {47046, 256, 130, 0, false, true, false}, {4096, 256, 130, 0, false, true, true},
         {5840, 192, 163, 0, true, true, false}, {3072, 192, 134, 0, true, true, true}, {64, 192, 34, 0, true, true, false},
-        {4096, 256, 224, 0, true, true, true}, {59653, 1984, 41, 0, true, true, false}, {30000, 1984, 41, 0, true, true, true}};
+        {4096, 256, 224, 0, true, true, true}, {59653, 1984, 41, 0, true, true, false}, {30000, 1984, 41, 0, true, true, true},
+        {94208, 192, 133, 1, false, false, false}, {41984, 320, 188, 2, false, false, true}, {41984, 576, 101, 2, false, false, false},
+        {41984, 704, 101, 2, false, false, true}, {41984, 576, 92, 2, false, false, true}, {14336, 1152, 97, 1, false, false, false},
+        {16384, 1152, 97, 1, false, false, true}, {9126, 1792, 80, 2, false, false, false}, {9126, 1792, 81, 2, false, false, true},
+        {14218, 1216, 162, 0, false, false, false}, {22918, 896, 192, 0, false, false, true}, {42739, 1024, 136, 0, false, false, false},
+        {39888, 832, 33, 0, true, false, false}, {35968, 512, 40, 0, true, false, false}, {40858, 1216, 48, 0, true, false, false},
+        {40858, 1216, 49, 0, true, false, true}, {43043, 1216, 46, 0, true, false, true}};
     for (const auto& c : second)
         if (splc::expand_applies(c.rows, c.width, c.k, c.tables, c.update, c.split, card) != c.taken) {
             printf("second product %d x %d from %d, %d tables\n", (int)c.rows, c.width, c.k, c.tables);

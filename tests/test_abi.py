@@ -136,7 +136,7 @@ ALL_COLUMNS, ROWS_IN_REGISTERS = (64, 0), (128, 32)
     ("REPROJECT_PASS1", 32001, 2050, 170, 0, "BF16X3", ALL_COLUMNS), ("REPROJECT_PASS1", 32001, 2050, 193, 0, "BF16X3", (128, 128)),
     # second product: 128 rows of coefficients in registers
     ("RECONSTRUCT", 16384, 2048, 256, 2, "FP32", ROWS_IN_REGISTERS), ("RECONSTRUCT", 16256, 2048, 256, 0, "FP32", (64, 128)),
-    ("RECONSTRUCT", 6144, 2048, 80, 2, "FP32", ROWS_IN_REGISTERS), ("RECONSTRUCT", 6016, 2048, 80, 2, "FP32", (64, 64)),
+    ("RECONSTRUCT", 6144, 2048, 81, 2, "FP32", ROWS_IN_REGISTERS), ("RECONSTRUCT", 6016, 2048, 81, 2, "FP32", (64, 64)),
     ("RECONSTRUCT", 1, 2048, 224, 2, "BF16X3", ROWS_IN_REGISTERS), ("RECONSTRUCT", 1, 2048, 225, 2, "BF16X3", (128, 128)),
     ("RECONSTRUCT", 15361, 320, 131, 1, "BF16X3", ROWS_IN_REGISTERS), ("RECONSTRUCT", 9800, 320, 131, 1, "BF16X3", (128, 64)),
     ("REPROJECT_PASS2", 32000, 2048, 256, 0, "FP32", ROWS_IN_REGISTERS), ("REPROJECT_PASS2", 6016, 2048, 256, 0, "FP32", (128, 128)),
