@@ -186,10 +186,12 @@ constexpr bool few_streams(int64_t chunks, int kappa, bool from_params, bool gen
 // chunks' pairs at kappa 32 ... 16: taken one by one, every XCD fetches each of these lines for itself.
 // Worth it where messages are a large part of the traffic and a small part of a line; otherwise the order of the table keeps
 // memory busier.  Time in the table's order / in runs, MI355X, quantised, 9000 to 100,000 chunks:
-//   aggregate_update, kappa 16 ... 48: 32 replicas 1.02 ... 1.24, 24: 1.02 ... 1.25, 20: 0.98 ... 1.18, 16: 0.95 ... 1.09, 2 to 8:
-//     0.93 ... 0.97, 64: 0.99 ... 1.03; kappa 64: 24 to 32 replicas 1.00 ... 1.15 from 12,000 chunks on, 0.99 at 9000, 64
-//     replicas 0.96 ... 0.98; kappa 96 and 128: 0.97 ... 1.17; 4096 chunks, 32 replicas: 0.97 ... 1.16, 1500: 0.93 ... 0.97;
-//   aggregate, kappa 16 ... 64: 24 to 32 replicas 1.00 ... 1.27, 64: 1.01 ... 1.14, 20: 0.94 ... 1.13, 4: 0.92 ... 1.05;
+//   aggregate_update, kappa 16 ... 48: 24 and 32 replicas 1.01 ... 1.29, 20: 0.98 ... 1.18, 16: 0.95 ... 1.09, 2 to 8: 0.93 ... 0.97; 40 to
+//     64: 1.01 ... 1.14 while the messages are below 240 MB, from there 0.93 ... 1.04; kappa 64: 24 to 48 replicas 1.00 ... 1.15 from
+//     12,000 chunks on, 0.99 at 9000, 64 replicas 0.96 ... 0.99; kappa 96 and 128: 0.97 ... 1.17; 4096 chunks, 32 replicas: 0.97 ...
+//     1.16, 1500: 0.93 ... 0.97;
+//   aggregate, kappa 16 ... 64: 24 to 64 replicas 1.00 ... 1.34 below 240 MB, 0.94 ... 1.05 from 260 MB on (the last-level cache
+//     holds 256), 20: 0.94 ... 1.13, 4: 0.92 ... 1.05;
 //   without quantisation (the values are whole lines), 32, kappa 32: 0.95 ... 1.12; 128: 0.94 ... 1.01.
 constexpr uint32_t kChunkRun = 16;
 constexpr uint32_t entry_in_runs(uint32_t place, uint32_t entries) {
@@ -198,9 +200,10 @@ constexpr uint32_t entry_in_runs(uint32_t place, uint32_t entries) {
     const uint32_t slot = place / 8;
     return (slot / kChunkRun * 8 + place % 8) * kChunkRun + slot % kChunkRun;
 }
-constexpr bool chunks_in_runs(int64_t entries, int replicas, int kappa, bool quantised) {
+constexpr bool chunks_in_runs(int64_t entries, int replicas, int kappa, bool quantised, bool update) {
     if (!quantised || replicas < 24 || entries < 9000) return false;
-    return kappa <= 48 || (kappa <= 64 && replicas <= 48 && entries >= 12000);
+    if (kappa > 48 && (kappa > 64 || replicas > 48 || entries < 12000)) return false;
+    return (update && replicas <= 32) || entries * replicas * (2 * kappa + 8) < 240000000;
 }
 
 // Whether no two of these address ranges [first, second) share a byte; empty ranges share none.

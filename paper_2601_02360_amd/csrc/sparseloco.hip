@@ -1640,7 +1640,7 @@ void launch_aggregate(const sparseloco_plan* plan, int n_replicas, const uint16_
                            plan->d_chunks, gen_entries(plan, false), n_replicas, (uint32_t)plan->kappa, pairs, aux,
                            dbar, theta, eta, n_reset, (uint32_t)plan->n_tensors,
                            plan->layout == SPLC_LAYOUT_FLAT && splc::chunks_in_runs(plan->n_entries, n_replicas, plan->kappa,
-                                                                                    QUANT == SPLC_QUANT_2BIT), reset);
+                                                                                    QUANT == SPLC_QUANT_2BIT, UPDATE), reset);
 }
 
 template <int QUANT, bool STEP>
