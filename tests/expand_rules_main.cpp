@@ -111,8 +111,10 @@ int main() {
             }
         }
     }
+    // (the first ones are the plans of test_gpu_aggregate_runs.py)
     const struct { int64_t entries; int replicas, kappa; bool update, runs; } aggregations[] = {
-        {9000, 32, 16, false, true}, {8999, 32, 16, true, false}, {9083, 24, 33, true, true}, {12160, 33, 64, true, true},
+        {9000, 32, 16, false, true}, {8999, 32, 16, true, false}, {9084, 24, 33, true, true}, {12160, 33, 64, true, true},
+        {9084, 24, 33, false, true}, {12160, 33, 64, false, true}, {9000, 32, 16, true, true},
         {200000, 24, 24, false, false}, {200000, 24, 24, true, true}, {130000, 28, 32, false, false}, {130000, 32, 32, true, true},
         {130000, 40, 48, true, false}, {200000, 40, 24, true, false}, {100000, 40, 24, true, true}, {100000, 48, 48, true, false},
         {37105, 64, 32, true, true}, {37105, 23, 32, true, false}, {240000, 24, 16, false, true}, {100000, 24, 65, true, false}};

@@ -63,15 +63,33 @@ def assert_within(got, want, bar, what):
         return float(np.nanmax(np.where(bar > 0, err / bar, 0.0)))
 
 
+class Misplaced:
+    """Copies of tensors from element 65 of larger buffers: aligned to 4 bytes and no more, with guard values around them."""
+    EDGE, GUARD = 65, 12345
+
+    def __init__(self):
+        self.buffers = []
+
+    def __call__(self, t):
+        buf = torch.full((t.numel() + 2 * self.EDGE,), self.GUARD, dtype=t.dtype, device="cuda")
+        self.buffers.append(buf)
+        return buf[self.EDGE:-self.EDGE].view(t.shape).copy_(t)
+
+    def check(self):
+        for buf in self.buffers:
+            assert (buf[:self.EDGE] == self.GUARD).all() and (buf[-self.EDGE:] == self.GUARD).all(), "written beside an array"
+
+
 # ---------------------------------------------------------------- re-projection (section 2.4)
 
-def check_reproject(vocab, d, k, seed, mode, rows=None):
-    """rows: check these rows only (the oracle's products are row-independent); default all."""
+def check_reproject(vocab, d, k, seed, mode, rows=None, place=torch.clone):
+    """rows: check these rows only (the oracle's products are row-independent); default all.  place: puts the arrays of the
+    call into memory (Misplaced, or as they come)."""
     u32 = W.orthonormal_basis(d, k, seed, "cuda")
     ts, tp = gpu_randn((vocab, d), seed + 1, 0.02), gpu_randn((vocab, d), seed + 2, 0.02)
-    g_ts, g_tp = ts.clone(), tp.clone()
-    ws = torch.full((max(vocab * k, 1),), float("nan"), device="cuda")
-    B.sparseloco_reproject_embedding(g_ts, g_tp, u32, ws, matmul=mode)
+    g_ts, g_tp = place(ts), place(tp)
+    ws = place(torch.full((max(vocab * k, 1),), float("nan"), device="cuda"))
+    B.sparseloco_reproject_embedding(g_ts, g_tp, place(u32), ws, matmul=mode)
     torch.cuda.synchronize()
     sel = slice(None) if rows is None else torch.as_tensor(rows, device="cuda")
     T, P, U = f64(ts[sel]), f64(tp[sel]), f64(u32)
@@ -146,21 +164,25 @@ def test_argument_checks():
 
 # ---------------------------------------------------------------- stage boundary (section 2.2)
 
-def check_stage_boundary(rows, seq, d, k, vocab, use_perp, use_pos, seed, mode, what=""):
-    u32 = W.orthonormal_basis(d, k, seed, "cuda")
-    x = gpu_randn((rows, d), seed + 1)
-    tp = gpu_randn((vocab, d), seed + 2, 0.5) if use_perp else None
-    pos = gpu_randn((seq, d), seed + 3, 0.5) if use_pos else None
+def check_stage_boundary(rows, seq, d, k, vocab, use_perp, use_pos, seed, mode, what="", place=torch.clone, outside_ids=False):
+    """place: as in check_reproject; outside_ids: with token ids below 0 and from vocab on, which are clamped."""
+    u32 = place(W.orthonormal_basis(d, k, seed, "cuda"))
+    x = place(gpu_randn((rows, d), seed + 1))
+    tp = place(gpu_randn((vocab, d), seed + 2, 0.5)) if use_perp else None
+    pos = place(gpu_randn((seq, d), seed + 3, 0.5)) if use_pos else None
     tok = None
     if use_perp:
         g = torch.Generator(device="cuda").manual_seed(seed + 4)
         tok = torch.randint(0, vocab, (rows,), generator=g, device="cuda", dtype=torch.int32)
-    out_t = torch.full((rows, k), float("nan"), device="cuda")
+        if outside_ids:
+            tok[0::7], tok[1::7], tok[2::21], tok[9::21] = -1, vocab, 2 ** 31 - 1, -2 ** 31
+        tok = place(tok)
+    out_t = place(torch.full((rows, k), float("nan"), device="cuda"))
     B.sparseloco_subspace_project(x, u32, out_t, t_perp=tp, token_ids=tok, pos_embed=pos, matmul=mode)
     X, U = f64(x), f64(u32)
     TP = None if tp is None else f64(tp)
     PS = None if pos is None else f64(pos)
-    TK = None if tok is None else tok.cpu().numpy()
+    TK = None if tok is None else tok.clamp(0, vocab - 1).cpu().numpy()
     want_t = subspace.project(X, U, TP, TK, PS)
     t_rows = np.zeros_like(X) if TP is None else TP[TK]
     p_rows = np.zeros_like(X) if PS is None else PS[np.arange(rows) % seq]
@@ -169,7 +191,7 @@ def check_stage_boundary(rows, seq, d, k, vocab, use_perp, use_pos, seed, mode, 
     bar_t = U24 * ((C * np.abs(a_exact) + 2 * (np.abs(X) + np.abs(t_rows) + np.abs(p_rows))) @ absU)
     worst = [assert_within(f64(out_t), want_t, bar_t, "project " + what)]
     # reconstruct from the GPU's own x_tilde, compared with the oracle applied to the same x_tilde
-    out_h = torch.full((rows, d), float("nan"), device="cuda")
+    out_h = place(torch.full((rows, d), float("nan"), device="cuda"))
     B.sparseloco_subspace_reconstruct(out_t, u32, out_h, t_perp=tp, token_ids=tok, pos_embed=pos, matmul=mode)
     XT = f64(out_t)
     want_h = subspace.reconstruct(XT, U, TP, TK, PS)
@@ -198,7 +220,10 @@ STAGE_SHAPES = [
     (64, 8, 48, 1, 3, True, True), (2000, 200, 2048, 170, 100, True, False),
     # 128-row tiles of the projection: 128 x 128 (k = 256, 32768 rows) and 128 x 64 (k = 192), with and without tables
     (32768, 1024, 512, 256, 1000, True, True), (22016, 512, 384, 192, 300, False, False),
-    (33000, 1000, 320, 250, 77, False, True)]
+    (33000, 1000, 320, 250, 77, False, True),
+    # the same with one table, and both on 128 x 64; reconstructions on 64 x 128 with one table
+    (61500, 700, 130, 100, 90, True, False), (61500, 700, 130, 33, 90, True, False), (61500, 700, 130, 33, 90, False, True),
+    (61500, 700, 130, 33, 90, True, True), (300, 70, 250, 200, 40, True, False), (300, 70, 250, 200, 40, False, True)]
 
 
 @pytest.mark.parametrize("rows,seq,d,k,vocab,use_perp,use_pos", STAGE_SHAPES)
