@@ -74,27 +74,39 @@ constexpr bool shared_evenly(int64_t rows, int width, int units) {
 //     and fewer than 4096 tiles, or not shared evenly: 0.88 ... 1.09), width to 256 0.88 ... 1.06, k 80 0.89 ... 1.06 (the GEMM kernel's
 //     steps are of 16 k); without, from 4096 tiles (k above 224: 8192) and k 128 on 0.97 ... 1.13, half 0.90 ... 1.07 (median 0.98);
 //     fewer tiles 0.77 ... 1.06.
+constexpr bool expand_takes_k(int k, int tables, bool update, bool split) {
+    if (k <= 32 || k > (split ? 224 : 256)) return false;
+    if (split) return update || tables > 0 || k > 64;
+    if (update) return k > 40 && k != 48;
+    return tables > 0 ? k > 80 : k >= 128 && (k - 1) % 32 >= 16;
+}
+// Whether there are products of so many steps of 32 k: what the launch instantiates.
+constexpr bool expand_takes_steps(int steps, int tables, bool update, bool split) {
+    for (int k = 32 * steps - 31; k <= 32 * steps; ++k)
+        if (expand_takes_k(k, tables, update, split)) return true;
+    return false;
+}
 template <class Units>
 constexpr bool expand_applies(int64_t rows, int width, int k, int tables, bool update, bool split, Units units) {
-    if (width % 32 != 0 || width >= 1 << 20 || k <= 32 || k > (split ? 224 : 256)) return false;
+    if (width % 32 != 0 || width >= 1 << 20 || !expand_takes_k(k, tables, update, split)) return false;
     const int64_t tiles = (rows + 127) / 128 * (width / 32);
     if (tiles >= int64_t(1) << 31) return false;
-    if (update && !split) return tiles >= 3072 && k > 40 && k != 48;
+    if (update && !split) return tiles >= 3072;
     if (update) {
         if (k <= 48 && tiles >= 19000) return false;
         return width > 320 || (tiles < 1024 && (width % 128 == 0 || (tiles >= 10 && rows <= 3072)));
     }
     const bool half = (k - 1) % 32 < 16;
     if (split) {
-        if ((k <= 64 && tables == 0) || (width % 128 != 0 && tiles < 1200)) return false;
+        if (width % 128 != 0 && tiles < 1200) return false;
         if (tables == 1 || tiles < 1024) return true;
         if (tables == 0) return width > 256 && (!half || shared_evenly(rows, width, units()));
         if (k <= 40) return false;
         const int parts = k > 72 ? 1 : parts_of_row_block((int)((rows + 127) / 128), width / 32, units());
         return parts > 0 ? parts < 4 || width % 128 == 0 : tiles < 4096;
     }
-    if (width <= 256 || tiles < 3072 || k <= 80) return false;
-    if (tables == 0) return !half && k >= 128 && width > 320 && tiles >= (k > 224 ? 8192 : 4096);
+    if (width <= 256 || tiles < 3072) return false;
+    if (tables == 0) return width > 320 && tiles >= (k > 224 ? 8192 : 4096);
     return !half || (width > 640 && tiles >= (tables == 2 ? 3072 : 4096) && shared_evenly(rows, width, units()));
 }
 
@@ -123,18 +135,28 @@ constexpr bool expand_applies(int64_t rows, int width, int k, int tables, bool u
 // Fewer blocks go to the projection of few rows or, some of them, to the GEMM kernel (0.5 ... 0.9).  d is bounded because the
 // kernels address U and 64 rows of x by 32-bit byte offsets.  units_of_device(): compute units, asked of the runtime only where
 // d and k do not refuse by themselves.
+constexpr bool contract_takes_k(int k, int tables, bool split) {
+    if (split) return k > 64 && k <= 192;
+    return tables > 0 ? k > 128 && k <= 256 : k >= 160 && k <= 192;
+}
+// Whether there are products of so many times 64 columns: what the launch instantiates.
+constexpr bool contract_takes_columns(int times, int tables, bool split) {
+    for (int k = 64 * times - 63; k <= 64 * times; ++k)
+        if (contract_takes_k(k, tables, split)) return true;
+    return false;
+}
 template <class Units>
 constexpr bool contract_applies(int64_t rows, int d, int k, int tables, bool split, Units units_of_device) {
-    if (k <= (split ? 64 : 128) || k > (split ? 192 : 256) || d < (split ? 512 : 1024) || d >= 1 << 20) return false;
+    if (!contract_takes_k(k, tables, split) || d < (split ? 512 : 1024) || d >= 1 << 20) return false;
     const int64_t units = units_of_device();
     const int64_t blocks = (rows + 63) / 64, rounds = (blocks + units - 1) / units;
     const int64_t percent = rounds > 0 ? blocks * 100 / (rounds * units) : 0;       // of the units, in the rounds' average
     const bool lines = d % 32 == 0;              // rows of whole 128-byte lines
     if (!split) {
-        if (k > 192) return tables > 0 && percent >= (rounds == 1 ? 60 : 80) && d >= (rounds == 1 ? 1536 : rounds == 3 ? 1024 : 1280);
+        if (k > 192) return percent >= (rounds == 1 ? 60 : 80) && d >= (rounds == 1 ? 1536 : rounds == 3 ? 1024 : 1280);
         if (percent < 67) return false;
         const bool full = rounds <= 2 || (rounds <= 4 && percent >= 88);
-        if (tables == 0) return k >= 160 && full && d >= (lines ? 1280 : 1536);
+        if (tables == 0) return full && d >= (lines ? 1280 : 1536);
         return tables == 2 || full || !lines;
     }
     if (k > 128) {

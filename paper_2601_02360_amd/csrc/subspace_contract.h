@@ -413,7 +413,8 @@ void launch_contract(const ContractArgs& g, hipStream_t st) {
     const dim3 grid((unsigned)((g.rows + 63) / 64)), block(512);
     auto run = [&](auto tp, auto pe) {
         constexpr bool TP = decltype(tp)::value, PE = decltype(pe)::value;
-        if constexpr (SPLIT) hipLaunchKernelGGL((contract_kernel<NJ, TP, PE>), grid, block, 0, st, g);
+        if constexpr (!splc::contract_takes_columns(NJ, TP + PE, SPLIT)) return;
+        else if constexpr (SPLIT) hipLaunchKernelGGL((contract_kernel<NJ, TP, PE>), grid, block, 0, st, g);
         else hipLaunchKernelGGL((contract_fp32_kernel<NJ, TP, PE>), grid, block, 0, st, g);
     };
     const std::true_type yes;

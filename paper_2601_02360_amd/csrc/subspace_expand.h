@@ -371,16 +371,19 @@ __global__ __launch_bounds__(512, 2) void expand_kernel(ExpandArgs g) {
 template <int MATH, int EPI>
 void launch_expand(const ExpandArgs& g, int groups, hipStream_t st) {
     const dim3 grid((unsigned)groups), block(512);
+    auto run = [&](auto steps) {
+        constexpr int KS = decltype(steps)::value;
+        if constexpr (splc::expand_takes_steps(KS, (EPI & EPI_PERP ? 1 : 0) + (EPI & EPI_POS ? 1 : 0), EPI == EPI_UPDATE, MATH == MATH_BF16X3))
+            hipLaunchKernelGGL((expand_kernel<MATH, KS, EPI>), grid, block, 0, st, g);
+    };
     switch ((g.k + 31) / 32) {
-        case 2: hipLaunchKernelGGL((expand_kernel<MATH, 2, EPI>), grid, block, 0, st, g); break;
-        case 3: hipLaunchKernelGGL((expand_kernel<MATH, 3, EPI>), grid, block, 0, st, g); break;
-        case 4: hipLaunchKernelGGL((expand_kernel<MATH, 4, EPI>), grid, block, 0, st, g); break;
-        case 5: hipLaunchKernelGGL((expand_kernel<MATH, 5, EPI>), grid, block, 0, st, g); break;
-        case 6: hipLaunchKernelGGL((expand_kernel<MATH, 6, EPI>), grid, block, 0, st, g); break;
-        case 7: hipLaunchKernelGGL((expand_kernel<MATH, 7, EPI>), grid, block, 0, st, g); break;
-        case 8:
-            if constexpr (MATH == MATH_F32) hipLaunchKernelGGL((expand_kernel<MATH, 8, EPI>), grid, block, 0, st, g);
-            break;
+        case 2: run(std::integral_constant<int, 2>{}); break;
+        case 3: run(std::integral_constant<int, 3>{}); break;
+        case 4: run(std::integral_constant<int, 4>{}); break;
+        case 5: run(std::integral_constant<int, 5>{}); break;
+        case 6: run(std::integral_constant<int, 6>{}); break;
+        case 7: run(std::integral_constant<int, 7>{}); break;
+        case 8: run(std::integral_constant<int, 8>{}); break;
     }
 }
 // units: compute units, each of which holds one workgroup

@@ -111,6 +111,32 @@ int main() {
             }
         }
     }
+    // whatever is taken has a kernel, and every kernel has something that is taken
+    for (bool split : {false, true})
+        for (int tables : {0, 1, 2}) {
+            for (bool update : {false, true})
+                for (int steps = 1; steps <= 9; ++steps) {
+                    bool taken = false;
+                    for (int k = 32 * steps - 31; k <= 32 * steps; ++k)
+                        for (int64_t rows : {1, 1000, 16384, 50304})
+                            for (int width : {256, 512, 1088, 2048})
+                                taken |= splc::expand_applies(rows, width, k, update ? 0 : tables, update, split, card);
+                    if (taken != splc::expand_takes_steps(steps, update ? 0 : tables, update, split)) {
+                        printf("second product of %d steps, %d tables\n", steps, tables);
+                        return 1;
+                    }
+                }
+            for (int times = 1; times <= 5; ++times) {
+                bool taken = false;
+                for (int k = 64 * times - 63; k <= 64 * times; ++k)
+                    for (int64_t rows : {1, 5000, 16384, 32768, 50304})
+                        for (int d : {512, 1023, 1088, 2048}) taken |= splc::contract_applies(rows, d, k, tables, split, card);
+                if (taken != splc::contract_takes_columns(times, tables, split)) {
+                    printf("first product of %d x 64 columns, %d tables\n", times, tables);
+                    return 1;
+                }
+            }
+        }
     // (the first ones are the plans of test_gpu_aggregate_runs.py)
     const struct { int64_t entries; int replicas, kappa; bool update, runs; } aggregations[] = {
         {9000, 32, 16, false, true}, {8999, 32, 16, true, false}, {9084, 24, 33, true, true}, {12160, 33, 64, true, true},
