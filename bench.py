@@ -128,6 +128,23 @@ def mfma_roofline(kernel, flops, ms, math):
             "frac": ach / MFMA_FP32_PEAK_TFLOPS, "traffic": None}
 
 
+def product_kernels(ops, rows, d, k, tables, math):
+    """Names of the kernels that the library takes for the products `ops` [(SPLC_OP_*, what for)] of a shape."""
+    from paper_2601_02360_amd import binding as B
+    mm = B.SPLC_MATMUL_BF16X3 if math == "bf16x3" else B.SPLC_MATMUL_FP32
+
+    def name(op):
+        tile = B.subspace_kernel_choice(op, rows, d, k, tables, mm)
+        if tile == (64, 0):
+            return "contract_kernel" if math == "bf16x3" else "contract_fp32_kernel"
+        if tile == (128, 32):
+            return "expand_kernel"
+        if tile[0] == 16:
+            return "project_narrow_kernel" if d % 32 == 0 and k <= (16 if tables == 2 else 32) else "project_rows_kernel"
+        return "gemm_kernel"
+    return " + ".join("%s (%s)" % (name(op), what) for op, what in ops)
+
+
 def bench_reproject(args):
     """Section 2.4's embedding re-projection at the 1B shape: vocabulary 32000, d 2048, k = d/8."""
     import numpy as np
@@ -155,6 +172,8 @@ def bench_reproject(args):
     ms = 1e3 * (time.perf_counter() - t0) / args.steps
     ms_ev = sum(a.elapsed_time(b) for a, b in ev) / len(ev)
     flops = 4.0 * vocab * d * k
+    kernels = product_kernels([(B.SPLC_OP_REPROJECT_PASS1, "pass 1"), (B.SPLC_OP_REPROJECT_PASS2, "pass 2")], vocab, d, k, 0,
+                              args.math)
     bytes_ = 4.0 * (vocab * d * 5 + 2 * vocab * k + 2 * d * k)       # T_S read twice + written, T_perp read + written, coefficients
     result = {
         "metric": "embedding re-projection rows/sec (section 2.4: T_S <- Pi_S(T_S), T_perp += T_S - Pi_S(T_S))",
@@ -166,10 +185,10 @@ def bench_reproject(args):
                    "algorithmic_bytes": bytes_,
                    "hbm_gbs": bytes_ / (ms_ev * 1e-3) / 1e9},
         # a narrow basis (k <= 64: most of the paper's sweep) makes the five passes over the table the bound
-        "roofline": ({"bound": "hbm", "kernel": "project_narrow_kernel / gemm_kernel (pass 1) + gemm_kernel (pass 2)",
+        "roofline": ({"bound": "hbm", "kernel": kernels,
                       "achieved": bytes_ / (ms_ev * 1e-3) / 1e9, "peak": HBM_PEAK_GBS, "unit": "GB/s",
                       "frac": bytes_ / (ms_ev * 1e-3) / 1e9 / HBM_PEAK_GBS, "traffic": None} if k <= 64 else
-                     mfma_roofline("gemm_kernel (both passes)", flops, ms_ev, args.math)),
+                     mfma_roofline(kernels, flops, ms_ev, args.math)),
     }
     if not args.no_cpu:
         from oracle import subspace
@@ -238,12 +257,13 @@ def bench_project(args):
     # paper's sweep) that traffic, not the matrix pipe, is the bound.
     bytes_dir = 4.0 * (2 * rows * d + rows * k + d * k + seq * d)
     narrow = k <= 64
+    kernels = product_kernels([(B.SPLC_OP_PROJECT, "project"), (B.SPLC_OP_RECONSTRUCT, "reconstruct")], rows, d, k, 2, args.math)
     if narrow:
         gbs = 2 * bytes_dir / ((ms_p + ms_r) * 1e-3) / 1e9
-        roofline = {"bound": "hbm", "kernel": "project_narrow_kernel / gemm_kernel (project) + gemm_kernel (reconstruct)",
+        roofline = {"bound": "hbm", "kernel": kernels,
                     "achieved": gbs, "peak": HBM_PEAK_GBS, "unit": "GB/s", "frac": gbs / HBM_PEAK_GBS, "traffic": None}
     else:
-        roofline = mfma_roofline("gemm_kernel (project + reconstruct)", flops, ms_p + ms_r, args.math)
+        roofline = mfma_roofline(kernels, flops, ms_p + ms_r, args.math)
     result = {
         "metric": "stage-boundary tokens/sec (section 2.2: project to the subspace + reconstruct)",
         "value": rows / (ms * 1e-3), "unit": "tokens/s", "n_gpus": 1, "steps": args.steps, "warmup": args.warmup,

@@ -16,7 +16,9 @@
 // For a narrow basis (most of the subspace sizes the paper sweeps) these products are bound by memory
 // traffic, not by the matrix pipe.  The GEMM kernel's 64 x 64 tile handles that well; where it does not
 // (few or no tables to gather, small k), project_narrow_kernel takes over (16 x 16 x 4 MFMAs, operands
-// loaded from global memory directly in MFMA layout, no barrier in the loop).
+// loaded from global memory directly in MFMA layout, no barrier in the loop).  Other sizes have kernels of their own too:
+// few rows (project_rows_kernel below), wide bases (subspace_contract.h and subspace_expand.h: first products with all columns
+// per workgroup, second ones with rows in registers).  first_product and second_product say which kernel a call takes.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 

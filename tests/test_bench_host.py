@@ -40,6 +40,17 @@ def test_cpu_baseline_leg_on_a_tiny_replica_set():
     assert out["single_thread_value"] > 0 and "threads" in out["sample"]
 
 
+def test_kernel_names_of_the_products():
+    from paper_2601_02360_amd import binding as B
+    boundary = [(B.SPLC_OP_PROJECT, "project"), (B.SPLC_OP_RECONSTRUCT, "reconstruct")]
+    passes = [(B.SPLC_OP_REPROJECT_PASS1, "pass 1"), (B.SPLC_OP_REPROJECT_PASS2, "pass 2")]
+    assert bench.product_kernels(boundary, 16384, 2048, 256, 2, "fp32") == "contract_fp32_kernel (project) + expand_kernel (reconstruct)"
+    assert bench.product_kernels(boundary, 16384, 1536, 192, 2, "bf16x3") == "contract_kernel (project) + expand_kernel (reconstruct)"
+    assert bench.product_kernels(boundary, 16384, 1536, 16, 2, "fp32") == "project_narrow_kernel (project) + gemm_kernel (reconstruct)"
+    assert bench.product_kernels(boundary, 2048, 768, 96, 2, "fp32") == "project_rows_kernel (project) + gemm_kernel (reconstruct)"
+    assert bench.product_kernels(passes, 32000, 2048, 256, 0, "fp32") == "gemm_kernel (pass 1) + expand_kernel (pass 2)"
+
+
 def test_more_than_one_gpu_is_refused():
     r = subprocess.run([sys.executable, os.path.join(ROOT, "bench.py"), "--gpus", "2"], capture_output=True, text=True)
     assert r.returncode != 0 and "ONE GPU" in r.stderr and not r.stdout.strip()
