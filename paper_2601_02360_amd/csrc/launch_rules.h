@@ -56,7 +56,7 @@ constexpr bool shared_evenly(int64_t rows, int width, int units) {
 // 128-byte lines in a row (with rows of 1100 or 1300 floats it takes 1.2 to 1.6 times as long), k above 32 (below, memory
 // bounds both) and what fits its registers and LDS: k <= 256, split products 224.  tiles: of 128 rows x 32 columns.
 // half: the last step of 32 k is at most half used.  Time of the GEMM kernel over time of expand_kernel, MI355X, inputs that the
-// call before did not leave in a cache:
+// call before did not leave in a cache (profiles/subspace_rules_measured.txt):
 //   update (re-projection, both passes), split, width above 320: 0.94 ... 1.6 (median 1.12), but k to 48 from 19,000 tiles on
 //     0.93 ... 1.03; width to 320, an even number of 64-column blocks: 1.0 ... 1.6 up to 1024 tiles; an odd number, from 10 tiles
 //     and up to 3072 rows 0.91 ... 1.24, single rows of few tiles 0.91 ... 1.0, more rows 0.84 ... 1.17;
@@ -112,7 +112,8 @@ constexpr bool expand_applies(int64_t rows, int width, int k, int tables, bool u
 
 // First product of the subspace calls: contract_kernel (split products) and contract_fp32_kernel, one workgroup per compute
 // unit and 64 rows with all columns, instead of the GEMM kernel.  Time of the GEMM kernel over theirs, MI355X, by blocks of
-// 64 rows (256 units; a second round of workgroups begins with block 257):
+// 64 rows (256 units; a second round of workgroups begins with block 257; profiles/subspace_rules_measured.txt, and below
+// the lines profiles/contract_fp32_rule_measured.txt):
 //   split (rounds of workgroups, and percent of the units that have one on average over them; lines: rows of whole 128-byte
 //   lines, which the GEMM kernel reads faster; inputs that the call before did not leave in a cache):
 //     k 129 ... 192, one round from a third of the units on 0.97 ... 1.71, but with tables on other rows than lines, d below 768
@@ -207,7 +208,8 @@ constexpr bool few_streams(int64_t chunks, int kappa, bool from_params, bool gen
 // eight runs keep their place.  kChunkRun chunks' levels (8 bytes each) are one cache line, and so are two to four
 // chunks' pairs at kappa 32 ... 16: taken one by one, every XCD fetches each of these lines for itself.
 // Worth it where messages are a large part of the traffic and a small part of a line; otherwise the order of the table keeps
-// memory busier.  Time in the table's order / in runs, MI355X, quantised, 9000 to 100,000 chunks:
+// memory busier.  Time in the table's order / in runs, MI355X, quantised, 9000 to 240,000 chunks
+// (profiles/aggregate_runs_measured.txt):
 //   aggregate_update, kappa 16 ... 48: 24 and 32 replicas 1.01 ... 1.29, 20: 0.98 ... 1.18, 16: 0.95 ... 1.09, 2 to 8: 0.93 ... 0.97; 40 to
 //     64: 1.01 ... 1.14 while the messages are below 240 MB, from there 0.93 ... 1.04; kappa 64: 24 to 48 replicas 1.00 ... 1.15 from
 //     12,000 chunks on, 0.99 at 9000, 64 replicas 0.96 ... 0.99; kappa 96 and 128: 0.97 ... 1.17; 4096 chunks, 32 replicas: 0.97 ...

@@ -12,9 +12,10 @@
 // memory in the layout of the MFMA (the permutation of columns that this makes is undone by the sum at the end) and are
 // split tile by tile.  Splitting, staging and the requests of the next rounds sit between the products; one barrier a round.
 // The four partial sums are added through LDS in the order of k steps.  Two waves per SIMD (256 registers: requesting A two
-// rounds ahead instead of one does not fit and gains nothing where it does).
+// rounds ahead instead of one does not fit and gains nothing where it does; with both tables at NJ = 3 two registers are spilled).
 //
-// Bound: the chip's power limit (1.5 to 1.7 GHz).  GEMM kernel / this, us: 16384 x 1536 onto 192, no tables 78 / 58, both 93 / 65;
+// Bound: neither pipe alone: matrix pipes 49 ... 56 % busy at 1.75 to 1.85 GHz (fp32 products: 2.3 GHz), the vector ALU splits
+// beside them.  GEMM kernel / this, us: 16384 x 1536 onto 192, no tables 78 / 58, both 93 / 65;
 // onto 128: 61 / 40, 60 / 49; 31813 x 1791 onto 182, both tables: 335 / 183; 44032 x 1324 onto 175: 188 / 141.
 
 struct ContractArgs {
@@ -249,7 +250,8 @@ __global__ __launch_bounds__(512, 2) void contract_kernel(ContractArgs g) {
 // multiplies the set {t, 4 + t}, so that a lane reads its row of A as 16 bytes and needs four rows of U.  A row of U is
 // requested anew as soon as its products are issued, x and its tables a round ahead, 256 bytes of a row at a time.
 //
-// Bound: the fp32 matrix pipe (at 16384 x 2048 onto 256 no tables 133 us of at least 109).  The GEMM kernel gathers and
+// Bound: the fp32 matrix pipe (at 16384 x 2048 onto 256 no tables 133 us of at least 109; with both tables 78 % busy at
+// 2.3 GHz).  The GEMM kernel gathers and
 // subtracts a row twice and pads 129 ... 192 columns to 256.  GEMM kernel / this, us, one card: 16384 x 2048 onto 256, both tables
 // 168 / 146; 16384 x 1536 onto 192: 97 / 85; 32768 x 2048 onto 256: 309 / 293; without tables 132 / 133.  128 bytes of a row
 // at a time: 156; the order of all instructions fixed: 169; free over a whole group instead of half a group: 151 to 146.

@@ -64,12 +64,13 @@ constexpr int kOnce = 2;                         // AUX: non-temporal
 // of the next U tile, the exchange of the two halves of the previous tile's sums (through LDS, from which it is read back in
 // rows, so that a lane finishes four neighbouring columns and whole 128-byte lines are written), its tables requested,
 // the tile before that finished.  One barrier a tile, before the last k step, whose operands are in registers by then.
-// Two waves per SIMD (256 registers).
+// Two waves per SIMD (256 registers; split products with both tables and k above 192 spill four).
 //
-// Bound: fp32 by the matrix pipe (8192 of 9300 cycles of a tile at K = 256, 2.3 GHz), split products by the chip's power
-// limit (2304 of 3700 cycles at K = 192, the clock at 1.5 to 1.7 GHz; of 2.3 us a tile 1.4 are products, 0.4 staging, 0.5
-// stores).  Before / now, us: 16384 x 1536 from 192, both tables, split 72.6 / 57.1, fp32 90.9 / 81.7; 16384 x 2048 from
-// 256, both tables, fp32 149 / 140; re-projection 41472 x 1792, k 192, split 497 / 442.
+// Bound: fp32 by the matrix pipe (79 % busy with both tables at K = 256, 74 % in the update, 2.3 GHz); split products by
+// neither pipe alone (51 % busy with both tables at K = 192, 39 % in the update, at 1.8 to 2.0 GHz: splitting, staging and stores sit
+// between the products).  Before / now, us: 16384 x 1536 from 192, both tables, split 72.6 / 57.1, fp32 90.9 / 81.7; 16384 x
+// 2048 from 256, both tables, fp32 149 / 140; re-projection 41472 x 1792, k 192, split 497 / 442; update at 32000 x 2048 from
+// 256, fp32: 320 / 321.
 struct ExpandArgs {
     const float* a;
     const float* u;
@@ -280,7 +281,7 @@ __global__ __launch_bounds__(512, 2) void expand_kernel(ExpandArgs g) {
         constexpr int PER = SPLIT ? 6 : 8, NM = PER * KS;      // products per k step, per tile
         const int next = 32 * after(ct), second = 32 * after(after(ct));
         auto side = [&](int m) {
-            // m = 0 .. NM - 1: after product m.  
+            // m = 0 .. NM - 1: after product m.
             constexpr int CHUNKS = 3 + 2 * NU;
             const int lo = m * CHUNKS / (NM - PER), hi = (m + 1) * CHUNKS / (NM - PER);
             for (int q = lo; q < hi && q < CHUNKS; ++q) {
