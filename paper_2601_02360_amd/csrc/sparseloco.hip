@@ -44,31 +44,13 @@ struct ChunkDesc {
     uint8_t h;                           // local rows present (1..64)
     uint8_t w;                           // width of every row but the last
     uint8_t last_w;                      // width of the last row (flat tail), = w for a tile
-    uint8_t vec;                         // 4-element vector accesses apply: bit 0 for fp32 arrays (all 4096
-                                         // elements present), bit 1 for bf16 arrays (also every row start even)
+    uint8_t vec;                         // bit 0: complete (all 4096 elements present), every 4-element vector whole;
+                                         // bit 1: and every row of a bf16 array starts at a dword
     uint32_t id;                         // chunk number (position of its message in pairs / scales / values)
     uint32_t reserved;
 };
 static_assert(sizeof(ChunkDesc) == 32, "chunk table entries are 32 bytes");
 
-// Local index -> present in the chunk?
-__device__ __forceinline__ bool present(const ChunkDesc& d, uint32_t idx) {
-    const uint32_t lr = idx >> 6, lc = idx & 63u;
-    return lr + 1 < d.h ? lc < d.w : (lr + 1 == d.h && lc < d.last_w);
-}
-// Local index -> element offset from the chunk's origin.
-__device__ __forceinline__ uint32_t elem_of(const ChunkDesc& d, uint32_t idx) {
-    return (idx >> 6) * d.stride + (idx & 63u);
-}
-// The same for an element that is present, 0 (the chunk's first element) for one that is not: a load that need not be
-// made conditional.
-__device__ __forceinline__ uint32_t present_or_first(const ChunkDesc& d, uint32_t idx) {
-    return present(d, idx) ? elem_of(d, idx) : 0u;
-}
-// Whether round i (kThreads indices, four rows) of an edge chunk's walk can hold anything, looked at four rounds at a
-// time: short chunks (the tail of a tensor, mostly) skip the address arithmetic of the rest, tall ones branch rarely
-// (outer update of a tail of 17 / 4095 elements: 2.78 / 4.17 -> 1.90 / 3.62 us).
-__device__ __forceinline__ bool round_used(const ChunkDesc& d, int i) { return 16 * (i >> 2) < (int)d.h; }
 // Address of lane tid's 4-element vector in slot s (local rows 16 s + tid / 16, columns 4 (tid % 16)...).
 // The slot part is uniform and stays in scalar registers; the per-lane part is one 32-bit byte
 // offset shared by all slots and arrays (a chunk spans less than 4 GiB: stride < 2^24).
@@ -79,23 +61,41 @@ __device__ __forceinline__ T* vec_at(T* origin, const ChunkDesc& d, int tid, int
     using Byte = typename std::conditional<std::is_const<T>::value, const char, char>::type;
     return reinterpret_cast<T*>(reinterpret_cast<Byte*>(origin) + slot_bytes + lane_bytes);
 }
-// Bit el of the result: element el of lane tid is present.
-__device__ __forceinline__ uint32_t present_mask(const ChunkDesc& d, int tid) {
-    if (d.n_c == (uint32_t)kChunk) return 0xFFFFu;
-    uint32_t m = 0;
-#pragma unroll
-    for (int el = 0; el < 16; ++el)
-        m |= present(d, (uint32_t)((el >> 2) * 1024 + tid * 4 + (el & 3))) ? (1u << el) : 0u;
-    return m;
+// Edge chunks, four elements at a time.  Of the four elements of lane tid in slot s the first n are present (absent ones
+// are always the last: rows end, they do not begin, inside a vector).  A lane with n < 4 reads the vector that ENDS at its
+// last element, which `pull` then brings to the front, and a lane with none reads the one that ends at the chunk's first
+// (up to) four: every lane loads unconditionally, all of a lane's loads are in flight at once, and an edge chunk costs
+// little more than a complete one (compress, against element by element: 23 tiles of 37- and 141-column matrices 14.0 -> 9.0 us, 1075
+// tiles of 42 columns 23.1 -> 14.6; three tensors of which two end in a tail 7.6 -> 6.0).  What a vector holds before its row belongs
+// to the same tensor and is thrown away; where nothing need lie there (`narrow`: the first rows of a matrix of fewer than four
+// columns, a tensor of fewer than four elements) the four are read one by one, the tensor's first in place of those before it.
+struct EdgeVec {
+    uint32_t n;                          // elements present
+    uint32_t from4;                      // first element read, relative to the chunk's origin, plus 4
+};
+__device__ __forceinline__ EdgeVec edge_vec(const ChunkDesc& d, int tid, int s) {
+    const uint32_t lr = (uint32_t)s * 16u + ((uint32_t)tid >> 4), lc = ((uint32_t)tid & 15u) * 4u;
+    const uint32_t width = lr + 1 < d.h ? d.w : (lr + 1 == d.h ? d.last_w : 0u);
+    const uint32_t n = width > lc ? (width - lc < 4u ? width - lc : 4u) : 0u;
+    const uint32_t w0 = d.h > 1 ? d.w : d.last_w;
+    return {n, n ? lr * d.stride + lc + n : (w0 < 4u ? w0 : 4u)};
 }
-
-// Element `at` of a chunk, as "uniform base + 32-bit byte offset of the lane" (a chunk spans less than 4 GiB).
+__device__ __forceinline__ bool narrow(const ChunkDesc& d) {
+    return d.offset == 0 && (d.h > 1 ? d.w : d.last_w) < 4;       // (any other chunk has four elements before its origin)
+}
+// Where the vector of `v` starts in an array whose element at the chunk's origin is *origin.
 template <class T>
-__device__ __forceinline__ T* elem_at(T* origin, uint32_t at) {
+__device__ __forceinline__ T* edge_at(T* origin, EdgeVec v) {
     using Byte = typename std::conditional<std::is_const<T>::value, const char, char>::type;
-    return reinterpret_cast<T*>(reinterpret_cast<Byte*>(origin) + at * (uint32_t)sizeof(T));
+    return reinterpret_cast<T*>(reinterpret_cast<Byte*>(origin) - 4 * sizeof(T) + (uint64_t)(v.from4 * (uint32_t)sizeof(T)));
 }
-
+// The n elements at the end of four to the front, +0 behind them.
+__device__ __forceinline__ void pull(uint32_t n, float& a, float& b, float& c, float& d) {
+    const bool one = (n & 1u) != 0, two = n == 1u || n == 2u;     // by 4 - n: 3 = 1 + 2, 2, 1
+    a = one ? b : a; b = one ? c : b; c = one ? d : c;
+    a = two ? c : a; b = two ? d : b;
+    a = n > 0 ? a : 0.f; b = n > 1 ? b : 0.f; c = n > 2 ? c : 0.f; d = n > 3 ? d : 0.f;
+}
 enum { MODE_PARAMS_F32 = 0, MODE_DIRECT_F32 = 1, MODE_DIRECT_BF16 = 2 };
 
 // Streaming accesses: every dense array is touched exactly once per launch, so loads and stores
@@ -104,11 +104,11 @@ enum { MODE_PARAMS_F32 = 0, MODE_DIRECT_F32 = 1, MODE_DIRECT_BF16 = 2 };
 // The vector types promise only 4-byte alignment: rows of a tile start at any multiple of 4 bytes,
 // and global memory accepts dword-aligned multi-dword accesses.
 typedef float vfloat4 __attribute__((ext_vector_type(4), aligned(4)));
-typedef uint32_t vuint2 __attribute__((ext_vector_type(2), aligned(4)));
 
 // Every tensor lives in global memory; saying so lets the compiler emit global_ instead of flat_
 // instructions.
 #define SPLC_GLOBAL __attribute__((address_space(1)))
+typedef uint32_t vuint2 __attribute__((ext_vector_type(2), aligned(2)));        // rows of bf16 may start at any element
 __device__ __forceinline__ float4 stream_load4(const float* p) {
     vfloat4 v = __builtin_nontemporal_load((const SPLC_GLOBAL vfloat4*)p);
     return make_float4(v.x, v.y, v.z, v.w);
@@ -117,10 +117,42 @@ __device__ __forceinline__ uint2 stream_load4(const uint16_t* p) {       // four
     vuint2 v = __builtin_nontemporal_load((const SPLC_GLOBAL vuint2*)p);
     return make_uint2(v.x, v.y);
 }
+__device__ __forceinline__ float4 cached_load4(const float* p) {
+    vfloat4 v = *(const SPLC_GLOBAL vfloat4*)p;
+    return make_float4(v.x, v.y, v.z, v.w);
+}
+__device__ __forceinline__ uint2 cached_load4(const uint16_t* p) {
+    vuint2 v = *(const SPLC_GLOBAL vuint2*)p;
+    return make_uint2(v.x, v.y);
+}
+__device__ __forceinline__ float4 edge_load4_narrow(const float* origin, EdgeVec v) {
+    auto at = [&](uint32_t j) { return origin[v.from4 + j < 4 ? 0u : v.from4 + j - 4]; };
+    return make_float4(at(0), at(1), at(2), at(3));
+}
+__device__ __forceinline__ uint2 edge_load4_narrow(const uint16_t* origin, EdgeVec v) {
+    auto at = [&](uint32_t j) { return (uint32_t)origin[v.from4 + j < 4 ? 0u : v.from4 + j - 4]; };
+    return make_uint2(at(0) | at(1) << 16, at(2) | at(3) << 16);
+}
+template <bool STREAM, class T>
+__device__ __forceinline__ auto load4(const T* p) {
+    if constexpr (STREAM) return stream_load4(p);
+    else return cached_load4(p);
+}
 __device__ __forceinline__ void stream_store4(float* p, float4 v) {
     vfloat4 t = {v.x, v.y, v.z, v.w};
     __builtin_nontemporal_store(t, (SPLC_GLOBAL vfloat4*)p);
 }
+template <bool STREAM>
+__device__ __forceinline__ void store4(float* p, float4 v) {
+    vfloat4 t = {v.x, v.y, v.z, v.w};
+    if constexpr (STREAM) stream_store4(p, v);
+    else *(SPLC_GLOBAL vfloat4*)p = t;
+}
+// Whether the rows of a complete chunk are whole cache lines.  Those of a tile in a matrix whose row length is no
+// multiple of 32 floats share their first and last line with the neighbouring tiles, and are accessed without the hint:
+// with it the lines are gone from the L2 when the neighbour asks for them (20M parameters in rows of 1219 and 3687: compress
+// 83 -> 62 us, aggregate 28 -> 20; the one-launch step of four replicas, 47M in rows of 1925 and 5295: 847 -> 619).
+__device__ __forceinline__ bool whole_lines(const ChunkDesc& d) { return d.stride % 32u == 0; }
 
 __device__ __forceinline__ uint32_t lanes_below(uint64_t mask) {
     return __builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u));
@@ -131,94 +163,116 @@ __device__ __forceinline__ float fold(float beta, float e, float delta) {
     return __fadd_rn(__fmul_rn(beta, e), delta);
 }
 
-template <int MODE>
-__device__ __forceinline__ void load_fold_full(const void* __restrict__ a, const void* __restrict__ b,
-                                               const float* __restrict__ e, const ChunkDesc& d, int tid,
-                                               float beta, float (&x)[16]) {
-    const float* pe = e + d.offset;
+// One slot folded: from parameters, from an fp32 or from a bf16 pseudo-gradient (bf16 -> fp32 is the exact widening: the
+// 16 bits become the upper half of the word).
+__device__ __forceinline__ void fold4(float beta, float4 e, float4 o, float4 l, float* x) {
+    x[0] = fold(beta, e.x, __fsub_rn(o.x, l.x));
+    x[1] = fold(beta, e.y, __fsub_rn(o.y, l.y));
+    x[2] = fold(beta, e.z, __fsub_rn(o.z, l.z));
+    x[3] = fold(beta, e.w, __fsub_rn(o.w, l.w));
+}
+__device__ __forceinline__ void fold4(float beta, float4 e, float4 delta, float* x) {
+    x[0] = fold(beta, e.x, delta.x);
+    x[1] = fold(beta, e.y, delta.y);
+    x[2] = fold(beta, e.z, delta.z);
+    x[3] = fold(beta, e.w, delta.w);
+}
+__device__ __forceinline__ void fold4(float beta, float4 e, uint2 delta, float* x) {
+    x[0] = fold(beta, e.x, __uint_as_float(delta.x << 16));
+    x[1] = fold(beta, e.y, __uint_as_float(delta.x & 0xFFFF0000u));
+    x[2] = fold(beta, e.z, __uint_as_float(delta.y << 16));
+    x[3] = fold(beta, e.w, __uint_as_float(delta.y & 0xFFFF0000u));
+}
+
+// All loads of a lane are in flight before the first is waited for.
+template <int MODE, class Chunk>
+__device__ __forceinline__ void load_fold(const void* __restrict__ a, const void* __restrict__ b, const float* __restrict__ e,
+                                          float beta, float (&x)[16], const Chunk& chunk) {
+    using Source = typename std::conditional<MODE == MODE_DIRECT_BF16, uint16_t, float>::type;
+    const float* pe = e + chunk.d.offset;
+    const Source* pa = static_cast<const Source*>(a) + chunk.d.offset;
     float4 ev[4];
 #pragma unroll
-    for (int s = 0; s < 4; ++s) ev[s] = stream_load4(vec_at(pe, d, tid, s));
-    if (MODE == MODE_PARAMS_F32) {
-        const float* po = static_cast<const float*>(a) + d.offset;
-        const float* pl = static_cast<const float*>(b) + d.offset;
-        float4 ov[4], lv[4];
+    for (int s = 0; s < 4; ++s) ev[s] = chunk.load(pe, s);
+    decltype(chunk.load(pa, 0)) av[4];
 #pragma unroll
-        for (int s = 0; s < 4; ++s) ov[s] = stream_load4(vec_at(po, d, tid, s));
+    for (int s = 0; s < 4; ++s) av[s] = chunk.load(pa, s);
+    if constexpr (MODE == MODE_PARAMS_F32) {
+        const float* pb = static_cast<const float*>(b) + chunk.d.offset;
+        float4 bv[4];
 #pragma unroll
-        for (int s = 0; s < 4; ++s) lv[s] = stream_load4(vec_at(pl, d, tid, s));
+        for (int s = 0; s < 4; ++s) bv[s] = chunk.load(pb, s);
 #pragma unroll
-        for (int s = 0; s < 4; ++s) {
-            x[4 * s + 0] = fold(beta, ev[s].x, __fsub_rn(ov[s].x, lv[s].x));
-            x[4 * s + 1] = fold(beta, ev[s].y, __fsub_rn(ov[s].y, lv[s].y));
-            x[4 * s + 2] = fold(beta, ev[s].z, __fsub_rn(ov[s].z, lv[s].z));
-            x[4 * s + 3] = fold(beta, ev[s].w, __fsub_rn(ov[s].w, lv[s].w));
-        }
-    } else if (MODE == MODE_DIRECT_F32) {
-        const float* pd = static_cast<const float*>(a) + d.offset;
-        float4 dv[4];
-#pragma unroll
-        for (int s = 0; s < 4; ++s) dv[s] = stream_load4(vec_at(pd, d, tid, s));
-        __builtin_amdgcn_sched_barrier(0);            // all eight in flight before the first is waited for
-#pragma unroll
-        for (int s = 0; s < 4; ++s) {
-            x[4 * s + 0] = fold(beta, ev[s].x, dv[s].x);
-            x[4 * s + 1] = fold(beta, ev[s].y, dv[s].y);
-            x[4 * s + 2] = fold(beta, ev[s].z, dv[s].z);
-            x[4 * s + 3] = fold(beta, ev[s].w, dv[s].w);
-        }
+        for (int s = 0; s < 4; ++s) fold4(beta, ev[s], av[s], bv[s], x + 4 * s);
     } else {
-        // bf16 -> fp32 is the exact widening: the 16 bits become the upper half of the word
-        const uint16_t* pd = static_cast<const uint16_t*>(a) + d.offset;
-        uint2 dv[4];
+        __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-        for (int s = 0; s < 4; ++s) dv[s] = stream_load4(vec_at(pd, d, tid, s));
-        __builtin_amdgcn_sched_barrier(0);            // all eight in flight before the first is waited for
-#pragma unroll
-        for (int s = 0; s < 4; ++s) {
-            x[4 * s + 0] = fold(beta, ev[s].x, __uint_as_float(dv[s].x << 16));
-            x[4 * s + 1] = fold(beta, ev[s].y, __uint_as_float(dv[s].x & 0xFFFF0000u));
-            x[4 * s + 2] = fold(beta, ev[s].z, __uint_as_float(dv[s].y << 16));
-            x[4 * s + 3] = fold(beta, ev[s].w, __uint_as_float(dv[s].y & 0xFFFF0000u));
-        }
+        for (int s = 0; s < 4; ++s) fold4(beta, ev[s], av[s], x + 4 * s);
+    }
+}
+// The present ones (bits of `there`, the lowest first) of four elements of an edge chunk.
+__device__ __forceinline__ void store_edge(float* p, uint32_t there, float4 v) {
+    if (there == 0xFu) {
+        store4<false>(p, v);
+    } else {
+        if (there & 1u) p[0] = v.x;
+        if (there & 2u) p[1] = v.y;
+        if (there & 4u) p[2] = v.z;
     }
 }
 
-// Edge chunks: element by element, absent elements = +0.  An absent element's loads go to element 0 of the chunk, which
-// every chunk has: with unconditional loads all of a lane's elements are in flight at once (under a condition each
-// waits for its own before the next is requested).
-template <int MODE>
-__device__ __forceinline__ void load_fold_scalar(const void* __restrict__ a, const void* __restrict__ b,
-                                                 const float* __restrict__ e, const ChunkDesc& d, int tid,
-                                                 float beta, uint32_t pmask, float (&x)[16]) {
-    using Source = typename std::conditional<MODE == MODE_DIRECT_BF16, uint16_t, float>::type;
-    const Source* pa = static_cast<const Source*>(a) + d.offset;
-    const float* pb = MODE == MODE_PARAMS_F32 ? static_cast<const float*>(b) + d.offset : nullptr;
-    const float* pe = e + d.offset;
-    // eight elements at a time, indices from an opaque copy of the lane number (none of them is kept for the
-    // selection): otherwise this path would set the register count of the kernel
-#pragma unroll
-    for (int half = 0; half < 16; half += 8) {
-        int t = tid;
-        asm volatile("" : "+v"(t));
-        float ev[8], dv[8], lv[8];
-#pragma unroll
-        for (int i = 0; i < 8; ++i) {
-            const int el = half + i;
-            const uint32_t idx = (el >> 2) * 1024 + t * 4 + (el & 3);
-            const uint32_t at = (pmask & (1u << el)) ? elem_of(d, idx) : 0u;
-            ev[i] = *elem_at(pe, at);
-            if (MODE == MODE_DIRECT_BF16) dv[i] = __uint_as_float((uint32_t)*elem_at(pa, at) << 16);
-            else dv[i] = *elem_at(pa, at);
-            if (MODE == MODE_PARAMS_F32) lv[i] = *elem_at(pb, at);
-        }
-#pragma unroll
-        for (int i = 0; i < 8; ++i) {
-            if (MODE == MODE_PARAMS_F32) dv[i] = __fsub_rn(dv[i], lv[i]);
-            x[half + i] = (pmask & (1u << (half + i))) ? fold(beta, ev[i], dv[i]) : 0.f;
-        }
-        __builtin_amdgcn_sched_barrier(0);
+// What lane tid reads and writes of slot s of the array whose element at the chunk's origin is *p.  What is read of an
+// edge chunk is still to be pulled.
+template <bool STREAM>
+struct CompleteChunk {
+    const ChunkDesc& d;
+    int tid;
+    template <class T> __device__ __forceinline__ auto load(const T* p, int s) const { return load4<STREAM>(vec_at(p, d, tid, s)); }
+    __device__ __forceinline__ void store(float* p, int s, float4 v) const { store4<STREAM>(vec_at(p, d, tid, s), v); }
+};
+template <bool NARROW>
+struct EdgeChunk {
+    const ChunkDesc& d;
+    int tid;
+    template <class T> __device__ __forceinline__ auto load(const T* p, int s) const {
+        const EdgeVec v = edge_vec(d, tid, s);
+        if constexpr (NARROW) return edge_load4_narrow(p, v);
+        else return load4<false>(edge_at(p, v));
     }
+    __device__ __forceinline__ void store(float* p, int s, float4 v) const {
+        store_edge(vec_at(p, d, tid, s), (1u << edge_vec(d, tid, s).n) - 1u, v);
+    }
+};
+// use(chunk) with the way this chunk is accessed.
+template <bool VEC, class Use>
+__device__ __forceinline__ void with_chunk(const ChunkDesc& d, int tid, Use use) {
+    if constexpr (VEC) {
+        // (the statements that say which side this is keep the compiler from merging the two, which drops the hint)
+        if (whole_lines(d)) {
+            asm volatile("; whole lines from here");
+            use(CompleteChunk<true>{d, tid});
+            asm volatile("; whole lines to here");
+        } else {
+            asm volatile("; shared lines from here");
+            use(CompleteChunk<false>{d, tid});
+            asm volatile("; shared lines to here");
+        }
+    } else {
+        if (narrow(d)) use(EdgeChunk<true>{d, tid});
+        else use(EdgeChunk<false>{d, tid});
+    }
+}
+// The present elements of an edge chunk to the front of their vectors, +0 for absent ones; returns the mask of the
+// present ones (bit el: element el of lane tid).
+__device__ __forceinline__ uint32_t pull_all(const ChunkDesc& d, int tid, float (&x)[16]) {
+    uint32_t pmask = 0;
+#pragma unroll
+    for (int s = 0; s < 4; ++s) {
+        const uint32_t n = edge_vec(d, tid, s).n;
+        pull(n, x[4 * s], x[4 * s + 1], x[4 * s + 2], x[4 * s + 3]);
+        pmask |= ((1u << n) - 1u) << (4 * s);
+    }
+    return pmask;
 }
 
 // Shared state of one chunk's selection.
@@ -230,7 +284,7 @@ struct SelectShared {
     alignas(16) uint32_t count[4][4];        // filter: candidates per wave and slot
     uint32_t bucket[16];                     // general path: entries per 256-element bucket (bucket = idx >> 8)
     uint32_t t0[4];                          // per-wave lower bounds of the threshold
-    uint32_t t1[4];                          // the same, second kind (edge chunks)
+    uint32_t t1[4];                          // edge chunks: non-empty lanes per wave, their non-empty slots << 16
     uint32_t wmax[4];                        // per-wave maxima of the keys
     uint32_t cut;                            // general path: index of the last kept entry among equals
 };
@@ -501,10 +555,28 @@ __device__ __forceinline__ Threshold find_threshold(SelectShared& sh, const floa
         uint32_t tmax = 0;
 #pragma unroll
         for (int el = 0; el < 16; ++el) tmax = key(el) > tmax ? key(el) : tmax;      // (absent ones are 0)
+        const uint32_t wave_max = wave_extreme_u32<true>(tmax);
         // Largest X (low 13 bits zero) with at least m = kappa_c / 4 lanes of this wave that hold a present element
         // >= X.  Those elements are distinct, so over four waves at least 4*m >= kappa_c elements are
-        // >= min X: the threshold cannot be below it.  A wave with fewer than m non-empty lanes (edge
-        // chunks) leaves X = 0, which makes every present element a candidate.
+        // >= min X: the threshold cannot be below it.
+        uint32_t m = (kappa_c + 3) >> 2;
+        bool by_slots = false;
+        if (edge) {
+            // The waves of an edge chunk hold unequal numbers of elements: each answers for a share of kappa_c that is
+            // in proportion to its non-empty lanes or, where the chunk has fewer of those than kappa_c (few columns), to
+            // its non-empty slots of lanes, whose largest elements are distinct too.  A chunk with fewer slots than
+            // kappa_c leaves X = 0: every present element is a candidate.
+            uint32_t slots = 0;
+#pragma unroll
+            for (int s = 0; s < 4; ++s) slots += (uint32_t)__popcll(__ballot((pmask & (0xFu << (4 * s))) != 0));
+            const uint32_t lanes = (uint32_t)__popcll(__ballot(pmask != 0));
+            if (lane == 0) sh.t1[wave] = lanes | (slots << 16);
+            __syncthreads();
+            const uint32_t all = __builtin_amdgcn_readfirstlane(sh.t1[0] + sh.t1[1] + sh.t1[2] + sh.t1[3]);
+            by_slots = (all & 0xFFFFu) < kappa_c;
+            const uint32_t of_all = by_slots ? all >> 16 : all & 0xFFFFu, of_wave = by_slots ? slots : lanes;
+            m = of_all < kappa_c ? 257u : (kappa_c * of_wave + of_all - 1) / of_all;
+        }
         auto reached_by = [&](uint32_t lanes) {               // two bits a step: the chain of steps is what it costs
             uint32_t X = 0;
 #pragma unroll
@@ -517,25 +589,35 @@ __device__ __forceinline__ Threshold find_threshold(SelectShared& sh, const floa
             }
             return X;
         };
-        const uint32_t X = reached_by((kappa_c + 3) >> 2);
-        const uint32_t wave_max = wave_extreme_u32<true>(tmax);
-        // Edge chunks may leave waves with too few elements for that; a wave that alone holds kappa_c lanes with an
-        // element >= Y bounds the threshold as well.
-        const uint32_t Y = edge ? reached_by(kappa_c) : 0u;
+        uint32_t X = 0;
+        if (!by_slots) {
+            X = reached_by(m);
+        } else {
+            uint32_t top[4];
+#pragma unroll
+            for (int s = 0; s < 4; ++s) {
+                top[s] = 0;
+#pragma unroll
+                for (int j = 0; j < 4; ++j) top[s] = key(4 * s + j) > top[s] ? key(4 * s + j) : top[s];
+            }
+#pragma unroll 1
+            for (int b = 30; b >= 13; --b) {
+                const uint32_t t = X + (1u << b);
+                uint32_t c = 0;
+#pragma unroll
+                for (int s = 0; s < 4; ++s) c += (uint32_t)__popcll(__ballot(top[s] >= t));
+                X = c >= m ? t : X;
+            }
+        }
         if (lane == 0) {
             sh.t0[wave] = X;
             sh.wmax[wave] = wave_max;
-            if (edge) sh.t1[wave] = Y;
         }
         __syncthreads();
         uint32_t T0 = sh.t0[0];
         T0 = sh.t0[1] < T0 ? sh.t0[1] : T0;
         T0 = sh.t0[2] < T0 ? sh.t0[2] : T0;
         T0 = sh.t0[3] < T0 ? sh.t0[3] : T0;
-        if (edge) {
-#pragma unroll
-            for (int w = 0; w < 4; ++w) T0 = sh.t1[w] > T0 ? sh.t1[w] : T0;
-        }
         T0 = __builtin_amdgcn_readfirstlane(T0);
         uint32_t amax = sh.wmax[0];
         amax = sh.wmax[1] > amax ? sh.wmax[1] : amax;
@@ -752,20 +834,18 @@ __device__ __forceinline__ void store_ef(float* __restrict__ e, const ChunkDesc&
         for (int s = 0; s < 4; ++s)
             stream_store4(vec_at(pe, d, tid, s), make_float4(x[4 * s], x[4 * s + 1], x[4 * s + 2], x[4 * s + 3]));
     } else {
-        // from an opaque copy of the lane number: the sixteen offsets of the loads are not kept for these stores
+        // from an opaque copy of the lane number: nothing of the loads' addresses is kept for these stores
         int t = tid;
         asm volatile("" : "+v"(t));
 #pragma unroll
-        for (int el = 0; el < 16; ++el) {
-            const uint32_t idx = (el >> 2) * 1024 + t * 4 + (el & 3);
-            if (pmask & (1u << el)) *elem_at(pe, elem_of(d, idx)) = x[el];
-        }
+        for (int s = 0; s < 4; ++s)
+            store_edge(vec_at(pe, d, t, s), (pmask >> (4 * s)) & 0xFu,
+                       make_float4(x[4 * s], x[4 * s + 1], x[4 * s + 2], x[4 * s + 3]));
     }
 }
 
 // Lines 1-4 of the update equations, one replica, one chunk per workgroup.
-// vec: the chunk is complete and allows 4-element vector accesses (the streaming path); else edge chunks and rows that
-// start at odd bf16 elements, element by element.  Only the loads and stores differ: one copy of the selection keeps
+// vec: the chunk is complete; else an edge chunk.  Only the loads and stores differ: one copy of the selection keeps
 // the code, which a cold launch fetches from memory, short.
 template <int MODE, int QUANT>
 __device__ __forceinline__ void compress_body(SelectShared& sh, bool vec, const ChunkDesc* __restrict__ chunks,
@@ -786,10 +866,10 @@ __device__ __forceinline__ void compress_body(SelectShared& sh, bool vec, const 
     uint32_t pmask = 0xFFFFu;
     float x[16];
     if (vec) {
-        load_fold_full<MODE>(pa, pb, pe, d, tid, beta, x);
+        with_chunk<true>(d, tid, [&](const auto& chunk) { load_fold<MODE>(pa, pb, pe, beta, x, chunk); });
     } else {
-        pmask = present_mask(d, tid);
-        load_fold_scalar<MODE>(pa, pb, pe, d, tid, beta, pmask, x);
+        with_chunk<false>(d, tid, [&](const auto& chunk) { load_fold<MODE>(pa, pb, pe, beta, x, chunk); });
+        pmask = pull_all(d, tid, x);
     }
     select_quantise_pack<QUANT>(sh, x, tid, lane, wave, d.n_c, pmask, kappa, force_radix, radix_counter,
                                 pairs_out + c * kappa, aux_out + c * kappa, aux_out + 2 * c);
@@ -797,8 +877,7 @@ __device__ __forceinline__ void compress_body(SelectShared& sh, bool vec, const 
     else store_ef<false>(pe, d, tid, pmask, x);
 }
 
-// The chunk table lists the n_gen element-wise chunks first: workgroups from n_gen on take the
-// streaming path (one launch; the branch is uniform per workgroup).
+// The chunk table lists the n_gen edge chunks first (one launch; the branch is uniform per workgroup).
 template <int MODE, int QUANT>
 __global__ __launch_bounds__(kThreads) void compress_kernel(const ChunkDesc* __restrict__ chunks, uint32_t n_gen,
                                                             const void* const* __restrict__ src_a,
@@ -1002,22 +1081,18 @@ __device__ __forceinline__ void compress_batch_body(SelectShared& sh, float* so,
     const uint32_t n_c = VEC ? (uint32_t)kChunk : d.n_c;
     const uint32_t kappa_c = kappa < n_c ? kappa : n_c;
     const float* po = to_tab[d.tensor] + d.offset;
-    const uint32_t pmask0 = VEC ? 0xFFFFu : present_mask(d, tid);
 
-    // The theta_outer chunk waits in LDS (each lane re-reads only what it wrote, so no barrier is
+    // The theta_outer chunk waits in LDS, as it was read (each lane re-reads only what it wrote, so no barrier is
     // needed); keeping it in registers across the replica loop would cost occupancy.
     float4* so4 = reinterpret_cast<float4*>(so);
-    if (VEC) {
+    with_chunk<VEC>(d, tid, [&](const auto& chunk) {
+        float4 v[4];
 #pragma unroll
-        for (int s = 0; s < 4; ++s) so4[s * kThreads + tid] = stream_load4(vec_at(po, d, tid, s));
-    } else {
+        for (int s = 0; s < 4; ++s) v[s] = chunk.load(po, s);
+        __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-        for (int el = 0; el < 16; ++el) {
-            const uint32_t idx = (el >> 2) * 1024 + tid * 4 + (el & 3);
-            const float v = *elem_at(po, (pmask0 & (1u << el)) ? elem_of(d, idx) : 0u);
-            so[idx] = (pmask0 & (1u << el)) ? v : 0.f;
-        }
-    }
+        for (int s = 0; s < 4; ++s) so4[s * kThreads + tid] = v[s];
+    });
     float4* sum4 = reinterpret_cast<float4*>(sum);
     if (STEP) {
 #pragma unroll
@@ -1027,46 +1102,21 @@ __device__ __forceinline__ void compress_batch_body(SelectShared& sh, float* so,
         // Per-lane index arithmetic is recomputed in every round: hoisting it out of the loop would
         // pin some 60 registers across the whole selection and halve the occupancy.
         int t = tid;
-        uint32_t pmask = pmask0;
-        asm volatile("" : "+v"(t), "+v"(pmask));
+        asm volatile("" : "+v"(t));
         const float* pl = tl_tab[(size_t)r * n_tensors + d.tensor] + d.offset;
         float* pe = ef_tab[(size_t)r * n_tensors + d.tensor];
         float x[16];
-        if (VEC) {
+        with_chunk<VEC>(d, t, [&](const auto& chunk) {
             float4 lv[4], ev[4];
 #pragma unroll
-            for (int s = 0; s < 4; ++s) lv[s] = stream_load4(vec_at(pl, d, t, s));
+            for (int s = 0; s < 4; ++s) lv[s] = chunk.load(pl, s);
 #pragma unroll
-            for (int s = 0; s < 4; ++s) ev[s] = stream_load4(vec_at(pe + d.offset, d, t, s));
+            for (int s = 0; s < 4; ++s) ev[s] = chunk.load(pe + d.offset, s);
+            __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-            for (int s = 0; s < 4; ++s) {
-                const float4 ov = so4[s * kThreads + t];
-                x[4 * s + 0] = fold(beta, ev[s].x, __fsub_rn(ov.x, lv[s].x));
-                x[4 * s + 1] = fold(beta, ev[s].y, __fsub_rn(ov.y, lv[s].y));
-                x[4 * s + 2] = fold(beta, ev[s].z, __fsub_rn(ov.z, lv[s].z));
-                x[4 * s + 3] = fold(beta, ev[s].w, __fsub_rn(ov.w, lv[s].w));
-            }
-        } else {
-#pragma unroll
-            for (int half = 0; half < 16; half += 8) {    // absent elements: as in load_fold_scalar
-                float lv[8], ev[8];
-#pragma unroll
-                for (int i = 0; i < 8; ++i) {
-                    const int el = half + i;
-                    const uint32_t idx = (el >> 2) * 1024 + t * 4 + (el & 3);
-                    const uint32_t at = (pmask & (1u << el)) ? elem_of(d, idx) : 0u;
-                    lv[i] = *elem_at(pl, at);
-                    ev[i] = *elem_at(pe + d.offset, at);
-                }
-#pragma unroll
-                for (int i = 0; i < 8; ++i) {
-                    const int el = half + i;
-                    const float v = fold(beta, ev[i], __fsub_rn(so[(el >> 2) * 1024 + t * 4 + (el & 3)], lv[i]));
-                    x[el] = (pmask & (1u << el)) ? v : 0.f;
-                }
-                __builtin_amdgcn_sched_barrier(0);
-            }
-        }
+            for (int s = 0; s < 4; ++s) fold4(beta, ev[s], so4[s * kThreads + t], lv[s], x + 4 * s);
+        });
+        const uint32_t pmask = VEC ? 0xFFFFu : pull_all(d, t, x);
         float* aux_r = aux_tab[r];
         const Threshold th = find_threshold<false, true>(sh, x, t, t & 63, wave, kappa_c, kappa, pmask, !VEC, force_radix,
                                                          radix_counter);
@@ -1081,33 +1131,22 @@ __device__ __forceinline__ void compress_batch_body(SelectShared& sh, float* so,
     float* th = to_tab[d.tensor] + d.offset;
     float* pd = dbar_tab ? dbar_tab[d.tensor] + d.offset : nullptr;
     const int n_reset = reset ? n_replicas : 0;
-    if (VEC) {
+    with_chunk<VEC>(d, tid, [&](const auto& chunk) {
 #pragma unroll
         for (int s = 0; s < 4; ++s) {
             float4 v = sum4[s * kThreads + tid], tn = so4[s * kThreads + tid];
+            if (!VEC) pull(edge_vec(d, tid, s).n, tn.x, tn.y, tn.z, tn.w);
             v.x = __fdiv_rn(v.x, m); v.y = __fdiv_rn(v.y, m); v.z = __fdiv_rn(v.z, m); v.w = __fdiv_rn(v.w, m);
-            if (pd) stream_store4(vec_at(pd, d, tid, s), v);
+            if (pd) chunk.store(pd, s, v);
             tn.x = __fsub_rn(tn.x, __fmul_rn(eta, v.x));
             tn.y = __fsub_rn(tn.y, __fmul_rn(eta, v.y));
             tn.z = __fsub_rn(tn.z, __fmul_rn(eta, v.z));
             tn.w = __fsub_rn(tn.w, __fmul_rn(eta, v.w));
-            stream_store4(vec_at(th, d, tid, s), tn);
+            chunk.store(th, s, tn);
             for (int r = 0; r < n_reset; ++r)
-                stream_store4(vec_at(tl_tab[(size_t)r * n_tensors + d.tensor] + d.offset, d, tid, s), tn);
+                chunk.store(tl_tab[(size_t)r * n_tensors + d.tensor] + d.offset, s, tn);
         }
-    } else {
-#pragma unroll
-        for (int el = 0; el < 16; ++el) {
-            if (!(pmask0 & (1u << el))) continue;
-            const uint32_t idx = (el >> 2) * 1024 + tid * 4 + (el & 3);
-            const uint32_t at = elem_of(d, idx);
-            const float v = __fdiv_rn(sum[idx], m);
-            if (pd) pd[at] = v;
-            const float tn = __fsub_rn(so[idx], __fmul_rn(eta, v));
-            th[at] = tn;
-            for (int r = 0; r < n_reset; ++r) tl_tab[(size_t)r * n_tensors + d.tensor][d.offset + at] = tn;
-        }
-    }
+    });
 }
 
 // Four workgroups per compute unit (three on large plans, see reserve_lds): the register allocation is held to 128.
@@ -1292,9 +1331,11 @@ __device__ __forceinline__ void aggregate_body(float* acc, const ChunkDesc* __re
     float* th = UPDATE ? theta_tab[d.tensor] + d.offset : nullptr;
     float* po = dbar_tab ? dbar_tab[d.tensor] + d.offset : nullptr;
     float4 tv[4];
-    if (UPDATE && VEC) {
+    if (UPDATE) {
+        with_chunk<VEC>(d, tid, [&](const auto& chunk) {
 #pragma unroll
-        for (int s = 0; s < 4; ++s) tv[s] = stream_load4(vec_at(th, d, tid, s));
+            for (int s = 0; s < 4; ++s) tv[s] = chunk.load(th, s);
+        });
     }
 #pragma unroll
     for (int s = 0; s < 4; ++s) acc4[s * kThreads + tid] = make_float4(0.f, 0.f, 0.f, 0.f);
@@ -1310,45 +1351,25 @@ __device__ __forceinline__ void aggregate_body(float* acc, const ChunkDesc* __re
         __syncthreads();
     }
     const float m = (float)n_replicas;
-    if (VEC) {
+    with_chunk<VEC>(d, tid, [&](const auto& chunk) {
 #pragma unroll
         for (int s = 0; s < 4; ++s) {
             float4 v = acc4[s * kThreads + tid];
             v.x = __fdiv_rn(v.x, m); v.y = __fdiv_rn(v.y, m); v.z = __fdiv_rn(v.z, m); v.w = __fdiv_rn(v.w, m);
-            if (po) stream_store4(vec_at(po, d, tid, s), v);
+            if (po) chunk.store(po, s, v);
             if (UPDATE) {
                 float4 t = tv[s];
+                if (!VEC) pull(edge_vec(d, tid, s).n, t.x, t.y, t.z, t.w);
                 t.x = __fsub_rn(t.x, __fmul_rn(eta, v.x));
                 t.y = __fsub_rn(t.y, __fmul_rn(eta, v.y));
                 t.z = __fsub_rn(t.z, __fmul_rn(eta, v.z));
                 t.w = __fsub_rn(t.w, __fmul_rn(eta, v.w));
-                stream_store4(vec_at(th, d, tid, s), t);
+                chunk.store(th, s, t);
                 for (int r = 0; r < n_reset; ++r)
-                    stream_store4(vec_at(reset_tab[(size_t)r * n_tensors + d.tensor] + d.offset, d, tid, s), t);
+                    chunk.store(reset_tab[(size_t)r * n_tensors + d.tensor] + d.offset, s, t);
             }
         }
-    } else {
-        float te[16];
-        if (UPDATE) {
-#pragma unroll
-            for (int i = 0; i < 16; ++i)
-                if (round_used(d, i)) te[i] = *elem_at(th, present_or_first(d, tid + kThreads * i));
-        }
-#pragma unroll
-        for (int i = 0; i < 16; ++i) {
-            if (!round_used(d, i)) break;
-            const uint32_t idx = tid + kThreads * i;
-            if (!present(d, idx)) continue;
-            const uint32_t at = elem_of(d, idx);
-            const float v = __fdiv_rn(acc[idx], m);
-            if (po) po[at] = v;
-            if (UPDATE) {
-                const float t = __fsub_rn(te[i], __fmul_rn(eta, v));
-                th[at] = t;
-                for (int r = 0; r < n_reset; ++r) reset_tab[(size_t)r * n_tensors + d.tensor][d.offset + at] = t;
-            }
-        }
-    }
+    });
 }
 
 template <int QUANT, int UPDATE>
@@ -1444,36 +1465,26 @@ __device__ __forceinline__ void outer_update_body(const ChunkDesc* __restrict__ 
     const ChunkDesc d = chunks[blockIdx.x];
     float* th = theta_tab[d.tensor] + d.offset;
     const float* db = dbar_tab[d.tensor] + d.offset;
-    if (VEC) {
+    with_chunk<VEC>(d, tid, [&](const auto& chunk) {
         float4 t[4], g[4];
 #pragma unroll
-        for (int s = 0; s < 4; ++s) t[s] = stream_load4(vec_at(th, d, tid, s));
+        for (int s = 0; s < 4; ++s) t[s] = chunk.load(th, s);
 #pragma unroll
-        for (int s = 0; s < 4; ++s) g[s] = stream_load4(vec_at(db, d, tid, s));
+        for (int s = 0; s < 4; ++s) g[s] = chunk.load(db, s);
 #pragma unroll
         for (int s = 0; s < 4; ++s) {
+            if (!VEC) {
+                const uint32_t n = edge_vec(d, tid, s).n;
+                pull(n, t[s].x, t[s].y, t[s].z, t[s].w);
+                pull(n, g[s].x, g[s].y, g[s].z, g[s].w);
+            }
             t[s].x = __fsub_rn(t[s].x, __fmul_rn(eta, g[s].x));
             t[s].y = __fsub_rn(t[s].y, __fmul_rn(eta, g[s].y));
             t[s].z = __fsub_rn(t[s].z, __fmul_rn(eta, g[s].z));
             t[s].w = __fsub_rn(t[s].w, __fmul_rn(eta, g[s].w));
-            stream_store4(vec_at(th, d, tid, s), t[s]);
+            chunk.store(th, s, t[s]);
         }
-    } else {
-        float t[16], g[16];
-#pragma unroll
-        for (int i = 0; i < 16; ++i) {
-            if (!round_used(d, i)) break;
-            const uint32_t at = present_or_first(d, tid + kThreads * i);
-            t[i] = *elem_at(th, at);
-            g[i] = *elem_at(db, at);
-        }
-#pragma unroll
-        for (int i = 0; i < 16; ++i) {
-            if (!round_used(d, i)) break;
-            const uint32_t idx = tid + kThreads * i;
-            if (present(d, idx)) th[elem_of(d, idx)] = __fsub_rn(t[i], __fmul_rn(eta, g[i]));
-        }
-    }
+    });
 }
 
 __global__ __launch_bounds__(kThreads) void outer_update_kernel(const ChunkDesc* __restrict__ chunks, uint32_t n_gen,
@@ -1499,9 +1510,8 @@ struct sparseloco_plan {
     int64_t n_params = 0;
     std::vector<int64_t> numel;
     int layout = SPLC_LAYOUT_FLAT;
-    // Chunk table, ordered [edge chunks | complete, vector-able for fp32 only | complete, vector-able for
-    // fp32 and bf16]; every entry carries its chunk number.  The slow element-wise chunks come first so
-    // that they overlap with the streaming ones instead of forming the tail of the launch.
+    // Chunk table, ordered [edge chunks | complete, odd row length | other complete ones]; every entry carries its chunk
+    // number.  The edge chunks, which take a little longer, come first so that they do not form the tail of the launch.
     // A tiled plan takes complete tiles four at a time where four lie side by side ("strips", one entry each:
     // origin, stride and chunk number of the first tile); only the other chunks are in the table above.  Its
     // outer update, which is element-wise, walks the tensors as flat chunks (a table of its own).
@@ -1509,8 +1519,7 @@ struct sparseloco_plan {
     ChunkDesc* d_chunks = nullptr;
     ChunkDesc* h_chunks = nullptr;       // pinned source of the asynchronous upload, kept until destroy
     int64_t n_entries = 0;               // entries of the chunk table (= n_chunks unless there are strips)
-    int64_t n_gen_f32 = 0;               // entries of the first class
-    int64_t n_gen_bf16 = 0;              // entries of the first two classes
+    int64_t n_gen = 0;                   // edge chunks among them
     int64_t n_strips = 0;
     ChunkDesc* d_strips = nullptr;       // inside d_chunks' allocation
     ChunkDesc* d_update = nullptr;       // = d_chunks for a flat plan
@@ -1597,11 +1606,6 @@ bool on_small_plan_disjoint(const sparseloco_plan* plan, Collect collect) {
     }
 }
 
-// Entries of the chunk table that take the element-wise path (they come first in the table).
-unsigned gen_entries(const sparseloco_plan* plan, bool bf16_source) {
-    return (unsigned)(bf16_source ? plan->n_gen_bf16 : plan->n_gen_f32);
-}
-
 // LDS that a launch on a large plan reserves so that only `groups_per_unit` of its workgroups, which use `used` bytes
 // each, fit on a compute unit (splc::few_streams).  LDS is handed out in 1280-byte units.
 unsigned reserve_lds(int groups_per_unit, size_t used) {
@@ -1623,7 +1627,7 @@ void launch_compress(const sparseloco_plan* plan, const void* const* a, const vo
     if (plan->n_entries > 0)
         hipLaunchKernelGGL((compress_kernel<MODE, QUANT>), dim3((unsigned)plan->n_entries), dim3(kThreads),
                            reserve_lds_compress(plan, plan->n_entries, MODE == MODE_PARAMS_F32, sizeof(SelectShared)), stream, plan->d_chunks,
-                           gen_entries(plan, MODE == MODE_DIRECT_BF16), a, b, ef, beta, (uint32_t)plan->kappa,
+                           (unsigned)plan->n_gen, a, b, ef, beta, (uint32_t)plan->kappa,
                            force_radix, plan->radix_counter, pairs_out, aux_out);
 }
 
@@ -1637,7 +1641,7 @@ void launch_aggregate(const sparseloco_plan* plan, int n_replicas, const uint16_
                            n_reset, (uint32_t)plan->n_tensors, reset);
     if (plan->n_entries > 0)
         hipLaunchKernelGGL((aggregate_kernel<QUANT, UPDATE>), dim3((unsigned)plan->n_entries), dim3(kThreads), 0, stream,
-                           plan->d_chunks, gen_entries(plan, false), n_replicas, (uint32_t)plan->kappa, pairs, aux,
+                           plan->d_chunks, (unsigned)plan->n_gen, n_replicas, (uint32_t)plan->kappa, pairs, aux,
                            dbar, theta, eta, n_reset, (uint32_t)plan->n_tensors,
                            plan->layout == SPLC_LAYOUT_FLAT && splc::chunks_in_runs(plan->n_entries, n_replicas, plan->kappa,
                                                                                     QUANT == SPLC_QUANT_2BIT, UPDATE), reset);
@@ -1789,9 +1793,8 @@ void append_chunks(std::vector<ChunkDesc>& table, uint32_t tensor, int64_t rows,
 
 int chunk_class(const ChunkDesc& d) { return d.vec == 0 ? 0 : (d.vec == 1 ? 1 : 2); }
 
-// Order in which workgroups take the entries: element-wise chunks first (they are the slow ones and should
-// overlap with the rest instead of forming the tail), then the chunks that allow vector accesses for fp32 only,
-// then those that allow them for bf16 too.  For a tiled plan, inside each class every XCD gets a run of
+// Order in which workgroups take the entries: edge chunks first (they take a little longer and should not form the
+// tail), then complete chunks in matrices of odd row length, then the other complete ones.  For a tiled plan, inside each class every XCD gets a run of
 // consecutive tiles: workgroups go to the eight XCDs round-robin by number, neighbouring tiles of a tile row
 // continue each other's row segments (and share the cache lines on their common edge when the row length is no
 // multiple of 32 floats), so neighbours should meet in one L2.  Only the order of processing changes: a chunk's
@@ -1912,13 +1915,10 @@ int plan_build(sparseloco_plan** out, int n_tensors, const int64_t* rows, const 
     const bool with_strips = !t.strips.empty();
     const std::vector<ChunkDesc>& main_table = with_strips ? t.rest : t.all;
     plan->n_entries = (int64_t)main_table.size();
-    for (const ChunkDesc& cd : main_table) {
-        plan->n_gen_f32 += cd.vec == 0;
-        plan->n_gen_bf16 += cd.vec != 3;
-    }
+    plan->n_gen = count_class0(main_table);
     plan->n_strips = (int64_t)t.strips.size();
     plan->n_update = tiled ? (int64_t)t.update.size() : plan->n_entries;
-    plan->n_update_gen = tiled ? count_class0(t.update) : plan->n_gen_f32;
+    plan->n_update_gen = tiled ? count_class0(t.update) : plan->n_gen;
     plan->n_all_gen = count_class0(t.all);
     // device layout: [main table | strips | update table (tiled) | every chunk (with strips)]
     const size_t n_main = main_table.size(), n_str = t.strips.size(), n_upd = tiled ? t.update.size() : 0,
