@@ -186,6 +186,18 @@ constexpr bool replicas_side_by_side(int64_t chunks, int replicas, bool step, bo
     return chunks <= kFewChunks && !(step && replicas == 1) && buffers_disjoint;
 }
 
+// Compression of a tiled plan: strips of four tiles (1024 lanes, two per compute unit) and a second launch for the tiles
+// outside them, or every tile by itself in one launch.  A strip asks for nine cache lines where its tiles ask for twelve,
+// which is what large plans are bound by; it takes longer from end to end, and below some rounds of workgroups that, and
+// the second launch, are what counts.  Time of the tiles over time of the strips, MI355X, matrices of 330 to 2050 columns:
+//   from parameters, kappa 32 / 128: 560 strips 0.72 / 0.65, 832 0.77 / 0.72, 952 0.94 / 0.89, 1400 1.05 / 1.01, 1664 1.07 / 1.01,
+//     2240 1.17 / 1.18, 4422 1.23 / 1.23, 7370 1.19 / 1.19, 57,000 1.13 / 1.13;
+//   from bf16, kappa 32 / 64 / 128: 560 0.60 / 0.61 / 0.58, 1400 1.01 / 0.97 / 0.92, 1664 0.98 / 0.98 / 0.89, 2240 1.12 / 1.07 / 0.98,
+//     2496 1.08 / 1.06 / 0.91, 2948 1.15 / 1.10 / 1.05, 4160 1.17 / 1.15 / 1.02, 7370 1.16 / 1.12 / 1.06.
+constexpr bool strips_pay(int64_t strips, int kappa, bool bf16) {
+    return strips >= (!bf16 ? 1400 : (kappa <= 64 ? 1750 : 2900));
+}
+
 // Large plans stream far more than the last-level cache holds, and there fewer workgroups per compute unit than would fit
 // keep the memory busier (fewer streams in flight at once) -- as long as memory is what bounds: with other sources, which
 // move less per chunk, and with messages or data that need the general path of the selection, the workgroups left out are

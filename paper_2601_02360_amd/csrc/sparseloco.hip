@@ -897,7 +897,7 @@ __global__ __launch_bounds__(kThreads) void compress_kernel(const ChunkDesc* __r
 // A workgroup that owns one 64 x 64 tile touches 256-byte row segments; when the matrix's row length is not a
 // multiple of 32 floats every such segment straddles three 128-byte cache lines instead of two, and the lines on
 // a tile's left and right edge are requested again by its neighbours.  So wherever four complete tiles lie side
-// by side, ONE workgroup of 1024 lanes takes all four: global memory is accessed row by row (a wave covers one
+// by side, and there are many of them (splc::strips_pay), ONE workgroup of 1024 lanes takes all four: global memory is accessed row by row (a wave covers one
 // 1024-byte row of the strip per instruction: nine lines instead of twelve, none shared with another
 // workgroup), the folded values pass through LDS, where each 256-lane group picks up "its" tile in the usual
 // chunk layout and runs the selection exactly as the one-tile kernel does, and the new error-feedback values go
@@ -1391,71 +1391,6 @@ __global__ __launch_bounds__(kThreads) void aggregate_kernel(const ChunkDesc* __
                                              eta, n_reset, n_tensors, reset_tab, entry);
 }
 
-// Line 5 for a strip of four complete 64 x 64 tiles (see compress_strip_kernel): the four 256-lane groups
-// accumulate the messages of their tiles side by side; the mean (and the parameters) leave and enter row by row.
-template <int QUANT, int UPDATE>
-__global__ __launch_bounds__(kStripThreads, 8) void aggregate_strip_kernel(const ChunkDesc* __restrict__ strips,
-                                                                        int n_replicas, uint32_t kappa,
-                                                                        const uint16_t* const* __restrict__ pairs_tab,
-                                                                        const float* const* __restrict__ aux_tab,
-                                                                        float* const* __restrict__ dbar_tab,
-                                                                        float* const* __restrict__ theta_tab, float eta,
-                                                                        int n_reset, uint32_t n_tensors,
-                                                                        float* const* __restrict__ reset_tab) {
-    __shared__ __align__(16) float acc[kStripTiles][kChunk];
-    const int tid = threadIdx.x;
-    const int lane = tid & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int group = __builtin_amdgcn_readfirstlane(tid >> 8);
-    const int gtid = tid & (kThreads - 1);
-    const int gwave = __builtin_amdgcn_readfirstlane((tid >> 6) & 3);
-    const ChunkDesc d = strips[blockIdx.x];
-    const uint32_t q = (uint32_t)lane >> 4, lc = ((uint32_t)lane & 15u) * 4u;
-    float* th = UPDATE ? strip_base(theta_tab[d.tensor] + d.offset, d, wave) : nullptr;
-    float* po = dbar_tab ? strip_base(dbar_tab[d.tensor] + d.offset, d, wave) : nullptr;
-    float4* acc4 = reinterpret_cast<float4*>(&acc[group][0]);
-#pragma unroll
-    for (int s = 0; s < 4; ++s) acc4[s * kThreads + gtid] = make_float4(0.f, 0.f, 0.f, 0.f);
-    const uint32_t kappa_c = kappa < (uint32_t)kChunk ? kappa : (uint32_t)kChunk;
-    const uint64_t c = (uint64_t)d.id + (uint64_t)group;
-    if (kappa_c <= 64) {
-        accumulate_chunk<QUANT, 1>(acc[group], c, kappa, kappa_c, n_replicas, pairs_tab, aux_tab, lane, gwave);
-    } else if (kappa_c <= 128) {
-        accumulate_chunk<QUANT, 2>(acc[group], c, kappa, kappa_c, n_replicas, pairs_tab, aux_tab, lane, gwave);
-    } else if (kappa_c <= 256) {
-        accumulate_chunk<QUANT, 4>(acc[group], c, kappa, kappa_c, n_replicas, pairs_tab, aux_tab, lane, gwave);
-    } else {
-        __syncthreads();
-        if (gwave == 0) accumulate_chunk_any<QUANT>(acc[group], c, kappa, kappa_c, n_replicas, pairs_tab, aux_tab, lane);
-        __syncthreads();
-    }
-    const float m = (float)n_replicas;
-    // The parameters are fetched only now: held across the accumulation they would cost the registers that let
-    // two of these workgroups share a compute unit, and the second workgroup hides this latency.
-    float4 tv[4];
-    if (UPDATE) {
-#pragma unroll
-        for (int i = 0; i < 4; ++i) tv[i] = stream_load4(strip_at<const float>(th, strip_offset(d, i, lane)));
-    }
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        float4 v = *reinterpret_cast<const float4*>(&acc[q][strip_row(i, wave) * 64u + lc]);
-        v.x = __fdiv_rn(v.x, m); v.y = __fdiv_rn(v.y, m); v.z = __fdiv_rn(v.z, m); v.w = __fdiv_rn(v.w, m);
-        if (po) stream_store4(strip_at(po, strip_offset(d, i, lane)), v);
-        if (UPDATE) {
-            float4 t = tv[i];
-            t.x = __fsub_rn(t.x, __fmul_rn(eta, v.x));
-            t.y = __fsub_rn(t.y, __fmul_rn(eta, v.y));
-            t.z = __fsub_rn(t.z, __fmul_rn(eta, v.z));
-            t.w = __fsub_rn(t.w, __fmul_rn(eta, v.w));
-            stream_store4(strip_at(th, strip_offset(d, i, lane)), t);
-            for (int r = 0; r < n_reset; ++r)
-                stream_store4(strip_at(strip_base(reset_tab[(size_t)r * n_tensors + d.tensor] + d.offset, d, wave),
-                                       strip_offset(d, i, lane)), t);
-        }
-    }
-}
-
 // Line 5, second half: theta = fl(theta - fl(eta * delta_bar)).
 template <bool VEC>
 __device__ __forceinline__ void outer_update_body(const ChunkDesc* __restrict__ chunks,
@@ -1512,8 +1447,8 @@ struct sparseloco_plan {
     int layout = SPLC_LAYOUT_FLAT;
     // Chunk table, ordered [edge chunks | complete, odd row length | other complete ones]; every entry carries its chunk
     // number.  The edge chunks, which take a little longer, come first so that they do not form the tail of the launch.
-    // A tiled plan takes complete tiles four at a time where four lie side by side ("strips", one entry each:
-    // origin, stride and chunk number of the first tile); only the other chunks are in the table above.  Its
+    // The compression of a large tiled plan takes complete tiles four at a time where four lie side by side ("strips", one
+    // entry each: origin, stride and chunk number of the first tile); only the other chunks are in the table above.  Its
     // outer update, which is element-wise, walks the tensors as flat chunks (a table of its own).
     // One device allocation holds [chunks | strips | flat chunks of the update | every chunk one by one].
     ChunkDesc* d_chunks = nullptr;
@@ -1524,7 +1459,7 @@ struct sparseloco_plan {
     ChunkDesc* d_strips = nullptr;       // inside d_chunks' allocation
     ChunkDesc* d_update = nullptr;       // = d_chunks for a flat plan
     int64_t n_update = 0, n_update_gen = 0;
-    ChunkDesc* d_all = nullptr;          // every chunk one by one, for the batched compress (= d_chunks without strips)
+    ChunkDesc* d_all = nullptr;          // every chunk one by one, for all other kernels (= d_chunks without strips)
     int64_t n_all_gen = 0;
 };
 
@@ -1620,31 +1555,28 @@ template <int MODE, int QUANT>
 void launch_compress(const sparseloco_plan* plan, const void* const* a, const void* const* b, float* const* ef,
                      float beta, uint16_t* pairs_out, float* aux_out, hipStream_t stream) {
     const int force_radix = plan->select == SPLC_SELECT_RADIX ? 1 : 0;
-    if (plan->n_strips > 0)
+    const bool strips = splc::strips_pay(plan->n_strips, plan->kappa, MODE == MODE_DIRECT_BF16);
+    const int64_t entries = strips ? plan->n_entries : plan->n_chunks;
+    if (strips)
         hipLaunchKernelGGL((compress_strip_kernel<MODE, QUANT>), dim3((unsigned)plan->n_strips), dim3(kStripThreads), 0,
                            stream, plan->d_strips, a, b, ef, beta, (uint32_t)plan->kappa, force_radix,
                            plan->radix_counter, pairs_out, aux_out);
-    if (plan->n_entries > 0)
-        hipLaunchKernelGGL((compress_kernel<MODE, QUANT>), dim3((unsigned)plan->n_entries), dim3(kThreads),
-                           reserve_lds_compress(plan, plan->n_entries, MODE == MODE_PARAMS_F32, sizeof(SelectShared)), stream, plan->d_chunks,
-                           (unsigned)plan->n_gen, a, b, ef, beta, (uint32_t)plan->kappa,
-                           force_radix, plan->radix_counter, pairs_out, aux_out);
+    if (entries > 0)
+        hipLaunchKernelGGL((compress_kernel<MODE, QUANT>), dim3((unsigned)entries), dim3(kThreads),
+                           reserve_lds_compress(plan, entries, MODE == MODE_PARAMS_F32, sizeof(SelectShared)), stream,
+                           strips ? plan->d_chunks : plan->d_all, (unsigned)(strips ? plan->n_gen : plan->n_all_gen), a, b,
+                           ef, beta, (uint32_t)plan->kappa, force_radix, plan->radix_counter, pairs_out, aux_out);
 }
 
 template <int QUANT, int UPDATE>
 void launch_aggregate(const sparseloco_plan* plan, int n_replicas, const uint16_t* const* pairs,
                       const float* const* aux, float* const* dbar, float* const* theta, float eta, int n_reset,
                       float* const* reset, hipStream_t stream) {
-    if (plan->n_strips > 0)
-        hipLaunchKernelGGL((aggregate_strip_kernel<QUANT, UPDATE>), dim3((unsigned)plan->n_strips), dim3(kStripThreads),
-                           0, stream, plan->d_strips, n_replicas, (uint32_t)plan->kappa, pairs, aux, dbar, theta, eta,
-                           n_reset, (uint32_t)plan->n_tensors, reset);
-    if (plan->n_entries > 0)
-        hipLaunchKernelGGL((aggregate_kernel<QUANT, UPDATE>), dim3((unsigned)plan->n_entries), dim3(kThreads), 0, stream,
-                           plan->d_chunks, (unsigned)plan->n_gen, n_replicas, (uint32_t)plan->kappa, pairs, aux,
-                           dbar, theta, eta, n_reset, (uint32_t)plan->n_tensors,
-                           plan->layout == SPLC_LAYOUT_FLAT && splc::chunks_in_runs(plan->n_entries, n_replicas, plan->kappa,
-                                                                                    QUANT == SPLC_QUANT_2BIT, UPDATE), reset);
+    hipLaunchKernelGGL((aggregate_kernel<QUANT, UPDATE>), dim3((unsigned)plan->n_chunks), dim3(kThreads), 0, stream,
+                       plan->d_all, (unsigned)plan->n_all_gen, n_replicas, (uint32_t)plan->kappa, pairs, aux, dbar, theta,
+                       eta, n_reset, (uint32_t)plan->n_tensors,
+                       plan->layout == SPLC_LAYOUT_FLAT && splc::chunks_in_runs(plan->n_chunks, n_replicas, plan->kappa,
+                                                                                QUANT == SPLC_QUANT_2BIT, UPDATE), reset);
 }
 
 template <int QUANT, bool STEP>
@@ -1663,8 +1595,7 @@ void launch_compress_batch(const sparseloco_plan* plan, int n_replicas, bool dis
                                        stream);
         return;
     }
-    // Strips are taken tile by tile here: a strip entry is followed, in the device table, by nothing this kernel
-    // could use, so the batched path walks the per-chunk view kept behind the update table.
+    // (tile by tile, also where compress takes strips)
     const size_t used = sizeof(SelectShared) + sizeof(float) * (kChunk + (STEP ? kChunk : 4));
     hipLaunchKernelGGL((compress_batch_kernel<QUANT, STEP>), dim3((unsigned)plan->n_chunks), dim3(kThreads),
                        reserve_lds_compress(plan, plan->n_chunks, true, used), stream,

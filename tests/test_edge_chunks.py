@@ -99,3 +99,13 @@ def test_what_lies_around_an_edge_chunk_is_left_alone():
     B.sparseloco_aggregate_update(plan, [pairs], views[0], 1.0, aux=[aux])
     for b in bufs:
         assert np.all(parity.to_np(b)[start - 1] == 77.0)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("rows,direct,kappa", [(64 * 349, None, 32), (64 * 350 + 3, None, 128), (64 * 437, "bf16", 64),
+                                               (64 * 438 + 3, "bf16", 64), (64 * 724, "bf16", 65), (64 * 725, "bf16", 65)])
+def test_strips_and_tiles_on_both_sides_of_the_line(rows, direct, kappa):
+    """Matrices of 1030 columns, four strips a tile row: the largest plan that is compressed tile by tile, and the
+    smallest (with rows to spare) that takes strips."""
+    case = case_of([(rows, 1030)], True, 1, kappa, direct)
+    parity.check(case, kappa, fused="no_mean", what="%d rows kappa=%d" % (rows, kappa))
