@@ -107,6 +107,35 @@ def lib():
     return _lib
 
 
+_native_calls = None
+
+
+def _native():
+    """The module that makes the launching calls (csrc/calls.cpp).  Its functions return the status, or None for arguments
+    that have to be looked at here."""
+    global _native_calls
+    if _native_calls is None:
+        lib()
+        try:
+            from . import _calls
+        except ImportError as e:
+            raise RuntimeError("_calls.so is not built; run `python -m paper_2601_02360_amd.build`") from e
+        _native_calls = _calls
+    return _native_calls
+
+
+def _done(rc: Optional[int], where: str) -> bool:
+    """Whether a native call has been made.  What it refused is refused below, with the reason."""
+    if rc == SPLC_EHIP:
+        raise SparseLoCoError(rc, where)
+    return rc == SPLC_OK
+
+
+def _given(stream) -> Optional[int]:
+    """The stream argument of a native call: None for the current one."""
+    return None if stream is None else (_stream(stream) or 0)
+
+
 # The current stream's handle without building a torch.cuda.Stream object (2 us of a call that otherwise takes 4).
 _raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
 
@@ -375,6 +404,16 @@ def sparseloco_compress(plan: Plan, ef, pairs_out: torch.Tensor, aux_out: torch.
                         theta_outer=None, theta_local=None, delta=None, replica: int = 0, stream=None) -> None:
     """Lines 1-4 of the update equations for one replica.  ef / theta_* / delta: Tensors bindings or lists of
     tensors (bound on the fly); replica: which set of multi-set bindings."""
+    bound = type(ef) is Tensors and (type(delta) is Tensors or
+                                     (delta is None and type(theta_outer) is Tensors and type(theta_local) is Tensors))
+    if bound:
+        n = plan._num_chunks
+        a, b = (delta._h.value, None) if delta is not None else (theta_outer._h.value, theta_local._h.value)
+        rc = _native().compress(plan._h.value, SPLC_DELTA_FROM_PARAMS if delta is None else SPLC_DELTA_DIRECT, a, b,
+                                ef._h.value, replica, beta, n * plan.kappa, n * (2 if plan.quant else plan.kappa),
+                                pairs_out, aux_out, _given(stream))
+        if _done(rc, "sparseloco_compress"):
+            return
     nch = plan.num_chunks
     _check_tensor(pairs_out, nch * plan.kappa, torch.int16, "pairs_out")
     _check_tensor(aux_out, nch * (2 if plan.quant else plan.kappa), torch.float32, "aux_out")
@@ -393,6 +432,10 @@ def sparseloco_compress(plan: Plan, ef, pairs_out: torch.Tensor, aux_out: torch.
 def sparseloco_aggregate(plan: Plan, messages, delta_bar_out, *, aux=None, stream=None) -> None:
     """Mean over replicas of the decoded messages into dense fp32 tensors.  messages: a Messages binding, or the
     list of pair buffers with aux= the list of level/value buffers."""
+    if type(messages) is Messages and type(delta_bar_out) is Tensors:
+        rc = _native().aggregate(plan._h.value, messages._h.value, delta_bar_out._h.value, _given(stream))
+        if _done(rc, "sparseloco_aggregate"):
+            return
     m = plan._messages(messages, aux, stream)
     rc = lib().sparseloco_aggregate(plan.handle, m.handle, _h(plan._tensors(delta_bar_out, stream=stream)),
                                     _stream(stream))
@@ -402,6 +445,10 @@ def sparseloco_aggregate(plan: Plan, messages, delta_bar_out, *, aux=None, strea
 
 def sparseloco_outer_update(plan: Plan, theta_outer, delta_bar, outer_lr: float, *, stream=None) -> None:
     """theta_outer -= outer_lr * delta_bar, in place."""
+    if type(theta_outer) is Tensors and type(delta_bar) is Tensors:
+        rc = _native().outer_update(plan._h.value, theta_outer._h.value, delta_bar._h.value, outer_lr, _given(stream))
+        if _done(rc, "sparseloco_outer_update"):
+            return
     rc = lib().sparseloco_outer_update(plan.handle, _h(plan._tensors(theta_outer, stream=stream)),
                                        _h(plan._tensors(delta_bar, stream=stream)), float(outer_lr), _stream(stream))
     if rc != SPLC_OK:
@@ -412,6 +459,11 @@ def sparseloco_aggregate_update(plan: Plan, messages, theta_outer, outer_lr: flo
                                 reset=None, stream=None) -> None:
     """Mean over replicas and outer update in one pass (theta_outer in place); delta_bar_out optional;
     reset: a Tensors binding (or per replica a list of theta_local tensors) that receives the new theta_outer."""
+    if type(messages) is Messages and type(theta_outer) is Tensors and delta_bar_out is None and reset is None:
+        rc = _native().aggregate_update(plan._h.value, messages._h.value, theta_outer._h.value, outer_lr, None, None,
+                                        _given(stream))
+        if _done(rc, "sparseloco_aggregate_update"):
+            return
     m = plan._messages(messages, aux, stream)
     rc = lib().sparseloco_aggregate_update(plan.handle, m.handle, _h(plan._tensors(theta_outer, stream=stream)),
                                            float(outer_lr), _h(plan._tensors(delta_bar_out, stream=stream)),
@@ -439,6 +491,13 @@ def sparseloco_outer_step_batch(plan: Plan, theta_outer, theta_local, ef, messag
     """The whole outer step of a single-node simulation in one launch: sparseloco_compress_batch followed by
     sparseloco_aggregate_update over the same replicas, bit for bit.  reset=True also writes the new theta_outer
     into the replicas' theta_local."""
+    if (type(theta_outer) is Tensors and type(theta_local) is Tensors and type(ef) is Tensors
+            and type(messages_out) is Messages and delta_bar_out is None):
+        rc = _native().outer_step_batch(plan._h.value, theta_local.n_sets if n_replicas is None else n_replicas,
+                                        theta_outer._h.value, theta_local._h.value, ef._h.value, beta, outer_lr,
+                                        messages_out._h.value, None, 1 if reset else 0, _given(stream))
+        if _done(rc, "sparseloco_outer_step_batch"):
+            return
     tl, e = plan._tensors(theta_local, stream=stream), plan._tensors(ef, stream=stream)
     m = plan._messages(messages_out, aux_out, stream)
     n = tl.n_sets if n_replicas is None else int(n_replicas)
@@ -490,6 +549,8 @@ def sparseloco_reproject_embedding(t_s: torch.Tensor, t_perp: torch.Tensor, u: t
                                    coeff_ws: torch.Tensor, *, matmul: int = SPLC_MATMUL_FP32, stream=None) -> None:
     """T_perp += T_S - T_S U U^T; T_S = T_S U U^T (in place).  t_s, t_perp: [vocab, d]; u: [d, k];
     coeff_ws: at least vocab * k floats."""
+    if _done(_native().reproject(t_s, t_perp, u, coeff_ws, matmul, _given(stream)), "sparseloco_reproject_embedding"):
+        return
     if t_s.dim() != 2 or u.dim() != 2:
         raise ValueError("t_s and u must be matrices")
     vocab, d = t_s.shape
@@ -546,6 +607,8 @@ def _check_stage_boundary(rows, d, k, wide, narrow, u, t_perp, token_ids, pos_em
 def sparseloco_subspace_project(x: torch.Tensor, u: torch.Tensor, out: torch.Tensor, *, t_perp=None, token_ids=None,
                                 pos_embed=None, matmul: int = SPLC_MATMUL_FP32, stream=None) -> None:
     """out[rows, k] = (x - t_perp[token_ids] - pos_embed[row % seq_len]) @ u;  x: [rows, d], u: [d, k]."""
+    if _done(_native().project(x, u, out, t_perp, token_ids, pos_embed, matmul, _given(stream)), "sparseloco_subspace_project"):
+        return
     if x.dim() != 2 or u.dim() != 2:
         raise ValueError("x and u must be matrices")
     rows, d = x.shape
@@ -563,6 +626,9 @@ def sparseloco_subspace_reconstruct(x_tilde: torch.Tensor, u: torch.Tensor, out:
                                     token_ids=None, pos_embed=None, matmul: int = SPLC_MATMUL_FP32,
                                     stream=None) -> None:
     """out[rows, d] = x_tilde @ u.T + t_perp[token_ids] + pos_embed[row % seq_len]."""
+    if _done(_native().reconstruct(x_tilde, u, out, t_perp, token_ids, pos_embed, matmul, _given(stream)),
+             "sparseloco_subspace_reconstruct"):
+        return
     if x_tilde.dim() != 2 or u.dim() != 2:
         raise ValueError("x_tilde and u must be matrices")
     rows, k = x_tilde.shape
