@@ -242,6 +242,32 @@ constexpr bool chunks_in_runs(int64_t entries, int replicas, int kappa, bool qua
     return (update && replicas <= 32) || entries * replicas * (2 * kappa + 8) < 240000000;
 }
 
+// Aggregation: workgroups that share a compute unit (0: all that fit, eight) and, with the outer update, whether theta is read
+// only after the messages have been added (late: the reads of some workgroups then meet the writes of others) or with the
+// first of them (its latency then hides behind theirs).  The dense mean alone is a stream of writes that waits for
+// messages, and wants all workgroups that fit; with theta read as well, memory is kept busiest by four or five.  Time,
+// MI355X, us, messages not in a cache, all that fit / five, early / five, late / four, late:
+//   update, quantised, flat: 72,400 chunks, kappa 32: 3 replicas 403 / 395 / 368 / 371, 8: 409 / 395 / 379 / 400, 12: 406 / 394 /
+//     435 / 469, 16: 414 / 401 / 393 / 435, 20: 422 / 406 / 436 / 481, 24: 420 / 417 / 423 / 472; kappa 64, 12: 426 / 421 / 419 / 471,
+//     16: 448 / 440 / 425 / 440, 20: 460 / 445 / 438 / 485, 24: 462 / 456 / 458 / 487; 32: 481 / 474 / 477 / 507; kappa 128, 12: 472 / 461 /
+//     449 / 475, 24: 529 / 514 / 499 / 549; 205,000 chunks, kappa 32, 3: 1165 / 1128 / 1069 / 1030, 8: 1179 / 1167 / 1083 / 1121;
+//     5000 and 8400 chunks: within 3 % of each other; kappa 256, 16: 513 / 520 / 541 / 570;
+//   unquantised, flat: 72,400, kappa 32, 4 replicas 409 / 404 / 377 / 381, 16: 481 / 468 / 442 / 466, 32: 528 / 526 / 507 / 507; kappa 64,
+//     8: 483 / 481 / 460 / 446, 16: 539 / 531 / 516 / 503; kappa 128, 5: 862 / 780 / 756 / 763 (128,000), 32: 755 / 756 / 755 / 736;
+//   tiles of 2050 columns, which share cache lines: 69,000, kappa 32, 4: 473 / 456 / 452 / 449, 16: 503 / 484 / 501 / 514, 32: 529 / 514 /
+//     550 / 556; 25,600, kappa 32, 4: 173 / 167 / 170 / 172, 64, 24: 201 / 197 / 214 / 218;
+//   mean only, all that fit / five / four: 225,000 chunks, kappa 64, 8 replicas 724 / 840 / 919; unquantised, kappa 32, 8: 739 / 849 / 941;
+//     64, 8: 300 / 265 / 291 (69,000); 128, 5: 442 / 499 / 570 (128,000), 16: 254 / 246 / 238 (39,000), 83 / 81 / 75 (10,240).
+struct AggregatePace { int groups_per_unit; bool theta_late; };
+constexpr AggregatePace aggregate_pace(int64_t chunks, int replicas, int kappa, bool quantised, bool flat, bool update) {
+    if (chunks < kFewStreams) return AggregatePace{0, false};
+    const bool heavy = !quantised && replicas >= 8 && kappa >= 64;       // messages of the order of the chunk itself
+    if (!update) return AggregatePace{heavy ? (replicas * kappa >= 1024 ? 4 : 5) : 0, false};
+    if (kappa > 128) return AggregatePace{0, false};
+    const bool late = flat && (!quantised || replicas <= 8 || (kappa >= 64 && replicas <= 24));
+    return AggregatePace{flat && heavy ? 4 : 5, late};
+}
+
 // Whether no two of these address ranges [first, second) share a byte; empty ranges share none.
 inline bool disjoint(std::vector<std::pair<uintptr_t, uintptr_t>> ranges) {
     std::sort(ranges.begin(), ranges.end());

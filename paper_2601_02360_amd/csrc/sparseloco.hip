@@ -1202,32 +1202,35 @@ constexpr int kAggBatch = 8;
 template <int QUANT, int KP>
 struct MessageBatch {
     uint32_t p[kAggBatch][KP];
-    float lo[kAggBatch], hi[kAggBatch], val[kAggBatch][KP];
+    float val[kAggBatch][KP];            // unquantised: the values
+    float level[kAggBatch];              // quantised: the two levels, in the even and the odd lanes
 
-    // Fetch replicas r0 .. r0+7 of chunk c (all loads issued together).
+    // Fetch replicas r0 .. r0+7 of chunk c.  Every load is unconditional -- a replica or an entry past the last one repeats
+    // that one, and is not applied -- so that the pointers of all eight are on their way together, and then all their
+    // messages: under a condition each replica's pointers are waited for before the next one's are requested.  The levels
+    // come by vector loads because a wait for LDS would wait for scalar ones too.
     __device__ __forceinline__ void load(uint64_t c, uint32_t kappa, uint32_t kappa_c, int r0, int n_replicas,
                                          const uint16_t* const* __restrict__ pairs_tab,
                                          const float* const* __restrict__ aux_tab, int lane) {
+        const SPLC_GLOBAL uint16_t* pr[kAggBatch];
+        const SPLC_GLOBAL float* ar[kAggBatch];
 #pragma unroll
         for (int i = 0; i < kAggBatch; ++i) {
-            lo[i] = hi[i] = 0.f;
+            const int r = r0 + i < n_replicas ? r0 + i : n_replicas - 1;
+            pr[i] = (const SPLC_GLOBAL uint16_t*)pairs_tab[r];
+            ar[i] = (const SPLC_GLOBAL float*)aux_tab[r];
+        }
+        __builtin_amdgcn_sched_barrier(0);
+        uint32_t at[KP];
 #pragma unroll
-            for (int k = 0; k < KP; ++k) { p[i][k] = 0xFFFFu; val[i][k] = 0.f; }
-            if (r0 + i < n_replicas) {
-                const uint16_t* pr = pairs_tab[r0 + i] + c * kappa;
-                const float* ar = aux_tab[r0 + i];
-                if (QUANT == SPLC_QUANT_2BIT) {
-                    lo[i] = ar[2 * c];
-                    hi[i] = ar[2 * c + 1];
-                }
+        for (int k = 0; k < KP; ++k) at[k] = lane + 64 * k < kappa_c ? lane + 64 * k : kappa_c - 1;
 #pragma unroll
-                for (int k = 0; k < KP; ++k) {
-                    const uint32_t t = lane + 64 * k;
-                    if (t < kappa_c) {
-                        p[i][k] = pr[t];
-                        if (QUANT == SPLC_QUANT_NONE) val[i][k] = ar[c * kappa + t];
-                    }
-                }
+        for (int i = 0; i < kAggBatch; ++i) {
+            if (QUANT == SPLC_QUANT_2BIT) level[i] = (ar[i] + 2 * c)[lane & 1];
+#pragma unroll
+            for (int k = 0; k < KP; ++k) {
+                p[i][k] = (pr[i] + c * kappa)[at[k]];
+                if (QUANT == SPLC_QUANT_NONE) val[i][k] = (ar[i] + c * kappa)[at[k]];
             }
         }
     }
@@ -1237,14 +1240,19 @@ struct MessageBatch {
 #pragma unroll
         for (int i = 0; i < kAggBatch; ++i) {
             if (r0 + i < n_replicas) {
+                float lo = 0.f, hi = 0.f;
+                if (QUANT == SPLC_QUANT_2BIT) {
+                    lo = __uint_as_float((uint32_t)__builtin_amdgcn_readlane((int)__float_as_uint(level[i]), 0));
+                    hi = __uint_as_float((uint32_t)__builtin_amdgcn_readlane((int)__float_as_uint(level[i]), 1));
+                }
 #pragma unroll
                 for (int k = 0; k < KP; ++k) {
                     const uint32_t t = lane + 64 * k;
                     const uint32_t idx = p[i][k] & 0xFFFu;
                     float q;
                     if (QUANT == SPLC_QUANT_2BIT) {
-                        const float level = (p[i][k] & 0x1000u) ? hi[i] : lo[i];
-                        q = (p[i][k] & 0x2000u) ? -level : level;
+                        const float l = (p[i][k] & 0x1000u) ? hi : lo;
+                        q = (p[i][k] & 0x2000u) ? -l : l;
                     } else {
                         q = val[i][k];
                     }
@@ -1307,19 +1315,25 @@ __device__ __forceinline__ void accumulate_chunk_any(float* acc, uint64_t c, uin
 
 // Line 5 of the update equations.  One workgroup per chunk; all lanes clear the 16 KB LDS
 // accumulator, the waves apply the messages batch by batch, all lanes divide once by M and write.
+// KP: entries of a message per lane (kappa up to 64 KP; 0: any kappa).  A kernel for each takes 24 to 53 registers up to
+// kappa 64 where one for all took 85, so eight workgroups share a compute unit instead of five; with that and the loads of a
+// batch in flight together (MessageBatch), messages that are not in a cache cost less: mean of 225,000 chunks, kappa 64,
+// 8 replicas 820 -> 723 us (floor 640), 69,000 chunks, kappa 32, 32 replicas 343 -> 306, tiles of 2050 columns 414 -> 362.
+// How many of them share a unit, and when theta is read: splc::aggregate_pace.
 //   UPDATE = 0: delta_bar = acc / M is written densely (sparseloco_aggregate).
 //   UPDATE = 1: theta = fl(theta - fl(eta * delta_bar)) is applied in the same pass, and the new theta
 //               is also copied into n_reset further parameter sets (the replicas' theta_local, which
 //               restart from the synchronised parameters: section 2.1, inner step); delta_bar is
 //               written only if a table for it is given (sparseloco_aggregate_update).
-template <int QUANT, int UPDATE, bool VEC>
+template <int QUANT, int UPDATE, bool VEC, int KP>
 __device__ __forceinline__ void aggregate_body(float* acc, const ChunkDesc* __restrict__ chunks, int n_replicas,
                                                              uint32_t kappa,
                                                              const uint16_t* const* __restrict__ pairs_tab,
                                                              const float* const* __restrict__ aux_tab,
                                                              float* const* __restrict__ dbar_tab,
                                                              float* const* __restrict__ theta_tab, float eta, int n_reset,
-                                               uint32_t n_tensors, float* const* __restrict__ reset_tab, uint32_t entry) {
+                                               uint32_t n_tensors, float* const* __restrict__ reset_tab, bool theta_late,
+                                               uint32_t entry) {
     const int tid = threadIdx.x;
     const int lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -1331,31 +1345,37 @@ __device__ __forceinline__ void aggregate_body(float* acc, const ChunkDesc* __re
     float* th = UPDATE ? theta_tab[d.tensor] + d.offset : nullptr;
     float* po = dbar_tab ? dbar_tab[d.tensor] + d.offset : nullptr;
     float4 tv[4];
-    if (UPDATE) {
+    auto load_theta = [&] {
         with_chunk<VEC>(d, tid, [&](const auto& chunk) {
 #pragma unroll
             for (int s = 0; s < 4; ++s) tv[s] = chunk.load(th, s);
         });
-    }
+    };
+    if (UPDATE && !theta_late) load_theta();
 #pragma unroll
     for (int s = 0; s < 4; ++s) acc4[s * kThreads + tid] = make_float4(0.f, 0.f, 0.f, 0.f);
-    if (kappa_c <= 64) {
-        accumulate_chunk<QUANT, 1>(acc, c, kappa, kappa_c, n_replicas, pairs_tab, aux_tab, lane, wave);
-    } else if (kappa_c <= 128) {
-        accumulate_chunk<QUANT, 2>(acc, c, kappa, kappa_c, n_replicas, pairs_tab, aux_tab, lane, wave);
-    } else if (kappa_c <= 256) {
-        accumulate_chunk<QUANT, 4>(acc, c, kappa, kappa_c, n_replicas, pairs_tab, aux_tab, lane, wave);
+    if constexpr (KP > 0) {
+        accumulate_chunk<QUANT, KP>(acc, c, kappa, kappa_c, n_replicas, pairs_tab, aux_tab, lane, wave);
     } else {
         __syncthreads();
         if (wave == 0) accumulate_chunk_any<QUANT>(acc, c, kappa, kappa_c, n_replicas, pairs_tab, aux_tab, lane);
         __syncthreads();
     }
+    if (UPDATE && theta_late) load_theta();
     const float m = (float)n_replicas;
+    // a power of two divides exactly like its inverse multiplies: one rounding of the same value
+    const bool halves = (n_replicas & (n_replicas - 1)) == 0;
+    const float inverse = __fdiv_rn(1.f, m);
     with_chunk<VEC>(d, tid, [&](const auto& chunk) {
 #pragma unroll
         for (int s = 0; s < 4; ++s) {
             float4 v = acc4[s * kThreads + tid];
-            v.x = __fdiv_rn(v.x, m); v.y = __fdiv_rn(v.y, m); v.z = __fdiv_rn(v.z, m); v.w = __fdiv_rn(v.w, m);
+            if (halves) {
+                v.x = __fmul_rn(v.x, inverse); v.y = __fmul_rn(v.y, inverse);
+                v.z = __fmul_rn(v.z, inverse); v.w = __fmul_rn(v.w, inverse);
+            } else {
+                v.x = __fdiv_rn(v.x, m); v.y = __fdiv_rn(v.y, m); v.z = __fdiv_rn(v.z, m); v.w = __fdiv_rn(v.w, m);
+            }
             if (po) chunk.store(po, s, v);
             if (UPDATE) {
                 float4 t = tv[s];
@@ -1372,23 +1392,23 @@ __device__ __forceinline__ void aggregate_body(float* acc, const ChunkDesc* __re
     });
 }
 
-template <int QUANT, int UPDATE>
+template <int QUANT, int UPDATE, int KP>
 __global__ __launch_bounds__(kThreads) void aggregate_kernel(const ChunkDesc* __restrict__ chunks, uint32_t n_gen,
                                                              int n_replicas, uint32_t kappa,
                                                              const uint16_t* const* __restrict__ pairs_tab,
                                                              const float* const* __restrict__ aux_tab,
                                                              float* const* __restrict__ dbar_tab,
                                                              float* const* __restrict__ theta_tab, float eta,
-                                                             int n_reset, uint32_t n_tensors, bool in_runs,
+                                                             int n_reset, uint32_t n_tensors, bool in_runs, bool theta_late,
                                                              float* const* __restrict__ reset_tab) {
     __shared__ __align__(16) float acc[kChunk];
     const uint32_t entry = in_runs ? splc::entry_in_runs(blockIdx.x, gridDim.x) : blockIdx.x;
     if (entry >= n_gen)
-        aggregate_body<QUANT, UPDATE, true>(acc, chunks, n_replicas, kappa, pairs_tab, aux_tab, dbar_tab, theta_tab, eta,
-                                            n_reset, n_tensors, reset_tab, entry);
+        aggregate_body<QUANT, UPDATE, true, KP>(acc, chunks, n_replicas, kappa, pairs_tab, aux_tab, dbar_tab, theta_tab, eta,
+                                                n_reset, n_tensors, reset_tab, theta_late, entry);
     else
-        aggregate_body<QUANT, UPDATE, false>(acc, chunks, n_replicas, kappa, pairs_tab, aux_tab, dbar_tab, theta_tab,
-                                             eta, n_reset, n_tensors, reset_tab, entry);
+        aggregate_body<QUANT, UPDATE, false, KP>(acc, chunks, n_replicas, kappa, pairs_tab, aux_tab, dbar_tab, theta_tab,
+                                                 eta, n_reset, n_tensors, reset_tab, theta_late, entry);
 }
 
 // Line 5, second half: theta = fl(theta - fl(eta * delta_bar)).
@@ -1572,11 +1592,21 @@ template <int QUANT, int UPDATE>
 void launch_aggregate(const sparseloco_plan* plan, int n_replicas, const uint16_t* const* pairs,
                       const float* const* aux, float* const* dbar, float* const* theta, float eta, int n_reset,
                       float* const* reset, hipStream_t stream) {
-    hipLaunchKernelGGL((aggregate_kernel<QUANT, UPDATE>), dim3((unsigned)plan->n_chunks), dim3(kThreads), 0, stream,
-                       plan->d_all, (unsigned)plan->n_all_gen, n_replicas, (uint32_t)plan->kappa, pairs, aux, dbar, theta,
-                       eta, n_reset, (uint32_t)plan->n_tensors,
-                       plan->layout == SPLC_LAYOUT_FLAT && splc::chunks_in_runs(plan->n_chunks, n_replicas, plan->kappa,
-                                                                                QUANT == SPLC_QUANT_2BIT, UPDATE), reset);
+    const bool flat = plan->layout == SPLC_LAYOUT_FLAT;
+    const bool in_runs = flat && splc::chunks_in_runs(plan->n_chunks, n_replicas, plan->kappa, QUANT == SPLC_QUANT_2BIT, UPDATE);
+    const splc::AggregatePace pace =
+        splc::aggregate_pace(plan->n_chunks, n_replicas, plan->kappa, QUANT == SPLC_QUANT_2BIT, flat, UPDATE);
+    const unsigned reserved = pace.groups_per_unit ? reserve_lds(pace.groups_per_unit, sizeof(float) * kChunk) : 0u;
+    auto launch = [&](auto per_lane) {
+        hipLaunchKernelGGL((aggregate_kernel<QUANT, UPDATE, decltype(per_lane)::value>), dim3((unsigned)plan->n_chunks),
+                           dim3(kThreads), reserved, stream, plan->d_all, (unsigned)plan->n_all_gen, n_replicas,
+                           (uint32_t)plan->kappa, pairs, aux, dbar, theta, eta, n_reset, (uint32_t)plan->n_tensors, in_runs,
+                           pace.theta_late, reset);
+    };
+    if (plan->kappa <= 64) launch(std::integral_constant<int, 1>{});
+    else if (plan->kappa <= 128) launch(std::integral_constant<int, 2>{});
+    else if (plan->kappa <= 256) launch(std::integral_constant<int, 4>{});
+    else launch(std::integral_constant<int, 0>{});
 }
 
 template <int QUANT, bool STEP>

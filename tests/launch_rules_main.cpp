@@ -68,8 +68,24 @@ static int check_few_streams() {
     return 0;
 }
 
+// The aggregation's pace: small plans take all workgroups that fit, the mean alone reads no theta.
+static int check_aggregate_pace() {
+    for (int64_t chunks : {1, 8191, 8192, 24000, 220000})
+        for (int replicas : {1, 8, 9, 24, 25, 1024})
+            for (int kappa : {1, 63, 64, 128, 129, 4096})
+                for (int i = 0; i < 8; ++i) {
+                    const splc::AggregatePace p = splc::aggregate_pace(chunks, replicas, kappa, i & 1, i & 2, i & 4);
+                    const bool plain = chunks < splc::kFewStreams && (p.groups_per_unit || p.theta_late);
+                    if ((p.groups_per_unit && (p.groups_per_unit < 4 || p.groups_per_unit > 5)) || plain || (p.theta_late && !(i & 4))) {
+                        printf("aggregate_pace: %ld chunks, %d replicas, kappa %d, %d\n", (long)chunks, replicas, kappa, i);
+                        return 1;
+                    }
+                }
+    return 0;
+}
+
 int main() {
-    if (check_unguarded_tiles() || check_side_by_side() || check_few_streams()) return 1;
+    if (check_unguarded_tiles() || check_side_by_side() || check_few_streams() || check_aggregate_pace()) return 1;
     printf("ok\n");
     return 0;
 }

@@ -1,0 +1,58 @@
+"""The aggregation's kernels: entries per lane (kappa up to 64, 128, 256 and more), batches of eight replicas with a last one
+that is not full, a division by M that is a power of two or not (subnormal sums among them), and on plans of 8192 chunks and
+more the orders in which theta and the messages are read.  The sum over replicas in order, formed with torch, is bit-exact."""
+import pytest
+import torch
+
+from paper_2601_02360_amd import binding as B
+from test_gpu_aggregate_runs import CHUNK, messages
+
+pytestmark = pytest.mark.gpu
+
+
+def check(numels, kappa, replicas, quant, tiny=False):
+    total = sum(numels)
+    mean = torch.zeros(total, device="cuda")
+    pairs, aux = [], []
+    for p, levels, position, value in messages(numels, kappa, replicas, seed=kappa + replicas):
+        if tiny:                                 # every second position gets subnormal values
+            small = position % 2 == 0
+            value = torch.where(small, value * 2.0 ** -140, value)
+        if not quant:
+            sent = p != -1
+            levels = torch.zeros(p.numel(), device="cuda")
+            levels[sent] = value
+            p = torch.where(sent, p & 0xFFF, p)
+        pairs.append(p)
+        aux.append(levels)
+        mean[position] += value                  # a replica sends a position once
+    mean = (mean.cpu() / replicas).cuda()
+    theta = torch.randn(total, generator=torch.Generator(device="cuda").manual_seed(1), device="cuda")
+    want = theta - 0.5 * mean
+    plan = B.Plan(numels, kappa, quant=quant)
+    received = plan.bind_messages(pairs, aux)
+    got = torch.full_like(mean, float("nan"))
+    B.sparseloco_aggregate(plan, received, plan.bind(list(got.split(numels))))
+    assert torch.equal(got, mean)
+    got.fill_(float("nan"))
+    local = torch.full((2, total), float("nan"), device="cuda")
+    B.sparseloco_aggregate_update(plan, received, plan.bind(list(theta.split(numels))), 0.5,
+                                  delta_bar_out=plan.bind(list(got.split(numels))),
+                                  reset=plan.bind([list(t.split(numels)) for t in local]))
+    assert torch.equal(got, mean) and torch.equal(theta, want)
+    assert torch.equal(local[0], want) and torch.equal(local[1], want)
+
+
+@pytest.mark.parametrize("quant", [True, False])
+@pytest.mark.parametrize("kappa", [1, 63, 64, 65, 128, 129, 256, 257])
+@pytest.mark.parametrize("replicas", [1, 7, 8, 9, 32, 33])
+def test_entries_and_batches(kappa, replicas, quant):
+    check([CHUNK * 3 + 70, 5, CHUNK], kappa, replicas, quant, tiny=not quant)
+
+
+# theta late: 3; 9 of kappa 64; 8 of kappa 64 unquantised (fewer groups a unit) / with the first messages: 9 of kappa 16; 2 of kappa 200
+@pytest.mark.parametrize("kappa,replicas,quant", [(16, 3, True), (16, 9, True), (64, 9, True), (200, 2, True), (64, 8, False),
+                                                  (128, 8, False), (32, 5, False)])
+@pytest.mark.parametrize("chunks", [8191, 8192])
+def test_large_plans(chunks, kappa, replicas, quant):
+    check([CHUNK * (chunks - 2) + 100, 3], kappa, replicas, quant)
