@@ -124,7 +124,16 @@ struct StoreCoeff {
 };
 
 // Pass 2: v = Pi_S(T_S)[row][col .. col+3].
+// LINES: rows are whole 128-byte lines.  Otherwise the pieces of neighbouring tiles share lines, and are accessed without the
+// non-temporal hint: a line stays in the L2 until the neighbour asks for it (re-projection, split, 46544 x 1930, k 87: 537 -> 477 us,
+// 32997 x 1930, 176: 504 -> 473, 34548 x 2047, 168: 532 -> 508, 20481 x 715, 79: 136 -> 125; fp32 0.97 ... 1.2, median 1.02).
+template <bool LINES>
 struct UpdateEmbedding {
+    static __device__ __forceinline__ vfloat4 get(const float* p) { return LINES ? ldg4_once(p) : ldg4(p); }
+    static __device__ __forceinline__ void put(float* p, vfloat4 v) {
+        if (LINES) stg4_once(p, v);
+        else stg4(p, v);
+    }
     // This epilogue moves four arrays; a kernel that carries it is as much bound by memory as by the matrix
     // pipe, and gains when the workgroups that share a compute unit are not all in their epilogue at once.
     static constexpr bool kStaggeredStart = true;
@@ -135,16 +144,16 @@ struct UpdateEmbedding {
     int compute_units;       // of the device, for the staggered start
     __device__ __forceinline__ void load(int row, int col, vfloat4 (&r)[2]) const {
         const int64_t at = (int64_t)row * ld + col;
-        r[0] = ldg4_once(t_s + at);
-        r[1] = ldg4_once(t_perp + at);
+        r[0] = get(t_s + at);
+        r[1] = get(t_perp + at);
     }
     __device__ __forceinline__ void store(int row, int col, vfloat4 v, const vfloat4 (&r)[2]) const {
         const int64_t at = (int64_t)row * ld + col;
         vfloat4 q;
 #pragma unroll
         for (int i = 0; i < 4; ++i) q[i] = __fadd_rn(r[1][i], __fsub_rn(r[0][i], v[i]));
-        stg4_once(t_perp + at, q);
-        stg4_once(t_s + at, v);
+        put(t_perp + at, q);
+        put(t_s + at, v);
     }
     __device__ __forceinline__ void operator()(int row, int col, vfloat4 v, int n_cols) const {
         const int64_t at = (int64_t)row * ld + col;
@@ -1145,9 +1154,12 @@ int reproject_impl(float* t_s, float* t_perp, const float* u, float* coeff_ws, i
     // pass 2: Pi = coeff U^T           (M x d) = (M x k)(k x d), U given as d x k = the N x K form
     if (second_product(none, M, d, k, true, split) == Second::expand)
         launch_expand<EPI_UPDATE>(ExpandArgs{coeff_ws, u, t_s, t_perp, none, M, d, k, 0, 0}, matmul, units, st);
+    else if (d % 32 == 0)
+        launch_gemm<true>(coeff_ws, (int64_t)k, u, (int64_t)k, M, d, k, NoPrologue{},
+                          UpdateEmbedding<true>{t_s, t_perp, (int64_t)d, units}, matmul, st);
     else
         launch_gemm<true>(coeff_ws, (int64_t)k, u, (int64_t)k, M, d, k, NoPrologue{},
-                          UpdateEmbedding{t_s, t_perp, (int64_t)d, units}, matmul, st);
+                          UpdateEmbedding<false>{t_s, t_perp, (int64_t)d, units}, matmul, st);
     return hipGetLastError() == hipSuccess ? SPLC_OK : SPLC_EHIP;
 }
 
