@@ -137,7 +137,7 @@ def product_kernels(ops, rows, d, k, tables, math):
         tile = B.subspace_kernel_choice(op, rows, d, k, tables, mm)
         if tile == (64, 0):
             return "contract_kernel" if math == "bf16x3" else "contract_fp32_kernel"
-        if tile == (128, 32):
+        if tile in ((128, 32), (128, 33)):
             return "expand_kernel"
         if tile[0] == 16:
             return "project_narrow_kernel" if d % 32 == 0 and k <= (16 if tables == 2 else 32) else "project_rows_kernel"

@@ -52,9 +52,9 @@ constexpr bool shared_evenly(int64_t rows, int width, int units) {
 }
 
 // Second product of the subspace calls (out [rows, width] = coefficients [rows, k] U^T): expand_kernel, which keeps rows of
-// coefficients in registers and walks along the columns, instead of the GEMM kernel's tile per workgroup.  It needs whole
-// 128-byte lines in a row (with rows of 1100 or 1300 floats it takes 1.2 to 1.6 times as long), k above 32 (below, memory
-// bounds both) and what fits its registers and LDS: k <= 256, split products 224.  tiles: of 128 rows x 32 columns.
+// coefficients in registers and walks along the columns, instead of the GEMM kernel's tile per workgroup.  It needs k above
+// 32 (below, memory bounds both) and what fits its registers and LDS: k <= 256, split products 224; for the update also whole
+// 128-byte lines in a row.  tiles: of 128 rows x 32 columns.
 // half: the last step of 32 k is at most half used.  Time of the GEMM kernel over time of expand_kernel, MI355X, inputs that the
 // call before did not leave in a cache (profiles/subspace_rules_measured.txt):
 //   update (re-projection, both passes), split, width above 320: 0.94 ... 1.6 (median 1.12), but k to 48 from 19,000 tiles on
@@ -108,6 +108,38 @@ constexpr bool expand_applies(int64_t rows, int width, int k, int tables, bool u
     if (width <= 256 || tiles < 3072) return false;
     if (tables == 0) return width > 320 && tiles >= (k > 224 ? 8192 : 4096);
     return !half || (width > 640 && tiles >= (tables == 2 ? 3072 : 4096) && shared_evenly(rows, width, units()));
+}
+
+// The same for the reconstruction where rows are no whole lines (the GEMM kernel's non-temporal accesses there lose the lines that
+// its tiles share).  Time of the GEMM kernel over time of expand_kernel, as above, 3300 shapes of 257 to 2050 columns:
+//   split, one table 1.04 ... 4.2 (median 1.6); both, below 4096 tiles 0.94 ... 3.9 (median 1.6), from there k from 65 on 0.95 ...
+//     1.29, to 64 and, from 12,000 tiles on, to 128 0.87 ... 1.25; none, k from 65 on: an even number of 64-column blocks, below 512
+//     tiles 0.97 ... 1.69, from 4096 on 0.95 ... 1.31, between 0.81 ... 1.35; an odd number, below 256 0.99 ... 1.27, from 2048 on
+//     0.99 ... 1.48, between 0.82 ... 1.5;
+//   fp32 with tables, width no multiple of 4: k 81 ... 128 0.91 ... 1.54 (both, odd, from 4096 tiles on 0.94 ... 1.09); k 129 ... 192,
+//     from 1024 tiles on 0.93 ... 1.35, below 0.85 ... 1.39; k from 193 on, even 0.98 ... 1.79, odd, from 4096 tiles on 0.99 ... 1.16,
+//     below 0.80 ... 1.19; a multiple of 4, one table, from 3072 tiles on 0.95 ... 1.3, else 0.83 ... 1.4; none 0.69 ... 1.15.
+constexpr bool expand_takes_k_across_lines(int k, int tables, bool split) {
+    if (split) return k > (tables > 0 ? 32 : 64) && k <= 224;
+    return tables > 0 && k > 80 && k <= 256;
+}
+constexpr bool expand_takes_steps_across_lines(int steps, int tables, bool split) {
+    for (int k = 32 * steps - 31; k <= 32 * steps; ++k)
+        if (expand_takes_k_across_lines(k, tables, split)) return true;
+    return false;
+}
+constexpr bool expand_applies_across_lines(int64_t rows, int width, int k, int tables, bool split) {
+    if (width % 32 == 0 || width < 33 || width >= 1 << 20 || !expand_takes_k_across_lines(k, tables, split)) return false;
+    const int64_t tiles = (rows + 127) / 128 * ((width + 31) / 32);
+    if (rows < 1 || tiles >= int64_t(1) << 31) return false;
+    const bool odd = (width + 63) / 64 % 2 != 0;
+    if (split) {
+        if (tables == 0) return odd ? tiles < 256 || tiles >= 2048 : tiles < 512 || tiles >= 4096;
+        return tables == 1 || tiles < 4096 || (k > 64 && (tiles < 12000 || k > 128));
+    }
+    if (width % 4 == 0) return tables == 1 && tiles >= 3072;
+    if (k <= 128) return !(tables == 2 && odd && tiles >= 4096);
+    return k > 192 ? !odd || tiles >= 4096 : tiles >= 1024;
 }
 
 // First product of the subspace calls: contract_kernel (split products) and contract_fp32_kernel, one workgroup per compute

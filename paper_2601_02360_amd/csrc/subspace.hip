@@ -1124,7 +1124,9 @@ First first_product(const HighRank& h, int rows, int d, int k, bool split, Units
 enum class Second { expand, gemm };
 Second second_product(const HighRank& h, int rows, int d, int k, bool update, bool split) {
     const int tables = (h.t_perp ? 1 : 0) + (h.pos ? 1 : 0);
-    return splc::expand_applies(rows, d, k, tables, update, split, compute_units) && tables_in_32_bits(h, rows) ? Second::expand : Second::gemm;
+    const bool expand = splc::expand_applies(rows, d, k, tables, update, split, compute_units) ||
+                        (!update && splc::expand_applies_across_lines(rows, d, k, tables, split));
+    return expand && tables_in_32_bits(h, rows) ? Second::expand : Second::gemm;
 }
 
 bool valid_matmul(int matmul) { return matmul == SPLC_MATMUL_FP32 || matmul == SPLC_MATMUL_BF16X3; }
@@ -1252,7 +1254,7 @@ extern "C" int sparseloco_subspace_kernel_choice(int op, int64_t rows, int d, in
         case SPLC_OP_RECONSTRUCT:
         case SPLC_OP_REPROJECT_PASS2: {
             const bool update = op == SPLC_OP_REPROJECT_PASS2;
-            if (second_product(h, M, d, k, update, split) == Second::expand) return 128 * 256 + 32;
+            if (second_product(h, M, d, k, update, split) == Second::expand) return 128 * 256 + (d % 32 == 0 ? 32 : 33);
             t = choose_gemm_tile(true, M, d, k, n_tab, !update, matmul);
             break;
         }

@@ -53,8 +53,12 @@ __device__ __forceinline__ void buffer_put(Buffer b, uint32_t at, valigned4 v) {
 }
 constexpr int kOnce = 2;                         // AUX: non-temporal
 
-// out[M, N] = A U^T (+ epilogue) for row-major A [M, K] and U [N, K], 32 < K <= 32 KS, N a multiple of 32: the second
+// out[M, N] = A U^T (+ epilogue) for row-major A [M, K] and U [N, K], 32 < K <= 32 KS, N > 32: the second
 // product of the subspace calls, whose reduction is short and whose output is long.
+// LINES: N is a multiple of 32.  Otherwise the last tile begins at column N - 32, so that all of its columns exist -- those it
+// shares with the tile before come out the same, from the same operands in the same order, whoever stores them last (code for
+// a part of a tile made the compiler spill 70 registers per lane) -- and output and tables go without the non-temporal
+// hint: neighbouring tiles share cache lines, which with the hint are fetched twice and written in parts.
 //
 // gemm_kernel above starts a workgroup per output tile, so that with K = 192 an epilogue that moves up to four arrays
 // follows every twelve K tiles, and the operands of a row block are fetched, split and stored to LDS again for every
@@ -70,7 +74,8 @@ constexpr int kOnce = 2;                         // AUX: non-temporal
 // neither pipe alone (51 % busy with both tables at K = 192, 39 % in the update, at 1.8 to 2.0 GHz: splitting, staging and stores sit
 // between the products).  Before / now, us: 16384 x 1536 from 192, both tables, split 72.6 / 57.1, fp32 90.9 / 81.7; 16384 x
 // 2048 from 256, both tables, fp32 149 / 140; re-projection 41472 x 1792, k 192, split 497 / 442; update at 32000 x 2048 from
-// 256, fp32: 320 / 321.
+// 256, fp32: 320 / 321.  Rows of no whole lines, against the GEMM kernel, one table, split: 3938 x 1291 from 92 36.1 / 25.4,
+// 16384 x 1002 from 120 and its like 1.3 times as fast, few rows twice (splc::expand_applies_across_lines).
 struct ExpandArgs {
     const float* a;
     const float* u;
@@ -82,11 +87,13 @@ struct ExpandArgs {
 };
 enum { EPI_PERP = 1, EPI_POS = 2, EPI_UPDATE = 4 };
 
-template <int MATH, int KS, int EPI>
+template <int MATH, int KS, int EPI, bool LINES>
 __global__ __launch_bounds__(512, 2) void expand_kernel(ExpandArgs g) {
     constexpr int CH = 4 * KS;                   // groups of eight k
     constexpr int NU = (KS + 1) / 2;             // groups of four k of a U tile that a lane stages
     constexpr bool SPLIT = MATH == MATH_BF16X3;
+    static_assert(LINES || EPI != EPI_UPDATE, "columns of two tiles would be updated twice");
+    constexpr int ONCE = LINES ? kOnce : 0;
     // split: three planes of groups of eight k; fp32: groups of four k, as they are
     __shared__ vuint4 pieces[2][SPLIT ? 3 : 2][CH][33];
     __shared__ valigned4 sums[2][4][2][32][8];   // partial sums of a tile: [row][four columns, their place turned by the row]
@@ -95,7 +102,8 @@ __global__ __launch_bounds__(512, 2) void expand_kernel(ExpandArgs g) {
     const int rg = wave & 3, kg = wave >> 2;
     const int M = g.m, N = g.n, K = g.k;
 
-    const int groups = gridDim.x, col_tiles = N / 32;
+    const int groups = gridDim.x, col_tiles = LINES ? N / 32 : (N + 31) / 32;
+    auto column = [&](int t) { return LINES || 32 * t + 32 <= N ? 32 * t : N - 32; };       // first one of a tile
     // neighbouring runs share rows and table lines: each XCD takes a contiguous eighth of them
     const int place = groups % 8 == 0 ? (int)(blockIdx.x & 7) * (groups / 8) + (int)(blockIdx.x >> 3) : (int)blockIdx.x;
     const splc::TileRun run = splc::tile_run(place, groups, g.row_blocks, col_tiles, g.parts);
@@ -230,15 +238,15 @@ __global__ __launch_bounds__(512, 2) void expand_kernel(ExpandArgs g) {
             if (EPI & EPI_PERP) v[i] = __fadd_rn(v[i], tab[0][e][i]);
             if (EPI & EPI_POS) v[i] = __fadd_rn(v[i], tab[1][e][i]);
         }
-        if (EPI == EPI_UPDATE) buffer_put<kOnce>(perp, at, w);
-        buffer_put<kOnce>(out, at, v);
+        if (EPI == EPI_UPDATE) buffer_put<ONCE>(perp, at, w);
+        buffer_put<ONCE>(out, at, v);
     };
     // what put(e) will combine with the product of a tile
     auto request = [&](int e, int n0) {
         if (EPI == EPI_UPDATE) {
             const uint32_t at = o_off + 32u * (uint32_t)(e * N) + 4u * (uint32_t)n0;
-            tab[0][e] = buffer_get<kOnce>(out, at);
-            tab[1][e] = buffer_get<kOnce>(perp, at);
+            tab[0][e] = buffer_get<ONCE>(out, at);
+            tab[1][e] = buffer_get<ONCE>(perp, at);
         } else {
             if (EPI & EPI_PERP) tab[0][e] = *(const SPLC_GLOBAL vfloat4*)((const char*)(g.h.t_perp + n0) + t_off[e]);
             if (EPI & EPI_POS) tab[1][e] = *(const SPLC_GLOBAL vfloat4*)((const char*)(g.h.pos + n0) + p_off[e]);
@@ -261,11 +269,11 @@ __global__ __launch_bounds__(512, 2) void expand_kernel(ExpandArgs g) {
 
     int buf = 0;
     auto after = [&](int t) { return t + 1 < col_tiles ? t + 1 : 0; };   // past the last tile of all: staged, not used
-    fetch(32 * ct);
+    fetch(column(ct));
     take_rows(rb);
 #pragma unroll
-    for (int i = 0; i < NU; ++i) stash(i, 0, 32 * ct, 0), stash(i, 1, 32 * ct, 0);
-    fetch(32 * after(ct));
+    for (int i = 0; i < NU; ++i) stash(i, 0, column(ct), 0), stash(i, 1, column(ct), 0);
+    fetch(column(after(ct)));
     constexpr int NF = SPLIT ? 3 : 2;
     vuint4 f[2][NF];
     auto operands = [&](int b, int s, int set) {
@@ -279,7 +287,7 @@ __global__ __launch_bounds__(512, 2) void expand_kernel(ExpandArgs g) {
     // step, whose operands are in registers by then; behind it the first operands of the next tile are requested.
     auto tile = [&](v16f& acc, const v16f& before) {
         constexpr int PER = SPLIT ? 6 : 8, NM = PER * KS;      // products per k step, per tile
-        const int next = 32 * after(ct), second = 32 * after(after(ct));
+        const int next = column(after(ct)), second = column(after(after(ct)));
         auto side = [&](int m) {
             // m = 0 .. NM - 1: after product m.
             constexpr int CHUNKS = 3 + 2 * NU;
@@ -356,26 +364,29 @@ __global__ __launch_bounds__(512, 2) void expand_kernel(ExpandArgs g) {
 #pragma unroll
         for (int e = 0; e < 2; ++e) {
             put(e, 32 * (ct - 2), ct - 2 >= from);
-            request(e, 32 * (ct - 1));
+            request(e, column(ct - 1));
         }
         exchange((ct - 1) & 1, acc1);
         __syncthreads();
         receive((ct - 1) & 1);
 #pragma unroll
-        for (int e = 0; e < 2; ++e) put(e, 32 * (ct - 1), true);
+        for (int e = 0; e < 2; ++e) put(e, column(ct - 1), true);
         if (left == 0) return;
         take_rows(++rb);
         ct = 0;
     }
 }
 
-template <int MATH, int EPI>
+template <int MATH, int EPI, bool LINES>
 void launch_expand(const ExpandArgs& g, int groups, hipStream_t st) {
     const dim3 grid((unsigned)groups), block(512);
     auto run = [&](auto steps) {
         constexpr int KS = decltype(steps)::value;
-        if constexpr (splc::expand_takes_steps(KS, (EPI & EPI_PERP ? 1 : 0) + (EPI & EPI_POS ? 1 : 0), EPI == EPI_UPDATE, MATH == MATH_BF16X3))
-            hipLaunchKernelGGL((expand_kernel<MATH, KS, EPI>), grid, block, 0, st, g);
+        constexpr int tables = (EPI & EPI_PERP ? 1 : 0) + (EPI & EPI_POS ? 1 : 0);
+        constexpr bool split = MATH == MATH_BF16X3;
+        if constexpr (LINES ? splc::expand_takes_steps(KS, tables, EPI == EPI_UPDATE, split)
+                            : splc::expand_takes_steps_across_lines(KS, tables, split))
+            hipLaunchKernelGGL((expand_kernel<MATH, KS, EPI, LINES>), grid, block, 0, st, g);
     };
     switch ((g.k + 31) / 32) {
         case 2: run(std::integral_constant<int, 2>{}); break;
@@ -390,10 +401,19 @@ void launch_expand(const ExpandArgs& g, int groups, hipStream_t st) {
 // units: compute units, each of which holds one workgroup
 template <int EPI>
 void launch_expand(ExpandArgs g, int matmul, int units, hipStream_t st) {
+    const int col_tiles = (g.n + 31) / 32;
     g.row_blocks = (g.m + 127) / 128;
-    g.parts = splc::parts_of_row_block(g.row_blocks, g.n / 32, units);
-    const int64_t tiles = (int64_t)g.row_blocks * (g.n / 32);
+    g.parts = splc::parts_of_row_block(g.row_blocks, col_tiles, units);
+    const int64_t tiles = (int64_t)g.row_blocks * col_tiles;
     const int groups = g.parts ? g.parts * g.row_blocks : (int)(tiles < units ? tiles : units);
-    if (matmul == SPLC_MATMUL_BF16X3) launch_expand<MATH_BF16X3, EPI>(g, groups, st);
-    else launch_expand<MATH_F32, EPI>(g, groups, st);
+    const bool split = matmul == SPLC_MATMUL_BF16X3;
+    if constexpr (EPI != EPI_UPDATE) {           // (splc::expand_applies asks for whole lines there)
+        if (g.n % 32 != 0) {
+            if (split) launch_expand<MATH_BF16X3, EPI, false>(g, groups, st);
+            else launch_expand<MATH_F32, EPI, false>(g, groups, st);
+            return;
+        }
+    }
+    if (split) launch_expand<MATH_BF16X3, EPI, true>(g, groups, st);
+    else launch_expand<MATH_F32, EPI, true>(g, groups, st);
 }
