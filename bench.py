@@ -134,10 +134,10 @@ def product_kernels(ops, rows, d, k, tables, math):
     mm = B.SPLC_MATMUL_BF16X3 if math == "bf16x3" else B.SPLC_MATMUL_FP32
 
     def name(op):
-        tile = B.subspace_kernel_choice(B.SPLC_OP_RECONSTRUCT_ANY_WIDTH if op == B.SPLC_OP_RECONSTRUCT else op, rows, d, k, tables, mm)
+        tile = B.subspace_kernel_choice(op, rows, d, k, tables, mm)
         if tile == (64, 0):
             return "contract_kernel" if math == "bf16x3" else "contract_fp32_kernel"
-        if tile in ((128, 32), (128, 33)):
+        if tile == (128, 32):
             return "expand_kernel"
         if tile[0] == 16:
             return "project_narrow_kernel" if d % 32 == 0 and k <= (16 if tables == 2 else 32) else "project_rows_kernel"

@@ -347,16 +347,11 @@ int sparseloco_subspace_reconstruct(const float* x_tilde, const float* t_perp, c
  * Returns tile_rows * 256 + tile_cols of a workgroup's output tile -- 128 or 64 by 128 or 64 for the GEMM
  * kernel, 16 by 16 or 16 by 32 for the narrow projection kernel, 16 by 32 or 16 by 64 for the projection of few
  * rows, 64 by 0 for the first product with all columns of 64 rows per workgroup, 128 by 32 for the second product
- * with 128 rows of coefficients in registers and 128 by 33 for the same where the output's rows are no whole 128-byte
- * lines -- or a negative status.  The answer is that of the launch on the current device (without one: for 256 compute
- * units), except that the last three leave tables of 2^30 floats and more, whose size is not asked here, to the GEMM
- * kernel.  SPLC_OP_RECONSTRUCT answers for a d that is no multiple of 32 with the tile that the GEMM kernel has there;
- * SPLC_OP_RECONSTRUCT_ANY_WIDTH with what the call launches, at every d.
+ * with 128 rows of coefficients in registers -- or a negative status.  The answer is that of the launch on the current
+ * device (without one: for 256 compute units), except that the last two leave tables of 2^30 floats and more, whose
+ * size is not asked here, to the GEMM kernel.
  */
-enum {
-    SPLC_OP_PROJECT = 0, SPLC_OP_RECONSTRUCT = 1, SPLC_OP_REPROJECT_PASS1 = 2, SPLC_OP_REPROJECT_PASS2 = 3,
-    SPLC_OP_RECONSTRUCT_ANY_WIDTH = 4
-};
+enum { SPLC_OP_PROJECT = 0, SPLC_OP_RECONSTRUCT = 1, SPLC_OP_REPROJECT_PASS1 = 2, SPLC_OP_REPROJECT_PASS2 = 3 };
 int sparseloco_subspace_kernel_choice(int op, int64_t rows, int d, int k, int tables, int matmul);
 
 /*

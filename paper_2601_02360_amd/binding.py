@@ -43,7 +43,6 @@ EXPORTS = [
 ]
 
 SPLC_OP_PROJECT, SPLC_OP_RECONSTRUCT, SPLC_OP_REPROJECT_PASS1, SPLC_OP_REPROJECT_PASS2 = 0, 1, 2, 3
-SPLC_OP_RECONSTRUCT_ANY_WIDTH = 4
 SPLC_MAX_REPLICAS = 1024
 SPLC_STREAM_READ, SPLC_STREAM_WRITE, SPLC_STREAM_COPY, SPLC_STREAM_R2W1, SPLC_STREAM_R3W1 = 0, 1, 2, 3, 4
 
@@ -583,7 +582,7 @@ def sparseloco_reproject_embedding_noalloc(t_s: torch.Tensor, t_perp: torch.Tens
 
 def subspace_kernel_choice(op: int, rows: int, d: int, k: int, tables: int = 0, matmul: int = SPLC_MATMUL_FP32):
     """(tile_rows, tile_cols) of the kernel variant a matrix call takes for this shape (host logic only); (64, 0): all
-    columns of 64 rows per workgroup; (128, 33): rows in registers, an output whose rows are no whole lines."""
+    columns of 64 rows per workgroup; (128, 32): 128 rows of coefficients in registers."""
     rc = lib().sparseloco_subspace_kernel_choice(int(op), int(rows), int(d), int(k), int(tables), int(matmul))
     if rc < 0:
         raise SparseLoCoError(rc, "sparseloco_subspace_kernel_choice")

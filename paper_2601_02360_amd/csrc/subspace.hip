@@ -1237,8 +1237,7 @@ extern "C" int sparseloco_subspace_kernel_choice(int op, int64_t rows, int d, in
     const int M = (int)rows;
     const bool split = matmul == SPLC_MATMUL_BF16X3;
     const float* const some = reinterpret_cast<const float*>(&op);      // only tested for being non-null
-    const bool any_width = op == SPLC_OP_RECONSTRUCT_ANY_WIDTH;
-    const int n_tab = op == SPLC_OP_PROJECT || op == SPLC_OP_RECONSTRUCT || any_width ? tables : 0;
+    const int n_tab = op == SPLC_OP_PROJECT || op == SPLC_OP_RECONSTRUCT ? tables : 0;
     const HighRank h{n_tab >= 1 ? some : nullptr, nullptr, 0, n_tab >= 2 ? some : nullptr, 1, (int64_t)d};
     GemmTile t;
     switch (op) {
@@ -1253,11 +1252,9 @@ extern "C" int sparseloco_subspace_kernel_choice(int op, int64_t rows, int d, in
             t = choose_gemm_tile(false, M, k, d, n_tab, false, matmul);
             break;
         case SPLC_OP_RECONSTRUCT:
-        case SPLC_OP_RECONSTRUCT_ANY_WIDTH:
         case SPLC_OP_REPROJECT_PASS2: {
             const bool update = op == SPLC_OP_REPROJECT_PASS2;
-            if ((d % 32 == 0 || any_width) && second_product(h, M, d, k, update, split) == Second::expand)
-                return 128 * 256 + (d % 32 == 0 ? 32 : 33);
+            if (second_product(h, M, d, k, update, split) == Second::expand) return 128 * 256 + 32;
             t = choose_gemm_tile(true, M, d, k, n_tab, !update, matmul);
             break;
         }

@@ -92,8 +92,9 @@ def test_kernel_choice_follows_the_documented_rule():
     assert c(B.SPLC_OP_REPROJECT_PASS2, 32000, 2040, 192) == (64, 64)
     assert c(B.SPLC_OP_RECONSTRUCT, 16384, 2040, 256, 2) == (64, 128)
     assert c(B.SPLC_OP_REPROJECT_PASS2, 32000, 2040, 256, 0, B.SPLC_MATMUL_BF16X3) == (128, 128)
-    with pytest.raises(B.SparseLoCoError):
-        c(9, 100, 64, 8)
+    for op in (4, 9):
+        with pytest.raises(B.SparseLoCoError):
+            c(op, 100, 64, 8)
     with pytest.raises(B.SparseLoCoError):
         c(B.SPLC_OP_PROJECT, 100, 64, 65)
 
@@ -102,14 +103,14 @@ def test_kernel_choice_follows_the_documented_rule():
     # fp32 reconstruction from 129 to 192 columns: 128 columns from eight 64 x 128 tiles per compute unit on
     ("RECONSTRUCT", 1024, 1536, 160, 2, "FP32", (64, 64)), ("RECONSTRUCT", 4096, 1536, 192, 2, "FP32", (64, 64)),
     ("RECONSTRUCT", 8191, 2040, 160, 0, "FP32", (64, 128)), ("RECONSTRUCT", 8128, 2040, 160, 0, "FP32", (64, 64)),
-    ("RECONSTRUCT", 16384, 1530, 192, 2, "FP32", (64, 128)), ("RECONSTRUCT", 16384, 1530, 128, 2, "FP32", (64, 64)),
+    ("RECONSTRUCT", 16384, 1532, 192, 2, "FP32", (64, 128)), ("RECONSTRUCT", 16384, 1532, 128, 2, "FP32", (64, 64)),
     ("REPROJECT_PASS2", 50304, 2040, 192, 0, "FP32", (64, 64)),
     # split operands, N x K, an odd number of column blocks
-    ("RECONSTRUCT", 1024, 2050, 170, 2, "BF16X3", (128, 64)), ("RECONSTRUCT", 32768, 2050, 170, 2, "BF16X3", (128, 64)),
-    ("RECONSTRUCT", 16384, 1470, 170, 0, "BF16X3", (128, 128)), ("RECONSTRUCT", 16256, 1470, 170, 0, "BF16X3", (128, 64)),
+    ("RECONSTRUCT", 1024, 2050, 230, 2, "BF16X3", (128, 64)), ("RECONSTRUCT", 32768, 2050, 120, 2, "BF16X3", (128, 64)),
+    ("RECONSTRUCT", 16384, 1470, 230, 0, "BF16X3", (128, 128)), ("RECONSTRUCT", 16256, 1470, 230, 0, "BF16X3", (128, 64)),
     ("RECONSTRUCT", 16384, 1472, 64, 0, "BF16X3", (128, 128)), ("RECONSTRUCT", 16256, 1472, 64, 0, "BF16X3", (128, 64)),
     ("RECONSTRUCT", 16384, 1472, 48, 0, "BF16X3", (128, 64)), ("RECONSTRUCT", 16384, 2050, 48, 0, "BF16X3", (128, 128)),
-    ("RECONSTRUCT", 16384, 1530, 48, 2, "BF16X3", (128, 128)), ("RECONSTRUCT", 50000, 950, 170, 0, "BF16X3", (128, 64)),
+    ("RECONSTRUCT", 16384, 1530, 48, 2, "BF16X3", (128, 128)), ("RECONSTRUCT", 50000, 950, 230, 0, "BF16X3", (128, 64)),
     ("REPROJECT_PASS2", 32001, 2050, 170, 0, "BF16X3", (128, 128)), ("REPROJECT_PASS2", 32000, 1984, 230, 0, "BF16X3", (128, 64)),
     ("REPROJECT_PASS2", 6000, 2050, 170, 0, "BF16X3", (128, 64)), ("REPROJECT_PASS2", 9600, 1470, 170, 0, "BF16X3", (128, 128)),
     ("REPROJECT_PASS2", 9472, 1470, 170, 0, "BF16X3", (128, 64)),
@@ -140,6 +141,10 @@ ALL_COLUMNS, ROWS_IN_REGISTERS = (64, 0), (128, 32)
     ("RECONSTRUCT", 1, 2048, 224, 2, "BF16X3", ROWS_IN_REGISTERS), ("RECONSTRUCT", 1, 2048, 225, 2, "BF16X3", (128, 128)),
     ("RECONSTRUCT", 15361, 320, 131, 1, "BF16X3", ROWS_IN_REGISTERS), ("RECONSTRUCT", 9800, 320, 131, 1, "BF16X3", (128, 64)),
     ("REPROJECT_PASS2", 32000, 2048, 256, 0, "FP32", ROWS_IN_REGISTERS), ("REPROJECT_PASS2", 6016, 2048, 256, 0, "FP32", (128, 128)),
+    # ... also where the output's rows are no whole cache lines
+    ("RECONSTRUCT", 16384, 1530, 192, 2, "FP32", ROWS_IN_REGISTERS), ("RECONSTRUCT", 16384, 1532, 192, 2, "FP32", (64, 128)),
+    ("RECONSTRUCT", 16384, 2050, 170, 2, "BF16X3", ROWS_IN_REGISTERS), ("RECONSTRUCT", 32768, 2050, 128, 2, "BF16X3", (128, 64)),
+    ("RECONSTRUCT", 32768, 2050, 129, 2, "BF16X3", ROWS_IN_REGISTERS), ("RECONSTRUCT", 1024, 2050, 225, 1, "BF16X3", (128, 64)),
     ("REPROJECT_PASS2", 32000, 1984, 170, 0, "BF16X3", ROWS_IN_REGISTERS), ("REPROJECT_PASS2", 32001, 2050, 170, 0, "BF16X3", (128, 128))])
 def test_kernel_choice_names_the_kernel_that_runs(op, rows, d, k, tables, matmul, kernel):
     """The two kernels that take a call before the GEMM kernel does, and their neighbours that it keeps."""

@@ -223,7 +223,10 @@ STAGE_SHAPES = [
     (33000, 1000, 320, 250, 77, False, True),
     # the same with one table, and both on 128 x 64; reconstructions on 64 x 128 with one table
     (61500, 700, 130, 100, 90, True, False), (61500, 700, 130, 33, 90, True, False), (61500, 700, 130, 33, 90, False, True),
-    (61500, 700, 130, 33, 90, True, True), (300, 70, 250, 200, 40, True, False), (300, 70, 250, 200, 40, False, True)]
+    (61500, 700, 130, 33, 90, True, True), (300, 70, 250, 200, 40, True, False), (300, 70, 250, 200, 40, False, True),
+    # the same on the GEMM kernel in both modes: a width that is a multiple of four, a k that split products leave to it
+    (300, 70, 252, 230, 40, True, False), (300, 70, 252, 230, 40, False, True), (333, 37, 385, 226, 100, True, True),
+    (700, 70, 508, 250, 60, True, False), (500, 50, 705, 300, 30, False, True)]
 
 
 @pytest.mark.parametrize("rows,seq,d,k,vocab,use_perp,use_pos", STAGE_SHAPES)
@@ -276,19 +279,26 @@ def test_long_projections_on_64_row_tiles(rows, seq, d, k, vocab, use_perp, use_
     check_stage_boundary(rows, seq, d, k, vocab, use_perp, use_pos, seed=rows + d + k, mode=matmul_mode)
 
 
-# Reconstructions and re-projections on both sides of the lines of the tile choice that depend on the number of tiles
-LINE_SHAPES = [("x", 1024, 1530, 160, True), ("x", 8191, 2040, 160, False), ("x", 8191, 2040, 160, True), ("x", 1000, 2050, 170, True),
-               ("x", 12300, 2050, 40, False), ("r", 7000, 2050, 30, False), ("r", 6000, 1980, 50, False)]
+# Reconstructions and re-projections on both sides of the lines of the GEMM kernel's tile choice that depend on the number of
+# tiles: mode, operation, rows, d, k, tables, tile
+FP32, X3 = B.SPLC_MATMUL_FP32, B.SPLC_MATMUL_BF16X3
+LINE_SHAPES = [
+    (FP32, "x", 1024, 1530, 160, 2, (64, 64)), (FP32, "x", 8191, 2040, 160, 0, (64, 128)), (FP32, "x", 8191, 2040, 160, 2, (64, 128)),
+    (FP32, "x", 1000, 2050, 170, 2, (64, 64)), (FP32, "x", 12300, 2050, 40, 0, (64, 64)), (FP32, "r", 7000, 2050, 30, 0, (64, 64)),
+    (FP32, "r", 6000, 1980, 50, 0, (64, 64)), (FP32, "x", 1024, 1528, 250, 1, (64, 128)),
+    (X3, "x", 1024, 1530, 230, 2, (128, 128)), (X3, "x", 8191, 2040, 230, 0, (128, 128)), (X3, "x", 8191, 2040, 230, 2, (128, 128)),
+    (X3, "x", 1000, 2050, 230, 2, (128, 64)), (X3, "x", 12300, 2050, 40, 0, (128, 128)), (X3, "x", 12300, 2050, 60, 2, (128, 64)),
+    (X3, "x", 16256, 1470, 230, 0, (128, 64)), (X3, "r", 7000, 2050, 30, 0, (128, 128)), (X3, "r", 6000, 1980, 50, 0, (128, 64))]
 
 
-@pytest.mark.parametrize("op,rows,d,k,tables", LINE_SHAPES)
-def test_reconstruction_and_reprojection_at_the_lines_of_the_tile_choice(op, rows, d, k, tables, matmul_mode):
+@pytest.mark.parametrize("mode,op,rows,d,k,tables,tile", LINE_SHAPES)
+def test_reconstruction_and_reprojection_at_the_lines_of_the_tile_choice(mode, op, rows, d, k, tables, tile):
     second = B.SPLC_OP_REPROJECT_PASS2 if op == "r" else B.SPLC_OP_RECONSTRUCT
-    assert B.subspace_kernel_choice(second, rows, d, k, 2 * tables, matmul_mode) != (128, 32)     # the GEMM kernel
+    assert B.subspace_kernel_choice(second, rows, d, k, tables, mode) == tile
     if op == "r":
-        check_reproject(rows, d, k, seed=rows + d + k, mode=matmul_mode)
+        check_reproject(rows, d, k, seed=rows + d + k, mode=mode)
     else:
-        check_stage_boundary(rows, 500, d, k, 100, tables, tables, seed=rows + d + k, mode=matmul_mode)
+        check_stage_boundary(rows, 500, d, k, 100, tables >= 1, tables == 2, seed=rows + d + k, mode=mode)
 
 
 def test_every_kernel_variant_is_reached(matmul_mode):

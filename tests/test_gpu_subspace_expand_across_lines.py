@@ -24,14 +24,14 @@ SHAPES = [
 
 @pytest.mark.parametrize("mode,rows,d,k,use_perp,use_pos,taken", SHAPES)
 def test_reconstruction(mode, rows, d, k, use_perp, use_pos, taken):
-    assert (B.subspace_kernel_choice(B.SPLC_OP_RECONSTRUCT_ANY_WIDTH, rows, d, k, use_perp + use_pos, mode) == (128, 33)) == taken
+    assert (B.subspace_kernel_choice(B.SPLC_OP_RECONSTRUCT, rows, d, k, use_perp + use_pos, mode) == (128, 32)) == taken
     check_stage_boundary(rows, min(rows, 1000), d, k, 50, use_perp, use_pos, seed=rows + d + k, mode=mode)
 
 
 @pytest.mark.parametrize("mode,rows,d,k", [(X3, 513, 257, 191), (X3, 2050, 1283, 34), (FP32, 3390, 1299, 82), (FP32, 129, 251, 250)])
 def test_arrays_aligned_to_four_bytes_and_ids_outside_the_table(mode, rows, d, k):
     """Guard values around every array; token ids beyond both ends."""
-    assert B.subspace_kernel_choice(B.SPLC_OP_RECONSTRUCT_ANY_WIDTH, rows, d, k, 2, mode) == (128, 33)
+    assert B.subspace_kernel_choice(B.SPLC_OP_RECONSTRUCT, rows, d, k, 2, mode) == (128, 32)
     place = Misplaced()
     check_stage_boundary(rows, 300, d, k, 77, True, True, seed=rows + d + k, mode=mode, place=place, outside_ids=True)
     place.check()
