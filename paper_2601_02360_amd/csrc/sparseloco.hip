@@ -1199,23 +1199,23 @@ __global__ __launch_bounds__(kThreads) void compress_each_kernel(const ChunkDesc
 // receives its addends in ascending replica order -- deterministic, no float atomics, no sort.
 constexpr int kAggBatch = 8;
 
-template <int QUANT, int KP>
+template <int QUANT, int KP, int N>
 struct MessageBatch {
-    uint32_t p[kAggBatch][KP];
-    float val[kAggBatch][KP];            // unquantised: the values
-    float level[kAggBatch];              // quantised: the two levels, in the even and the odd lanes
+    uint32_t p[N][KP];
+    float val[N][KP];                    // unquantised: the values
+    float level[N];                      // quantised: the two levels, in the even and the odd lanes
 
-    // Fetch replicas r0 .. r0+7 of chunk c.  Every load is unconditional -- a replica or an entry past the last one repeats
-    // that one, and is not applied -- so that the pointers of all eight are on their way together, and then all their
+    // Fetch replicas r0 .. r0 + N - 1 of chunk c.  Every load is unconditional -- a replica or an entry past the last one repeats
+    // that one, and is not applied -- so that the pointers of all of them are on their way together, and then all their
     // messages: under a condition each replica's pointers are waited for before the next one's are requested.  The levels
     // come by vector loads because a wait for LDS would wait for scalar ones too.
     __device__ __forceinline__ void load(uint64_t c, uint32_t kappa, uint32_t kappa_c, int r0, int n_replicas,
                                          const uint16_t* const* __restrict__ pairs_tab,
                                          const float* const* __restrict__ aux_tab, int lane) {
-        const SPLC_GLOBAL uint16_t* pr[kAggBatch];
-        const SPLC_GLOBAL float* ar[kAggBatch];
+        const SPLC_GLOBAL uint16_t* pr[N];
+        const SPLC_GLOBAL float* ar[N];
 #pragma unroll
-        for (int i = 0; i < kAggBatch; ++i) {
+        for (int i = 0; i < N; ++i) {
             const int r = r0 + i < n_replicas ? r0 + i : n_replicas - 1;
             pr[i] = (const SPLC_GLOBAL uint16_t*)pairs_tab[r];
             ar[i] = (const SPLC_GLOBAL float*)aux_tab[r];
@@ -1225,7 +1225,7 @@ struct MessageBatch {
 #pragma unroll
         for (int k = 0; k < KP; ++k) at[k] = lane + 64 * k < kappa_c ? lane + 64 * k : kappa_c - 1;
 #pragma unroll
-        for (int i = 0; i < kAggBatch; ++i) {
+        for (int i = 0; i < N; ++i) {
             if (QUANT == SPLC_QUANT_2BIT) level[i] = (ar[i] + 2 * c)[lane & 1];
 #pragma unroll
             for (int k = 0; k < KP; ++k) {
@@ -1238,7 +1238,7 @@ struct MessageBatch {
     // Add them to the accumulator, replica after replica.
     __device__ __forceinline__ void apply(float* acc, uint32_t kappa_c, int r0, int n_replicas, int lane) const {
 #pragma unroll
-        for (int i = 0; i < kAggBatch; ++i) {
+        for (int i = 0; i < N; ++i) {
             if (r0 + i < n_replicas) {
                 float lo = 0.f, hi = 0.f;
                 if (QUANT == SPLC_QUANT_2BIT) {
@@ -1268,19 +1268,19 @@ struct MessageBatch {
 
 // All lanes of the workgroup call this after the accumulator has been cleared (no barrier needed
 // before the call; one is taken inside before the first add).  Ends with a barrier.
-template <int QUANT, int KP>
+template <int QUANT, int KP, int N>
 __device__ __forceinline__ void accumulate_chunk(float* acc, uint64_t c, uint32_t kappa, uint32_t kappa_c,
                                                  int n_replicas, const uint16_t* const* __restrict__ pairs_tab,
                                                  const float* const* __restrict__ aux_tab, int lane, int wave) {
-    const int n_batches = (n_replicas + kAggBatch - 1) / kAggBatch;
-    MessageBatch<QUANT, KP> mb;
-    if (wave < n_batches) mb.load(c, kappa, kappa_c, wave * kAggBatch, n_replicas, pairs_tab, aux_tab, lane);
+    const int n_batches = (n_replicas + N - 1) / N;
+    MessageBatch<QUANT, KP, N> mb;
+    if (wave < n_batches) mb.load(c, kappa, kappa_c, wave * N, n_replicas, pairs_tab, aux_tab, lane);
     __syncthreads();                                   // accumulator cleared by every lane
     for (int g = 0; g < n_batches; ++g) {
         if (wave == (g & 3)) {
-            mb.apply(acc, kappa_c, g * kAggBatch, n_replicas, lane);
+            mb.apply(acc, kappa_c, g * N, n_replicas, lane);
             if (g + 4 < n_batches)
-                mb.load(c, kappa, kappa_c, (g + 4) * kAggBatch, n_replicas, pairs_tab, aux_tab, lane);
+                mb.load(c, kappa, kappa_c, (g + 4) * N, n_replicas, pairs_tab, aux_tab, lane);
         }
         __syncthreads();
     }
@@ -1315,7 +1315,7 @@ __device__ __forceinline__ void accumulate_chunk_any(float* acc, uint64_t c, uin
 
 // Line 5 of the update equations.  One workgroup per chunk; all lanes clear the 16 KB LDS
 // accumulator, the waves apply the messages batch by batch, all lanes divide once by M and write.
-// KP: entries of a message per lane (kappa up to 64 KP; 0: any kappa).  A kernel for each takes 24 to 53 registers up to
+// KP: entries of a message per lane of a complete chunk (splc::entries_per_lane; 0: any kappa).  A kernel for each takes 24 to 53 registers up to
 // kappa 64 where one for all took 85, so eight workgroups share a compute unit instead of five; with that and the loads of a
 // batch in flight together (MessageBatch), messages that are not in a cache cost less: mean of 225,000 chunks, kappa 64,
 // 8 replicas 820 -> 723 us (floor 640), 69,000 chunks, kappa 32, 32 replicas 343 -> 306, tiles of 2050 columns 414 -> 362.
@@ -1354,8 +1354,21 @@ __device__ __forceinline__ void aggregate_body(float* acc, const ChunkDesc* __re
     if (UPDATE && !theta_late) load_theta();
 #pragma unroll
     for (int s = 0; s < 4; ++s) acc4[s * kThreads + tid] = make_float4(0.f, 0.f, 0.f, 0.f);
-    if constexpr (KP > 0) {
-        accumulate_chunk<QUANT, KP>(acc, c, kappa, kappa_c, n_replicas, pairs_tab, aux_tab, lane, wave);
+    auto accumulate = [&](auto per_lane, auto batch) {
+        accumulate_chunk<QUANT, decltype(per_lane)::value, decltype(batch)::value>(acc, c, kappa, kappa_c, n_replicas, pairs_tab,
+                                                                                   aux_tab, lane, wave);
+    };
+    using std::integral_constant;
+    // An edge chunk may hold fewer elements than kappa, and its messages are shorter then.  (Four entries per lane in batches
+    // of four: those of eight would take the registers that let eight workgroups share a unit.)
+    if (!VEC && KP != 1 && splc::entries_per_lane(kappa_c) == 1) {
+        accumulate(integral_constant<int, 1>{}, integral_constant<int, kAggBatch>{});
+    } else if (!VEC && (KP == 0 || KP == 4) && splc::entries_per_lane(kappa_c) == 2) {
+        accumulate(integral_constant<int, 2>{}, integral_constant<int, kAggBatch>{});
+    } else if (!VEC && KP == 0 && splc::entries_per_lane(kappa_c) == 4) {
+        accumulate(integral_constant<int, 4>{}, integral_constant<int, kAggBatch / 2>{});
+    } else if constexpr (KP > 0) {
+        accumulate(integral_constant<int, KP>{}, integral_constant<int, kAggBatch>{});
     } else {
         __syncthreads();
         if (wave == 0) accumulate_chunk_any<QUANT>(acc, c, kappa, kappa_c, n_replicas, pairs_tab, aux_tab, lane);
@@ -1603,10 +1616,12 @@ void launch_aggregate(const sparseloco_plan* plan, int n_replicas, const uint16_
                            (uint32_t)plan->kappa, pairs, aux, dbar, theta, eta, n_reset, (uint32_t)plan->n_tensors, in_runs,
                            pace.theta_late, reset);
     };
-    if (plan->kappa <= 64) launch(std::integral_constant<int, 1>{});
-    else if (plan->kappa <= 128) launch(std::integral_constant<int, 2>{});
-    else if (plan->kappa <= 256) launch(std::integral_constant<int, 4>{});
-    else launch(std::integral_constant<int, 0>{});
+    switch (splc::entries_per_lane((uint32_t)plan->kappa)) {
+        case 1: launch(std::integral_constant<int, 1>{}); break;
+        case 2: launch(std::integral_constant<int, 2>{}); break;
+        case 4: launch(std::integral_constant<int, 4>{}); break;
+        default: launch(std::integral_constant<int, 0>{}); break;
+    }
 }
 
 template <int QUANT, bool STEP>

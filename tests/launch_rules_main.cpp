@@ -84,8 +84,19 @@ static int check_aggregate_pace() {
     return 0;
 }
 
+// A lane takes as few entries as hold the message.
+static int check_entries_per_lane() {
+    const struct { uint32_t entries; int want; } cases[] = {{1, 1}, {64, 1}, {65, 2}, {128, 2}, {129, 4}, {256, 4}, {257, 0}, {4096, 0}};
+    for (const auto& c : cases)
+        if (splc::entries_per_lane(c.entries) != c.want) {
+            printf("entries_per_lane(%u)\n", c.entries);
+            return 1;
+        }
+    return 0;
+}
+
 int main() {
-    if (check_unguarded_tiles() || check_side_by_side() || check_few_streams() || check_aggregate_pace()) return 1;
+    if (check_unguarded_tiles() || check_side_by_side() || check_few_streams() || check_aggregate_pace() || check_entries_per_lane()) return 1;
     printf("ok\n");
     return 0;
 }

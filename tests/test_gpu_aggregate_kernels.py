@@ -50,6 +50,14 @@ def test_entries_and_batches(kappa, replicas, quant):
     check([CHUNK * 3 + 70, 5, CHUNK], kappa, replicas, quant, tiny=not quant)
 
 
+@pytest.mark.parametrize("quant", [True, False])
+@pytest.mark.parametrize("kappa", [65, 128, 129, 256, 257, 4096])
+@pytest.mark.parametrize("replicas", [1, 4, 9, 33])
+def test_chunks_of_fewer_elements_than_kappa(kappa, replicas, quant):
+    """Each takes the way of its own messages: one, two or four entries per lane, or one replica after the other."""
+    check([1, 63, 64, 65, 127, 128, 129, 255, 256, 257, 300, CHUNK + 40, 4095], kappa, replicas, quant)
+
+
 # theta late: 3; 9 of kappa 64; 8 of kappa 64 unquantised (fewer groups a unit) / with the first messages: 9 of kappa 16; 2 of kappa 200
 @pytest.mark.parametrize("kappa,replicas,quant", [(16, 3, True), (16, 9, True), (64, 9, True), (200, 2, True), (64, 8, False),
                                                   (128, 8, False), (32, 5, False)])
