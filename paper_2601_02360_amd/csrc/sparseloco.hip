@@ -1376,33 +1376,35 @@ __device__ __forceinline__ void aggregate_body(float* acc, const ChunkDesc* __re
     }
     if (UPDATE && theta_late) load_theta();
     const float m = (float)n_replicas;
-    // a power of two divides exactly like its inverse multiplies: one rounding of the same value
-    const bool halves = (n_replicas & (n_replicas - 1)) == 0;
-    const float inverse = __fdiv_rn(1.f, m);
-    with_chunk<VEC>(d, tid, [&](const auto& chunk) {
+    auto finish = [&](auto quotient) {
+        with_chunk<VEC>(d, tid, [&](const auto& chunk) {
 #pragma unroll
-        for (int s = 0; s < 4; ++s) {
-            float4 v = acc4[s * kThreads + tid];
-            if (halves) {
-                v.x = __fmul_rn(v.x, inverse); v.y = __fmul_rn(v.y, inverse);
-                v.z = __fmul_rn(v.z, inverse); v.w = __fmul_rn(v.w, inverse);
-            } else {
-                v.x = __fdiv_rn(v.x, m); v.y = __fdiv_rn(v.y, m); v.z = __fdiv_rn(v.z, m); v.w = __fdiv_rn(v.w, m);
+            for (int s = 0; s < 4; ++s) {
+                float4 v = acc4[s * kThreads + tid];
+                v.x = quotient(v.x); v.y = quotient(v.y); v.z = quotient(v.z); v.w = quotient(v.w);
+                if (po) chunk.store(po, s, v);
+                if (UPDATE) {
+                    float4 t = tv[s];
+                    if (!VEC) pull(edge_vec(d, tid, s).n, t.x, t.y, t.z, t.w);
+                    t.x = __fsub_rn(t.x, __fmul_rn(eta, v.x));
+                    t.y = __fsub_rn(t.y, __fmul_rn(eta, v.y));
+                    t.z = __fsub_rn(t.z, __fmul_rn(eta, v.z));
+                    t.w = __fsub_rn(t.w, __fmul_rn(eta, v.w));
+                    chunk.store(th, s, t);
+                    for (int r = 0; r < n_reset; ++r)
+                        chunk.store(reset_tab[(size_t)r * n_tensors + d.tensor] + d.offset, s, t);
+                }
             }
-            if (po) chunk.store(po, s, v);
-            if (UPDATE) {
-                float4 t = tv[s];
-                if (!VEC) pull(edge_vec(d, tid, s).n, t.x, t.y, t.z, t.w);
-                t.x = __fsub_rn(t.x, __fmul_rn(eta, v.x));
-                t.y = __fsub_rn(t.y, __fmul_rn(eta, v.y));
-                t.z = __fsub_rn(t.z, __fmul_rn(eta, v.z));
-                t.w = __fsub_rn(t.w, __fmul_rn(eta, v.w));
-                chunk.store(th, s, t);
-                for (int r = 0; r < n_reset; ++r)
-                    chunk.store(reset_tab[(size_t)r * n_tensors + d.tensor] + d.offset, s, t);
-            }
-        }
-    });
+        });
+    };
+    // A power of two divides exactly like its inverse multiplies: one rounding of the same value.  (The choice is made out here,
+    // for all slots at once: in their loop it slowed the division down, mean of 1000 chunks, kappa 16, 27 replicas 7.1 -> 7.6 us.)
+    if ((n_replicas & (n_replicas - 1)) == 0) {
+        const float inverse = __fdiv_rn(1.f, m);
+        finish([=](float x) { return __fmul_rn(x, inverse); });
+    } else {
+        finish([=](float x) { return __fdiv_rn(x, m); });
+    }
 }
 
 template <int QUANT, int UPDATE, int KP>
