@@ -274,6 +274,9 @@ constexpr bool chunks_in_runs(int64_t entries, int replicas, int kappa, bool qua
     return (update && replicas <= 32) || entries * replicas * (2 * kappa + 8) < 240000000;
 }
 
+// Whether an edge chunk of `rows` local rows holds anything in slot s, which is 16 of them.
+constexpr bool slot_used(int rows, int s) { return 16 * s < rows; }
+
 // Aggregation: entries of a chunk's message per lane of the wave that adds it, 0: one replica after the other by one wave, for
 // messages that would take too many registers.  A kernel is made for a plan's kappa; an edge chunk that holds fewer elements
 // than kappa takes the way of its own messages in it (mean over 17 replicas, 4000 chunks of 100 elements: kappa 512 35.9 -> 20.9

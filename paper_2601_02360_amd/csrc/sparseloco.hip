@@ -83,6 +83,11 @@ __device__ __forceinline__ EdgeVec edge_vec(const ChunkDesc& d, int tid, int s) 
 __device__ __forceinline__ bool narrow(const ChunkDesc& d) {
     return d.offset == 0 && (d.h > 1 ? d.w : d.last_w) < 4;       // (any other chunk has four elements before its origin)
 }
+// Whether slot s (16 rows) of a chunk holds anything.  The tail of a tensor, mostly, is a few rows: the aggregation and the
+// outer update leave its other slots out (4000 chunks of 40 elements: outer update 8.7 -> 5.3 us, mean over 17 replicas, kappa
+// 300, 13.6 -> 10.7; edge chunks that use all four take up to 0.2 us longer a launch).
+template <bool VEC>
+__device__ __forceinline__ bool slot_used(const ChunkDesc& d, int s) { return VEC || splc::slot_used(d.h, s); }
 // Where the vector of `v` starts in an array whose element at the chunk's origin is *origin.
 template <class T>
 __device__ __forceinline__ T* edge_at(T* origin, EdgeVec v) {
@@ -1348,7 +1353,8 @@ __device__ __forceinline__ void aggregate_body(float* acc, const ChunkDesc* __re
     auto load_theta = [&] {
         with_chunk<VEC>(d, tid, [&](const auto& chunk) {
 #pragma unroll
-            for (int s = 0; s < 4; ++s) tv[s] = chunk.load(th, s);
+            for (int s = 0; s < 4; ++s)
+                if (slot_used<VEC>(d, s)) tv[s] = chunk.load(th, s);
         });
     };
     if (UPDATE && !theta_late) load_theta();
@@ -1380,6 +1386,7 @@ __device__ __forceinline__ void aggregate_body(float* acc, const ChunkDesc* __re
         with_chunk<VEC>(d, tid, [&](const auto& chunk) {
 #pragma unroll
             for (int s = 0; s < 4; ++s) {
+                if (!slot_used<VEC>(d, s)) break;
                 float4 v = acc4[s * kThreads + tid];
                 v.x = quotient(v.x); v.y = quotient(v.y); v.z = quotient(v.z); v.w = quotient(v.w);
                 if (po) chunk.store(po, s, v);
@@ -1438,11 +1445,14 @@ __device__ __forceinline__ void outer_update_body(const ChunkDesc* __restrict__ 
     with_chunk<VEC>(d, tid, [&](const auto& chunk) {
         float4 t[4], g[4];
 #pragma unroll
-        for (int s = 0; s < 4; ++s) t[s] = chunk.load(th, s);
+        for (int s = 0; s < 4; ++s)
+            if (slot_used<VEC>(d, s)) t[s] = chunk.load(th, s);
 #pragma unroll
-        for (int s = 0; s < 4; ++s) g[s] = chunk.load(db, s);
+        for (int s = 0; s < 4; ++s)
+            if (slot_used<VEC>(d, s)) g[s] = chunk.load(db, s);
 #pragma unroll
         for (int s = 0; s < 4; ++s) {
+            if (!slot_used<VEC>(d, s)) break;
             if (!VEC) {
                 const uint32_t n = edge_vec(d, tid, s).n;
                 pull(n, t[s].x, t[s].y, t[s].z, t[s].w);

@@ -95,8 +95,24 @@ static int check_entries_per_lane() {
     return 0;
 }
 
+// A slot is left out exactly where none of its rows exists.
+static int check_slot_used() {
+    for (int rows = 1; rows <= 64; ++rows)
+        for (int s = 0; s < 4; ++s) {
+            bool any = false;
+            for (int r = 16 * s; r < 16 * s + 16; ++r) any |= r < rows;
+            if (splc::slot_used(rows, s) != any) {
+                printf("slot %d of %d rows\n", s, rows);
+                return 1;
+            }
+        }
+    return 0;
+}
+
 int main() {
-    if (check_unguarded_tiles() || check_side_by_side() || check_few_streams() || check_aggregate_pace() || check_entries_per_lane()) return 1;
+    if (check_unguarded_tiles() || check_side_by_side() || check_few_streams() || check_aggregate_pace() || check_entries_per_lane() ||
+        check_slot_used())
+        return 1;
     printf("ok\n");
     return 0;
 }
