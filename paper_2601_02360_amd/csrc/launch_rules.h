@@ -298,12 +298,14 @@ constexpr int entries_per_lane(uint32_t entries) { return entries <= 64 ? 1 : (e
 //   tiles of 2050 columns, which share cache lines: 69,000, kappa 32, 4: 473 / 456 / 452 / 449, 16: 503 / 484 / 501 / 514, 32: 529 / 514 /
 //     550 / 556; 25,600, kappa 32, 4: 173 / 167 / 170 / 172, 64, 24: 201 / 197 / 214 / 218;
 //   mean only, all that fit / five / four: 225,000 chunks, kappa 64, 8 replicas 724 / 840 / 919; unquantised, kappa 32, 8: 739 / 849 / 941;
-//     64, 8: 300 / 265 / 291 (69,000); 128, 5: 442 / 499 / 570 (128,000), 16: 254 / 246 / 238 (39,000), 83 / 81 / 75 (10,240).
+//     70,000 chunks, kappa 64, 8: 311 / 282 / 324, 9: 294 / 309 / 354, 17: 336 / 343 / 383, 32: 408 / 410 / 426; kappa 128, 8: 350 / 324 / 313,
+//     12: 363 / 356 / 375, 17: 411 / 415 / 433, 32: 562 / 556 / 568; kappa 200, 27: - / 685 / 749; 25,000, kappa 64, 17: 138 / 133 / 142;
+//     messages in a cache, 70,000, kappa 64, 17: 295 / 313 / 356, kappa 128, 17: 373 / 374 / 399.
 struct AggregatePace { int groups_per_unit; bool theta_late; };
 constexpr AggregatePace aggregate_pace(int64_t chunks, int replicas, int kappa, bool quantised, bool flat, bool update) {
     if (chunks < kFewStreams) return AggregatePace{0, false};
     const bool heavy = !quantised && replicas >= 8 && kappa >= 64;       // messages of the order of the chunk itself
-    if (!update) return AggregatePace{heavy ? (replicas * kappa >= 1024 ? 4 : 5) : 0, false};
+    if (!update) return AggregatePace{heavy ? (replicas == 8 && kappa >= 128 ? 4 : 5) : 0, false};
     if (kappa > 128) return AggregatePace{0, false};
     const bool late = flat && (!quantised || replicas <= 8 || (kappa >= 64 && replicas <= 24));
     return AggregatePace{flat && heavy ? 4 : 5, late};

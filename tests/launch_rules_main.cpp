@@ -68,19 +68,35 @@ static int check_few_streams() {
     return 0;
 }
 
-// The aggregation's pace: small plans take all workgroups that fit, the mean alone reads no theta.
+// The aggregation's pace on both sides of each line (the second half: test_large_plans of test_gpu_aggregate_kernels.py).
 static int check_aggregate_pace() {
-    for (int64_t chunks : {1, 8191, 8192, 24000, 220000})
-        for (int replicas : {1, 8, 9, 24, 25, 1024})
-            for (int kappa : {1, 63, 64, 128, 129, 4096})
-                for (int i = 0; i < 8; ++i) {
-                    const splc::AggregatePace p = splc::aggregate_pace(chunks, replicas, kappa, i & 1, i & 2, i & 4);
-                    const bool plain = chunks < splc::kFewStreams && (p.groups_per_unit || p.theta_late);
-                    if ((p.groups_per_unit && (p.groups_per_unit < 4 || p.groups_per_unit > 5)) || plain || (p.theta_late && !(i & 4))) {
-                        printf("aggregate_pace: %ld chunks, %d replicas, kappa %d, %d\n", (long)chunks, replicas, kappa, i);
-                        return 1;
-                    }
-                }
+    const struct { int64_t chunks; int replicas, kappa; bool quantised, flat, update; int groups; bool late; } cases[] = {
+        {8191, 8, 64, true, true, true, 0, false}, {8191, 32, 128, false, false, false, 0, false}, {8191, 3, 16, false, true, true, 0, false},
+        // the mean alone: only unquantised messages of the order of the chunk itself
+        {8192, 32, 128, true, true, false, 0, false}, {8192, 7, 128, false, true, false, 0, false}, {8192, 8, 63, false, true, false, 0, false},
+        {8192, 8, 64, false, true, false, 5, false}, {8192, 8, 127, false, true, false, 5, false}, {8192, 8, 128, false, true, false, 4, false},
+        {8192, 8, 256, false, false, false, 4, false}, {8192, 9, 128, false, true, false, 5, false}, {220000, 17, 64, false, true, false, 5, false},
+        {220000, 32, 256, false, false, false, 5, false}, {220000, 1024, 4096, false, true, false, 5, false},
+        // with the update, quantised
+        {8192, 8, 16, true, true, true, 5, true}, {8192, 9, 16, true, true, true, 5, false}, {8192, 9, 63, true, true, true, 5, false},
+        {8192, 9, 64, true, true, true, 5, true}, {8192, 24, 128, true, true, true, 5, true}, {8192, 25, 128, true, true, true, 5, false},
+        {8192, 1, 128, true, true, true, 5, true}, {8192, 1, 129, true, true, true, 0, false}, {8192, 8, 64, true, false, true, 5, false},
+        {220000, 32, 64, true, false, true, 5, false},
+        // with the update, unquantised
+        {8192, 7, 64, false, true, true, 5, true}, {8192, 8, 63, false, true, true, 5, true}, {8192, 8, 64, false, true, true, 4, true},
+        {8192, 1024, 128, false, true, true, 4, true}, {8192, 32, 129, false, true, true, 0, false}, {8192, 32, 64, false, false, true, 5, false},
+        {8192, 3, 16, true, true, true, 5, true}, {8192, 9, 16, true, true, true, 5, false}, {8192, 9, 64, true, true, true, 5, true},
+        {8192, 2, 200, true, true, true, 0, false}, {8192, 8, 64, false, true, true, 4, true}, {8192, 8, 128, false, true, true, 4, true},
+        {8192, 5, 32, false, true, true, 5, true}, {8192, 9, 64, true, true, false, 0, false}, {8192, 8, 64, false, true, false, 5, false},
+        {8192, 8, 128, false, true, false, 4, false}, {8192, 5, 32, false, true, false, 0, false}};
+    for (const auto& c : cases) {
+        const splc::AggregatePace p = splc::aggregate_pace(c.chunks, c.replicas, c.kappa, c.quantised, c.flat, c.update);
+        if (p.groups_per_unit != c.groups || p.theta_late != c.late) {
+            printf("aggregate_pace: %ld chunks, %d replicas, kappa %d, %d %d %d: %d %d\n", (long)c.chunks, c.replicas, c.kappa,
+                   c.quantised, c.flat, c.update, p.groups_per_unit, p.theta_late);
+            return 1;
+        }
+    }
     return 0;
 }
 
