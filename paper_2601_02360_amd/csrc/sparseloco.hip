@@ -154,9 +154,12 @@ __device__ __forceinline__ void store4(float* p, float4 v) {
     else *(SPLC_GLOBAL vfloat4*)p = t;
 }
 // Whether the rows of a complete chunk are whole cache lines.  Those of a tile in a matrix whose row length is no
-// multiple of 32 floats share their first and last line with the neighbouring tiles, and are accessed without the hint:
-// with it the lines are gone from the L2 when the neighbour asks for them (20M parameters in rows of 1219 and 3687: compress
-// 83 -> 62 us, aggregate 28 -> 20; the one-launch step of four replicas, 47M in rows of 1925 and 5295: 847 -> 619).
+// multiple of 32 floats share their first and last line with the neighbouring tiles.  The aggregation and the calls that walk
+// over replicas access them without the hint: with it the lines are gone from the L2 when the neighbour asks for them (20M
+// parameters in rows of 3687, mean 30 -> 17 us; the one-launch step of two replicas 201 -> 128).  The compression of one replica
+// reads with the hint and stores the error feedback without.  20M parameters in rows of 3687, us, nothing in a cache / arrays as
+// the call before left them: from parameters 85 / 70 (hint for both 89 / 85, for the store only 106 / 74), from fp32 63 / 53
+// (70 / 66, 75 / 55), from bf16 55 / 50 (64 / 65, 64 / 52).
 __device__ __forceinline__ bool whole_lines(const ChunkDesc& d) { return d.stride % 32u == 0; }
 
 __device__ __forceinline__ uint32_t lanes_below(uint64_t mask) {
@@ -829,15 +832,20 @@ __device__ __forceinline__ void select_quantise_pack(SelectShared& sh, float (&x
                                     scales_c);
 }
 
-// The error-feedback buffer is rewritten densely (line 4 of the update equations).
-template <bool VEC>
+// The error-feedback buffer is rewritten densely (line 4 of the update equations).  BATCH: by a call that walks over replicas,
+// which keeps the hint also where lines are shared (without it the one-launch step takes 0.98 to 1.06 of the time).
+template <bool VEC, bool BATCH>
 __device__ __forceinline__ void store_ef(float* __restrict__ e, const ChunkDesc& d, int tid, uint32_t pmask,
                                          const float (&x)[16]) {
     float* pe = e + d.offset;
-    if (VEC) {
+    auto store = [&](const auto& chunk) {
 #pragma unroll
-        for (int s = 0; s < 4; ++s)
-            stream_store4(vec_at(pe, d, tid, s), make_float4(x[4 * s], x[4 * s + 1], x[4 * s + 2], x[4 * s + 3]));
+        for (int s = 0; s < 4; ++s) chunk.store(pe, s, make_float4(x[4 * s], x[4 * s + 1], x[4 * s + 2], x[4 * s + 3]));
+    };
+    if constexpr (VEC && BATCH) {
+        store(CompleteChunk<true>{d, tid});
+    } else if constexpr (VEC) {
+        with_chunk<true>(d, tid, store);
     } else {
         // from an opaque copy of the lane number: nothing of the loads' addresses is kept for these stores
         int t = tid;
@@ -871,15 +879,15 @@ __device__ __forceinline__ void compress_body(SelectShared& sh, bool vec, const 
     uint32_t pmask = 0xFFFFu;
     float x[16];
     if (vec) {
-        with_chunk<true>(d, tid, [&](const auto& chunk) { load_fold<MODE>(pa, pb, pe, beta, x, chunk); });
+        load_fold<MODE>(pa, pb, pe, beta, x, CompleteChunk<true>{d, tid});
     } else {
         with_chunk<false>(d, tid, [&](const auto& chunk) { load_fold<MODE>(pa, pb, pe, beta, x, chunk); });
         pmask = pull_all(d, tid, x);
     }
     select_quantise_pack<QUANT>(sh, x, tid, lane, wave, d.n_c, pmask, kappa, force_radix, radix_counter,
                                 pairs_out + c * kappa, aux_out + c * kappa, aux_out + 2 * c);
-    if (vec) store_ef<true>(pe, d, tid, pmask, x);
-    else store_ef<false>(pe, d, tid, pmask, x);
+    if (vec) store_ef<true, false>(pe, d, tid, pmask, x);
+    else store_ef<false, false>(pe, d, tid, pmask, x);
 }
 
 // The chunk table lists the n_gen edge chunks first (one launch; the branch is uniform per workgroup).
@@ -1127,7 +1135,7 @@ __device__ __forceinline__ void compress_batch_body(SelectShared& sh, float* so,
                                                          radix_counter);
         quantise_pack_sum<QUANT, STEP>(sh, th, x, sum, t, t & 63, wave, kappa_c, kappa, pmask, pairs_tab[r] + c * kappa,
                                        aux_r + c * kappa, aux_r + 2 * c);
-        store_ef<VEC>(pe, d, t, pmask, x);
+        store_ef<VEC, true>(pe, d, t, pmask, x);
         __syncthreads();          // every lane is done with `sh` before the next replica re-initialises it
     }
     if (!STEP) return;
