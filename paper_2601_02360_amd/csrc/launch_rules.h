@@ -221,13 +221,22 @@ constexpr bool replicas_side_by_side(int64_t chunks, int replicas, bool step, bo
 // Compression of a tiled plan: strips of four tiles (1024 lanes, two per compute unit) and a second launch for the tiles
 // outside them, or every tile by itself in one launch.  A strip asks for nine cache lines where its tiles ask for twelve,
 // which is what large plans are bound by; it takes longer from end to end, and below some rounds of workgroups that, and
-// the second launch, are what counts.  Time of the tiles over time of the strips, MI355X, matrices of 330 to 2050 columns:
-//   from parameters, kappa 32 / 128: 560 strips 0.72 / 0.65, 832 0.77 / 0.72, 952 0.94 / 0.89, 1400 1.05 / 1.01, 1664 1.07 / 1.01,
-//     2240 1.17 / 1.18, 4422 1.23 / 1.23, 7370 1.19 / 1.19, 57,000 1.13 / 1.13;
-//   from bf16, kappa 32 / 64 / 128: 560 0.60 / 0.61 / 0.58, 1400 1.01 / 0.97 / 0.92, 1664 0.98 / 0.98 / 0.89, 2240 1.12 / 1.07 / 0.98,
-//     2496 1.08 / 1.06 / 0.91, 2948 1.15 / 1.10 / 1.05, 4160 1.17 / 1.15 / 1.02, 7370 1.16 / 1.12 / 1.06.
-constexpr bool strips_pay(int64_t strips, int kappa, bool bf16) {
-    return strips >= (!bf16 ? 1400 : (kappa <= 64 ? 1750 : 2900));
+// the second launch, are what counts.  Where the general path of the selection is taken often (from some 200 entries on) all four
+// tiles of a strip take it together.  Time of the tiles over time of the strips, MI355X, matrices of 330 to 5630 columns,
+// nothing in a cache / arrays as the call before left them (profiles/strips_measured.txt):
+//   from parameters, kappa 32 ... 192: 1120 strips 0.89 ... 0.99 / 0.78 ... 0.85, 1720 1.01 ... 1.09 / 0.86 ... 0.90, 2240 0.97 ... 1.12 /
+//     0.80 ... 0.89, 2960 0.98 ... 1.09 / 0.85 ... 0.92, 4480 1.00 ... 1.27 / 0.98 ... 1.15, 9000 1.12 ... 1.33 / 1.08 ... 1.31;
+//     kappa 256: 9000 0.94 ... 0.96 / 0.91 ... 0.95, 40,000 1.07 / 1.05; 512 and 1024: 4480 0.94 ... 1.00 / 0.88 ... 0.98, 9000 1.01 ... 1.04;
+//   from fp32, kappa 32 ... 192: 1400 0.85 ... 0.96 / 0.75 ... 0.82, 2240 0.85 ... 1.06 / 0.70 ... 0.88, 2960 1.05 ... 1.13 / 0.85 ... 0.95, 4480 1.04 ...
+//     1.23 / 0.86 ... 1.15; kappa 256 ... 1024: 0.68 ... 0.82 at every size;
+//   from bf16, kappa 32 / 64: 2240 0.95 ... 1.00 / 0.91 ... 0.97 (in a cache 0.78 ... 0.89), 2600 1.05 / 0.99 (0.81 ... 0.92), 4480 1.05 ... 1.19
+//     (0.96 ... 1.11); kappa 128: 2960 0.94 ... 0.99 (0.81 ... 0.87), 3600 0.99 (0.82), 4480 1.05 (0.91 ... 1.03); 160: 4480 0.94 ... 0.99, 9000 1.01 ... 1.05;
+//     kappa 192 ... 1024: 0.64 ... 0.88 at every size.
+constexpr bool strips_pay(int64_t strips, int kappa, bool params, bool bf16) {
+    if (kappa > 192) return params && strips >= 9000;
+    if (!bf16) return strips >= 2200;
+    if (kappa > 128) return kappa <= 160 && strips >= 9000;
+    return strips >= (kappa <= 64 ? 2600 : 3600);
 }
 
 // Large plans stream far more than the last-level cache holds, and there fewer workgroups per compute unit than would fit

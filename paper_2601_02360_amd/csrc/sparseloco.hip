@@ -910,9 +910,9 @@ __global__ __launch_bounds__(kThreads) void compress_kernel(const ChunkDesc* __r
 // A workgroup that owns one 64 x 64 tile touches 256-byte row segments; when the matrix's row length is not a
 // multiple of 32 floats every such segment straddles three 128-byte cache lines instead of two, and the lines on
 // a tile's left and right edge are requested again by its neighbours.  So wherever four complete tiles lie side
-// by side, and there are many of them (splc::strips_pay), ONE workgroup of 1024 lanes takes all four: global memory is accessed row by row (a wave covers one
-// 1024-byte row of the strip per instruction: nine lines instead of twelve, none shared with another
-// workgroup), the folded values pass through LDS, where each 256-lane group picks up "its" tile in the usual
+// by side, and there are many of them (splc::strips_pay), ONE workgroup of 1024 lanes takes all four: global memory is
+// accessed row by row (a wave covers one 1024-byte row of the strip per instruction: nine lines instead of twelve, none
+// shared with another workgroup), the folded values pass through LDS, where each 256-lane group picks up "its" tile in the usual
 // chunk layout and runs the selection exactly as the one-tile kernel does, and the new error-feedback values go
 // back the same way.  Tiles left over at the end of a tile row, edge tiles and 1-D tensors stay with the
 // one-tile kernels.
@@ -1608,7 +1608,7 @@ template <int MODE, int QUANT>
 void launch_compress(const sparseloco_plan* plan, const void* const* a, const void* const* b, float* const* ef,
                      float beta, uint16_t* pairs_out, float* aux_out, hipStream_t stream) {
     const int force_radix = plan->select == SPLC_SELECT_RADIX ? 1 : 0;
-    const bool strips = splc::strips_pay(plan->n_strips, plan->kappa, MODE == MODE_DIRECT_BF16);
+    const bool strips = splc::strips_pay(plan->n_strips, plan->kappa, MODE == MODE_PARAMS_F32, MODE == MODE_DIRECT_BF16);
     const int64_t entries = strips ? plan->n_entries : plan->n_chunks;
     if (strips)
         hipLaunchKernelGGL((compress_strip_kernel<MODE, QUANT>), dim3((unsigned)plan->n_strips), dim3(kStripThreads), 0,
@@ -1908,7 +1908,11 @@ int plan_build(sparseloco_plan** out, int n_tensors, const int64_t* rows, const 
     plan->n_params = t.n_params;
     plan->numel.resize((size_t)n_tensors);
     for (int i = 0; i < n_tensors; ++i) plan->numel[(size_t)i] = (tiled ? rows[i] : 1) * cols[i];
-    const bool with_strips = !t.strips.empty();
+    // (kept where a compression of this plan takes them: from some source they pay)
+    const int64_t n_strips = (int64_t)t.strips.size();
+    const bool with_strips = splc::strips_pay(n_strips, kappa, true, false) || splc::strips_pay(n_strips, kappa, false, false) ||
+                             splc::strips_pay(n_strips, kappa, false, true);
+    if (!with_strips) t.strips.clear();
     const std::vector<ChunkDesc>& main_table = with_strips ? t.rest : t.all;
     plan->n_entries = (int64_t)main_table.size();
     plan->n_gen = count_class0(main_table);

@@ -19,7 +19,7 @@ RAGGED = [4096 * 5, 4096 * 3 + 17, 100, 4096, 1, 2047, 4096 * 2 + 4, 0, 4096 * 2
 TILED_SHAPES = [(128, 192), (130, 70), (64, 64), (1, 5000), (63, 65), (200, 3), (3, 200), (65, 129), (1, 1), (70, 66)]
 
 
-# matrices wide enough for strips (four complete tiles taken by one workgroup), with leftovers and edges around them
+# matrices wide enough for strips (four complete tiles side by side), with leftovers and edges around them
 STRIP_SHAPES = [(128, 1030), (64, 264), (70, 520), (200, 322), (130, 254), (64, 513), (1, 3000), (66, 2050), (3, 258),
                 (65, 450)]
 
@@ -60,9 +60,9 @@ def test_tiled_layout_params_mode(kappa, select):
 @pytest.mark.parametrize("select", [B.SPLC_SELECT_AUTO, B.SPLC_SELECT_RADIX])
 @pytest.mark.parametrize("kappa", [1, 32, 64, 200, 300])
 def test_tiled_layout_with_strips(kappa, select):
-    """Runs of four complete tiles go to one 1024-lane workgroup: row lengths that are and are not multiples of
-    32 floats, leftover tiles at the end of a tile row, edge tiles below and to the right, odd row lengths (no
-    strips), with both selection algorithms and wide messages."""
+    """Matrices in which four complete tiles lie side by side, on plans too small to take them as strips (test_gpu_strips.py
+    has those that do): row lengths that are and are not multiples of 32 floats, leftover tiles at the end of a tile row, edge
+    tiles below and to the right, odd row lengths, with both selection algorithms and wide messages."""
     case = gaussian_case(None, R=3, seed=700 + kappa, shapes=STRIP_SHAPES)
     parity.check(case, kappa, select=select, what="strips kappa=%d" % kappa)
 
@@ -75,9 +75,9 @@ def test_tiled_layout_with_strips_modes(direct, quant, fused):
 
 
 def test_strip_with_one_degenerate_tile():
-    """Inside one strip, one tile is constant (a 4096-way tie: the candidate filter gives up and the radix
-    select runs), one is all zero, one has few distinct values and one is ordinary: the four groups of the
-    workgroup must agree on the path and each still get its own tile right."""
+    """Of four tiles side by side one is constant (a 4096-way tie: the candidate filter gives up and the radix
+    select runs), one is all zero, one has few distinct values and one is ordinary; each by itself here, and as a strip,
+    whose groups have to agree on the path, in test_gpu_strips.py."""
     rng = np.random.default_rng(9)
     rows, cols = 64, 2 * 256 + 70
     x = (rng.standard_normal((rows, cols)) * 1e-3).astype(np.float32)
