@@ -111,7 +111,10 @@ constexpr bool expand_applies(int64_t rows, int width, int k, int tables, bool u
 }
 
 // The same for the reconstruction where rows are no whole lines (the GEMM kernel's non-temporal accesses there lose the lines that
-// its tiles share).  Time of the GEMM kernel over time of expand_kernel, as above, 3300 shapes of 257 to 2050 columns:
+// its tiles share), on 256 compute units.  The lines are those of 3300 shapes of 257 to 2050 columns, measured on both sides; what
+// they give to expand_kernel was measured from 33 to 16,000 columns (profiles/subspace_across_lines_measured.txt: narrow
+// rows too gain 1.03 to 2.6 in the median of every class, the least in fp32 with both tables, to 256 columns, from 1024
+// tiles on: 0.92 ... 1.3).  Time of the GEMM kernel over time of expand_kernel:
 //   split, one table 1.04 ... 4.2 (median 1.6); both, below 4096 tiles 0.94 ... 3.9 (median 1.6), from there k from 65 on 0.95 ...
 //     1.29, to 64 and, from 12,000 tiles on, to 128 0.87 ... 1.25; none, k from 65 on: an even number of 64-column blocks, below 512
 //     tiles 0.97 ... 1.69, from 4096 on 0.95 ... 1.31, between 0.81 ... 1.35; an odd number, below 256 0.99 ... 1.27, from 2048 on

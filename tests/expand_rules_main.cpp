@@ -47,6 +47,51 @@ int main() {
                             printf("width %d k %d\n", width, k);
                             return 1;
                         }
+    // nor across lines, and whatever is sent has a kernel (a launch of other steps would do nothing)
+    for (int width = 1; width <= 2100; width += width < 300 ? 1 : 7)
+        for (int wide : {width, width + 30000, (1 << 20) - 32 + width % 64})
+            for (int k = 1; k <= 300; ++k)
+                for (bool split : {false, true})
+                    for (int tables : {0, 1, 2})
+                        for (int64_t rows : {0, 1, 1000, 16384, 100000, 1 << 30}) {
+                            if (!splc::expand_applies_across_lines(rows, wide, k, tables, split)) continue;
+                            const bool steps = splc::expand_takes_steps_across_lines((k + 31) / 32, tables, split);
+                            const int64_t tiles = (rows + 127) / 128 * ((wide + 31) / 32);
+                            if (rows < 1 || wide % 32 == 0 || wide < 33 || wide >= 1 << 20 || k <= (split ? 32 : 80) || k > (split ? 224 : 256) ||
+                                (!split && tables == 0) || tiles >= int64_t(1) << 31 || !steps) {
+                                printf("across lines: rows %ld width %d k %d, %d tables\n", (long)rows, wide, k, tables);
+                                return 1;
+                            }
+                        }
+    for (bool split : {false, true})
+        for (int tables : {0, 1, 2})
+            for (int steps = 1; steps <= 9; ++steps) {
+                bool taken = false;
+                for (int k = 32 * steps - 31; k <= 32 * steps; ++k)
+                    for (int64_t rows : {1, 16384, 50304})
+                        for (int width : {100, 257, 1090, 2050}) taken |= splc::expand_applies_across_lines(rows, width, k, tables, split);
+                if (taken != splc::expand_takes_steps_across_lines(steps, tables, split)) {
+                    printf("across lines, %d steps, %d tables\n", steps, tables);
+                    return 1;
+                }
+            }
+    const struct { int64_t rows; int width, k, tables; bool split, taken; } across[] = {
+        {1, 33, 33, 1, true, true}, {1, 33, 33, 0, true, false}, {1, 130, 65, 0, true, true}, {1, 130, 64, 0, true, false},
+        {1, 31, 31, 1, true, false}, {1, 2050, 224, 2, true, true}, {1, 2050, 225, 2, true, false}, {1, 2048, 100, 1, true, false},
+        {15872, 1000, 40, 2, true, true}, {16384, 1000, 40, 2, true, false}, {16384, 1000, 65, 2, true, true}, {48000, 1000, 128, 2, true, false},
+        {47872, 1000, 128, 2, true, true}, {48000, 1000, 129, 2, true, true}, {48000, 1000, 33, 1, true, true},
+        {1792, 1100, 70, 0, true, true}, {1920, 1100, 70, 0, true, false}, {15104, 1100, 70, 0, true, true}, {14976, 1100, 70, 0, true, false},
+        {896, 1060, 70, 0, true, true}, {1024, 1060, 70, 0, true, false}, {7808, 1060, 70, 0, true, true}, {7680, 1060, 70, 0, true, false},
+        {1, 130, 81, 1, false, true}, {1, 130, 80, 1, false, false}, {100000, 130, 100, 0, false, false}, {1, 1001, 256, 1, false, true},
+        {1, 1001, 257, 1, false, false}, {12288, 1000, 100, 1, false, true}, {12160, 1000, 100, 1, false, false}, {12288, 1000, 100, 2, false, false},
+        {3200, 1307, 161, 2, false, true}, {3072, 1307, 161, 2, false, false}, {4096, 1001, 129, 1, false, true}, {3968, 1001, 129, 1, false, false},
+        {12800, 1307, 200, 1, false, true}, {12672, 1307, 200, 1, false, false}, {12800, 1307, 100, 2, false, false},
+        {12672, 1307, 100, 2, false, true}, {12800, 1307, 100, 1, false, true}, {1, 1001, 200, 2, false, true}};
+    for (const auto& c : across)
+        if (splc::expand_applies_across_lines(c.rows, c.width, c.k, c.tables, c.split) != c.taken) {
+            printf("across lines, line: rows %ld width %d k %d, %d tables, %d\n", (long)c.rows, c.width, c.k, c.tables, c.split);
+            return 1;
+        }
     for (int64_t rows : {0, 1, 5440, 11008, 16384, 16448, 32768, 1 << 24})
         for (int k : {1, 64, 65, 128, 129, 192, 193, 256, 257, 600})
             for (int d : {16, 511, 512, 1023, 1024, 2050, 1 << 20, 1 << 23})
