@@ -53,6 +53,47 @@ def test_every_form_of_argument_gives_the_same_step():
 
 
 @pytest.mark.gpu
+def test_plain_calls_are_taken(monkeypatch):
+    """Every call with plain arguments is made by the native function, with status OK, and not handed back to Python."""
+    native, made = B._native(), []
+
+    class Recorded:
+        def __getattr__(self, name):
+            def call(*args):
+                made.append((name, getattr(native, name)(*args)))
+                return made[-1][1]
+            return call
+    monkeypatch.setattr(B, "_native", lambda: Recorded())
+    n = 2 * 4096 + 5
+    plan = B.Plan([n], 32)
+    th, tl, ef, mean = (torch.zeros(n, device="cuda") for _ in range(4))
+    hth, htl, hef, hmean = (plan.bind([t]) for t in (th, tl, ef, mean))
+    delta = plan.bind([torch.zeros(n, device="cuda", dtype=torch.bfloat16)], dtype=torch.bfloat16)
+    pairs, aux = plan.message_buffers()
+    m = plan.bind_messages([pairs], [aux])
+    x, u, out = torch.zeros(8, 16, device="cuda"), torch.zeros(16, 4, device="cuda"), torch.zeros(8, 4, device="cuda")
+    table = torch.nn.Parameter(torch.zeros(5, 16, device="cuda"))
+    tables = dict(t_perp=table, token_ids=torch.zeros(8, dtype=torch.int32, device="cuda"), pos_embed=torch.zeros(4, 16, device="cuda"))
+    side = torch.cuda.Stream()
+    torch.cuda.synchronize()
+    for stream in (None, side, side.cuda_stream):
+        made.clear()
+        B.sparseloco_compress(plan, hef, pairs, aux, 0.95, theta_outer=hth, theta_local=htl, stream=stream)
+        B.sparseloco_compress(plan, hef, pairs, aux, 0.95, delta=delta, stream=stream)
+        B.sparseloco_aggregate(plan, m, hmean, stream=stream)
+        B.sparseloco_outer_update(plan, hth, hmean, 1.0, stream=stream)
+        B.sparseloco_aggregate_update(plan, m, hth, 1.0, stream=stream)
+        B.sparseloco_outer_step_batch(plan, hth, htl, hef, m, 0.95, 1.0, reset=True, stream=stream)
+        B.sparseloco_subspace_project(x, u, out, stream=stream)
+        B.sparseloco_subspace_project(x, u, out, **tables, stream=stream)
+        B.sparseloco_subspace_reconstruct(out, u, x, **tables, matmul=B.SPLC_MATMUL_BF16X3, stream=stream)
+        B.sparseloco_reproject_embedding(x, torch.zeros_like(x), u, out, stream=stream)
+        torch.cuda.synchronize()
+        assert made == [(name, B.SPLC_OK) for name in ("compress", "compress", "aggregate", "outer_update", "aggregate_update",
+                                                       "outer_step_batch", "project", "project", "reconstruct", "reproject")]
+
+
+@pytest.mark.gpu
 def test_what_was_refused_is_refused_with_its_reason():
     n = 4096
     plan = B.Plan([n], 32)
