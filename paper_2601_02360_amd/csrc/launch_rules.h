@@ -323,6 +323,17 @@ constexpr AggregatePace aggregate_pace(int64_t chunks, int replicas, int kappa, 
     return AggregatePace{flat && heavy ? 4 : 5, late};
 }
 
+// Mean alone, M no power of two: all sixteen divisions of a lane in front of its four stores, instead of each vector's between
+// its read and its store.  With divisions between them the stores of a row come apart, and lines that two waves or two tiles write
+// leave the L2 in parts.  Time of the stores one by one over time of the stores together, MI355X, messages in no cache
+// (profiles/aggregate_pace_measured.txt):
+//   tiles of 330 to 2050 columns, kappa * M from 192 on: 12,000 chunks 1.00 ... 1.16, 25,000 1.05 ... 1.17, 40,000 1.02 ... 1.26, 70,000 1.02 ...
+//     1.20; 96: 0.91 ... 1.11 (median 0.99); 2048 chunks 0.94 ... 1.01;
+//   flat: 12,000 chunks 0.98 ... 1.03, 40,000 0.97 ... 1.09; 2048 0.96 ... 0.98.
+constexpr bool stores_together(int64_t chunks, int replicas, int kappa) {
+    return chunks >= kFewStreams && (replicas & (replicas - 1)) != 0 && (int64_t)kappa * replicas >= 192;
+}
+
 // Whether no two of these address ranges [first, second) share a byte; empty ranges share none.
 inline bool disjoint(std::vector<std::pair<uintptr_t, uintptr_t>> ranges) {
     std::sort(ranges.begin(), ranges.end());

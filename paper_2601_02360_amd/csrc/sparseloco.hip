@@ -1346,7 +1346,7 @@ __device__ __forceinline__ void aggregate_body(float* acc, const ChunkDesc* __re
                                                              float* const* __restrict__ dbar_tab,
                                                              float* const* __restrict__ theta_tab, float eta, int n_reset,
                                                uint32_t n_tensors, float* const* __restrict__ reset_tab, bool theta_late,
-                                               uint32_t entry) {
+                                               bool stores_together, uint32_t entry) {
     const int tid = threadIdx.x;
     const int lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -1417,6 +1417,18 @@ __device__ __forceinline__ void aggregate_body(float* acc, const ChunkDesc* __re
     if ((n_replicas & (n_replicas - 1)) == 0) {
         const float inverse = __fdiv_rn(1.f, m);
         finish([=](float x) { return __fmul_rn(x, inverse); });
+    } else if (VEC && !UPDATE && stores_together) {
+        float4 v[4];
+#pragma unroll
+        for (int s = 0; s < 4; ++s) {
+            v[s] = acc4[s * kThreads + tid];
+            v[s].x = __fdiv_rn(v[s].x, m); v[s].y = __fdiv_rn(v[s].y, m); v[s].z = __fdiv_rn(v[s].z, m); v[s].w = __fdiv_rn(v[s].w, m);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+        with_chunk<VEC>(d, tid, [&](const auto& chunk) {
+#pragma unroll
+            for (int s = 0; s < 4; ++s) chunk.store(po, s, v[s]);
+        });
     } else {
         finish([=](float x) { return __fdiv_rn(x, m); });
     }
@@ -1430,15 +1442,15 @@ __global__ __launch_bounds__(kThreads) void aggregate_kernel(const ChunkDesc* __
                                                              float* const* __restrict__ dbar_tab,
                                                              float* const* __restrict__ theta_tab, float eta,
                                                              int n_reset, uint32_t n_tensors, bool in_runs, bool theta_late,
-                                                             float* const* __restrict__ reset_tab) {
+                                                             bool stores_together, float* const* __restrict__ reset_tab) {
     __shared__ __align__(16) float acc[kChunk];
     const uint32_t entry = in_runs ? splc::entry_in_runs(blockIdx.x, gridDim.x) : blockIdx.x;
     if (entry >= n_gen)
         aggregate_body<QUANT, UPDATE, true, KP>(acc, chunks, n_replicas, kappa, pairs_tab, aux_tab, dbar_tab, theta_tab, eta,
-                                                n_reset, n_tensors, reset_tab, theta_late, entry);
+                                                n_reset, n_tensors, reset_tab, theta_late, stores_together, entry);
     else
         aggregate_body<QUANT, UPDATE, false, KP>(acc, chunks, n_replicas, kappa, pairs_tab, aux_tab, dbar_tab, theta_tab,
-                                                 eta, n_reset, n_tensors, reset_tab, theta_late, entry);
+                                                 eta, n_reset, n_tensors, reset_tab, theta_late, stores_together, entry);
 }
 
 // Line 5, second half: theta = fl(theta - fl(eta * delta_bar)).
@@ -1634,7 +1646,7 @@ void launch_aggregate(const sparseloco_plan* plan, int n_replicas, const uint16_
         hipLaunchKernelGGL((aggregate_kernel<QUANT, UPDATE, decltype(per_lane)::value>), dim3((unsigned)plan->n_chunks),
                            dim3(kThreads), reserved, stream, plan->d_all, (unsigned)plan->n_all_gen, n_replicas,
                            (uint32_t)plan->kappa, pairs, aux, dbar, theta, eta, n_reset, (uint32_t)plan->n_tensors, in_runs,
-                           pace.theta_late, reset);
+                           pace.theta_late, splc::stores_together(plan->n_chunks, n_replicas, plan->kappa), reset);
     };
     switch (splc::entries_per_lane((uint32_t)plan->kappa)) {
         case 1: launch(std::integral_constant<int, 1>{}); break;

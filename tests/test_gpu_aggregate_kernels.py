@@ -65,3 +65,36 @@ def test_chunks_of_fewer_elements_than_kappa(kappa, replicas, quant):
 @pytest.mark.parametrize("chunks", [8191, 8192])
 def test_large_plans(chunks, kappa, replicas, quant):
     check([CHUNK * (chunks - 2) + 100, 3], kappa, replicas, quant)
+
+
+@pytest.mark.parametrize("cols", [2048, 2050])                  # rows of whole cache lines, or not
+@pytest.mark.parametrize("kappa,replicas,quant", [(64, 3, False), (31, 9, True), (200, 17, True), (300, 7, False)])
+def test_mean_of_tiles_with_stores_together(kappa, replicas, quant, cols):
+    """Complete tiles, edge tiles and flat chunks of a large tiled plan, against the mean that the aggregation with outer update
+    writes, whose divisions and stores take turns."""
+    shapes = [(64 * (8320 // -(-cols // 64)) - 3, cols), (65, 2), (1, 4100)]
+    table = B.chunk_table(shapes, True)
+    chunks = len(table)
+    assert chunks >= 8192
+    plan = B.Plan(shapes, kappa, quant=quant, tiled=True)
+    g = torch.Generator(device="cuda").manual_seed(kappa + replicas)
+    slot = torch.arange(kappa, device="cuda")
+    size = torch.empty(chunks, dtype=torch.int64)
+    size[torch.from_numpy(table["id"].astype("int64"))] = torch.from_numpy(table["n_c"].astype("int64"))
+    sent = slot < size.cuda()[:, None]
+    pairs, aux = [], []
+    for _ in range(replicas):
+        step = torch.randint(0, CHUNK // 2, (chunks, 1), generator=g, device="cuda") * 2 + 1
+        index = step * slot % CHUNK                             # distinct inside a message
+        if quant:
+            index = index + 4096 * torch.randint(0, 4, index.shape, generator=g, device="cuda")
+        pairs.append(torch.where(sent, index, torch.full_like(index, 0xFFFF)).to(torch.int32).to(torch.int16).reshape(-1))
+        aux.append(torch.randn(chunks * (2 if quant else kappa), generator=g, device="cuda"))
+    received = plan.bind_messages(pairs, aux)
+    numels = [r * c for r, c in shapes]
+    got, want = (torch.full((sum(numels),), float("nan"), device="cuda") for _ in range(2))
+    theta = torch.zeros_like(got)
+    B.sparseloco_aggregate(plan, received, plan.bind(list(got.split(numels))))
+    B.sparseloco_aggregate_update(plan, received, plan.bind(list(theta.split(numels))), 1.0,
+                                  delta_bar_out=plan.bind(list(want.split(numels))))
+    assert not got.isnan().any() and torch.equal(got.view(torch.int32), want.view(torch.int32))
