@@ -323,15 +323,24 @@ constexpr AggregatePace aggregate_pace(int64_t chunks, int replicas, int kappa, 
     return AggregatePace{flat && heavy ? 4 : 5, late};
 }
 
-// Mean alone, M no power of two: all sixteen divisions of a lane in front of its four stores, instead of each vector's between
-// its read and its store.  With divisions between them the stores of a row come apart, and lines that two waves or two tiles write
-// leave the L2 in parts.  Time of the stores one by one over time of the stores together, MI355X, messages in no cache
-// (profiles/aggregate_pace_measured.txt):
+// How the mean alone is divided and stored in a complete chunk; the results are the same.
+//   in_turn: a vector is read from the accumulator, divided and stored, and then the next one; a power of two by the
+//     multiplication with its inverse;
+//   together: the sixteen divisions of a lane stand in front of its four stores.  With divisions between them the stores of a row
+//     come apart, and lines that two waves or two tiles write leave the L2 in parts;
+//   divided: in turn, and powers of two are divided too.  With one message or two there is little to wait for, and writes that
+//     come as fast as a multiplication lets them get in each other's way.
+// Time, MI355X, messages in no cache (profiles/aggregate_pace_measured.txt), M no power of two, in turn over together:
 //   tiles of 330 to 2050 columns, kappa * M from 192 on: 12,000 chunks 1.00 ... 1.16, 25,000 1.05 ... 1.17, 40,000 1.02 ... 1.26, 70,000 1.02 ...
 //     1.20; 96: 0.91 ... 1.11 (median 0.99); 2048 chunks 0.94 ... 1.01;
 //   flat: 12,000 chunks 0.98 ... 1.03, 40,000 0.97 ... 1.09; 2048 0.96 ... 0.98.
-constexpr bool stores_together(int64_t chunks, int replicas, int kappa) {
-    return chunks >= kFewStreams && (replicas & (replicas - 1)) != 0 && (int64_t)kappa * replicas >= 192;
+// Flat, M one or two, kappa * M up to 64, multiplied over divided: 8192 chunks 0.97 ... 1.05, 12,000 0.98 ... 1.05, 45,000 1.07 ... 1.16, 150,000
+//   1.09 ... 1.15, messages in a cache 0.98 ... 1.04; four and eight messages 0.84 ... 1.07; tiles of 2048 columns 0.88 ... 1.03.
+enum class MeanStores { in_turn, together, divided };
+constexpr MeanStores mean_stores(int64_t chunks, int replicas, int kappa, bool flat) {
+    if (chunks < kFewStreams) return MeanStores::in_turn;
+    if (replicas <= 2) return flat && kappa * replicas <= 64 ? MeanStores::divided : MeanStores::in_turn;
+    return (replicas & (replicas - 1)) != 0 && (int64_t)kappa * replicas >= 192 ? MeanStores::together : MeanStores::in_turn;
 }
 
 // Whether no two of these address ranges [first, second) share a byte; empty ranges share none.

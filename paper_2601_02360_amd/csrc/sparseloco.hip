@@ -1346,7 +1346,7 @@ __device__ __forceinline__ void aggregate_body(float* acc, const ChunkDesc* __re
                                                              float* const* __restrict__ dbar_tab,
                                                              float* const* __restrict__ theta_tab, float eta, int n_reset,
                                                uint32_t n_tensors, float* const* __restrict__ reset_tab, bool theta_late,
-                                               bool stores_together, uint32_t entry) {
+                                               splc::MeanStores stores, uint32_t entry) {
     const int tid = threadIdx.x;
     const int lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -1414,10 +1414,10 @@ __device__ __forceinline__ void aggregate_body(float* acc, const ChunkDesc* __re
     };
     // A power of two divides exactly like its inverse multiplies: one rounding of the same value.  (The choice is made out here,
     // for all slots at once: in their loop it slowed the division down, mean of 1000 chunks, kappa 16, 27 replicas 7.1 -> 7.6 us.)
-    if ((n_replicas & (n_replicas - 1)) == 0) {
+    if ((n_replicas & (n_replicas - 1)) == 0 && (UPDATE || stores != splc::MeanStores::divided)) {
         const float inverse = __fdiv_rn(1.f, m);
         finish([=](float x) { return __fmul_rn(x, inverse); });
-    } else if (VEC && !UPDATE && stores_together) {
+    } else if (VEC && !UPDATE && stores == splc::MeanStores::together) {
         float4 v[4];
 #pragma unroll
         for (int s = 0; s < 4; ++s) {
@@ -1442,15 +1442,15 @@ __global__ __launch_bounds__(kThreads) void aggregate_kernel(const ChunkDesc* __
                                                              float* const* __restrict__ dbar_tab,
                                                              float* const* __restrict__ theta_tab, float eta,
                                                              int n_reset, uint32_t n_tensors, bool in_runs, bool theta_late,
-                                                             bool stores_together, float* const* __restrict__ reset_tab) {
+                                                             splc::MeanStores stores, float* const* __restrict__ reset_tab) {
     __shared__ __align__(16) float acc[kChunk];
     const uint32_t entry = in_runs ? splc::entry_in_runs(blockIdx.x, gridDim.x) : blockIdx.x;
     if (entry >= n_gen)
         aggregate_body<QUANT, UPDATE, true, KP>(acc, chunks, n_replicas, kappa, pairs_tab, aux_tab, dbar_tab, theta_tab, eta,
-                                                n_reset, n_tensors, reset_tab, theta_late, stores_together, entry);
+                                                n_reset, n_tensors, reset_tab, theta_late, stores, entry);
     else
         aggregate_body<QUANT, UPDATE, false, KP>(acc, chunks, n_replicas, kappa, pairs_tab, aux_tab, dbar_tab, theta_tab,
-                                                 eta, n_reset, n_tensors, reset_tab, theta_late, stores_together, entry);
+                                                 eta, n_reset, n_tensors, reset_tab, theta_late, stores, entry);
 }
 
 // Line 5, second half: theta = fl(theta - fl(eta * delta_bar)).
@@ -1646,7 +1646,7 @@ void launch_aggregate(const sparseloco_plan* plan, int n_replicas, const uint16_
         hipLaunchKernelGGL((aggregate_kernel<QUANT, UPDATE, decltype(per_lane)::value>), dim3((unsigned)plan->n_chunks),
                            dim3(kThreads), reserved, stream, plan->d_all, (unsigned)plan->n_all_gen, n_replicas,
                            (uint32_t)plan->kappa, pairs, aux, dbar, theta, eta, n_reset, (uint32_t)plan->n_tensors, in_runs,
-                           pace.theta_late, splc::stores_together(plan->n_chunks, n_replicas, plan->kappa), reset);
+                           pace.theta_late, splc::mean_stores(plan->n_chunks, n_replicas, plan->kappa, flat), reset);
     };
     switch (splc::entries_per_lane((uint32_t)plan->kappa)) {
         case 1: launch(std::integral_constant<int, 1>{}); break;

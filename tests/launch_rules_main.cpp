@@ -100,16 +100,20 @@ static int check_aggregate_pace() {
     return 0;
 }
 
-// Stores of the mean together on both sides of each line (second half: the plans of test_gpu_aggregate_kernels.py).
-static int check_stores_together() {
-    const struct { int64_t chunks; int replicas, kappa; bool want; } cases[] = {
-        {8192, 3, 64, true}, {8191, 3, 64, false}, {8192, 3, 63, false}, {8192, 4, 64, false}, {220000, 1024, 128, false}, {220000, 1023, 1, true},
-        {8192, 7, 4096, true}, {8192, 1, 4096, false}, {8192, 2, 4096, false}, {8192, 191, 1, false}, {8192, 193, 1, true},
-        {8192, 9, 64, true}, {8192, 2, 200, false}, {8192, 5, 32, false}, {8320, 3, 64, true}, {8320, 9, 31, true}, {8320, 17, 200, true},
-        {8320, 7, 300, true}};
+// Division and stores of the mean on both sides of each line (second half: the plans of test_gpu_aggregate_kernels.py).
+static int check_mean_stores() {
+    using splc::MeanStores;
+    const MeanStores turn = MeanStores::in_turn, together = MeanStores::together, divided = MeanStores::divided;
+    const struct { int64_t chunks; int replicas, kappa; bool flat; MeanStores want; } cases[] = {
+        {8192, 3, 64, true, together}, {8191, 3, 64, true, turn}, {8192, 3, 63, true, turn}, {8192, 4, 64, true, turn}, {220000, 1024, 128, false, turn},
+        {220000, 1023, 1, true, together}, {8192, 7, 4096, false, together}, {8192, 191, 1, true, turn}, {8192, 193, 1, false, together},
+        {8192, 1, 64, true, divided}, {8191, 1, 64, true, turn}, {8192, 1, 65, true, turn}, {8192, 1, 64, false, turn}, {220000, 2, 32, true, divided},
+        {8192, 2, 33, true, turn}, {8192, 4, 16, true, turn}, {8192, 1, 4096, true, turn}, {8192, 2, 4096, false, turn}, {1, 1, 1, true, turn},
+        {8192, 9, 64, true, together}, {8192, 2, 200, true, turn}, {8192, 2, 16, true, divided}, {8320, 3, 64, false, together},
+        {8320, 9, 31, false, together}, {8320, 17, 200, false, together}, {8320, 7, 300, false, together}};
     for (const auto& c : cases)
-        if (splc::stores_together(c.chunks, c.replicas, c.kappa) != c.want) {
-            printf("stores_together: %ld chunks, %d replicas, kappa %d\n", (long)c.chunks, c.replicas, c.kappa);
+        if (splc::mean_stores(c.chunks, c.replicas, c.kappa, c.flat) != c.want) {
+            printf("mean_stores: %ld chunks, %d replicas, kappa %d, %d\n", (long)c.chunks, c.replicas, c.kappa, c.flat);
             return 1;
         }
     return 0;
@@ -159,7 +163,7 @@ static int check_strips_pay() {
 }
 
 int main() {
-    if (check_unguarded_tiles() || check_side_by_side() || check_few_streams() || check_aggregate_pace() || check_stores_together() || check_entries_per_lane() ||
+    if (check_unguarded_tiles() || check_side_by_side() || check_few_streams() || check_aggregate_pace() || check_mean_stores() || check_entries_per_lane() ||
         check_slot_used() || check_strips_pay())
         return 1;
     printf("ok\n");

@@ -58,10 +58,10 @@ def test_chunks_of_fewer_elements_than_kappa(kappa, replicas, quant):
     check([1, 63, 64, 65, 127, 128, 129, 255, 256, 257, 300, CHUNK + 40, 4095], kappa, replicas, quant)
 
 
-# With the update, theta late: 3; 9 of kappa 64; the unquantised ones (8 of kappa 64 and 128 in fewer groups a unit) / with the
+# With the update, theta late: 2 and 3; 9 of kappa 64; the unquantised ones (8 of kappa 64 and 128 in fewer groups a unit) / with the
 # first messages: 9 of kappa 16; 2 of kappa 200.  (The lines: check_aggregate_pace of launch_rules_main.cpp.)
 @pytest.mark.parametrize("kappa,replicas,quant", [(16, 3, True), (16, 9, True), (64, 9, True), (200, 2, True), (64, 8, False),
-                                                  (128, 8, False), (32, 5, False)])
+                                                  (128, 8, False), (32, 5, False), (16, 2, True)])
 @pytest.mark.parametrize("chunks", [8191, 8192])
 def test_large_plans(chunks, kappa, replicas, quant):
     check([CHUNK * (chunks - 2) + 100, 3], kappa, replicas, quant)
