@@ -154,12 +154,10 @@ __device__ __forceinline__ void store4(float* p, float4 v) {
     else *(SPLC_GLOBAL vfloat4*)p = t;
 }
 // Whether the rows of a complete chunk are whole cache lines.  Those of a tile in a matrix whose row length is no
-// multiple of 32 floats share their first and last line with the neighbouring tiles.  The aggregation and the calls that walk
-// over replicas access them without the hint: with it the lines are gone from the L2 when the neighbour asks for them (20M
-// parameters in rows of 3687, mean 30 -> 17 us; the one-launch step of two replicas 201 -> 128).  The compression of one replica
-// reads with the hint and stores the error feedback without.  20M parameters in rows of 3687, us, nothing in a cache / arrays as
-// the call before left them: from parameters 85 / 70 (hint for both 89 / 85, for the store only 106 / 74), from fp32 63 / 53
-// (70 / 66, 75 / 55), from bf16 55 / 50 (64 / 65, 64 / 52).
+// multiple of 32 floats share their first and last line with the neighbouring tiles, and are accessed without the hint: with it
+// the lines are gone from the L2 when the neighbour asks for them (20M parameters in rows of 3687, mean 30 -> 17 us; the
+// one-launch step of two replicas 201 -> 128; compress of 6000 tiles of 1219 columns, loads and store with it / neither: from
+// parameters 97 / 66 us, in no cache 100 / 82, from fp32 76 / 49, 78 / 63, from bf16 67 / 43, 87 / 56).
 __device__ __forceinline__ bool whole_lines(const ChunkDesc& d) { return d.stride % 32u == 0; }
 
 __device__ __forceinline__ uint32_t lanes_below(uint64_t mask) {
@@ -251,12 +249,12 @@ struct EdgeChunk {
         store_edge(vec_at(p, d, tid, s), (1u << edge_vec(d, tid, s).n) - 1u, v);
     }
 };
-// use(chunk) with the way this chunk is accessed.
+// use(chunk) with the way this chunk is accessed.  hint: a complete one in any case with the streaming hint.
 template <bool VEC, class Use>
-__device__ __forceinline__ void with_chunk(const ChunkDesc& d, int tid, Use use) {
+__device__ __forceinline__ void with_chunk(const ChunkDesc& d, int tid, Use use, bool hint = false) {
     if constexpr (VEC) {
         // (the statements that say which side this is keep the compiler from merging the two, which drops the hint)
-        if (whole_lines(d)) {
+        if (whole_lines(d) || hint) {
             asm volatile("; whole lines from here");
             use(CompleteChunk<true>{d, tid});
             asm volatile("; whole lines to here");
@@ -832,8 +830,11 @@ __device__ __forceinline__ void select_quantise_pack(SelectShared& sh, float (&x
                                     scales_c);
 }
 
-// The error-feedback buffer is rewritten densely (line 4 of the update equations).  BATCH: by a call that walks over replicas,
-// which keeps the hint also where lines are shared (without it the one-launch step takes 0.98 to 1.06 of the time).
+// The error-feedback buffer is rewritten densely (line 4 of the update equations).  Where lines are shared the store goes without
+// the hint, but not by a call that walks over replicas (BATCH: without it the one-launch step takes 0.98 to 1.06 of the time)
+// and not on plans of few tiles, where less of the caches is left for what the next call reads (700 tiles, four replicas that
+// share theta_outer, 12.8 -> 11.8 us, from fp32 9.9 -> 9.3; 1500: 19.6 -> 21.4, from bf16 in no cache 18.8 -> 20.3; 6000, from bf16 43 -> 50).
+constexpr unsigned kFewTiles = 1024;
 template <bool VEC, bool BATCH>
 __device__ __forceinline__ void store_ef(float* __restrict__ e, const ChunkDesc& d, int tid, uint32_t pmask,
                                          const float (&x)[16]) {
@@ -845,7 +846,7 @@ __device__ __forceinline__ void store_ef(float* __restrict__ e, const ChunkDesc&
     if constexpr (VEC && BATCH) {
         store(CompleteChunk<true>{d, tid});
     } else if constexpr (VEC) {
-        with_chunk<true>(d, tid, store);
+        with_chunk<true>(d, tid, store, gridDim.x < kFewTiles);
     } else {
         // from an opaque copy of the lane number: nothing of the loads' addresses is kept for these stores
         int t = tid;
@@ -879,7 +880,7 @@ __device__ __forceinline__ void compress_body(SelectShared& sh, bool vec, const 
     uint32_t pmask = 0xFFFFu;
     float x[16];
     if (vec) {
-        load_fold<MODE>(pa, pb, pe, beta, x, CompleteChunk<true>{d, tid});
+        with_chunk<true>(d, tid, [&](const auto& chunk) { load_fold<MODE>(pa, pb, pe, beta, x, chunk); });
     } else {
         with_chunk<false>(d, tid, [&](const auto& chunk) { load_fold<MODE>(pa, pb, pe, beta, x, chunk); });
         pmask = pull_all(d, tid, x);
