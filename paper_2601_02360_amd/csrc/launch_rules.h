@@ -225,22 +225,14 @@ constexpr bool replicas_side_by_side(int64_t chunks, int replicas, bool step, bo
 // outside them, or every tile by itself in one launch.  A strip asks for nine cache lines where its tiles ask for twelve,
 // which is what large plans are bound by; it takes longer from end to end, and below some rounds of workgroups that, and
 // the second launch, are what counts.  Where the general path of the selection is taken often (from some 200 entries on) all four
-// tiles of a strip take it together.  Time of the tiles over time of the strips, MI355X, matrices of 330 to 5630 columns,
-// nothing in a cache / arrays as the call before left them (profiles/strips_measured.txt):
-//   from parameters, kappa 32 ... 192: 1120 strips 0.89 ... 0.99 / 0.78 ... 0.85, 1720 1.01 ... 1.09 / 0.86 ... 0.90, 2240 0.97 ... 1.12 /
-//     0.80 ... 0.89, 2960 0.98 ... 1.09 / 0.85 ... 0.92, 4480 1.00 ... 1.27 / 0.98 ... 1.15, 9000 1.12 ... 1.33 / 1.08 ... 1.31;
-//     kappa 256: 9000 0.94 ... 0.96 / 0.91 ... 0.95, 40,000 1.07 / 1.05; 512 and 1024: 4480 0.94 ... 1.00 / 0.88 ... 0.98, 9000 1.01 ... 1.04;
-//   from fp32, kappa 32 ... 192: 1400 0.85 ... 0.96 / 0.75 ... 0.82, 2240 0.85 ... 1.06 / 0.70 ... 0.88, 2960 1.05 ... 1.13 / 0.85 ... 0.95, 4480 1.04 ...
-//     1.23 / 0.86 ... 1.15; kappa 256 ... 1024: 0.68 ... 0.82 at every size;
-//   from bf16, kappa 32 / 64: 2240 0.95 ... 1.00 / 0.91 ... 0.97 (in a cache 0.78 ... 0.89), 2600 1.05 / 0.99 (0.81 ... 0.92), 4480 1.05 ... 1.19
-//     (0.96 ... 1.11); kappa 128: 2960 0.94 ... 0.99 (0.81 ... 0.87), 3600 0.99 (0.82), 4480 1.05 (0.91 ... 1.03); 160: 4480 0.94 ... 0.99, 9000 1.01 ... 1.05;
-//     kappa 192 ... 1024: 0.64 ... 0.88 at every size.
-constexpr bool strips_pay(int64_t strips, int kappa, bool params, bool bf16) {
-    if (kappa > 192) return params && strips >= 9000;
-    if (!bf16) return strips >= 2200;
-    if (kappa > 128) return kappa <= 160 && strips >= 9000;
-    return strips >= (kappa <= 64 ? 2600 : 3600);
-}
+// tiles of a strip take it together.  Time of the tiles over time of the strips, MI355X, 2050 columns, arrays as the call before left
+// them / four replicas in turn (from parameters) / nothing in a cache (profiles/strips_measured.txt):
+//   from parameters, kappa 32 and 128: 1496 strips 0.76 / 0.93 / 0.94, 2240 0.95 ... 0.99 / 0.99 / 0.98 ... 0.99, 3240 1.01 ... 1.03 / 1.04 ... 1.05 / 1.03 ...
+//     1.05, 4488 1.02 ... 1.04 / 1.02 ... 1.03 / 1.00 ... 1.03, 9984 1.03 ... 1.07 / 1.03 ... 1.05 / 1.03 ... 1.04;
+//   from fp32: 2240 0.77 ... 0.78 / 0.91 ... 0.96, 3240 0.98 ... 0.99 / 1.03 ... 1.05, 4488 0.98 ... 0.99 / 0.95 ... 0.97, 9984 1.05 ... 1.09 / 1.04 ... 1.08;
+//   from bf16: 2240 0.69 ... 0.75 / 0.92 ... 0.93, 3240 0.83 ... 0.87 / 0.97 ... 1.00, 4488 0.93 ... 0.96 / 0.95 ... 0.99, 9984 0.99 ... 1.04 / 1.02 ... 1.03;
+//   kappa 256: 0.67 ... 0.78 at every size from every source.
+constexpr bool strips_pay(int64_t strips, int kappa, bool params) { return kappa <= 192 && strips >= (params ? 2700 : 6500); }
 
 // Large plans stream far more than the last-level cache holds, and there fewer workgroups per compute unit than would fit
 // keep the memory busier (fewer streams in flight at once) -- as long as memory is what bounds: with other sources, which

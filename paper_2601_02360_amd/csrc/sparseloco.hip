@@ -1621,7 +1621,7 @@ template <int MODE, int QUANT>
 void launch_compress(const sparseloco_plan* plan, const void* const* a, const void* const* b, float* const* ef,
                      float beta, uint16_t* pairs_out, float* aux_out, hipStream_t stream) {
     const int force_radix = plan->select == SPLC_SELECT_RADIX ? 1 : 0;
-    const bool strips = splc::strips_pay(plan->n_strips, plan->kappa, MODE == MODE_PARAMS_F32, MODE == MODE_DIRECT_BF16);
+    const bool strips = splc::strips_pay(plan->n_strips, plan->kappa, MODE == MODE_PARAMS_F32);
     const int64_t entries = strips ? plan->n_entries : plan->n_chunks;
     if (strips)
         hipLaunchKernelGGL((compress_strip_kernel<MODE, QUANT>), dim3((unsigned)plan->n_strips), dim3(kStripThreads), 0,
@@ -1923,8 +1923,7 @@ int plan_build(sparseloco_plan** out, int n_tensors, const int64_t* rows, const 
     for (int i = 0; i < n_tensors; ++i) plan->numel[(size_t)i] = (tiled ? rows[i] : 1) * cols[i];
     // (kept where a compression of this plan takes them: from some source they pay)
     const int64_t n_strips = (int64_t)t.strips.size();
-    const bool with_strips = splc::strips_pay(n_strips, kappa, true, false) || splc::strips_pay(n_strips, kappa, false, false) ||
-                             splc::strips_pay(n_strips, kappa, false, true);
+    const bool with_strips = splc::strips_pay(n_strips, kappa, true) || splc::strips_pay(n_strips, kappa, false);
     if (!with_strips) t.strips.clear();
     const std::vector<ChunkDesc>& main_table = with_strips ? t.rest : t.all;
     plan->n_entries = (int64_t)main_table.size();

@@ -146,17 +146,15 @@ static int check_slot_used() {
 
 // Strips on both sides of each line.  Every plan of test_gpu_strips.py and of test_edge_chunks.py's test of both sides is on one.
 static int check_strips_pay() {
-    const struct { int64_t least; int kappa; bool params, bf16; } lines[] = {
-        {2200, 1, true, false}, {2200, 64, true, false}, {2200, 128, true, false}, {2200, 192, true, false}, {9000, 193, true, false},
-        {9000, 257, true, false}, {9000, 300, true, false}, {9000, 4096, true, false},
-        {2200, 32, false, false}, {2200, 128, false, false}, {2200, 192, false, false}, {-1, 193, false, false}, {-1, 4096, false, false},
-        {2600, 32, false, true}, {2600, 64, false, true}, {3600, 65, false, true}, {3600, 128, false, true}, {9000, 129, false, true},
-        {9000, 160, false, true}, {-1, 161, false, true}, {-1, 1024, false, true}};
+    const struct { int64_t least; int kappa; bool params; } lines[] = {
+        {2700, 1, true}, {2700, 64, true}, {2700, 128, true}, {2700, 192, true}, {-1, 193, true}, {-1, 4096, true},
+        {6500, 1, false}, {6500, 32, false}, {6500, 64, false}, {6500, 65, false}, {6500, 128, false}, {6500, 160, false}, {6500, 192, false},
+        {-1, 193, false}, {-1, 4096, false}};
     for (const auto& l : lines)
-        if (splc::strips_pay(0, l.kappa, l.params, l.bf16) ||
-            (l.least < 0 ? splc::strips_pay(int64_t(1) << 27, l.kappa, l.params, l.bf16)
-                         : splc::strips_pay(l.least - 1, l.kappa, l.params, l.bf16) || !splc::strips_pay(l.least, l.kappa, l.params, l.bf16))) {
-            printf("strips_pay: kappa %d, %d %d\n", l.kappa, l.params, l.bf16);
+        if (splc::strips_pay(0, l.kappa, l.params) ||
+            (l.least < 0 ? splc::strips_pay(int64_t(1) << 27, l.kappa, l.params)
+                         : splc::strips_pay(l.least - 1, l.kappa, l.params) || !splc::strips_pay(l.least, l.kappa, l.params))) {
+            printf("strips_pay: kappa %d, %d\n", l.kappa, l.params);
             return 1;
         }
     return 0;

@@ -102,8 +102,8 @@ def test_what_lies_around_an_edge_chunk_is_left_alone():
 
 
 @pytest.mark.gpu
-@pytest.mark.parametrize("rows,direct,kappa", [(64 * 549, None, 32), (64 * 550 + 3, None, 128), (64 * 649, "bf16", 64),
-                                               (64 * 650 + 3, "bf16", 64), (64 * 899, "bf16", 65), (64 * 900, "bf16", 65)])
+@pytest.mark.parametrize("rows,direct,kappa", [(64 * 674, None, 32), (64 * 675 + 3, None, 128), (64 * 1624, "bf16", 64),
+                                               (64 * 1625 + 3, "bf16", 64)])
 def test_strips_and_tiles_on_both_sides_of_the_line(rows, direct, kappa):
     """Matrices of 1030 columns, four strips a tile row: the largest plan that is compressed tile by tile, and the
     smallest (with rows to spare) that takes strips."""
