@@ -1,4 +1,4 @@
-"""Thin ctypes binding of libsparseloco.so: argument marshalling only.
+"""Thin binding of libsparseloco.so, ctypes and for the launching calls csrc/calls.cpp: argument marshalling only.
 
 Every step of the outer step (paper section 2.1) runs in the library's HIP
 kernels; this module turns torch tensors into device pointers (checking sizes,

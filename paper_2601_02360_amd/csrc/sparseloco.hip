@@ -912,10 +912,9 @@ __global__ __launch_bounds__(kThreads) void compress_kernel(const ChunkDesc* __r
 // multiple of 32 floats every such segment straddles three 128-byte cache lines instead of two, and the lines on
 // a tile's left and right edge are requested again by its neighbours.  So wherever four complete tiles lie side
 // by side, and there are many of them (splc::strips_pay), ONE workgroup of 1024 lanes takes all four: global memory is
-// accessed row by row (a wave covers one 1024-byte row of the strip per instruction: nine lines instead of twelve, none
-// shared with another workgroup), the folded values pass through LDS, where each 256-lane group picks up "its" tile in the usual
-// chunk layout and runs the selection exactly as the one-tile kernel does, and the new error-feedback values go
-// back the same way.  Tiles left over at the end of a tile row, edge tiles and 1-D tensors stay with the
+// accessed row by row (a wave covers one 1024-byte row of the strip per instruction: nine lines instead of twelve),
+// the folded values pass through LDS, where each 256-lane group picks up "its" tile in the usual chunk layout and runs
+// the selection exactly as the one-tile kernel does, and the new error-feedback values go back the same way.  Tiles left over at the end of a tile row, edge tiles and 1-D tensors stay with the
 // one-tile kernels.
 constexpr int kStripTiles = 4;
 constexpr int kStripThreads = kStripTiles * kThreads;
@@ -1803,11 +1802,12 @@ void append_chunks(std::vector<ChunkDesc>& table, uint32_t tensor, int64_t rows,
 int chunk_class(const ChunkDesc& d) { return d.vec == 0 ? 0 : (d.vec == 1 ? 1 : 2); }
 
 // Order in which workgroups take the entries: edge chunks first (they take a little longer and should not form the
-// tail), then complete chunks in matrices of odd row length, then the other complete ones.  For a tiled plan, inside each class every XCD gets a run of
-// consecutive tiles: workgroups go to the eight XCDs round-robin by number, neighbouring tiles of a tile row
-// continue each other's row segments (and share the cache lines on their common edge when the row length is no
-// multiple of 32 floats), so neighbours should meet in one L2.  Only the order of processing changes: a chunk's
-// number, and with it the place of its pairs in the message, is its `id`.
+// tail), then complete ones in matrices of odd row length, then the other complete ones (no kernel tells these two apart;
+// it is the order that sparseloco_chunk_table answers).  For a tiled plan, inside each class every XCD gets a run of consecutive tiles:
+// workgroups go to the eight XCDs round-robin by number, neighbouring tiles of a tile row continue each other's row
+// segments (and share the cache lines on their common edge when the row length is no multiple of 32 floats), so
+// neighbours should meet in one L2.  Only the order of processing changes: a chunk's number, and with it the place of
+// its pairs in the message, is its `id`.
 void order_for_launch(std::vector<ChunkDesc>& table, bool deal_to_xcds) {
     std::stable_sort(table.begin(), table.end(),
                      [](const ChunkDesc& a, const ChunkDesc& b) { return chunk_class(a) < chunk_class(b); });
